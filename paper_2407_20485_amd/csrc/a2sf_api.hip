@@ -144,7 +144,8 @@ a2sf_status prefill_impl(const void* q, const void* k, const void* v, int32_t n,
     cp.pos = cache->pos + (size_t)g0 * cache->capacity;
     cp.len = cache->len + g0;
     if (cache->dtype == A2SF_F32) {
-      launch_prefill_f32((const float*)qp, (const float*)kp, (const float*)vp, Gp, n, d, (float*)op, lp, st);
+      launch_prefill_f32((const float*)qp, (const float*)kp, (const float*)vp, Gp, n, d, (float*)op, lp, st,
+                         f32_first_lse_row(n, alpha));
       launch_scores_f32((const float*)qp, (const float*)kp, lp, Gp, n, d, alpha, ap, sp, st);
     } else {
       // without outputs only the rows the score kernel will read need their log-sum-exp
@@ -315,7 +316,8 @@ a2sf_status a2sf_prefill_gqa(const void* q, const void* k, const void* v, int32_
   AttnRect rc{n, n, nullptr};
   rc.kv_group = group;
   // without outputs only the rows the score kernel will read need their log-sum-exp
-  if (!o && cache->dtype == A2SF_BF16) rc.first_row = bf16_first_lse_row(n, cache->d, alpha);
+  if (!o)
+    rc.first_row = cache->dtype == A2SF_BF16 ? bf16_first_lse_row(n, cache->d, alpha) : f32_first_lse_row(n, alpha);
   // in parts of kPrefillPartHeads query heads, as the plain prompt phase and for the same reason
   const size_t e = cache->dtype == A2SF_F32 ? 4 : 2;
   const int B = budget.select + budget.recent;

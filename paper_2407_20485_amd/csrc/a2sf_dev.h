@@ -234,6 +234,32 @@ template <bool STREAM>
 __device__ __forceinline__ uint4 load16_as(const void* p) {
   return STREAM ? load16_stream(p) : load16(p);
 }
+// Direct global-to-LDS load: 16 (or 4) bytes at base + lane_off of every lane land at
+// lds_addr + 16 (4) * lane.  base and lds_addr are the same for the whole wave.  Written as an
+// instruction of its own and not through the compiler's builtin, because for the builtin the
+// compiler waits for ALL outstanding direct loads before the next LDS read of the same array
+// (it cannot tell the ring stages apart), which undoes every prefetch.  The loads are invisible
+// to the compiler's wait counting: the kernel waits itself (wait_vm, wait_vm_barrier) before the data is
+// read, and makes sure that a stage's readers are done before it is filled again.  The compiler's
+// own waits stay correct, since loads return in order: it can only wait for more than it needs.
+__device__ __forceinline__ void dma16(const void* base, uint32_t lane_off, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"(base) : "memory");
+}
+__device__ __forceinline__ void dma4(const void* base, uint32_t lane_off, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+               :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"(base) : "memory");
+}
+// At most LEFT of this wave's loads and stores outstanding; LDS reads done.
+template <int LEFT>
+__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LEFT) : "memory"); }
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+// Workgroup barrier that leaves LEFT of the wave's loads under way (a plain __syncthreads may
+// wait for all of them); the wave's LDS accesses are done.
+template <int LEFT>
+__device__ __forceinline__ void wait_vm_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(LEFT) : "memory");
+}
 __device__ __forceinline__ void store16(void* p, const uint4& v) { *reinterpret_cast<uint4*>(p) = v; }
 
 }  // namespace a2sf

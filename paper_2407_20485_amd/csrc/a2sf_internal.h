@@ -76,8 +76,8 @@ struct AttnRect {
   // k2 / v2 -- a chunk whose rows have not been copied behind the cached ones.
   const void* k2 = nullptr;
   const void* v2 = nullptr;
-  // Calls without outputs (bf16, d = 128): the log-sum-exp of the rows before first_row is not
-  // needed (the score kernel that follows skips them), so their row blocks are not computed.
+  // Calls without outputs (fp32; bf16 with d = 128): the log-sum-exp of the rows before first_row
+  // is not needed (the score kernel that follows skips them), so their row blocks are not computed.
   int first_row = 0;
 };
 // true when launch_attn_bf16 / launch_colscores_bf16 serve these sizes with kernels that read a
@@ -87,7 +87,9 @@ bool bf16_two_source_ok(int d, const AttnRect& rc, float alpha);
 // prefill_f32.hip / prefill_bf16.hip
 // lse2[g][i] = log2(sum_j exp(s_ij)) of the masked row i (s already scaled by 1/sqrt(d)).
 void launch_prefill_f32(const float* q, const float* k, const float* v, int G, int n, int d,
-                        float* o, float* lse2, hipStream_t st);
+                        float* o, float* lse2, hipStream_t st, int first_row = 0);
+// First prompt row whose log-sum-exp the fp32 score kernel uses.
+int f32_first_lse_row(int n, float alpha_max);
 // alpha_heads (device [G]) may be null: then every head uses `alpha`; otherwise `alpha` is an
 // upper bound of the per-head factors.
 void launch_scores_f32(const float* q, const float* k, const float* lse2, int G, int n, int d,

@@ -3,10 +3,12 @@ smallest and largest of a launch rule's range.  Against the float64 oracle, with
 of parity.py."""
 import dataclasses
 
+import numpy as np
 import pytest
 import torch
 
 import paper_2407_20485_amd as a2sf
+from oracle import a2sf_oracle as orc
 from paper_2407_20485_amd import synth
 import parity
 
@@ -39,3 +41,74 @@ def test_fp32_prompt_tiles(n, d):
     tiles, one to ten tiles."""
     for alpha in (0.0, 0.7, 1.0):
         prompt_and_steps(variant(0, heads=3, d=d, n=n, T=2, select=min(9, n), recent=4, name="fp32 tiles"), alpha)
+
+
+@pytest.mark.parametrize("L,G", [(1, 6), (255, 6), (1023, 6), (1024, 6), (1025, 6), (2048, 520), (2049, 520), (4096, 6),
+                                 (4097, 6), (8193, 6), (16385, 6), (32768, 6), (32769, 6), (70001, 6)])
+@pytest.mark.parametrize("form", ["slots", "consecutive", "gaps"])
+def test_selection_sizes(L, G, form):
+    """Every size class of the selection kernel, with and without stored positions (the newest ones
+    consecutive, or with gaps), ragged lengths; ties across the cut, equal scores, infinities."""
+    rng = np.random.default_rng(L + G)
+    stride = L + 1
+    check = [0, 1, 2, 3, 4, G - 1]
+    scores = rng.random((G, stride)).astype(np.float32) ** 8
+    scores[1] = np.round(scores[1] * 4) / 4
+    scores[2] = 0.25
+    scores[3, : L // 2] = -scores[3, : L // 2]
+    scores[4, : L // 3] = -np.inf
+    scores[4, L // 3 : L // 2] = np.inf
+    lens = rng.integers(max(1, L - 70), L + 1, size=G).astype(np.int32)
+    lens[0] = L
+    if form == "slots":
+        pos = None
+    elif form == "consecutive":
+        pos = np.stack([rng.permutation(stride) for _ in range(G)]).astype(np.int32)
+        lens[:] = L
+        pos[pos == stride - 1] = 2 ** 31 - 1 if L == 255 else stride - 1
+    else:
+        pos = np.stack([3 * rng.permutation(stride) for _ in range(G)]).astype(np.int32)
+    dev_scores, dev_lens = torch.from_numpy(scores).cuda(), torch.from_numpy(lens).cuda()
+    dev_pos = torch.from_numpy(pos).cuda() if pos is not None else None
+    for select, recent in ((L // 10, L // 7), (1, 0), (0, 1), (L - L // 2, 0), (L // 3, L - L // 3 - 1)):
+        if select + recent < 1:
+            continue
+        keep = torch.full((G, select + recent), -1, dtype=torch.int32, device="cuda")
+        n_keep = torch.zeros(G, dtype=torch.int32, device="cuda")
+        a2sf.a2sf_select(dev_scores, dev_pos, dev_lens, G, L, stride, select, recent, keep, n_keep)
+        torch.cuda.synchronize()
+        got, nk = keep.cpu().numpy(), n_keep.cpu().numpy()
+        for g in check:
+            n = int(lens[g])
+            p = pos[g, :n] if pos is not None else np.arange(n)
+            want = orc.select_keep(scores[g, :n].astype(np.float64), p, select, recent)
+            assert nk[g] == len(want)
+            assert np.array_equal(got[g, : nk[g]], np.sort(want)), (g, select, recent)
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 64), (torch.bfloat16, 128), (torch.float32, 64), (torch.float32, 128)])
+def test_compaction_rounds(dtype, d):
+    """Rounds of 256 rows per workgroup and column slices of 128 bytes: keep lists that end at, before
+    and behind the edge of a round, leave a prefix in place, or move nothing."""
+    rng = np.random.default_rng(d)
+    cap, G = 900, 8
+    keeps = [np.arange(300), np.arange(1, 257), np.arange(2, 515, 2), np.r_[np.arange(255), 256:700],
+             np.r_[np.arange(256), 300:557], np.array([899]), np.arange(0), np.sort(rng.permutation(900)[:769])]
+    c = a2sf.Cache(G, cap, d, dtype)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    for t in c.tensors()[:3]:
+        t.copy_(torch.randn(t.shape, generator=gen, device="cuda"))
+    c.pos.copy_(torch.arange(cap, device="cuda").int().expand(G, cap) * 2)
+    c.len.fill_(cap)
+    before = c.snapshot()
+    keep = torch.zeros((G, cap), dtype=torch.int32, device="cuda")
+    for g, k in enumerate(keeps):
+        keep[g, : len(k)] = torch.from_numpy(k.astype(np.int32)).cuda()
+    n_keep = torch.tensor([len(k) for k in keeps], dtype=torch.int32, device="cuda")
+    a2sf.a2sf_compact(c, keep, cap, n_keep)
+    torch.cuda.synchronize()
+    assert torch.equal(c.len, n_keep)
+    for g, k in enumerate(keeps):
+        at = torch.from_numpy(k).cuda()
+        for got, was in zip(c.tensors()[:4], before[:4]):
+            assert torch.equal(got[g, : len(k)], was[g, at])

@@ -246,6 +246,11 @@ __device__ __forceinline__ void dma16(const void* base, uint32_t lane_off, uint3
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"(base) : "memory");
 }
+// ... from an address per lane
+__device__ __forceinline__ void dma16_at(const void* p, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(p) : "memory");
+}
 __device__ __forceinline__ void dma4(const void* base, uint32_t lane_off, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"(base) : "memory");

@@ -33,7 +33,20 @@ matrix-op result only after two later matrix ops have been issued plus explicit 
 transcendental result is never consumed by the next instruction, and M0 writes are followed
 by s_nop before the DMA instruction.
 
-Usage: python gen_attn_fwd128x2.py [output path]
+A second stream (RAGGED) serves heads whose rows do not fill the last 256-row block, and any
+number of row blocks per head.  It differs in the steering only:
+  * the last block of a head streams as many tiles as any block of its index, but from the tile
+    that holds row n on the fetch goes through an out-of-line piece that keeps every address
+    inside the head: a partial tile repeats bytes of its last row (its missing keys are masked
+    for every row that exists), tiles past it are fetched from the next block's first rows (no row that
+    exists reads them);
+  * Q rows past the end are clamped the same way, and their results are not stored (the
+    execution mask is narrowed around each store);
+  * two consecutive rounds of a workgroup are a pair (row block nqb-1-p of head 2a, row block p of
+    head 2a+1), which costs 4 (nqb + 1) tiles for every p, so nqb need not be a power of two.
+
+Usage: python gen_attn_fwd128x2.py                    both streams, next to this file
+       python gen_attn_fwd128x2.py [--ragged] PATH    one of them
 """
 import os
 import sys
@@ -78,6 +91,13 @@ LSEW = (94, 96)         # log-sum-exp pointers
 KPN, VPN = 98, 82       # K / V pointers of the block after this one (this one again after the last)
 SGN, SQBN = 84, 85      # its head and row block
 SLO, SHI = 40, 99
+# ragged stream only
+TP, PT, LIM = 68, 70, 71      # tile from which the fetch is out of line; the partial tile; its largest lane offset
+NVALID = (72, 73)       # rows of block 0 / 1 that exist (from its first one on; may be negative)
+X0, X1, X2, X3 = 74, 75, 76, 77 # scratch
+QOF = (223, 224)        # per-lane offsets of the Q loads, per block
+
+RAGGED = False
 
 STAGE = 32768           # one LDS stage: K tile (16 KB) then V tile (16 KB)
 NSTAGE = 4
@@ -375,6 +395,35 @@ def pv_steps(fifo, p0, p1, odd, flip, next_reads, blocks=(0, 1), extra=None):
     return steps
 
 
+FETCH_BACK = {"K": [], "V": []}
+FETCH_FAR = []
+
+
+def lane_offsets(lo, base):
+    """Per-lane global offsets of a tile's four loads.  The loads 0 and 2 share M0 with the loads 1 and
+    3 and carry an immediate offset of -4096: their registers hold 4096 more."""
+    return [f"v_add_u32 {v(lo + u)}, {(u | 1) * 4096}, %[{base}]" for u in range(4)]
+
+
+def far_fetch(which):
+    """Label of the out-of-line piece of one fetch of the ragged stream, which comes back to the
+    instruction after the branch: per-lane offsets and pointer for tile s[j] >= s[TP]."""
+    j, p, pn, lo, base = (KJ, KP, KPN, KL, "kl0") if which == "K" else (VJ, VP, VPN, VL, "vl0")
+    i = len(FETCH_BACK["K"]) + len(FETCH_BACK["V"])
+    far, back, past = (f"Lf{x}{i}_%=" for x in "abc")
+    FETCH_BACK[which].append(back)
+    FETCH_FAR.extend(
+        [f"{far}:"] + lane_offsets(lo, base)
+        + [f"s_cmp_eq_u32 s{j}, s{PT}", f"s_cbranch_scc0 {past}",
+           f"s_add_u32 s{X3}, s{LIM}, 4096"]
+        + [f"v_min_u32 {v(lo + u)}, s{LIM if u & 1 else X3}, {v(lo + u)}" for u in range(4)]
+        + [f"s_branch {back}", f"{past}:",
+           # a tile of this block past its rows, or (from s[NTMAX] on) of the next block
+           f"s_cmp_lt_u32 s{j}, s{NTMAX}", f"s_cselect_b64 {sp(p)}, {sp(pn)}, {sp(p)}",
+           f"s_branch {back}"])
+    return far
+
+
 def dma_lines(which):
     """Fetch of the next K (or V) tile into LDS stage (tile number) % NSTAGE.  The tile stream
     does not stop at the end of a 256-row block: after the block's last tile come the first
@@ -388,10 +437,14 @@ def dma_lines(which):
           f"s_add_u32 s{ST1}, s{ST1}, %[wave_lds]"]
     # the instruction's immediate offset moves the global and the LDS address alike, and the
     # four loads of a wave sit 4 KB apart in both: one M0 value serves two loads
+    # (ragged: each load has an offset register of its own, as rows are clamped one by one)
     for u in (1, 3):
         ln += [f"s_add_u32 m0, s{ST1}, {off + u * 4096}", "s_nop 0",
-               f"global_load_lds_dwordx4 {v(lo + u)}, {sp(p)} offset:-4096",
+               f"global_load_lds_dwordx4 {v(lo + u - (1 if RAGGED else 0))}, {sp(p)} offset:-4096",
                f"global_load_lds_dwordx4 {v(lo + u)}, {sp(p)}"]
+    if RAGGED:
+        ln = [f"s_cmp_lt_u32 s{j}, s{TP}", f"s_cbranch_scc0 {far_fetch(which)}",
+              f"{FETCH_BACK[which][-1]}:"] + ln
     ln += [f"s_add_u32 s{p}, s{p}, 16384", f"s_addc_u32 s{p + 1}, s{p + 1}, 0",
            f"s_add_u32 s{j}, s{j}, 1",
            f"s_cmp_eq_u32 s{j}, s{NTMAX}",
@@ -538,14 +591,32 @@ Q_LOADS = 16   # memory instructions q_loads() issues
 STORES = 18    # memory instructions the epilogue issues
 
 
+def q_clamp(b, row):
+    """Ragged: a 32-row block that starts past the head's last row takes the last 32 rows instead,
+    one that holds it reads its missing rows from the last row.  (head * n + row in s[row])"""
+    return [f"s_sub_u32 s{X0}, s{row}, s{SHEAD}",            # first row in the head
+            f"s_sub_u32 s{X1}, %[n], s{X0}",                 # rows that exist
+            f"s_sub_u32 s{X1}, s{X1}, 1",
+            f"s_lshl_b32 s{X1}, s{X1}, 8",
+            f"s_add_u32 s{X1}, s{X1}, 16",
+            f"s_add_u32 s{X2}, s{SHEAD}, %[n]",
+            f"s_sub_u32 s{X2}, s{X2}, 32",
+            f"s_cmp_lt_u32 s{X0}, %[n]",
+            f"s_cselect_b32 s{row}, s{row}, s{X2}",
+            f"s_cselect_b32 s{X1}, s{X1}, 0x7fffffff",
+            f"v_min_u32 {v(QOF[b])}, s{X1}, %[qoff]"]
+
+
 def q_pointers():
     """Pointers of this wave's Q rows for the block (s[SG], s[SQB])."""
-    return block_rows() + pointer(QW[0], "q", ST1, 8) + pointer(QW[1], "q", PAIR, 8)
+    clamp = q_clamp(0, ST1) + q_clamp(1, PAIR) if RAGGED else []
+    return block_rows() + clamp + pointer(QW[0], "q", ST1, 8) + pointer(QW[1], "q", PAIR, 8)
 
 
 def q_loads():
     """Q straight into the accumulation registers (B-operand fragments)."""
-    return [f"global_load_dwordx4 {ar(Q[b] + 4 * kk, 4)}, %[qoff], {sp(QW[b])} offset:{kk * 32}"
+    off = [v(QOF[b]) if RAGGED else "%[qoff]" for b in (0, 1)]
+    return [f"global_load_dwordx4 {ar(Q[b] + 4 * kk, 4)}, {off[b]}, {sp(QW[b])} offset:{kk * 32}"
             for b in (0, 1) for kk in range(8)]
 
 
@@ -555,13 +626,29 @@ def look_ahead():
     two rounds together cost every workgroup the same) and s[HASNEXT] = 1; after the last round
     they are the current block again (whose first tiles are then simply fetched once more) and
     s[HASNEXT] = 0.  s[KPN], s[VPN] = that block's K and V."""
-    return [f"s_add_u32 s{ST0}, s{J}, 1",
-            f"s_lshl_b32 s{ST1}, s{ST0}, 5",
-            f"s_add_u32 s{ST1}, s{ST1}, %[vid0]",
-            f"s_lshr_b32 s{PAIR}, s{ST1}, %[lgnqb]",
-            f"s_and_b32 s{ST1}, s{ST1}, %[nqbm1]",
-            f"s_sub_u32 s{OB}, %[nqbm1], s{ST1}",
-            f"s_and_b32 s{OB + 1}, s{ST0}, 1",
+    if RAGGED:
+        # rounds 2k, 2k+1: pair vid0 + 32 k = a * nqb + p (a by the high product with the reciprocal)
+        start = [f"s_add_u32 s{ST0}, s{J}, 1",
+                 f"s_lshr_b32 s{ST1}, s{ST0}, 1",
+                 f"s_lshl_b32 s{ST1}, s{ST1}, 5",
+                 f"s_add_u32 s{ST1}, s{ST1}, %[vid0]",
+                 f"s_mul_hi_u32 s{PAIR}, s{ST1}, %[nqm]",
+                 f"s_add_u32 s{OB}, %[nqbm1], 1",
+                 f"s_mul_i32 s{OB}, s{PAIR}, s{OB}",
+                 f"s_sub_u32 s{ST1}, s{ST1}, s{OB}",
+                 f"s_and_b32 s{OB + 1}, s{ST0}, 1",
+                 f"s_lshl_b32 s{PAIR}, s{PAIR}, 1",
+                 f"s_add_u32 s{PAIR}, s{PAIR}, s{OB + 1}",
+                 f"s_sub_u32 s{OB}, %[nqbm1], s{ST1}"]
+    else:
+        start = [f"s_add_u32 s{ST0}, s{J}, 1",
+                 f"s_lshl_b32 s{ST1}, s{ST0}, 5",
+                 f"s_add_u32 s{ST1}, s{ST1}, %[vid0]",
+                 f"s_lshr_b32 s{PAIR}, s{ST1}, %[lgnqb]",
+                 f"s_and_b32 s{ST1}, s{ST1}, %[nqbm1]",
+                 f"s_sub_u32 s{OB}, %[nqbm1], s{ST1}",
+                 f"s_and_b32 s{OB + 1}, s{ST0}, 1"]
+    return start + [
             f"s_cmp_eq_u32 s{OB + 1}, 1",                     # odd round: from the short end
             f"s_cselect_b32 s{ST1}, s{ST1}, s{OB}",
             f"s_cmp_lt_u32 s{ST0}, %[rounds]",
@@ -603,9 +690,12 @@ def setup(out):
     """Once per launch: constants, the first block's Q and its first tiles."""
     out.e("; ---- setup")
     out.e(f"v_mov_b32 {v(NEGINF)}, 0xff800000")
-    for u in range(4):
-        out.e(f"v_add_u32 {v(KL + u)}, {u * 4096}, %[kl0]")
-        out.e(f"v_add_u32 {v(VL + u)}, {u * 4096}, %[vl0]")
+    if RAGGED:
+        out.ext(lane_offsets(KL, "kl0") + lane_offsets(VL, "vl0"))
+    else:
+        for u in range(4):
+            out.e(f"v_add_u32 {v(KL + u)}, {u * 4096}, %[kl0]")
+            out.e(f"v_add_u32 {v(VL + u)}, {u * 4096}, %[vl0]")
     out.e(f"s_mov_b32 s{J}, 0")
     out.e(f"s_mov_b32 s{SG}, %[g0]")
     out.e(f"s_mov_b32 s{SQB}, %[qb0]")
@@ -618,6 +708,10 @@ def setup(out):
     out.e(f"s_add_u32 s{NTMAX}, s{NTMAX}, 4")
     out.e(f"s_mov_b32 s{KJ}, 0")
     out.e(f"s_mov_b32 s{VJ}, 0")
+    if RAGGED:
+        out.e(f"s_mov_b32 s{TP}, 0x7fffffff")   # the first four tiles of a block are whole
+        out.e(f"s_mov_b32 s{PT}, 0x7fffffff")
+        out.e(f"s_mov_b32 s{LIM}, 0x7fffffff")
     for which in "KKVKVKV":
         dma(out, which)
 
@@ -631,6 +725,18 @@ def prologue(out):
     out.ext(pointer(LSEW[0], "l", ST1, 2) + pointer(LSEW[1], "l", PAIR, 2))
     out.e(f"s_sub_u32 s{ST1}, s{ST1}, s{SHEAD}")
     out.e(f"s_sub_u32 s{PAIR}, s{PAIR}, s{SHEAD}")
+    if RAGGED:
+        out.e(f"s_sub_u32 s{NVALID[0]}, %[n], s{ST1}")
+        out.e(f"s_sub_u32 s{NVALID[1]}, %[n], s{PAIR}")
+        # the head's last row block: tile n / 64 is partial (or the first one past the rows)
+        out.e(f"s_lshr_b32 s{X0}, %[n], 6")
+        out.e(f"s_and_b32 s{X1}, %[n], 63")
+        out.e(f"s_lshl_b32 s{LIM}, s{X1}, 8")
+        out.e(f"s_sub_u32 s{LIM}, s{LIM}, 16")
+        out.e(f"s_cmp_eq_u32 s{SQB}, %[nqbm1]")
+        out.e(f"s_cselect_b32 s{TP}, s{X0}, 0x7fffffff")
+        out.e(f"s_cmp_eq_u32 s{X1}, 0")
+        out.e(f"s_cselect_b32 s{PT}, 0x7fffffff, s{TP}")
     out.e(f"s_lshr_b32 s{TF0}, s{ST1}, 6")
     out.e(f"s_lshr_b32 s{TF1}, s{PAIR}, 6")
     out.e(f"s_lshr_b32 s{NTMAX}, s{ST0}, 6")
@@ -656,7 +762,8 @@ def prologue(out):
         out.e(f"v_accvgpr_write_b32 a{i}, 0")
     # this block's Q rows (and, long before them, its first tiles) have arrived; only the last
     # block's output stores, which were issued after them, may still be under way
-    out.e(f"s_waitcnt vmcnt({STORES})")
+    # (ragged: stores whose rows do not exist must not count, so everything is waited for)
+    out.e(f"s_waitcnt vmcnt({0 if RAGGED else STORES})")
     out.e("s_barrier")             # also: every wave has left the last block's tiles
     # S0(0), then S1(0) with block 0's first softmax (the one that has to find a maximum)
     # riding between its matrix ops.  K(0)'s fragments are read once per pass, i.e. twice per
@@ -692,8 +799,12 @@ def epilogue(out):
                  f"v_log_f32 {v(lg)}, {v(l)}",
                  f"v_rcp_f32 {v(inv)}, {v(l)}",
                  "s_nop 0",
-                 f"v_add_f32 {v(lg)}, {v(lg)}, {v(m)}",
-                 f"global_store_dword %[l32x4], {v(lg)}, {sp(LSEW[b])}"])
+                 f"v_add_f32 {v(lg)}, {v(lg)}, {v(m)}"])
+        if RAGGED:
+            out.ext([f"s_lshl_b32 s{X0}, s{NVALID[b]}, 2", f"v_cmpx_gt_i32 vcc, s{X0}, %[l32x4]", "s_nop 4"])
+        out.e(f"global_store_dword %[l32x4], {v(lg)}, {sp(LSEW[b])}")
+        if RAGGED:
+            out.e("s_mov_b64 exec, -1")
         for db in range(4):
             for i4 in range(4):
                 t = TMP + 4 * (n % 2)          # two sets of four temporaries
@@ -720,10 +831,18 @@ def epilogue(out):
             if u == 4:
                 out.e(f"s_add_u32 s{OB}, s{OB}, 4096")
                 out.e(f"s_addc_u32 s{OB + 1}, s{OB + 1}, 0")
+            if RAGGED:   # rows 4u + lane / 16 below the number that exist
+                out.ext([f"s_lshl_b32 s{X0}, s{NVALID[b]}, 8", f"s_sub_u32 s{X0}, s{X0}, {u * 1024}",
+                         f"v_cmpx_gt_i32 vcc, s{X0}, %[lanex16]", "s_nop 4"])
             out.e(f"global_store_dwordx4 %[lanex16], {vr(S1[b] + 4 * u, 4)}, {sp(OB)} offset:{(u & 3) * 1024}")
+            if RAGGED:
+                out.e("s_mov_b64 exec, -1")
 
 
-def generate():
+def generate(ragged=False):
+    global RAGGED
+    RAGGED = ragged
+    FETCH_BACK["K"].clear(), FETCH_BACK["V"].clear(), FETCH_FAR.clear()
     out = Out()
     setup(out)
     block = out.label("blk")
@@ -777,6 +896,7 @@ def generate():
     done = out.label("done")
     out.e(f"s_branch {done}")
     out.ext(out.far)
+    out.ext(FETCH_FAR)
     out.e(f"{done}:")
     return out.lines
 
@@ -791,20 +911,30 @@ def clobbers():
     return ", ".join(f'"{x}"' for x in c)
 
 
-def main():
-    here = os.path.dirname(os.path.abspath(__file__))
-    args = sys.argv[1:]
-    path = args[0] if args else os.path.join(here, "attn_fwd128x2_body.inc")
-    lines = generate()
+def write(path, ragged):
+    name = "A2SF_FWD128X2R" if ragged else "A2SF_FWD128X2"
+    lines = generate(ragged)
     with open(path, "w") as f:
         f.write("// Written by gen_attn_fwd128x2.py; edit the generator, not this file.\n")
-        f.write("#define A2SF_FWD128X2_ASM \\\n")
+        f.write(f"#define {name}_ASM \\\n")
         for ln in lines:
             assert '"' not in ln and "\\" not in ln
             f.write(f'  "{ln}\\n" \\\n')
         f.write('  ""\n')
-        f.write(f"#define A2SF_FWD128X2_CLOBBERS {clobbers()}\n")
+        f.write(f"#define {name}_CLOBBERS {clobbers()}\n")
     print(f"{path}: {len(lines)} lines")
+
+
+def main():
+    here = os.path.dirname(os.path.abspath(__file__))
+    args = sys.argv[1:]
+    ragged = "--ragged" in args
+    paths = [a for a in args if a != "--ragged"]
+    if paths:
+        write(paths[0], ragged)
+    else:
+        write(os.path.join(here, "attn_fwd128x2_body.inc"), False)
+        write(os.path.join(here, "attn_fwd128x2r_body.inc"), True)
 
 
 if __name__ == "__main__":

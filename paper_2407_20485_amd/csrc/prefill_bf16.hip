@@ -386,15 +386,13 @@ __device__ __forceinline__ void dma_tile(const bf16_t* __restrict__ Mg, int row0
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int rr = lane >> 4, pc = lane & 15;
+  const bf16_t* base = Mg + (size_t)row0 * 128;
+  const int most = n - 1 - row0;  // rows past the end repeat the last one
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int lrow = (u * 4 + wave) * 4 + rr;
     const int c = pc ^ (V_LAYOUT ? v_swizzle(lrow) : k_swizzle(lrow));
-    int r = row0 + lrow;
-    r = r < n ? r : n - 1;
-    __builtin_amdgcn_global_load_lds((const void*)(Mg + (size_t)r * 128 + c * 8),
-                                     (__attribute__((address_space(3))) void*)(tile + (u * 4 + wave) * 1024),
-                                     16, 0, 0);
+    dma16(base, (uint32_t)(min(lrow, most) * 256 + c * 16), (uint32_t)(size_t)(tile + (u * 4 + wave) * 1024));
   }
 }
 
@@ -413,9 +411,7 @@ __device__ __forceinline__ void dma_tile2(const bf16_t* __restrict__ A, const bf
     int r = row0 + lrow;
     r = r < n ? r : n - 1;
     const bf16_t* src = r < off ? A + (size_t)r * 128 : B + (size_t)(r - off) * 128;
-    __builtin_amdgcn_global_load_lds((const void*)(src + c * 8),
-                                     (__attribute__((address_space(3))) void*)(tile + (u * 4 + wave) * 1024),
-                                     16, 0, 0);
+    dma16_at(src + c * 8, (uint32_t)(size_t)(tile + (u * 4 + wave) * 1024));
   }
 }
 
@@ -437,10 +433,7 @@ __device__ __forceinline__ void dma_full_tile(const bf16_t* __restrict__ Mg, int
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const char* base = reinterpret_cast<const char*>(Mg) + (size_t)row0 * 256;
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
-    __builtin_amdgcn_global_load_lds((const void*)(base + loff[u]),
-                                     (__attribute__((address_space(3))) void*)(tile + (u * 4 + wave) * 1024),
-                                     16, 0, 0);
+  for (int u = 0; u < 4; ++u) dma16(base, (uint32_t)loff[u], (uint32_t)(size_t)(tile + (u * 4 + wave) * 1024));
 }
 
 constexpr int kScoreOnlyNB = 1;   // 32-row query blocks per wave when no outputs are wanted
@@ -451,12 +444,10 @@ __global__ __launch_bounds__(kThreads, !WITH_O ? kScoreOnlyOcc : (NB == 1 ? 2 : 
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, float* __restrict__ LSE2, AttnRect rc, int G, int nqb, float scale_log2e) {
   constexpr int D = 128, BM = kWaves * 32 * NB, KK = D / 16, DB = D / 32;
-  // [stage][K tile | V tile]; without outputs there are no V tiles.  A deeper ring (tiles
-  // fetched three steps ahead) was measured for that pass and is slower: it costs occupancy.
+  // [stage][K tile | V tile], two stages: a tile is fetched one step ahead; without outputs there
+  // are no V tiles.  A deeper ring was measured for that pass and is slower: it costs occupancy.
   constexpr int kBuf = (WITH_O ? 2 : 1) * kTileBytes;
-  constexpr int RING = 2;                        // tiles are fetched RING - 1 steps ahead
-  constexpr int kLoadsPerTile = WITH_O ? 8 : 4;  // direct-to-LDS loads a wave issues per fetch
-  static_assert((RING - 2) * kLoadsPerTile <= 15, "pending loads must fit the wait count used below");
+  constexpr int RING = 2;
   __shared__ __attribute__((aligned(1024))) char smem[RING * kBuf];
   lds_char* const lds = (lds_char*)smem;
 
@@ -548,19 +539,12 @@ __global__ __launch_bounds__(kThreads, !WITH_O ? kScoreOnlyOcc : (NB == 1 ? 2 : 
       if (WITH_O) dma_tile<true>(Vg, t * kTile, nk, buf + kTileBytes);
     }
   };
-  // a wave's loads complete in order: tile t has landed once at most the loads of the tiles
-  // fetched after it are outstanding
-  // `later` = tiles fetched after the one that is needed (at most RING - 2)
-  auto wait_all_but = [&](int later) {
-    if (later >= 2 && RING > 2) __builtin_amdgcn_s_waitcnt(0x0f70 | (2 * kLoadsPerTile));
-    else if (later == 1 && RING > 2) __builtin_amdgcn_s_waitcnt(0x0f70 | kLoadsPerTile);
-    else __builtin_amdgcn_s_waitcnt(0x0f70);
-  };
+  fetch(0, lds);
 #pragma unroll
-  for (int i = 0; i < RING - 1; ++i)
-    if (i < ntiles) fetch(i, lds + i * kBuf);
-  wait_all_but(min(RING - 2, ntiles - 1));  // tile 0; tiles 1 .. RING-2 may still be on their way
-  __syncthreads();
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qf[nb][kk].x));  // waited for here, not in the loop
+  wait_vm_barrier<0>();
 
   auto tile_step = [&](int t, const lds_char* kt, const lds_char* vt_) {
     const int key0 = t * kTile;
@@ -704,11 +688,9 @@ __global__ __launch_bounds__(kThreads, !WITH_O ? kScoreOnlyOcc : (NB == 1 ? 2 : 
       const int t = t0 + b;
       if (t >= ntiles) break;
       // the stage of tile t - 1 is free: every wave passed the barrier that ended its step
-      if (t + RING - 1 < ntiles) fetch(t + RING - 1, lds + ((b + RING - 1) % RING) * kBuf);
+      if (t + 1 < ntiles) fetch(t + 1, lds + ((b + 1) % RING) * kBuf);
       tile_step(t, lds + b * kBuf, lds + b * kBuf + kTileBytes);
-      // tile t + 1 for every wave of the workgroup
-      wait_all_but(min(RING - 2, ntiles - 2 - t));
-      __syncthreads();
+      wait_vm_barrier<0>();  // tile t + 1 for every wave of the workgroup
     }
   }
 
@@ -759,6 +741,7 @@ __global__ __launch_bounds__(kThreads, !WITH_O ? kScoreOnlyOcc : (NB == 1 ? 2 : 
 // per-lane offsets and per-wave pointers and hands them to that stream.  Requires
 // n % 256 == 0 and an output pointer.
 #include "attn_fwd128x2_body.inc"
+#include "attn_fwd128x2r_body.inc"
 
 constexpr int kX2Rows = 256;             // query rows per workgroup and block
 constexpr int kX2RingBytes = 4 * 32768;  // four stages of one K tile + one V tile
@@ -842,6 +825,91 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd128x2_kernel(
                  [wodd] "s"(wodd), [wave_lds] "s"(wave_lds), [kvs] "s"(kv_shift), [kvm] "s"(kv_magic),
                  [scale] "s"(scale_log2e)
                : A2SF_FWD128X2_CLOBBERS);
+}
+
+// The same for any n >= 512 and any number of row blocks per head (nqb = ceil(n / 256)): the stream
+// that clamps the fetches and narrows the stores of a head's last row block.
+// rounds > 1 (8 * kX2Slots workgroups): the work is the pairs P = a * nqb + p, (row block
+// nqb - 1 - p of head 2a, row block p of head 2a + 1); the workgroup in slot r of XCD x takes the
+// pairs x * (pairs / 8) + r + 32 k, k = 0 .. rounds / 2 - 1.
+// rounds == 1: first the `odd` blocks of a head without partner (head GQ - 1), longest first, then
+// the longer blocks of the pairs pair_base .. pair_base + pairs - 1, then the shorter ones.
+__global__ __launch_bounds__(kThreads, 1) void attn_fwd128x2r_kernel(
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+    bf16_t* __restrict__ O, float* __restrict__ LSE2, int n, int nqb, unsigned nqm, int GQ, int odd,
+    int pair_base, int pairs, int rounds, int kv_shift, unsigned kv_magic, float scale_log2e) {
+  __shared__ __attribute__((aligned(1024))) char smem[kX2LdsBytes];
+  int g0, qb0, vid0 = 0;
+  if (rounds > 1) {
+    vid0 = (int)(blockIdx.x % 8) * (pairs / 8) + (int)(blockIdx.x / 8);
+    g0 = 2 * (vid0 / nqb);
+    qb0 = nqb - 1 - vid0 % nqb;
+  } else if ((int)blockIdx.x < odd) {
+    g0 = GQ - 1;
+    qb0 = nqb - 1 - (int)blockIdx.x;
+  } else {
+    const int per = (pairs + 7) / 8, b = (int)blockIdx.x - odd;
+    const int second = b / (8 * per), i = (b % 8) * per + (b % (8 * per)) / 8;
+    if (i >= pairs) return;
+    const int P = pair_base + i, p = P % nqb;
+    const int longer = p < nqb - 1 - p ? 0 : 1;  // of the blocks nqb - 1 - p and p
+    const int which = second ^ longer;           // 0: row block nqb - 1 - p of the even head
+    g0 = 2 * (P / nqb) + which;
+    qb0 = which ? p : nqb - 1 - p;
+  }
+  g0 = __builtin_amdgcn_readfirstlane(g0);
+  qb0 = __builtin_amdgcn_readfirstlane(qb0);
+  const int nqbm1 = nqb - 1;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  const unsigned lds0 = (unsigned)(size_t)smem;  // LDS byte address of the stage ring
+
+  // K fragment (16 d-chunk 2kk+h of key row l32): row base and the kk-independent swizzle term
+  const unsigned krow = lds0 + l32 * 256, hx16 = (unsigned)((h ^ k_swizzle(l32)) << 4);
+  // V fragment (see attn_fwd128_kernel): source lane (r, qd) of group gq, key rows 4h + r
+  const int i16 = lane & 15, r4 = i16 >> 2, qd = i16 & 3, gq = (lane >> 4) & 1;
+  const unsigned clvs16 = (unsigned)(((2 * gq + (qd >> 1)) ^ v_swizzle(r4)) << 4);
+  const unsigned vrow = lds0 + kTileBytes + (4 * h + r4) * 256 + (qd & 1) * 8;
+  // DMA: this wave fills rows 16u + 4 wave + rr of a tile, lane (rr, pc) the chunk slot pc
+  const int rr = lane >> 4, pc = lane & 15, lrow = 4 * wave + rr;
+  const unsigned kl0 = (unsigned)(lrow * 256 + ((pc ^ k_swizzle(lrow)) << 4));
+  const unsigned vl0 = (unsigned)(lrow * 256 + ((pc ^ v_swizzle(lrow)) << 4));
+  const unsigned qoff = (unsigned)(l32 * 256 + h * 16);
+  const int lv = l32 - 4 * h;
+  const unsigned l32x4 = l32 * 4, lanex16 = lane * 16;
+  // epilogue: a wave's 32 x 128 output blocks go, one after the other, through its own 8 KB
+  // strip of LDS above the ring
+  const unsigned strip = lds0 + kX2RingBytes + wave * 8192;
+  const unsigned strip_w = strip + l32 * 256 + 8 * h, x16 = (unsigned)((l32 & 15) << 4);
+  const unsigned strip_r = strip + rr * 256, crr16 = (unsigned)((pc ^ rr) << 4);
+
+  // Rows: a 256-row block is cut into eight 32-row blocks; wave w owns blocks w ("block 0")
+  // and 7 - w ("block 1"), so that every wave has the same number of key tiles to go through
+  // although the rows further down see more keys.
+  const int w32a = 32 * wave, w32b = 32 * (7 - wave), wodd = wave & 1;
+  const unsigned wave_lds = lds0 + wave * 1024;
+  const unsigned long long qa = (unsigned long long)Q, ka = (unsigned long long)K,
+                           va = (unsigned long long)V, oa = (unsigned long long)O,
+                           la = (unsigned long long)LSE2;
+
+  asm volatile(A2SF_FWD128X2R_ASM
+               :
+               : [hx16] "v"(hx16), [krow] "v"(krow), [clvs16] "v"(clvs16), [vrow] "v"(vrow),
+                 [kl0] "v"(kl0), [vl0] "v"(vl0), [qoff] "v"(qoff), [lv] "v"(lv),
+                 [l32x4] "v"(l32x4), [lanex16] "v"(lanex16), [strip_w] "v"(strip_w),
+                 [x16] "v"(x16), [crr16] "v"(crr16), [strip_r] "v"(strip_r),
+                 [qlo] "s"((unsigned)qa), [qhi] "s"((unsigned)(qa >> 32)),
+                 [klo] "s"((unsigned)ka), [khi] "s"((unsigned)(ka >> 32)),
+                 [vlo] "s"((unsigned)va), [vhi] "s"((unsigned)(va >> 32)),
+                 [olo] "s"((unsigned)oa), [ohi] "s"((unsigned)(oa >> 32)),
+                 [llo] "s"((unsigned)la), [lhi] "s"((unsigned)(la >> 32)),
+                 [n] "s"(n), [g0] "s"(g0), [qb0] "s"(qb0), [vid0] "s"(vid0), [rounds] "s"(rounds),
+                 [nqm] "s"(nqm), [nqbm1] "s"(nqbm1), [w32a] "s"(w32a), [w32b] "s"(w32b),
+                 [wodd] "s"(wodd), [wave_lds] "s"(wave_lds), [kvs] "s"(kv_shift), [kvm] "s"(kv_magic),
+                 [scale] "s"(scale_log2e)
+               : A2SF_FWD128X2R_CLOBBERS);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1010,14 +1078,14 @@ void launch_fwd(const void* q, const void* k, const void* v, int G_kv, int n, vo
     // Two query blocks per wave pay off once a workgroup streams enough key tiles to amortise
     // the start and end of a row block: from n = 2048 with one workgroup per block, from
     // n = 512 in the persistent form, which overlaps them with the neighbouring blocks.
-    if (o && n % kX2Rows == 0 && (long long)G * n < (1ll << 31)) {
-      const int nqb2 = n / kX2Rows;
+    if (o && n >= kX2MinRowsPersistent && (long long)G * n < (1ll << 31)) {
+      const int nqb2 = (n + kX2Rows - 1) / kX2Rows;
       const long long items = (long long)G * nqb2;
-      // persistent form: needs the id arithmetic of its later rounds to be shifts and an even
-      // number of full rounds (two rounds together cost every workgroup the same)
-      const bool persistent = (nqb2 & (nqb2 - 1)) == 0 && nqb2 <= kX2Slots &&
-                              items >= 2 * 8 * kX2Slots && items < (1ll << 31);
-      if (n >= kX2MinRows || (persistent && n >= kX2MinRowsPersistent)) {
+      const int chunk = 2 * 8 * kX2Slots;  // items of two rounds of the persistent launch
+      const bool persistent = items >= chunk && items < (1ll << 31);
+      // whole row blocks whose number divides a round: ids are split by shifts
+      const bool aligned = n % kX2Rows == 0 && (nqb2 & (nqb2 - 1)) == 0 && nqb2 <= kX2Slots;
+      if (persistent && aligned) {
         auto launch = [&](int id_base, int ids, int rounds) {
           const unsigned grid2 = rounds > 1 ? 8 * kX2Slots : (unsigned)(((ids + 7) / 8) * 8);
           hipLaunchKernelGGL(attn_fwd128x2_kernel, dim3(grid2), dim3(kThreads), 0, st,
@@ -1026,10 +1094,24 @@ void launch_fwd(const void* q, const void* k, const void* v, int G_kv, int n, vo
         };
         // persistent part: an even number of full rounds; what is left over goes one workgroup
         // per row block
-        const int chunk = 2 * 8 * kX2Slots;
-        const int main_ids = persistent ? (int)(items / chunk) * chunk : 0;
-        if (main_ids) launch(0, main_ids, main_ids / (8 * kX2Slots));
+        const int main_ids = (int)(items / chunk) * chunk;
+        launch(0, main_ids, main_ids / (8 * kX2Slots));
         if (items > main_ids) launch(main_ids, (int)(items - main_ids), 1);
+        return;
+      }
+      if (n >= kX2MinRows || persistent) {
+        const unsigned nqm = (unsigned)((1ull << 32) / (unsigned)nqb2) + 1u;  // exact below 2^32 / nqb2
+        const int all = (G / 2) * nqb2, odd = (G % 2) * nqb2;
+        auto launch = [&](int odd_blocks, int base, int pairs, int rounds) {
+          const unsigned grid2 = rounds > 1 ? 8 * kX2Slots : (unsigned)(odd_blocks + 16 * ((pairs + 7) / 8));
+          hipLaunchKernelGGL(attn_fwd128x2r_kernel, dim3(grid2), dim3(kThreads), 0, st, (const bf16_t*)q,
+                             (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, lse2, n, nqb2, nqm, G, odd_blocks,
+                             base, pairs, rounds, kv_shift, kv_magic, scale_log2e);
+        };
+        // pairs of whole double rounds in the persistent form (its ids stay below 2^32 / nqb2: n < 2^24)
+        const int main_pairs = (long long)all * nqb2 < (1ll << 32) ? all / (8 * kX2Slots) * (8 * kX2Slots) : 0;
+        if (main_pairs) launch(0, 0, main_pairs, main_pairs / (4 * kX2Slots));
+        if (odd || all > main_pairs) launch(odd, main_pairs, all - main_pairs, 1);
         return;
       }
     }
@@ -1303,9 +1385,7 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_stream128_kernel(
     const int stage = (t_last - t) % kStreamStages;
     const int tt = max(t, 0);
     dma_tile<false>(Qg, tt * kTile, n, qs + stage * kTileBytes);
-    __builtin_amdgcn_global_load_lds((const void*)(lse + min(tt * kTile + lane, n - 1)),
-                                     (__attribute__((address_space(3))) void*)(lse_s + stage * 256),
-                                     4, 0, 0);
+    dma4(lse + (size_t)tt * kTile, (uint32_t)(min(lane, n - 1 - tt * kTile) * 4), (uint32_t)(size_t)(lse_s + stage * 256));
   };
   fetch(t_last);
   fetch(t_last - 1);
@@ -1329,13 +1409,16 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_stream128_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
 
+#pragma unroll
+  for (int b = 0; b < kStreamKB; ++b)
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(kf[b][kk].x));  // waited for here, not in the loop
   const RowWindow win(tol, log2_alpha);
   int lim = max(wc0, first_row);   // rows before `lim` add nothing to this wave's keys
   for (int t = t_last; t >= t_first; --t) {
     // tile t has landed: of this wave's fetches only those of tiles t-1 and t-2 (five loads
     // each) may still be under way
-    __builtin_amdgcn_s_waitcnt(0x0f70 | 10);  // vmcnt(10)
-    __syncthreads();
+    wait_vm_barrier<10>();
     fetch(t - 3);  // into the stage of tile t+1, which every wave has left
     const int row0 = t * kTile;
     if (row0 + kTile - 1 >= lim) {  // some row of the tile counts for a key of this wave
@@ -1398,7 +1481,7 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_stream128_kernel(
       t_first = max(t_first, wl / kTile);
     }
   }
-  __builtin_amdgcn_s_waitcnt(0x0f70);  // tiles fetched ahead of the last one used: let them land
+  wait_vm<0>();  // tiles fetched ahead of the last one used: let them land
   // sum over the 32 rows held by the lanes of one half
 #pragma unroll
   for (int b = 0; b < kStreamKB; ++b) {

@@ -112,3 +112,25 @@ def test_compaction_rounds(dtype, d):
         at = torch.from_numpy(k).cuda()
         for got, was in zip(c.tensors()[:4], before[:4]):
             assert torch.equal(got[g, : len(k)], was[g, at])
+
+
+@pytest.mark.parametrize("n,G", [(2049, 3), (2111, 2), (2240, 1), (2303, 3),          # one workgroup per row block
+                                 (513, 261), (640, 300), (767, 172), (1000, 129), (1537, 74)])   # pairs of blocks, plus the rest
+def test_ragged_prompts_of_whole_blocks_and_a_rest(n, G):
+    """The ragged attention stream: last row blocks of 1 to 255 rows, odd and even numbers of heads,
+    row blocks whose number is no power of two; outputs and scores of the first, middle and last heads."""
+    w = variant(1, heads=G, d=128, n=n, T=1, select=11, recent=9, name="ragged prompt")
+    sample = sorted({0, 1, G // 2, G - 2, G - 1} & set(range(G)))
+    p = parity.Problem(w, sample=sample)
+    guard = torch.full((G * n * 128 + 4096,), 7.0, dtype=torch.bfloat16, device="cuda")
+    o = guard[: G * n * 128].view(G, n, 128)
+    a2sf.a2sf_prefill(p.dev["q"], p.dev["k"], p.dev["v"], n, 0.6, 11, 9, p.cache, o=o, workspace=p.ws)
+    torch.cuda.synchronize()
+    assert bool((guard[G * n * 128:] == 7.0).all())          # nothing stored past the last row
+    assert bool(torch.isfinite(o.float()).all())
+    p.fetch()
+    for i in sample:
+        Q, K, V = (x[:n] for x in p.host[i])
+        O, S, oc = orc.prefill(Q, K, V, float(np.float32(0.6)), 11, 9)
+        assert np.abs(parity.to_f64(o[i]) - O).max() <= parity.O_TOL["bf16"]
+        parity.compare_cache(p, i, oc, f"head {i}", ordered=True)

@@ -152,8 +152,7 @@ a2sf_status prefill_impl(const void* q, const void* k, const void* v, int32_t n,
       launch_prefill_bf16(qp, kp, vp, Gp, n, d, op, lp, st, op ? 0 : bf16_first_lse_row(n, d, alpha));
       launch_scores_bf16(qp, kp, lp, Gp, n, d, alpha, ap, tol, sp, st);
     }
-    launch_select(sp, nullptr, nullptr, Gp, n, n, budget.select, budget.recent, kip, nkp, st);
-    launch_gather_prompt(kp, vp, sp, n, kip, B, nkp, cp, st);
+    launch_select_gather(kp, vp, sp, n, budget.select, budget.recent, kip, nkp, cp, st);
   }
   return launch_status();
 }
@@ -350,8 +349,7 @@ a2sf_status a2sf_prefill_gqa(const void* q, const void* k, const void* v, int32_
       launch_attn_bf16(qp, kp, vp, Gp, rc, d, op, lp, st);
       launch_colscores_bf16(qp, kp, lp, Gp, rc, n, d, alpha, sp, n, false, 0.f, st);
     }
-    launch_select(sp, nullptr, nullptr, Gp, n, n, budget.select, budget.recent, kip, nkp, st);
-    launch_gather_prompt(kp, vp, sp, n, kip, B, nkp, cp, st);
+    launch_select_gather(kp, vp, sp, n, budget.select, budget.recent, kip, nkp, cp, st);
   }
   return launch_status();
 }

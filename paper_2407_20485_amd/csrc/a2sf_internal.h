@@ -18,10 +18,10 @@ void launch_select(const float* scores, const int32_t* pos, const int32_t* len, 
 void launch_compact(const a2sf_cache& c, const int32_t* keep_idx, int keep_stride,
                     const int32_t* n_keep, hipStream_t st, const void* k2 = nullptr,
                     const void* v2 = nullptr, int m2 = 0, const int32_t* off_heads = nullptr);
-// Out-of-place gather of the prompt's surviving rows into the cache.
-void launch_gather_prompt(const void* k, const void* v, const float* scores_full, int n,
-                          const int32_t* keep_idx, int keep_stride, const int32_t* n_keep,
-                          const a2sf_cache& c, hipStream_t st);
+// Selection on a prompt's scores [G, n] and gather of the surviving rows into the cache.
+void launch_select_gather(const void* k, const void* v, const float* scores_full, int n, int select,
+                          int recent, int32_t* keep_idx, int32_t* n_keep, const a2sf_cache& c,
+                          hipStream_t st);
 
 // decode.hip
 struct DecodePlan {

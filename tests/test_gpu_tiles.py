@@ -134,3 +134,12 @@ def test_ragged_prompts_of_whole_blocks_and_a_rest(n, G):
         O, S, oc = orc.prefill(Q, K, V, float(np.float32(0.6)), 11, 9)
         assert np.abs(parity.to_f64(o[i]) - O).max() <= parity.O_TOL["bf16"]
         parity.compare_cache(p, i, oc, f"head {i}", ordered=True)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 128)])
+@pytest.mark.parametrize("budget,n", [(7, 40), (511, 700), (512, 700), (513, 700), (512, 300), (513, 300)])
+def test_gather_list_lengths(dtype, d, budget, n):
+    """Keep lists of up to 512 slots are copied by the workgroup that selects, longer ones by a kernel
+    of their own: both sides of the line, full lists and prompts shorter than the budget."""
+    prompt_and_steps(variant(1 if dtype == "bf16" else 0, heads=3, d=d, dtype=dtype, n=n, T=1, select=budget // 2,
+                             recent=budget - budget // 2, name="list lengths"), 0.8, steps=1)

@@ -149,7 +149,7 @@ a2sf_status prefill_impl(const void* q, const void* k, const void* v, int32_t n,
       launch_scores_f32((const float*)qp, (const float*)kp, lp, Gp, n, d, alpha, ap, sp, st);
     } else {
       // without outputs only the rows the score kernel will read need their log-sum-exp
-      launch_prefill_bf16(qp, kp, vp, Gp, n, d, op, lp, st, op ? 0 : bf16_first_lse_row(n, d, alpha));
+      launch_prefill_bf16(qp, kp, vp, Gp, n, d, op, lp, st, op ? 0 : bf16_first_lse_row(n, alpha));
       launch_scores_bf16(qp, kp, lp, Gp, n, d, alpha, ap, tol, sp, st);
     }
     launch_select_gather(kp, vp, sp, n, budget.select, budget.recent, kip, nkp, cp, st);
@@ -251,9 +251,9 @@ a2sf_status chunk_impl(const void* q, const void* k, const void* v, int32_t m, i
   AttnRect rc{m, C, len_old};
   rc.kv_group = group;
   const float decay = alpha > 0.f ? powf(alpha, (float)m) : 0.f;   // 0^m = 0 for m >= 1
-  // Where the kernels can read the chunk's K/V rows from the call's inputs, the rows are not
-  // copied behind the cached ones first: the compaction copies in those that are kept.
-  const bool two_source = cache->dtype == A2SF_BF16 && bf16_two_source_ok(d, rc, alpha);
+  // The bf16 kernels read the chunk's K/V rows from the call's inputs: the rows are not copied
+  // behind the cached ones first, the compaction copies in those that are kept.
+  const bool two_source = cache->dtype == A2SF_BF16;
   if (two_source) { rc.k2 = k; rc.v2 = v; }
 
   launch_chunk_append(k, v, m, pos0, *cache, len_old, !two_source, st);
@@ -316,7 +316,7 @@ a2sf_status a2sf_prefill_gqa(const void* q, const void* k, const void* v, int32_
   rc.kv_group = group;
   // without outputs only the rows the score kernel will read need their log-sum-exp
   if (!o)
-    rc.first_row = cache->dtype == A2SF_BF16 ? bf16_first_lse_row(n, cache->d, alpha) : f32_first_lse_row(n, alpha);
+    rc.first_row = cache->dtype == A2SF_BF16 ? bf16_first_lse_row(n, alpha) : f32_first_lse_row(n, alpha);
   // in parts of kPrefillPartHeads query heads, as the plain prompt phase and for the same reason
   const size_t e = cache->dtype == A2SF_F32 ? 4 : 2;
   const int B = budget.select + budget.recent;

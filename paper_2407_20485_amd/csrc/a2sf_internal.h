@@ -71,19 +71,15 @@ struct AttnRect {
   int kv_stride;
   const int32_t* off_heads;  // [G] device, or null: 0 for every head
   int kv_group = 1;
-  // Second source of key / value rows (bf16, d = 128, kv_group = 1 only): when set, a head's
+  // Second source of key / value rows (bf16 only): when set, a head's
   // keys 0 .. off-1 are rows of k / v and its keys off .. off+m-1 are the m rows [G, m, d] of
   // k2 / v2 -- a chunk whose rows have not been copied behind the cached ones.
   const void* k2 = nullptr;
   const void* v2 = nullptr;
-  // Calls without outputs (fp32; bf16 with d = 128): the log-sum-exp of the rows before first_row
-  // is not needed (the score kernel that follows skips them), so their row blocks are not computed.
+  // Calls without outputs: the log-sum-exp of the rows before first_row is not needed (the score
+  // kernel that follows skips them), so their row blocks are not computed.
   int first_row = 0;
 };
-// true when launch_attn_bf16 / launch_colscores_bf16 serve these sizes with kernels that read a
-// second key / value source
-bool bf16_two_source_ok(int d, const AttnRect& rc, float alpha);
-
 // prefill_f32.hip / prefill_bf16.hip
 // lse2[g][i] = log2(sum_j exp(s_ij)) of the masked row i (s already scaled by 1/sqrt(d)).
 void launch_prefill_f32(const float* q, const float* k, const float* v, int G, int n, int d,
@@ -113,7 +109,7 @@ void launch_prefill_bf16(const void* q, const void* k, const void* v, int G, int
                          void* o, float* lse2, hipStream_t st, int first_row = 0);
 // First prompt row whose log-sum-exp launch_scores_bf16 reads for these sizes (Section 3.3: the
 // forgetting factor takes older rows' contributions to 0; exactly 0 in fp32 before that row).
-int bf16_first_lse_row(int n, int d, float alpha_max);
+int bf16_first_lse_row(int n, float alpha_max);
 // tol > 0 (d = 128 only): rows whose whole remaining contribution is provably below tol * S_j
 // are skipped (see RowWindow in prefill_bf16.hip); tol = 0 computes every row of nonzero weight.
 void launch_scores_bf16(const void* q, const void* k, const float* lse2, int G, int n, int d,

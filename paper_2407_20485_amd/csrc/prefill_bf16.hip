@@ -27,94 +27,16 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 64;  // keys (attn_fwd) or query rows (col_scores) per LDS tile
-constexpr float kLazyRescale = 8.0f;  // log2 units
 constexpr int kPrefetch = 4;  // LDS fragment reads in flight ahead of their matrix op
-constexpr int kFwdNB = 1;     // 32-row query blocks per wave in attn_fwd_bf16_kernel / attn_fwd128_kernel
-constexpr int kFwdOcc = 2;    // workgroups per compute unit the register budget of attn_fwd_bf16_kernel is sized for
 
 __device__ __forceinline__ f32x16 mfma_bf16(const uint4& a, const uint4& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// ---- LDS layouts ----------------------------------------------------------------------
-// Row tile [64][D] bf16 in 16-byte chunks, chunk index XOR-swizzled by the row so that the
-// 16 lanes of a quarter-wave reading one chunk column of 16 consecutive rows hit 16
-// different bank groups, and the 16 lanes writing one row do too.
-template <int D>
-__device__ __forceinline__ int row_tile_unit(int row, int chunk) {
-  constexpr int CPR = D / 8;
-  const int swz = (CPR == 16) ? (row & 15) : ((row >> 1) & 7);
-  return row * CPR + (chunk ^ swz);
-}
-// Transposed V tile [D][64 keys] bf16, 128 bytes per d-row = 8 chunks of 8 keys.  Inside
-// each group of 16 keys the keys are stored in the order the matrix-core operand wants:
-// key kappa sits at 8*((kappa>>2)&1) + (kappa&3) + 4*(kappa>>3).
-__device__ __forceinline__ int vt_swizzle(int d) { return ((d >> 1) ^ (d >> 4)) & 7; }
-
-template <int D>
-struct Stage {
-  static constexpr int CPR = D / 8;
-  static constexpr int KU = kTile * CPR / kThreads;        // K units (16 B) per thread
-  static constexpr int VTASKS = 16 * CPR;                  // (key quad, d chunk) tasks
-  uint4 kreg[KU];
-  uint4 vreg[4];
-
-  template <bool WITH_V>
-  __device__ __forceinline__ void load(const bf16_t* __restrict__ Kg, const bf16_t* __restrict__ Vg,
-                                       int row0, int n) {
-    const int tid = threadIdx.x;
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const int unit = tid + u * kThreads;
-      int r = row0 + unit / CPR;
-      r = r < n ? r : n - 1;
-      kreg[u] = load16(Kg + (size_t)r * D + (unit % CPR) * 8);
-    }
-    if (WITH_V && tid < VTASKS) {
-      const int dc = tid % CPR, kq = tid / CPR;
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        int r = row0 + 4 * kq + rr;
-        r = r < n ? r : n - 1;
-        vreg[rr] = load16(Vg + (size_t)r * D + dc * 8);
-      }
-    }
-  }
-  template <bool WITH_V>
-  __device__ __forceinline__ void store(uint4* ks, char* vt) const {
-    const int tid = threadIdx.x;
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const int unit = tid + u * kThreads;
-      ks[row_tile_unit<D>(unit / CPR, unit % CPR)] = kreg[u];
-    }
-    if (WITH_V && tid < VTASKS) {
-      const int dc = tid % CPR, kq = tid / CPR;
-      const int chunk = 2 * (kq >> 2) + (kq & 1), half = (kq & 3) >> 1;
-      const uint32_t* x0 = reinterpret_cast<const uint32_t*>(&vreg[0]);
-      const uint32_t* x1 = reinterpret_cast<const uint32_t*>(&vreg[1]);
-      const uint32_t* x2 = reinterpret_cast<const uint32_t*>(&vreg[2]);
-      const uint32_t* x3 = reinterpret_cast<const uint32_t*>(&vreg[3]);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int w = i >> 1, d = dc * 8 + i;
-        uint2 out;
-        if (i & 1) {
-          out.x = (x0[w] >> 16) | (x1[w] & 0xFFFF0000u);
-          out.y = (x2[w] >> 16) | (x3[w] & 0xFFFF0000u);
-        } else {
-          out.x = (x0[w] & 0xFFFFu) | (x1[w] << 16);
-          out.y = (x2[w] & 0xFFFFu) | (x3[w] << 16);
-        }
-        *reinterpret_cast<uint2*>(vt + d * 128 + ((chunk ^ vt_swizzle(d)) << 4) + half * 8) = out;
-      }
-    }
-  }
-};
 
 // Workgroup id -> flat work id such that each of the 8 accelerator dies (which receive
 // consecutive workgroup ids round-robin) works on a contiguous range of work ids, i.e. on
@@ -125,223 +47,9 @@ __device__ __forceinline__ long long xcd_contiguous_id(long long total) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Geometry as in AttnRect: n = rc.m query rows per head; row i sees keys 0 .. off + i of the nk =
-// off + n keys of its head (the prompt phase: off = 0, the keys are the rows' own).
-template <int D, int NB, bool WITH_O>
-__global__ __launch_bounds__(kThreads, kFwdOcc) void attn_fwd_bf16_kernel(
-    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-    bf16_t* __restrict__ O, float* __restrict__ LSE2, AttnRect rc, int G, int nqb, float scale_log2e) {
-  constexpr int BM = kWaves * 32 * NB;
-  constexpr int CPR = D / 8;
-  constexpr int KK = D / 16;   // k-steps of the first product
-  constexpr int DB = D / 32;   // 32-wide blocks of the head dimension
-  __shared__ uint4 ks[2][kTile * CPR];
-  __shared__ __attribute__((aligned(16))) char vt[WITH_O ? 2 : 1][WITH_O ? D * 128 : 16];
-
-  const long long total = (long long)G * nqb;
-  const long long vid = xcd_contiguous_id(total);
-  if (vid >= total) return;
-  const int g = (int)(vid / nqb);
-  const int qb = nqb - 1 - (int)(vid % nqb);  // longest rows first
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: branches on it are scalar
-  const int l32 = lane & 31, h = lane >> 5;
-  const int n = rc.m;
-  const int gk = g / rc.kv_group;  // the K/V head this query head reads
-  const int off = rc.off_heads ? rc.off_heads[gk] : 0;
-  const int row0 = qb * BM;
-  if (off < 0) {  // a head the caller's precondition excludes: its rows are flagged with NaN
-    if (WITH_O)
-      for (int e = tid; e < min(BM, n - row0) * D; e += kThreads)
-        O[((size_t)g * n + row0) * D + e] = (bf16_t)0x7FC0;
-    return;
-  }
-  const int nk = off + n;  // keys of this head
-  const bf16_t* Qg = Q + (size_t)g * n * D;
-  const bf16_t* Kg = K + (size_t)gk * rc.kv_stride * D;
-  const bf16_t* Vg = V + (size_t)gk * rc.kv_stride * D;
-  const int wrow0 = row0 + wave * 32 * NB;  // first query row of this wave
-
-  // Q fragments (B operand): lane (query l32, half h) holds Q[query][16kk + 8h .. +7]
-  uint4 qf[NB][KK];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    int r = wrow0 + nb * 32 + l32;
-    r = r < n ? r : n - 1;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[nb][kk] = load16(Qg + (size_t)r * D + kk * 16 + h * 8);
-  }
-
-  f32x16 oacc[NB][DB];
-  float m[NB], lsum[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    m[nb] = -INFINITY;
-    lsum[nb] = 0.f;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) oacc[nb][db][i] = 0.f;
-  }
-
-  const int last_key = off + min(n, row0 + BM) - 1;  // newest key the block's rows see
-  const int ntiles = last_key / kTile + 1;
-  Stage<D> stg;
-  stg.template load<WITH_O>(Kg, Vg, 0, nk);
-  stg.template store<WITH_O>(ks[0], vt[0]);
-  __syncthreads();
-
-  for (int t = 0; t < ntiles; ++t) {
-    const int buf = t & 1;
-    if (t + 1 < ntiles) stg.template load<WITH_O>(Kg, Vg, (t + 1) * kTile, nk);
-    const int key0 = t * kTile;
-    if (key0 <= off + wrow0 + 32 * NB - 1) {  // some key of the tile is visible to this wave
-      // ---- S^T = K Q^T
-      f32x16 sacc[NB][2];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) sacc[nb][kb][i] = 0.f;
-      {
-        // fragment i = (kk, kb): the two key blocks alternate so that consecutive matrix
-        // instructions never depend on each other; LDS reads run kPrefetch fragments ahead.
-        constexpr int NF = 2 * KK;
-        uint4 fr[NF];
-        auto kfrag = [&](int i) {
-          return ks[buf][row_tile_unit<D>((i & 1) * 32 + l32, 2 * (i >> 1) + h)];
-        };
-#pragma unroll
-        for (int i = 0; i < kPrefetch && i < NF; ++i) fr[i] = kfrag(i);
-#pragma unroll
-        for (int i = 0; i < NF; ++i) {
-          if (i + kPrefetch < NF) fr[i + kPrefetch] = kfrag(i + kPrefetch);
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-            sacc[nb][i & 1] = mfma_bf16(fr[i], qf[nb][i >> 1], sacc[nb][i & 1]);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read
-          __builtin_amdgcn_sched_group_barrier(0x008, NB, 0); // then this step's matrix ops
-        }
-      }
-      const bool diag = key0 + kTile - 1 > off + wrow0;  // tile reaches past the wave's first row
-      uint4 pf[NB][2][2];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const int qrow = off + wrow0 + nb * 32 + l32;   // newest key this lane's row sees
-        if (diag) {
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-              const int key = key0 + kb * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
-              if (key > qrow) sacc[nb][kb][i] = -INFINITY;
-            }
-        }
-        float mx = sacc[nb][0][0];
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[nb][kb][i]);
-        mx = across_rows(mx, OpMax(), false, true);
-        // The running maximum only has to bound the exponents, not equal the true maximum:
-        // it is raised (and the accumulators rescaled) only when some row of the wave
-        // exceeds it by more than 2^kLazyRescale, so probabilities stay below that factor
-        // and the rescale, which costs a multiply per accumulator register, becomes rare.
-        // (Rows past the end of a ragged block can be fully masked: keep m finite.)
-        const float mxs = fmaxf(mx * scale_log2e, -1e30f);
-        if (__any(mxs > m[nb] + kLazyRescale)) {
-          const float m_new = fmaxf(m[nb], mxs);
-          const float corr = fast_exp2(m[nb] - m_new);
-          lsum[nb] *= corr;
-          if (WITH_O) {
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-              for (int i = 0; i < 16; ++i) oacc[nb][db][i] *= corr;
-          }
-          m[nb] = m_new;
-        }
-        float rs = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-          float p[16];
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            p[i] = fast_exp2(fmaf(sacc[nb][kb][i], scale_log2e, -m[nb]));
-            rs += p[i];
-          }
-          if (WITH_O) {
-#pragma unroll
-            for (int tt = 0; tt < 2; ++tt) {
-              uint4 w;
-              w.x = pack_bf16(p[8 * tt + 0], p[8 * tt + 1]);
-              w.y = pack_bf16(p[8 * tt + 2], p[8 * tt + 3]);
-              w.z = pack_bf16(p[8 * tt + 4], p[8 * tt + 5]);
-              w.w = pack_bf16(p[8 * tt + 6], p[8 * tt + 7]);
-              pf[nb][kb][tt] = w;
-            }
-          }
-        }
-        lsum[nb] += rs;
-      }
-      // ---- O^T += V^T P^T
-      if (WITH_O) {
-        // fragment i = (kb, tt, db): the head-dimension block is the fastest index, so that
-        // consecutive matrix instructions go to different accumulators (a dependent
-        // back-to-back pair costs 48 instead of 32 cycles).
-        constexpr int NF = DB * 4;
-        uint4 fr[NF];
-        auto vfrag = [&](int i) {
-          const int d = (i % DB) * 32 + l32;
-          return *reinterpret_cast<const uint4*>(vt[buf] + d * 128 + ((((i / DB) * 2 + h) ^ vt_swizzle(d)) << 4));
-        };
-#pragma unroll
-        for (int i = 0; i < kPrefetch && i < NF; ++i) fr[i] = vfrag(i);
-#pragma unroll
-        for (int i = 0; i < NF; ++i) {
-          if (i + kPrefetch < NF) fr[i + kPrefetch] = vfrag(i + kPrefetch);
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-            oacc[nb][i % DB] = mfma_bf16(fr[i], pf[nb][(i / DB) >> 1][(i / DB) & 1], oacc[nb][i % DB]);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, NB, 0);
-        }
-      }
-    }
-    if (t + 1 < ntiles) stg.template store<WITH_O>(ks[buf ^ 1], vt[WITH_O ? (buf ^ 1) : 0]);
-    __syncthreads();
-  }
-
-  // ---- epilogue
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    const int qrow = wrow0 + nb * 32 + l32;
-    const float l = across_rows(lsum[nb], OpAdd(), false, true);
-    if (qrow < n) {
-      if (h == 0) LSE2[(size_t)g * n + qrow] = m[nb] + log2f(l);
-      if (WITH_O) {
-        const float inv = 1.0f / l;
-        bf16_t* orow = O + ((size_t)g * n + qrow) * D;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int i4 = 0; i4 < 4; ++i4) {
-            uint2 w;
-            w.x = pack_bf16(oacc[nb][db][4 * i4 + 0] * inv, oacc[nb][db][4 * i4 + 1] * inv);
-            w.y = pack_bf16(oacc[nb][db][4 * i4 + 2] * inv, oacc[nb][db][4 * i4 + 3] * inv);
-            *reinterpret_cast<uint2*>(orow + db * 32 + 8 * i4 + 4 * h) = w;
-          }
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------
-// d = 128 variant built on two gfx950 features:
+// Masked attention rows, d = 64 or 128, on two gfx950 features:
 //  * K and V tiles go from global memory straight into LDS (global_load_lds, 16 bytes per
-//    lane, a wave fills 1 KB = 4 rows per instruction; lane l's data lands at base + 16 l,
+//    lane, a wave fills 1 KB = 4 (d = 64: 8) rows per instruction; lane l's data lands at base + 16 l,
 //    so the swizzle is applied by choosing which global chunk each lane fetches).  No
 //    staging registers, no LDS store instructions.
 //  * V stays row-major [key][d] in LDS; the V^T operand of O^T = V^T P^T is read with
@@ -349,7 +57,6 @@ __global__ __launch_bounds__(kThreads, kFwdOcc) void attn_fwd_bf16_kernel(
 //    lanes of a group: output lane i, element r  <-  source lane 4r + i/4, element i%4.
 //    Source lane (r, q) therefore points at V[key_r][d0 + 4q ..+3] and output lane i
 //    receives V[key_0..3][d0 + i]: exactly the 4 consecutive keys of one half operand.
-// Same mathematics and operand conventions as attn_fwd_bf16_kernel above.
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) char lds_char;
 
@@ -370,97 +77,117 @@ __device__ __forceinline__ void lds_write8(lds_char* p, const uint2& v) {
   *reinterpret_cast<__attribute__((address_space(3))) u32x2_t*>(p) = x;
 }
 
-constexpr int kTileBytes = kTile * 256;  // one 64-row tile of 128 bf16
+template <int D> constexpr int kTileBytesOf = kTile * D * 2;  // one 64-row tile
+constexpr int kTileBytes = kTileBytesOf<128>;
 
-// Chunk swizzles (16-byte chunks of a 256-byte row; the LDS has 64 four-byte banks).  K is
-// read 16 rows x one chunk column per 16 lanes: XOR with the row spreads them over all 16
-// chunk positions.  V is read by 32 lanes as 4 rows x 4 chunk columns x 2 halves: XOR with
-// 4*(row%4) sends the four rows to disjoint groups of four chunk positions.  Both measure
-// zero LDS bank conflicts (SQ_LDS_BANK_CONFLICT).
-__device__ __forceinline__ int k_swizzle(int row) { return row & 15; }
-__device__ __forceinline__ int v_swizzle(int row) { return (row & 3) << 2; }
+// Chunk swizzles (16-byte chunks of a row; the LDS has 64 four-byte banks, i.e. 16 chunks side by
+// side: one row of d = 128, two of d = 64).  K and Q are read 16 rows x one chunk column per 16
+// lanes: XOR with the row (d = 64: row pair) spreads them over all 16 places.  V is read by 32
+// lanes as 4 rows x 4 chunk columns x 2 halves: XOR with 4 * (row % 4) (d = 64: 4 * (row / 2 % 2))
+// sends the rows to disjoint groups of four places.  Both measure zero LDS bank conflicts
+// (SQ_LDS_BANK_CONFLICT).
+template <int D = 128>
+__device__ __forceinline__ int k_swizzle(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
+template <int D = 128>
+__device__ __forceinline__ int v_swizzle(int row) { return D == 128 ? (row & 3) << 2 : ((row >> 1) & 1) << 2; }
 
-template <bool V_LAYOUT>
-__device__ __forceinline__ void dma_tile(const bf16_t* __restrict__ Mg, int row0, int n,
-                                         lds_char* tile) {
+// Geometry of a tile fetch: a wave's load u fills the rows (4 u + wave) * kRowsPerLoad ..
+template <int D> constexpr int kRowsPerLoad = 512 / D;
+template <int D> constexpr int kLoadsPerWave = kTile / (4 * kRowsPerLoad<D>);
+
+template <int D, bool V_LAYOUT>
+__device__ __forceinline__ void tile_place(int u, int& lrow, int& chunk) {
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int rr = lane >> 4, pc = lane & 15;
-  const bf16_t* base = Mg + (size_t)row0 * 128;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % kWaves;
+  lrow = (u * 4 + wave) * kRowsPerLoad<D> + lane / (D / 8);
+  chunk = (lane % (D / 8)) ^ (V_LAYOUT ? v_swizzle<D>(lrow) : k_swizzle<D>(lrow));
+}
+template <int D, bool V_LAYOUT>
+__device__ __forceinline__ void dma_tile(const bf16_t* __restrict__ Mg, int row0, int n, lds_char* tile) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % kWaves;
+  const bf16_t* base = Mg + (size_t)row0 * D;
   const int most = n - 1 - row0;  // rows past the end repeat the last one
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int lrow = (u * 4 + wave) * 4 + rr;
-    const int c = pc ^ (V_LAYOUT ? v_swizzle(lrow) : k_swizzle(lrow));
-    dma16(base, (uint32_t)(min(lrow, most) * 256 + c * 16), (uint32_t)(size_t)(tile + (u * 4 + wave) * 1024));
+  for (int u = 0; u < kLoadsPerWave<D>; ++u) {
+    int lrow, c;
+    tile_place<D, V_LAYOUT>(u, lrow, c);
+    dma16(base, (uint32_t)(min(lrow, most) * D * 2 + c * 16), (uint32_t)(size_t)(tile + (u * 4 + wave) * 1024));
   }
 }
 
 // dma_tile for a tile that straddles two sources: rows below `off` are rows of A, rows from
 // `off` on are rows 0 .. of B (n rows in all).
-template <bool V_LAYOUT>
+template <int D, bool V_LAYOUT>
 __device__ __forceinline__ void dma_tile2(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                           int off, int row0, int n, lds_char* tile) {
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int rr = lane >> 4, pc = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % kWaves;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int lrow = (u * 4 + wave) * 4 + rr;
-    const int c = pc ^ (V_LAYOUT ? v_swizzle(lrow) : k_swizzle(lrow));
-    int r = row0 + lrow;
-    r = r < n ? r : n - 1;
-    const bf16_t* src = r < off ? A + (size_t)r * 128 : B + (size_t)(r - off) * 128;
+  for (int u = 0; u < kLoadsPerWave<D>; ++u) {
+    int lrow, c;
+    tile_place<D, V_LAYOUT>(u, lrow, c);
+    const int r = min(row0 + lrow, n - 1);
+    const bf16_t* src = r < off ? A + (size_t)r * D : B + (size_t)(r - off) * D;
     dma16_at(src + c * 8, (uint32_t)(size_t)(tile + (u * 4 + wave) * 1024));
   }
 }
 
 // Same as dma_tile for a tile that lies completely inside the matrix: the per-lane byte
 // offsets `loff` (row-in-tile and swizzled chunk) are loop invariants, the tile base is
-// wave-uniform, so a tile costs four load instructions and no address arithmetic per lane.
-template <bool V_LAYOUT>
-__device__ __forceinline__ void dma_offsets(int (&loff)[4]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int rr = lane >> 4, pc = lane & 15;
+// wave-uniform, so a tile costs its load instructions and no address arithmetic per lane.
+template <int D, bool V_LAYOUT>
+__device__ __forceinline__ void dma_offsets(int (&loff)[kLoadsPerWave<D>]) {
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int lrow = (u * 4 + wave) * 4 + rr;
-    loff[u] = lrow * 256 + ((pc ^ (V_LAYOUT ? v_swizzle(lrow) : k_swizzle(lrow))) << 4);
+  for (int u = 0; u < kLoadsPerWave<D>; ++u) {
+    int lrow, c;
+    tile_place<D, V_LAYOUT>(u, lrow, c);
+    loff[u] = lrow * D * 2 + c * 16;
   }
 }
+template <int D>
 __device__ __forceinline__ void dma_full_tile(const bf16_t* __restrict__ Mg, int row0,
-                                              const int (&loff)[4], lds_char* tile) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const char* base = reinterpret_cast<const char*>(Mg) + (size_t)row0 * 256;
+                                              const int (&loff)[kLoadsPerWave<D>], lds_char* tile) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % kWaves;
+  const bf16_t* base = Mg + (size_t)row0 * D;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) dma16(base, (uint32_t)loff[u], (uint32_t)(size_t)(tile + (u * 4 + wave) * 1024));
+  for (int u = 0; u < kLoadsPerWave<D>; ++u) dma16(base, (uint32_t)loff[u], (uint32_t)(size_t)(tile + (u * 4 + wave) * 1024));
 }
 
-constexpr int kScoreOnlyNB = 1;   // 32-row query blocks per wave when no outputs are wanted
-constexpr int kScoreOnlyOcc = 4;  // workgroups per compute unit then (32 KB of LDS each: K tiles only)
+// With outputs a wave works one tile ahead of itself: while the vector ALU forms the
+// probabilities of tile t, the matrix pipe forms the logits of tile t + 1 (the two are
+// interleaved in the instruction stream), then O += V(t)^T P(t).  K tiles are fetched two steps ahead,
+// V tiles one.  Exponentials are taken against the running maximum as it is, without looking for
+// the tile's own: floating point keeps their relative precision whatever their size, so the
+// maximum has to move (and O to be rescaled) only when a tile's sum leaves the range (>= 2^30, or not
+// a number: the first tile, whose running maximum is -inf).
+constexpr float kMoveMaximumAt = 1073741824.f;  // 2^30
 
-template <bool WITH_O, int NB>
-__global__ __launch_bounds__(kThreads, !WITH_O ? kScoreOnlyOcc : (NB == 1 ? 2 : 1)) void attn_fwd128_kernel(
+// KS = 2 (with outputs): eight waves, the second four take the odd tiles of the same 128 rows and the
+// two halves are merged at the end -- for launches that do not fill the chip, where the chain of
+// tiles of a head's last rows is what the call waits for.
+template <int D, bool WITH_O, int KS>
+__global__ __launch_bounds__(kThreads * KS, !WITH_O ? 4 : 2 / KS) void attn_fwd_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, float* __restrict__ LSE2, AttnRect rc, int G, int nqb, float scale_log2e) {
-  constexpr int D = 128, BM = kWaves * 32 * NB, KK = D / 16, DB = D / 32;
-  // [stage][K tile | V tile], two stages: a tile is fetched one step ahead; without outputs there
-  // are no V tiles.  A deeper ring was measured for that pass and is slower: it costs occupancy.
-  constexpr int kBuf = (WITH_O ? 2 : 1) * kTileBytes;
-  constexpr int RING = 2;
-  __shared__ __attribute__((aligned(1024))) char smem[RING * kBuf];
-  lds_char* const lds = (lds_char*)smem;
+  constexpr int BM = kWaves * 32, KK = D / 16, DB = D / 32, ROW = D * 2;
+  constexpr int kTB = kTileBytesOf<D>, NL = kLoadsPerWave<D>;
+  // two stages of K tiles, two of V tiles (none without outputs; a deeper ring was measured for
+  // that pass and is slower: it costs occupancy)
+  // (with outputs: and 4 KB that take the loads of a step that has nothing to fetch)
+  constexpr int kLds = WITH_O ? 4 * kTB + 4096 : 2 * kTB;
+  __shared__ __attribute__((aligned(1024))) char smem[KS * kLds];
+  __shared__ float m_other[KS > 1 ? BM : 1], l_other[KS > 1 ? BM : 1];
 
   const long long total = (long long)G * nqb;
   const long long vid = xcd_contiguous_id(total);
   if (vid >= total) return;
   const int g = (int)(vid / nqb);
-  // longest rows first; without outputs the launch covers only the nqb row blocks from the one
-  // that holds rc.first_row on
-  const int qb = (WITH_O ? 0 : rc.first_row / BM) + nqb - 1 - (int)(vid % nqb);
+  // longest rows first; the launch covers the nqb row blocks from the one that holds rc.first_row on
+  const int qb = rc.first_row / BM + nqb - 1 - (int)(vid % nqb);
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: branches on it are scalar
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % kWaves;  // wave-uniform: branches on it are scalar
+  const int part = KS > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) / kWaves : 0;  // of the tiles: part, part + KS, ...
+  lds_char* const lds = (lds_char*)smem + part * kLds;
   const int l32 = lane & 31, h = lane >> 5;
   const int n = rc.m;
   const int gk = g / rc.kv_group;  // the K/V head this query head reads
@@ -468,7 +195,7 @@ __global__ __launch_bounds__(kThreads, !WITH_O ? kScoreOnlyOcc : (NB == 1 ? 2 : 
   const int row0 = qb * BM;
   if (off < 0) {  // a head the caller's precondition excludes: its rows are flagged with NaN
     if (WITH_O)
-      for (int e = tid; e < min(BM, n - row0) * D; e += kThreads)
+      for (int e = tid; e < min(BM, n - row0) * D; e += kThreads * KS)
         O[((size_t)g * n + row0) * D + e] = (bf16_t)0x7FC0;
     return;
   }
@@ -479,256 +206,346 @@ __global__ __launch_bounds__(kThreads, !WITH_O ? kScoreOnlyOcc : (NB == 1 ? 2 : 
   // second source (keys off .. off+n-1), or null
   const bf16_t* K2g = rc.k2 ? (const bf16_t*)rc.k2 + (size_t)gk * n * D : nullptr;
   const bf16_t* V2g = rc.k2 ? (const bf16_t*)rc.v2 + (size_t)gk * n * D : nullptr;
-  const int wrow0 = row0 + wave * 32 * NB;  // first query row of this wave
+  const int wrow0 = row0 + wave * 32;  // first query row of this wave
 
   // Q fragments (B operand): lane (query l32, half h) holds Q[query][16kk + 8h .. +7]
-  uint4 qf[NB][KK];
+  uint4 qf[KK];
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    int r = wrow0 + nb * 32 + l32;
-    r = r < n ? r : n - 1;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[nb][kk] = load16(Qg + (size_t)r * D + kk * 16 + h * 8);
-  }
+  for (int kk = 0; kk < KK; ++kk) qf[kk] = load16(Qg + (size_t)min(wrow0 + l32, n - 1) * D + kk * 16 + h * 8);
   // per-lane LDS byte offsets inside a K / V tile
   int koff[KK];
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) koff[kk] = l32 * 256 + (((2 * kk + h) ^ k_swizzle(l32)) << 4);
+  for (int kk = 0; kk < KK; ++kk) koff[kk] = l32 * ROW + (((2 * kk + h) ^ k_swizzle<D>(l32)) << 4);
   int voff[DB];
   {
     const int i = lane & 15, r = i >> 2, qd = i & 3, gq = (lane >> 4) & 1;
-    const int cl = 2 * gq + (qd >> 1), vs = v_swizzle(4 * h + r);  // key = 8*x + 4h + r
+    const int cl = 2 * gq + (qd >> 1), vs = v_swizzle<D>(4 * h + r);  // key = 8*x + 4h + r
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-      voff[db] = (4 * h + r) * 256 + ((((4 * db + cl) ^ vs)) << 4) + (qd & 1) * 8;
-  }
-
-  f32x16 oacc[NB][DB];
-  float m[NB], lsum[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    m[nb] = -INFINITY;
-    lsum[nb] = 0.f;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) oacc[nb][db][i] = 0.f;
+    for (int db = 0; db < DB; ++db) voff[db] = (4 * h + r) * ROW + ((((4 * db + cl) ^ vs)) << 4) + (qd & 1) * 8;
   }
 
   const int last_key = off + min(n, row0 + BM) - 1;  // newest key the block's rows see
   const int ntiles = last_key / kTile + 1;
-  int k_loff[4], v_loff[4];
-  dma_offsets<false>(k_loff);
-  dma_offsets<true>(v_loff);
-  auto fetch = [&](int t, lds_char* buf) {  // K tile t and V tile t into buf | buf + 16 KB
+  int k_loff[NL], v_loff[NL];
+  dma_offsets<D, false>(k_loff);
+  if (WITH_O) dma_offsets<D, true>(v_loff);
+  auto fetch_k = [&](int t, lds_char* buf) {
     if (K2g && (t + 1) * kTile > off) {       // the tile holds rows of the second source
-      if (t * kTile >= off && (t + 1) * kTile <= nk) {
-        dma_full_tile(K2g, t * kTile - off, k_loff, buf);
-        if (WITH_O) dma_full_tile(V2g, t * kTile - off, v_loff, buf + kTileBytes);
-      } else {
-        dma_tile2<false>(Kg, K2g, off, t * kTile, nk, buf);
-        if (WITH_O) dma_tile2<true>(Vg, V2g, off, t * kTile, nk, buf + kTileBytes);
-      }
-      return;
-    }
-    if ((t + 1) * kTile <= nk) {
-      dma_full_tile(Kg, t * kTile, k_loff, buf);
-      if (WITH_O) dma_full_tile(Vg, t * kTile, v_loff, buf + kTileBytes);
+      if (t * kTile >= off && (t + 1) * kTile <= nk) dma_full_tile<D>(K2g, t * kTile - off, k_loff, buf);
+      else dma_tile2<D, false>(Kg, K2g, off, t * kTile, nk, buf);
+    } else if ((t + 1) * kTile <= nk) {
+      dma_full_tile<D>(Kg, t * kTile, k_loff, buf);
     } else {
-      dma_tile<false>(Kg, t * kTile, nk, buf);
-      if (WITH_O) dma_tile<true>(Vg, t * kTile, nk, buf + kTileBytes);
+      dma_tile<D, false>(Kg, t * kTile, nk, buf);
     }
   };
-  fetch(0, lds);
+  auto fetch_v = [&](int t, lds_char* buf) {
+    if (K2g && (t + 1) * kTile > off) {
+      if (t * kTile >= off && (t + 1) * kTile <= nk) dma_full_tile<D>(V2g, t * kTile - off, v_loff, buf);
+      else dma_tile2<D, true>(Vg, V2g, off, t * kTile, nk, buf);
+    } else if ((t + 1) * kTile <= nk) {
+      dma_full_tile<D>(Vg, t * kTile, v_loff, buf);
+    } else {
+      dma_tile<D, true>(Vg, t * kTile, nk, buf);
+    }
+  };
+  lds_char* const vst = lds + 2 * kTB;  // the V stages
+  if (part < ntiles) fetch_k(part, lds);
+  if (WITH_O) {
+    if (part < ntiles) fetch_v(part, vst);
+    if (part + KS < ntiles) fetch_k(part + KS, lds + kTB);
+  }
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qf[nb][kk].x));  // waited for here, not in the loop
+  for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qf[kk].x));  // waited for here, not in the loop
   wait_vm_barrier<0>();
 
-  auto tile_step = [&](int t, const lds_char* kt, const lds_char* vt_) {
-    const int key0 = t * kTile;
-    if (key0 > off + wrow0 + 32 * NB - 1) return;  // no key of the tile is visible to this wave
-    f32x16 sacc[NB][2];
+  float m = -INFINITY, lsum = 0.f;
+  const int newest = off + wrow0 + l32;  // newest key this lane's row sees
+  const int nt_wave = min(ntiles, (off + wrow0 + 31) / kTile + 1);  // tiles with a key this wave's rows see
+  // steps of the workgroup, and those with a tile for this wave (step u: tile part + KS u)
+  const int steps = (ntiles + KS - 1) / KS, steps_wave = nt_wave > part ? (nt_wave - part + KS - 1) / KS : 0;
+  // the 32 logits of a lane (its query against the keys 32 kb + 8 (i/4) + 4h + i%4 of tile t)
+  auto logits = [&](const lds_char* kt, f32x16 (&s)[2], auto between) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[kb][i] = 0.f;
+    constexpr int NF = 2 * KK;  // fragment i = (kk, kb): the two key blocks alternate, so that no
+    uint4 fr[NF];               // matrix op waits for the one before it
+#pragma unroll
+    for (int i = 0; i < kPrefetch; ++i) fr[i] = lds_read16(kt + (i & 1) * 32 * ROW + koff[i >> 1]);
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+      if (i + kPrefetch < NF) fr[i + kPrefetch] = lds_read16(kt + ((i + kPrefetch) & 1) * 32 * ROW + koff[(i + kPrefetch) >> 1]);
+      s[i & 1] = mfma_bf16(fr[i], qf[i >> 1], s[i & 1]);
+      between(i);
+    }
+  };
+  auto mask = [&](int t, f32x16 (&s)[2]) {  // causal, where tile t reaches past the wave's first row
+    if (t * kTile + kTile - 1 > off + wrow0) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sacc[nb][kb][i] = 0.f;
-    {
-      constexpr int NF = 2 * KK;  // fragment i = (kk, kb)
-      uint4 fr[NF];
+        for (int i = 0; i < 16; ++i)
+          if (t * kTile + kb * 32 + 8 * (i >> 2) + 4 * h + (i & 3) > newest) s[kb][i] = -INFINITY;
+    }
+  };
+  // a new running maximum that covers the tile (rare); returns the factor older sums shrink by
+  auto move_maximum = [&](const f32x16 (&s)[2]) {
+    float mx = s[0][0];
 #pragma unroll
-      for (int i = 0; i < kPrefetch; ++i) fr[i] = lds_read16(kt + (i & 1) * 32 * 256 + koff[i >> 1]);
+    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int i = 0; i < NF; ++i) {
-        if (i + kPrefetch < NF)
-          fr[i + kPrefetch] = lds_read16(kt + ((i + kPrefetch) & 1) * 32 * 256 + koff[(i + kPrefetch) >> 1]);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) sacc[nb][i & 1] = mfma_bf16(fr[i], qf[nb][i >> 1], sacc[nb][i & 1]);
-      }
-      // keep that order: kPrefetch reads up front, then one new read per fragment's matrix ops
+      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kb][i]);
+    mx = across_rows(mx, OpMax(), false, true);
+    // (rows past the end of a ragged block can be fully masked: keep m finite)
+    const float m_new = fmaxf(m, fmaxf(mx * scale_log2e, -1e30f));
+    const float corr = fast_exp2(m - m_new);  // 0 on the first tile
+    m = m_new;
+    return corr;
+  };
+
+  if constexpr (!WITH_O) {
+    auto tile_step = [&](int t, const lds_char* kt) {
+      if (t >= nt_wave) return;
+      f32x16 s[2];
+      logits(kt, s, [](int) {});
+      // keep that order: kPrefetch reads up front, then one new read per matrix op
       __builtin_amdgcn_sched_group_barrier(0x100, kPrefetch, 0);
 #pragma unroll
-      for (int i = 0; i < NF; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, NB, 0);
-        if (i + kPrefetch < NF) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      for (int i = 0; i < 2 * KK; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (i + kPrefetch < 2 * KK) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
-    }
-    const bool diag = key0 + kTile - 1 > off + wrow0;  // tile reaches past the wave's first row
-    uint4 pf[NB][2][2];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      if (diag) {  // causal mask
-        const int newest = off + wrow0 + nb * 32 + l32;  // newest key this lane's row sees
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int key = key0 + kb * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
-            if (key > newest) sacc[nb][kb][i] = -INFINITY;
-          }
-      }
-      if constexpr (!WITH_O) {
-        // Statistics only.  The exponentials are taken against the running maximum as it is,
-        // without looking for the tile's own: floating point keeps their relative precision
-        // whatever their size, so the maximum has to move only when a sum leaves the range
-        // (>= 2^30, or not a number: the first tile, whose running maximum is -inf).
-        float rs = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) rs += fast_exp2(fmaf(sacc[nb][kb][i], scale_log2e, -m[nb]));
-        if (__any(!(rs < 1073741824.f))) {
-          float mx = sacc[nb][0][0];
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[nb][kb][i]);
-          mx = across_rows(mx, OpMax(), false, true);
-          const float m_new = fmaxf(m[nb], fmaxf(mx * scale_log2e, -1e30f));
-          lsum[nb] *= fast_exp2(m[nb] - m_new);  // 0 on the first tile
-          m[nb] = m_new;
-          rs = 0.f;
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) rs += fast_exp2(fmaf(sacc[nb][kb][i], scale_log2e, -m_new));
-        }
-        lsum[nb] += rs;
-        continue;
-      }
-      float mx = sacc[nb][0][0];
+      mask(t, s);
+      float rs = 0.f;
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[nb][kb][i]);
-      mx = across_rows(mx, OpMax(), false, true);
-      const float mxs = fmaxf(mx * scale_log2e, -1e30f);
-      if (__any(mxs > m[nb] + kLazyRescale)) {  // see attn_fwd_bf16_kernel
-        const float m_new = fmaxf(m[nb], mxs);
-        const float corr = fast_exp2(m[nb] - m_new);
-        lsum[nb] *= corr;
-        if (WITH_O) {
+        for (int i = 0; i < 16; ++i) rs += fast_exp2(fmaf(s[kb][i], scale_log2e, -m));
+      if (__any(!(rs < kMoveMaximumAt))) {
+        lsum *= move_maximum(s);
+        rs = 0.f;
 #pragma unroll
-          for (int db = 0; db < DB; ++db)
+        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[nb][db][i] *= corr;
-        }
-        m[nb] = m_new;
+          for (int i = 0; i < 16; ++i) rs += fast_exp2(fmaf(s[kb][i], scale_log2e, -m));
       }
-      float rs = 0.f;
+      lsum += rs;
+    };
+    for (int t0 = 0; t0 < ntiles; t0 += 2) {
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        float p[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          p[i] = fast_exp2(fmaf(sacc[nb][kb][i], scale_log2e, -m[nb]));
-          rs += p[i];
-        }
-#pragma unroll
-        for (int tt = 0; tt < 2; ++tt)
-          pf[nb][kb][tt] = make_uint4(pack_bf16(p[8 * tt + 0], p[8 * tt + 1]), pack_bf16(p[8 * tt + 2], p[8 * tt + 3]),
-                                      pack_bf16(p[8 * tt + 4], p[8 * tt + 5]), pack_bf16(p[8 * tt + 6], p[8 * tt + 7]));
+      for (int b = 0; b < 2; ++b) {  // stage t % 2: LDS offsets are immediates
+        const int t = t0 + b;
+        if (t >= ntiles) break;
+        // the stage of tile t - 1 is free: every wave passed the barrier that ended its step
+        if (t + 1 < ntiles) fetch_k(t + 1, lds + (1 - b) * kTB);
+        tile_step(t, lds + b * kTB);
+        wait_vm_barrier<0>();  // tile t + 1 for every wave of the workgroup
       }
-      lsum[nb] += rs;
     }
-    if (WITH_O) {
+    const float l = across_rows(lsum, OpAdd(), false, true);
+    if (wrow0 + l32 < n && h == 0) LSE2[(size_t)g * n + wrow0 + l32] = m + log2f(l);
+  } else {
+    f32x16 oacc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
+    f32x16 sa[2], sb[2];
+    logits(lds, sa, [](int) {});
+    // every wave is done with K(0) before K(2) takes its place
+    wait_vm_barrier<0>();
+
+    // probabilities of tile t (logits in s) beside the logits of tile t + 1 (into s_next; past the
+    // wave's last tile they are formed from whatever the stage holds and not used), then O += V^T P
+    //
+    // The loads of a tile are issued one by one between the first matrix ops: a load of 1 KB keeps
+    // the compute unit's one address path busy for 16 cycles, and issued at once after the barrier the
+    // eight loads of all waves held every wave up for 700 of the 2800 cycles of a step.  So that the
+    // instruction stream is the same in every step, a step without a whole tile to fetch (none left;
+    // or a ragged or two-source tile, which was fetched before) sends its loads to the spare 4 KB.
+    // (all lanes then read the head's first 16 bytes of Q, which every head has.)
+    struct Fetch {
+      const char* from;
+      uint32_t to, stride, lanes;  // lanes: mask of the per-lane offsets
+    };
+    const uint32_t spare = (uint32_t)(size_t)(lds + 4 * kTB) + wave * 1024;
+    const auto whole_k = [&](int t, lds_char* buf) -> Fetch {
+      const uint32_t to = (uint32_t)(size_t)buf + wave * 1024;
+      if (t < ntiles) {
+        if (K2g && (t + 1) * kTile > off) {
+          if (t * kTile >= off && (t + 1) * kTile <= nk)
+            return {reinterpret_cast<const char*>(K2g + (size_t)(t * kTile - off) * D), to, 4096u, ~0u};
+          dma_tile2<D, false>(Kg, K2g, off, t * kTile, nk, buf);
+        } else if ((t + 1) * kTile <= nk) {
+          return {reinterpret_cast<const char*>(Kg + (size_t)t * kTile * D), to, 4096u, ~0u};
+        } else {
+          dma_tile<D, false>(Kg, t * kTile, nk, buf);
+        }
+      }
+      return {reinterpret_cast<const char*>(Qg), spare, 0u, 0u};
+    };
+    const auto whole_v = [&](int t, lds_char* buf) -> Fetch {
+      const uint32_t to = (uint32_t)(size_t)buf + wave * 1024;
+      if (t < ntiles) {
+        if (K2g && (t + 1) * kTile > off) {
+          if (t * kTile >= off && (t + 1) * kTile <= nk)
+            return {reinterpret_cast<const char*>(V2g + (size_t)(t * kTile - off) * D), to, 4096u, ~0u};
+          dma_tile2<D, true>(Vg, V2g, off, t * kTile, nk, buf);
+        } else if ((t + 1) * kTile <= nk) {
+          return {reinterpret_cast<const char*>(Vg + (size_t)t * kTile * D), to, 4096u, ~0u};
+        } else {
+          dma_tile<D, true>(Vg, t * kTile, nk, buf);
+        }
+      }
+      return {reinterpret_cast<const char*>(Qg), spare, 0u, 0u};
+    };
+    auto tile_step = [&](int t, const lds_char* kt_next, const lds_char* vt, f32x16 (&s)[2], f32x16 (&s_next)[2],
+                         const Fetch& fk, const Fetch& fv) {
+      const auto piece = [&](int i) {
+        if (i < NL) dma16(fk.from, (uint32_t)k_loff[i] & fk.lanes, fk.to + i * fk.stride);
+        else if (i < 2 * NL) dma16(fv.from, (uint32_t)v_loff[i - NL] & fv.lanes, fv.to + (i - NL) * fv.stride);
+      };
+      mask(t, s);
+      float rs = 0.f, e0 = 0.f, e1 = 0.f;
+      uint32_t pf[16];  // bf16 probabilities 2j, 2j + 1 (of the lane's 32, key block by key block)
+      const auto finish = [&](int j) {  // the pair whose exponentials were requested last
+        rs += e0;
+        rs += e1;
+        pf[j] = pack_bf16(e0, e1);
+      };
+      // between two matrix ops: a load, and the lane's share of the probabilities -- no result is used
+      // right behind the instruction that forms it
+      logits(kt_next, s_next, [&](int i) {
+        if (i < 2 * NL) piece(i);
+        constexpr int PAIRS = 16 / (2 * KK);
+#pragma unroll
+        for (int jj = 0; jj < PAIRS; ++jj) {
+          const int j = PAIRS * i + jj;
+          const float x0 = fmaf(s[j >> 3][(2 * j) & 15], scale_log2e, -m), x1 = fmaf(s[j >> 3][(2 * j + 1) & 15], scale_log2e, -m);
+          if (j > 0) finish(j - 1);
+          e0 = fast_exp2(x0);
+          e1 = fast_exp2(x1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      finish(15);
+      if (__any(!(rs < kMoveMaximumAt))) {
+        const float corr = move_maximum(s);
+        lsum *= corr;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) oacc[db][i] *= corr;
+        rs = 0.f;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          e0 = fast_exp2(fmaf(s[j >> 3][(2 * j) & 15], scale_log2e, -m));
+          e1 = fast_exp2(fmaf(s[j >> 3][(2 * j + 1) & 15], scale_log2e, -m));
+          finish(j);
+        }
+      }
+      lsum += rs;
       constexpr int NF = DB * 4;  // fragment i = (kb, tt, db), db fastest
       uint2 lo[NF], hi[NF];
       auto vread = [&](int i, uint2& a, uint2& b) {
-        const lds_char* p = vt_ + ((i / DB) * 16) * 256 + voff[i % DB];
+        const lds_char* p = vt + ((i / DB) * 16) * ROW + voff[i % DB];
         a = lds_read_tr16(p);
-        b = lds_read_tr16(p + 8 * 256);
+        b = lds_read_tr16(p + 8 * ROW);
       };
 #pragma unroll
       for (int i = 0; i < kPrefetch; ++i) vread(i, lo[i], hi[i]);
 #pragma unroll
       for (int i = 0; i < NF; ++i) {
         if (i + kPrefetch < NF) vread(i + kPrefetch, lo[i + kPrefetch], hi[i + kPrefetch]);
-        const uint4 a = make_uint4(lo[i].x, lo[i].y, hi[i].x, hi[i].y);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          oacc[nb][i % DB] = mfma_bf16(a, pf[nb][(i / DB) >> 1][(i / DB) & 1], oacc[nb][i % DB]);
+        const int w = 4 * (i / DB);
+        oacc[i % DB] = mfma_bf16(make_uint4(lo[i].x, lo[i].y, hi[i].x, hi[i].y),
+                                 make_uint4(pf[w], pf[w + 1], pf[w + 2], pf[w + 3]), oacc[i % DB]);
       }
       __builtin_amdgcn_sched_group_barrier(0x100, 2 * kPrefetch, 0);
 #pragma unroll
       for (int i = 0; i < NF; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, NB, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         if (i + kPrefetch < NF) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
       }
-    }
-  };
+    };
 
-  for (int t0 = 0; t0 < ntiles; t0 += RING) {
-    // tile t in stage t % RING: unrolled over the ring, all LDS offsets are immediates
+    for (int u0 = 0; u0 < steps_wave; u0 += 2) {
 #pragma unroll
-    for (int b = 0; b < RING; ++b) {
-      const int t = t0 + b;
-      if (t >= ntiles) break;
-      // the stage of tile t - 1 is free: every wave passed the barrier that ended its step
-      if (t + 1 < ntiles) fetch(t + 1, lds + ((b + 1) % RING) * kBuf);
-      tile_step(t, lds + b * kBuf, lds + b * kBuf + kTileBytes);
-      wait_vm_barrier<0>();  // tile t + 1 for every wave of the workgroup
-    }
-  }
-
-  // ---- epilogue.  The accumulator layout gives a lane 4 consecutive d of one row at a time:
-  // written straight to memory that is 32 rows x 16 bytes per instruction.  Instead each wave
-  // transposes its 32 x 128 output block through its own 8 KB strip of LDS (free after the
-  // loop's last barrier; 16-byte chunks XOR-swizzled by the row) and stores whole 256-byte
-  // rows, 4 rows per instruction.
-  lds_char* const ostrip = lds + wave * 8192;
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    const int qrow = wrow0 + nb * 32 + l32;
-    const float l = across_rows(lsum[nb], OpAdd(), false, true);
-    if (qrow < n && h == 0) LSE2[(size_t)g * n + qrow] = m[nb] + log2f(l);
-    if (WITH_O) {
-      const float inv = 1.0f / l;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          uint2 w;
-          w.x = pack_bf16(oacc[nb][db][4 * i4 + 0] * inv, oacc[nb][db][4 * i4 + 1] * inv);
-          w.y = pack_bf16(oacc[nb][db][4 * i4 + 2] * inv, oacc[nb][db][4 * i4 + 3] * inv);
-          // row l32, elements 32db + 8*i4 + 4h .. +3  ->  chunk 4db + i4, half h
-          lds_write8(ostrip + l32 * 256 + (((4 * db + i4) ^ (l32 & 15)) << 4) + 8 * h, w);
-        }
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-      __builtin_amdgcn_wave_barrier();
-      const int rr = lane >> 4, c = lane & 15;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int r = 4 * u + rr;
-        const uint4 v = lds_read16(ostrip + r * 256 + ((c ^ (r & 15)) << 4));
-        const int orow = wrow0 + nb * 32 + r;
-        if (orow < n) store16(O + ((size_t)g * n + orow) * D + c * 8, v);
+      for (int b = 0; b < 2; ++b) {  // stage u % 2: LDS offsets are immediates
+        if (u0 + b >= steps_wave) break;
+        const int t = part + KS * (u0 + b);
+        // free since the last barrier: the stages of K(u), whose logits are formed, and of V(u-1)
+        const Fetch fk = whole_k(t + 2 * KS, lds + b * kTB), fv = whole_v(t + KS, vst + (1 - b) * kTB);
+        if (b == 0) tile_step(t, lds + kTB, vst, sa, sb, fk, fv);
+        else tile_step(t, lds, vst + kTB, sb, sa, fk, fv);
+        wait_vm_barrier<0>();  // K(u+2) and V(u+1) for every wave of the workgroup
       }
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-      __builtin_amdgcn_wave_barrier();
+    }
+    // tiles that only the workgroup's later rows see: the wave still fetches its quarter
+    for (int u = steps_wave; u < steps; ++u) {
+      const int t = part + KS * u;
+      if (t + 2 * KS < ntiles) fetch_k(t + 2 * KS, lds + (u & 1) * kTB);
+      if (t + KS < ntiles) fetch_v(t + KS, vst + (1 - (u & 1)) * kTB);
+      wait_vm_barrier<0>();
+    }
+
+    // ---- epilogue.  The accumulator layout gives a lane 4 consecutive d of one row at a time:
+    // written straight to memory that is 32 rows x 16 bytes per instruction.  Instead each wave
+    // transposes its 32 x D output block through its own strip of LDS (free after the
+    // loop's last barrier; 16-byte chunks XOR-swizzled by the row) and stores whole rows, 1 KB per
+    // instruction.
+    float l = across_rows(lsum, OpAdd(), false, true);
+    if constexpr (KS > 1) {
+      // the second half's sums, through the rings (free after the loop's last barrier)
+      typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
+      static_assert(kWaves * DB * 4 * 1024 <= KS * kLds, "a register quad of all lanes per KB");
+      lds_char* const osum = (lds_char*)smem + wave * (DB * 4 * 1024) + lane * 16;
+      if (part == 1) {
+        if (h == 0) { m_other[wave * 32 + l32] = m; l_other[wave * 32 + l32] = l; }
+#pragma unroll
+        for (int i = 0; i < 4 * DB; ++i)
+          *reinterpret_cast<lds_f32x4*>(osum + i * 1024) =
+              f32x4_t{oacc[i >> 2][4 * (i & 3)], oacc[i >> 2][4 * (i & 3) + 1], oacc[i >> 2][4 * (i & 3) + 2], oacc[i >> 2][4 * (i & 3) + 3]};
+      }
+      __syncthreads();
+      if (part == 1) return;
+      const float m1 = m_other[wave * 32 + l32], l1 = l_other[wave * 32 + l32];
+      const float m_all = fmaxf(m, m1);  // this half has seen key 0: finite
+      const float f0 = fast_exp2(m - m_all), f1 = fast_exp2(m1 - m_all);  // 0 for a half without tiles
+      l = l * f0 + l1 * f1;
+      m = m_all;
+#pragma unroll
+      for (int i = 0; i < 4 * DB; ++i) {
+        const f32x4_t x = *reinterpret_cast<const lds_f32x4*>(osum + i * 1024);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) oacc[i >> 2][4 * (i & 3) + e] = oacc[i >> 2][4 * (i & 3) + e] * f0 + x[e] * f1;
+      }
+    }
+    if (wrow0 + l32 < n && h == 0) LSE2[(size_t)g * n + wrow0 + l32] = m + log2f(l);
+    // (with KS = 2 the merged waves' strips lie above what they read: the second ring)
+    lds_char* const ostrip = (lds_char*)smem + (KS - 1) * kLds + wave * 32 * ROW;
+    const float inv = 1.0f / l;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        uint2 w;
+        w.x = pack_bf16(oacc[db][4 * i4 + 0] * inv, oacc[db][4 * i4 + 1] * inv);
+        w.y = pack_bf16(oacc[db][4 * i4 + 2] * inv, oacc[db][4 * i4 + 3] * inv);
+        // row l32, elements 32db + 8*i4 + 4h .. +3  ->  chunk 4db + i4, half h
+        lds_write8(ostrip + l32 * ROW + (((4 * db + i4) ^ k_swizzle<D>(l32)) << 4) + 8 * h, w);
+      }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    constexpr int RPL = kRowsPerLoad<D>;
+    const int rr = lane / (D / 8), c = lane % (D / 8);
+#pragma unroll
+    for (int u = 0; u < 32 / RPL; ++u) {
+      const int r = RPL * u + rr;
+      const uint4 x = lds_read16(ostrip + r * ROW + ((c ^ k_swizzle<D>(r)) << 4));
+      if (wrow0 + r < n) store16(O + ((size_t)g * n + wrow0 + r) * D + c * 8, x);
     }
   }
 }
@@ -736,7 +553,7 @@ __global__ __launch_bounds__(kThreads, !WITH_O ? kScoreOnlyOcc : (NB == 1 ? 2 : 
 // ---------------------------------------------------------------------------------------
 // d = 128 with two 32-row query blocks per wave (64 rows per wave, 256 per workgroup) and one
 // wave per SIMD.  Same operand conventions, LDS tile layouts and mathematics as
-// attn_fwd128_kernel; the instruction stream (register map, phase schedule, hazards) is
+// attn_fwd_kernel; the instruction stream (register map, phase schedule, hazards) is
 // written by gen_attn_fwd128x2.py, whose header describes it.  This wrapper derives the
 // per-lane offsets and per-wave pointers and hands them to that stream.  Requires
 // n % 256 == 0 and an output pointer.
@@ -783,7 +600,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd128x2_kernel(
 
   // K fragment (16 d-chunk 2kk+h of key row l32): row base and the kk-independent swizzle term
   const unsigned krow = lds0 + l32 * 256, hx16 = (unsigned)((h ^ k_swizzle(l32)) << 4);
-  // V fragment (see attn_fwd128_kernel): source lane (r, qd) of group gq, key rows 4h + r
+  // V fragment (see attn_fwd_kernel): source lane (r, qd) of group gq, key rows 4h + r
   const int i16 = lane & 15, r4 = i16 >> 2, qd = i16 & 3, gq = (lane >> 4) & 1;
   const unsigned clvs16 = (unsigned)(((2 * gq + (qd >> 1)) ^ v_swizzle(r4)) << 4);
   const unsigned vrow = lds0 + kTileBytes + (4 * h + r4) * 256 + (qd & 1) * 8;
@@ -868,7 +685,7 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd128x2r_kernel(
 
   // K fragment (16 d-chunk 2kk+h of key row l32): row base and the kk-independent swizzle term
   const unsigned krow = lds0 + l32 * 256, hx16 = (unsigned)((h ^ k_swizzle(l32)) << 4);
-  // V fragment (see attn_fwd128_kernel): source lane (r, qd) of group gq, key rows 4h + r
+  // V fragment (see attn_fwd_kernel): source lane (r, qd) of group gq, key rows 4h + r
   const int i16 = lane & 15, r4 = i16 >> 2, qd = i16 & 3, gq = (lane >> 4) & 1;
   const unsigned clvs16 = (unsigned)(((2 * gq + (qd >> 1)) ^ v_swizzle(r4)) << 4);
   const unsigned vrow = lds0 + kTileBytes + (4 * h + r4) * 256 + (qd & 1) * 8;
@@ -913,152 +730,27 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd128x2r_kernel(
 }
 
 // ---------------------------------------------------------------------------------------
-// Geometry as in AttnRect (n = rc.m rows, keys 0 .. off + n - 1, row i sees keys <= off + i).
-// accumulate: the column sums are added to decay * S[] (a chunk: the cached tokens' older scores
-// decayed by alpha^m) instead of replacing it.
-template <int D>
-__global__ __launch_bounds__(kThreads) void col_scores_bf16_kernel(
-    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const float* __restrict__ LSE2,
-    float* __restrict__ S, AttnRect rc, int s_stride, bool accumulate, float decay, int G, int ncb,
-    int first_row, float log2_alpha, const float* __restrict__ alpha_heads, float scale_log2e) {
-  constexpr int BC = kWaves * 32;  // key columns per workgroup
-  constexpr int CPR = D / 8;
-  constexpr int KK = D / 16;
-  __shared__ uint4 qs[2][kTile * CPR];
-
-  const long long total = (long long)G * ncb;
-  const long long vid = xcd_contiguous_id(total);
-  if (vid >= total) return;
-  const int g = (int)(vid / ncb);
-  const int cb = (int)(vid % ncb);  // column block 0 has the most rows: first
-  const int n = rc.m;
-  const int off = rc.off_heads ? rc.off_heads[g] : 0;
-  const int nk = off + n;  // keys of this head
-  const int c0 = cb * BC;
-  if (off < 0 || c0 >= nk) return;
-  head_window(alpha_heads, g, n, first_row, log2_alpha);
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: branches on it are scalar
-  const int l32 = lane & 31, h = lane >> 5;
-  const bf16_t* Kg = K + (size_t)g * rc.kv_stride * D;
-  const int wc0 = c0 + wave * 32;  // first key of this wave
-
-  // K fragments (A operand): lane (key l32, half h) holds K[key][16kk + 8h .. +7]
-  uint4 kf[KK];
-  {
-    int r = wc0 + l32;
-    r = r < nk ? r : nk - 1;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) kf[kk] = load16(Kg + (size_t)r * D + kk * 16 + h * 8);
-  }
-  float acc[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-
-  const int t_begin = max(max(c0 - off, first_row), 0) / kTile;   // first row tile that sees a key of the block
-  const int t_end = (n + kTile - 1) / kTile;
-  for (int hq = 0; hq < rc.kv_group; ++hq) {  // the query heads that share this K/V head
-    const bf16_t* Qg = Q + ((size_t)g * rc.kv_group + hq) * n * D;
-    const float* lse = LSE2 + ((size_t)g * rc.kv_group + hq) * n;
-    Stage<D> stg;
-    stg.template load<false>(Qg, nullptr, t_begin * kTile, n);
-    __syncthreads();  // the previous query head's last tile has been read by every wave
-    stg.template store<false>(qs[0], nullptr);
-    __syncthreads();
-
-    for (int t = t_begin; t < t_end; ++t) {
-      const int buf = (t - t_begin) & 1;
-      const int row0 = t * kTile;
-      // the rows' log-sum-exp values are requested before the matrix ops that they follow (and
-      // before the next tile's loads, so that waiting for them does not wait for those)
-      float lse_r[2];
-#pragma unroll
-      for (int qb = 0; qb < 2; ++qb) lse_r[qb] = lse[min(row0 + qb * 32 + l32, n - 1)];
-      if (t + 1 < t_end) stg.template load<false>(Qg, nullptr, (t + 1) * kTile, n);
-      if (off + row0 + kTile - 1 >= wc0) {  // some row of the tile sees a key of this wave
-#pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-          f32x16 sacc;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
-#pragma unroll
-          for (int kk = 0; kk < KK; ++kk) {
-            const uint4 b = qs[buf][row_tile_unit<D>(qb * 32 + l32, 2 * kk + h)];
-            sacc = mfma_bf16(kf[kk], b, sacc);
-          }
-          const int r = row0 + qb * 32 + l32;
-          // exponent offset of row r: -lse_r + (n-1-r) log2(alpha); rows past the end, and rows
-          // whose weight is exactly 0 in fp32 (before first_row), add nothing
-          const float bias = (r < n && r >= first_row)
-                                 ? lse_r[qb] - (float)(n - 1 - r) * log2_alpha : INFINITY;
-          const bool diag = off + row0 + qb * 32 < wc0 + 31;  // block reaches above the diagonal
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int key = wc0 + 8 * (i >> 2) + 4 * h + (i & 3);
-            float p = fast_exp2(fmaf(sacc[i], scale_log2e, -bias));
-            if (diag && key > off + r) p = 0.f;
-            acc[i] += p;
-          }
-        }
-      }
-      if (t + 1 < t_end) stg.template store<false>(qs[buf ^ 1], nullptr);
-      __syncthreads();
-    }
-  }
-  // sum over the 32 queries (lanes with the same half)
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    acc[i] = group_sum<32>(acc[i]);
-  }
-  if (l32 == 0) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int key = wc0 + 8 * (i >> 2) + 4 * h + (i & 3);
-      if (key < nk) {
-        float* out = S + (size_t)g * s_stride + key;
-        *out = accumulate ? fmaf(decay, *out, acc[i]) : acc[i];
-      }
-    }
-  }
-}
-
-// attn_fwd_bf16_kernel for any head size and geometry
+// One workgroup with split keys per compute unit (140 KB of LDS).  As long as every row block has a unit to
+// itself, the launch lasts as long as a head's last rows and half the chain is nearly half the time (one
+// head x 2000, whole call: 65 -> 43 us; 32 x 1024: 25.0 -> 22.7 in the kernel).  Beyond that, two workgroups
+// of four waves per unit share it better (kernel, KS = 1 / 2: 40 heads x 1024 32.1 / 35.4 us, 64 x 1000 34.9 / 42.0,
+// 300 x 200 22.4 / 32.3).
+constexpr unsigned kSplitKeysMaxBlocks = 256;
 template <int D>
 void launch_fwd_rect(const void* q, const void* k, const void* v, int G, const AttnRect& rc, void* o,
                      float* lse2, hipStream_t st) {
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)D);
   const int GQ = G * rc.kv_group;  // query heads
-  if constexpr (D == 128) {
-    // direct-to-LDS tiles and transposing LDS reads; without outputs one row block per wave
-    const int nb = o ? 1 : kScoreOnlyNB;
-    const int bm = kWaves * 32 * nb;
-    const int nqb = (rc.m + bm - 1) / bm - (o ? 0 : rc.first_row / bm);  // row blocks to compute
-    const long long total = (long long)GQ * nqb;
-    const unsigned grid = (unsigned)(((total + 7) / 8) * 8);
-    if (o)
-      hipLaunchKernelGGL((attn_fwd128_kernel<true, 1>), dim3(grid), dim3(kThreads), 0, st,
-                         (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, lse2, rc, GQ,
-                         nqb, scale_log2e);
-    else
-      hipLaunchKernelGGL((attn_fwd128_kernel<false, kScoreOnlyNB>), dim3(grid), dim3(kThreads), 0, st,
-                         (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)nullptr, lse2,
-                         rc, GQ, nqb, scale_log2e);
-    return;
-  }
-  constexpr int NB = kFwdNB;
-  constexpr int BM = kWaves * 32 * NB;
-  const int nqb = (rc.m + BM - 1) / BM;
-  const long long total = (long long)GQ * nqb;
-  const unsigned grid = (unsigned)(((total + 7) / 8) * 8);
-  if (o)
-    hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, NB, true>), dim3(grid), dim3(kThreads), 0, st,
-                       (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, lse2, rc, GQ,
-                       nqb, scale_log2e);
-  else
-    hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, NB, false>), dim3(grid), dim3(kThreads), 0, st,
-                       (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)nullptr, lse2,
-                       rc, GQ, nqb, scale_log2e);
+  constexpr int bm = kWaves * 32;
+  const int nqb = (rc.m + bm - 1) / bm - (o ? 0 : rc.first_row / bm);  // row blocks to compute
+  const unsigned grid = (unsigned)((((long long)GQ * nqb + 7) / 8) * 8);
+#define A2SF_FWD(WITH_O, KS)                                                                          \
+  hipLaunchKernelGGL((attn_fwd_kernel<D, WITH_O, KS>), dim3(grid), dim3(kThreads * KS), 0, st, (const bf16_t*)q, \
+                     (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, lse2, rc, GQ, nqb, scale_log2e)
+  if (!o) A2SF_FWD(false, 1);
+  else if (grid <= kSplitKeysMaxBlocks) A2SF_FWD(true, 2);
+  else A2SF_FWD(true, 1);
+#undef A2SF_FWD
 }
 
 // Square geometry (a whole prompt): G K/V heads, kv_group query heads each.
@@ -1078,7 +770,10 @@ void launch_fwd(const void* q, const void* k, const void* v, int G_kv, int n, vo
     // Two query blocks per wave pay off once a workgroup streams enough key tiles to amortise
     // the start and end of a row block: from n = 2048 with one workgroup per block, from
     // n = 512 in the persistent form, which overlaps them with the neighbouring blocks.
-    if (o && n >= kX2MinRowsPersistent && (long long)G * n < (1ll << 31)) {
+    // Few row blocks: the split keys of attn_fwd_kernel<.., 2> shorten the longest chain of tiles
+    // (8 heads x 4096, whole call: 122.6 us here, 73.5 there).
+    const bool few = (long long)G * ((n + kWaves * 32 - 1) / (kWaves * 32)) <= kSplitKeysMaxBlocks;
+    if (o && !few && n >= kX2MinRowsPersistent && (long long)G * n < (1ll << 31)) {
       const int nqb2 = (n + kX2Rows - 1) / kX2Rows;
       const long long items = (long long)G * nqb2;
       const int chunk = 2 * 8 * kX2Slots;  // items of two rounds of the persistent launch
@@ -1115,20 +810,18 @@ void launch_fwd(const void* q, const void* k, const void* v, int G_kv, int n, vo
         return;
       }
     }
-    // Without outputs the pass is bound by the vector ALU as much as by the matrix cores
-    // (fma + exp + add per logit against 1/16 matrix op): one 32-row block per wave at four
-    // workgroups per compute unit overlaps the two better than two blocks per wave at two
-    // (16384 heads of n = 2048: 11.1 ms against 12.75).
-    AttnRect rc{n, n, nullptr, kv_group};
-    rc.first_row = o ? 0 : first_row;
-    launch_fwd_rect<D>(q, k, v, G_kv, rc, o, lse2, st);
-  } else {
-    launch_fwd_rect<D>(q, k, v, G_kv, AttnRect{n, n, nullptr, kv_group}, o, lse2, st);
   }
+  // Without outputs the pass is bound by the vector ALU as much as by the matrix cores
+  // (fma + exp + add per logit against 1/16 matrix op): one 32-row block per wave at four
+  // workgroups per compute unit overlaps the two better than two blocks per wave at two
+  // (16384 heads of n = 2048: 11.1 ms against 12.75).
+  AttnRect rc{n, n, nullptr, kv_group};
+  rc.first_row = o ? 0 : first_row;
+  launch_fwd_rect<D>(q, k, v, G_kv, rc, o, lse2, st);
 }
 
 // ---------------------------------------------------------------------------------------
-// col_scores for a short row window (alpha well below 1), d = 128.  Only rows >= first_row
+// col_scores for a short row window (alpha well below 1).  Only rows >= first_row
 // contribute (see first_contributing_row), at most kTailTiles tiles of 64 rows.  One
 // workgroup per head (with few heads: per share of a head's keys) stages those Q rows in LDS
 // once (direct global-to-LDS loads) and then walks over its key blocks: a wave keeps 32 keys
@@ -1163,12 +856,13 @@ struct RowWindow {
   }
 };
 
-__global__ __launch_bounds__(kThreads, 2) void col_scores_tail128_kernel(
+template <int D>
+__global__ __launch_bounds__(kThreads, 2) void col_scores_tail_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const float* __restrict__ LSE2,
     float* __restrict__ S, AttnRect rc, int s_stride, bool accumulate, float decay, int first_row,
     float log2_alpha, const float* __restrict__ alpha_heads, float scale_log2e, float tol, int ksplit) {
-  constexpr int D = 128, KK = D / 16, BC = kWaves * 32;
-  __shared__ __attribute__((aligned(1024))) char smem[kTailTiles * kTileBytes];
+  constexpr int KK = D / 16, BC = kWaves * 32, kTB = kTileBytesOf<D>;
+  __shared__ __attribute__((aligned(1024))) char smem[kTailTiles * kTB];
   __shared__ __attribute__((aligned(16))) float strip[kWaves][32 * kTailKB];   // a wave's scores of one step
   lds_char* const qs = (lds_char*)smem;
 
@@ -1199,11 +893,11 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_tail128_kernel(
   const int ntile = (n - r_lo + kTile - 1) / kTile;      // <= kTailTiles (checked by the host)
 #pragma unroll
   for (int tt = 0; tt < kTailTiles; ++tt)
-    if (tt < ntile) dma_tile<false>(Qg, r_lo + tt * kTile, n, qs + tt * kTileBytes);
+    if (tt < ntile) dma_tile<D, false>(Qg, r_lo + tt * kTile, n, qs + tt * kTB);
 
   int qoff[KK];
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) qoff[kk] = l32 * 256 + (((2 * kk + h) ^ k_swizzle(l32)) << 4);
+  for (int kk = 0; kk < KK; ++kk) qoff[kk] = l32 * D * 2 + (((2 * kk + h) ^ k_swizzle<D>(l32)) << 4);
   // exponent offset of this lane's row in each 32-row block: lse_i - (n-1-i) log2 alpha;
   // +inf (probability 0) for rows past the end or before the window
   // (all loads issued before the first is used: the address is clamped, not the load skipped)
@@ -1256,7 +950,7 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_tail128_kernel(
         for (int b = 0; b < kTailKB; ++b)
 #pragma unroll
           for (int i = 0; i < 16; ++i) sacc[b][i] = 0.f;
-        const lds_char* qt = qs + rb * 32 * 256;
+        const lds_char* qt = qs + rb * 32 * D * 2;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
           const uint4 qf = lds_read16(qt + qoff[kk]);
@@ -1336,109 +1030,141 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_tail128_kernel(
 }
 
 // ---------------------------------------------------------------------------------------
-// col_scores for a long row window (alpha close to 1), d = 128: the streaming form of
-// col_scores_tail128_kernel.  A workgroup owns 256 key columns (a wave two blocks of 32 keys,
-// their K fragments resident in registers for the whole kernel) and walks down the rows that
-// see them; Q tiles of 64 rows arrive by direct global-to-LDS loads in a ring of four stages,
-// three tiles ahead of the one being used.  One barrier per tile publishes the tile that has
-// landed and frees the stage of the previous one for the next fetch.
+// col_scores for a long row window (alpha close to 1) and for grouped-query heads: the
+// streaming form of col_scores_tail_kernel.  A workgroup owns 256 key columns (a wave two blocks of 32
+// keys, their K fragments resident in registers for the whole kernel) and walks down the rows that
+// see them, one query head of the group after the other; Q tiles of 64 rows arrive by direct
+// global-to-LDS loads in a ring of four stages, three tiles ahead of the one being used.  One barrier
+// per tile publishes the tile that has landed and frees the stage of the previous one for the next fetch.
+// Geometry as in AttnRect (n = rc.m rows, keys 0 .. off + n - 1, row i sees keys <= off + i).
+// accumulate: the column sums are added to decay * S[] (a chunk: the cached tokens' older scores
+// decayed by alpha^m) instead of replacing it.
 constexpr int kStreamStages = 4;
-constexpr int kStreamKB = 2;  // 32-key blocks per wave
 
-__global__ __launch_bounds__(kThreads, 2) void col_scores_stream128_kernel(
+// RS = 2 (without a tolerance): eight waves, the second four take the odd tiles for the same keys, each
+// half with a ring of its own; their sums meet at the end.  For launches whose workgroups are all
+// resident at once, which last as long as the column block with the most rows.
+// KB: 32-key blocks per wave.  Two share every Q fragment read from LDS; with d = 64, where the matrix work per
+// logit is half, more waves with one block each hide the vector work better (96 x 1777, alpha = 1: 74 -> 63 us).
+template <int D, int KB, int RS>
+__global__ __launch_bounds__(kThreads * RS, (D == 64 && KB == 1 ? 4 : 2) / RS) void col_scores_stream_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const float* __restrict__ LSE2,
-    float* __restrict__ S, int n, int G, int ncb, int first_row, float log2_alpha,
-    const float* __restrict__ alpha_heads, float scale_log2e, float tol) {
-  constexpr int D = 128, KK = D / 16, BC = kWaves * 32 * kStreamKB;
+    float* __restrict__ S, AttnRect rc, int s_stride, bool accumulate, float decay, int G, int ncb, int first_row,
+    float log2_alpha, const float* __restrict__ alpha_heads, float scale_log2e, float tol) {
+  constexpr int KK = D / 16, BC = kWaves * 32 * KB, kTB = kTileBytesOf<D>;
+  constexpr int NL = kLoadsPerWave<D>, kLoads = NL + 1;  // loads of a wave per tile
   // Q tiles, then per wave and stage the 64 log-sum-exp values of the tile's rows
-  __shared__ __attribute__((aligned(1024))) char smem[kStreamStages * kTileBytes + kWaves * kStreamStages * 256];
+  constexpr int kLds = kStreamStages * kTB + kWaves * kStreamStages * 256;
+  __shared__ __attribute__((aligned(1024))) char smem[RS * kLds];
   __shared__ int wave_lim[kWaves];
-  lds_char* const qs = (lds_char*)smem;
+  __shared__ float other[RS > 1 ? BC : 1];
 
   const long long total = (long long)G * ncb;
   const long long vid = xcd_contiguous_id(total);
   if (vid >= total) return;
   const int g = (int)(vid / ncb);
   const int cb = (int)(vid % ncb);  // column block 0 has the most rows: first
+  const int n = rc.m;
+  const int off = rc.off_heads ? rc.off_heads[g] : 0;
+  const int nk = off + n;  // keys of this head
+  const int c0 = cb * BC;
+  if (off < 0 || c0 >= nk) return;
   head_window(alpha_heads, g, n, first_row, log2_alpha);
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: branches on it are scalar
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % kWaves;  // wave-uniform: branches on it are scalar
+  const int part = RS > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) / kWaves : 0;
+  lds_char* const qs = (lds_char*)smem + part * kLds;
   const int l32 = lane & 31, h = lane >> 5;
-  const bf16_t* Qg = Q + (size_t)g * n * D;
-  const bf16_t* Kg = K + (size_t)g * n * D;
-  const float* lse = LSE2 + (size_t)g * n;
-  const int c0 = cb * BC;
-  const int wc0 = c0 + wave * 32 * kStreamKB;  // first key of this wave
+  const bf16_t* Qg = Q + (size_t)g * rc.kv_group * n * D;  // the group's rows lie one head after the other
+  const bf16_t* Kg = K + (size_t)g * rc.kv_stride * D;
+  const bf16_t* K2g = rc.k2 ? (const bf16_t*)rc.k2 + (size_t)g * n * D : nullptr;  // keys off .. from here
+  const float* lse = LSE2 + (size_t)g * rc.kv_group * n;
+  const int wc0 = c0 + wave * 32 * KB;  // first key of this wave
 
-  // Tiles are walked from the newest rows down: with a tolerance the newest row tells how far
-  // back the workgroup has to go (RowWindow), and without one the order does not matter.
+  // Tiles are walked from the newest rows down: with a tolerance (one query head per K/V head) the
+  // newest row tells how far back the workgroup has to go (RowWindow), and without one the order
+  // does not matter.
   const int t_last = (n + kTile - 1) / kTile - 1;
-  int t_first = max(c0, first_row) / kTile;      // oldest tile any wave of the workgroup needs
-  lds_char* const lse_s = qs + kStreamStages * kTileBytes +
-                          __builtin_amdgcn_readfirstlane(wave) * (kStreamStages * 256);
-  // Q tile t into its ring stage (every wave a quarter of the rows) and the rows' log-sum-exp
-  // values into the wave's own strip of that stage: five loads per wave, always issued (a tile
-  // below the window is clamped onto tile t_first and never used), so that the wait counts in
-  // the loop are the same for every tile
-  auto fetch = [&](int t) {
-    const int stage = (t_last - t) % kStreamStages;
-    const int tt = max(t, 0);
-    dma_tile<false>(Qg, tt * kTile, n, qs + stage * kTileBytes);
-    dma4(lse + (size_t)tt * kTile, (uint32_t)(min(lane, n - 1 - tt * kTile) * 4), (uint32_t)(size_t)(lse_s + stage * 256));
+  int t_first = max(max(c0 - off, first_row), 0) / kTile;  // oldest tile any wave of the workgroup needs
+  lds_char* const lse_s = qs + kStreamStages * kTB + wave * (kStreamStages * 256);
+  // tile f of the sequence is tile t_last - f % per_head of query head f / per_head; this half takes
+  // the tiles part, part + RS, ...
+  int per_head = t_last - t_first + 1;
+  // The half's next Q tile into the next ring stage (every wave a quarter of the rows) and the rows'
+  // log-sum-exp values into the wave's own strip of that stage; always issued (past the last tile the
+  // last one again, never used), so that the wait counts in the loop are the same for every tile.
+  int f_hq = 0, f_i = part, f_stage = 0;  // query head and place in its sequence of the next fetch
+  int f_loff[NL];
+  dma_offsets<D, false>(f_loff);
+  auto fetch = [&]() {
+    while (f_i >= per_head) {
+      if (f_hq + 1 < rc.kv_group) { ++f_hq; f_i -= per_head; }
+      else f_i = per_head - 1;
+    }
+    const size_t head = (size_t)f_hq * n;
+    const int row0 = (t_last - f_i) * kTile;
+    if (row0 + kTile <= n) dma_full_tile<D>(Qg + head * D, row0, f_loff, qs + f_stage * kTB);
+    else dma_tile<D, false>(Qg + head * D, row0, n, qs + f_stage * kTB);
+    dma4(lse + head + row0, (uint32_t)(min(lane, n - 1 - row0) * 4), (uint32_t)(size_t)(lse_s + f_stage * 256));
+    f_stage = (f_stage + 1) % kStreamStages;
+    f_i += RS;
   };
-  fetch(t_last);
-  fetch(t_last - 1);
-  fetch(t_last - 2);
+  fetch();
+  fetch();
+  fetch();
 
   // K fragments (A operand): lane (key l32, half h) holds K[key][16kk + 8h .. +7]
-  uint4 kf[kStreamKB][KK];
+  uint4 kf[KB][KK];
 #pragma unroll
-  for (int b = 0; b < kStreamKB; ++b) {
-    int r = wc0 + b * 32 + l32;
-    r = r < n ? r : n - 1;
+  for (int b = 0; b < KB; ++b) {
+    const int r = min(wc0 + b * 32 + l32, nk - 1);
+    const bf16_t* row = (K2g && r >= off) ? K2g + (size_t)(r - off) * D : Kg + (size_t)r * D;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) kf[b][kk] = load16(Kg + (size_t)r * D + kk * 16 + h * 8);
+    for (int kk = 0; kk < KK; ++kk) kf[b][kk] = load16(row + kk * 16 + h * 8);
   }
   int qoff[KK];
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) qoff[kk] = l32 * 256 + (((2 * kk + h) ^ k_swizzle(l32)) << 4);
-  float acc[kStreamKB][16];
+  for (int kk = 0; kk < KK; ++kk) qoff[kk] = l32 * D * 2 + (((2 * kk + h) ^ k_swizzle<D>(l32)) << 4);
+  float acc[KB][16];
 #pragma unroll
-  for (int b = 0; b < kStreamKB; ++b)
+  for (int b = 0; b < KB; ++b)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
 
 #pragma unroll
-  for (int b = 0; b < kStreamKB; ++b)
+  for (int b = 0; b < KB; ++b)
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(kf[b][kk].x));  // waited for here, not in the loop
   const RowWindow win(tol, log2_alpha);
-  int lim = max(wc0, first_row);   // rows before `lim` add nothing to this wave's keys
-  for (int t = t_last; t >= t_first; --t) {
-    // tile t has landed: of this wave's fetches only those of tiles t-1 and t-2 (five loads
-    // each) may still be under way
-    wait_vm_barrier<10>();
-    fetch(t - 3);  // into the stage of tile t+1, which every wave has left
+  int lim = max(wc0 - off, first_row);   // rows before `lim` add nothing to this wave's keys
+  int stage = 0, i_seq = part;
+  const int steps = (rc.kv_group * per_head + RS - 1) / RS;
+  for (int u = 0; u < steps; ++u, stage = (stage + 1) % kStreamStages, i_seq += RS) {
+    while (i_seq >= per_head) i_seq -= per_head;
+    const int t = t_last - i_seq;
+    const bool own = RS == 1 || u * RS + part < rc.kv_group * per_head;  // (the second half may be one tile short)
+    // this tile has landed: of this wave's fetches only those of the next two may still be under way
+    wait_vm_barrier<2 * kLoads>();
+    fetch();  // into the stage of the previous tile, which every wave has left
     const int row0 = t * kTile;
-    if (row0 + kTile - 1 >= lim) {  // some row of the tile counts for a key of this wave
-      const int stage = (t_last - t) % kStreamStages;
-      const lds_char* qt = qs + stage * kTileBytes;
+    if (own && row0 + kTile - 1 >= lim) {  // some row of the tile counts for a key of this wave
+      const lds_char* qt = qs + stage * kTB;
       const __attribute__((address_space(3))) float* lse_t =
           (const __attribute__((address_space(3))) float*)(lse_s + stage * 256);
       float zmin[2] = {INFINITY, INFINITY};
 #pragma unroll
       for (int qb = 1; qb >= 0; --qb) {
-        f32x16 sacc[kStreamKB];
+        f32x16 sacc[KB];
 #pragma unroll
-        for (int b = 0; b < kStreamKB; ++b)
+        for (int b = 0; b < KB; ++b)
 #pragma unroll
           for (int i = 0; i < 16; ++i) sacc[b][i] = 0.f;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
-          const uint4 qf = lds_read16(qt + qb * 32 * 256 + qoff[kk]);
+          const uint4 qf = lds_read16(qt + qb * 32 * D * 2 + qoff[kk]);
 #pragma unroll
-          for (int b = 0; b < kStreamKB; ++b) sacc[b] = mfma_bf16(kf[b][kk], qf, sacc[b]);
+          for (int b = 0; b < KB; ++b) sacc[b] = mfma_bf16(kf[b][kk], qf, sacc[b]);
         }
         const int r = row0 + qb * 32 + l32;
         // exponent offset of row r: lse_r - (n-1-r) log2(alpha); rows past the end, and rows
@@ -1448,20 +1174,20 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_stream128_kernel(
         if (win.on && t == t_last) {   // log2 of the newest row's smallest probability, per lane
           float zm = INFINITY;
 #pragma unroll
-          for (int b = 0; b < kStreamKB; ++b)
+          for (int b = 0; b < KB; ++b)
 #pragma unroll
             for (int i = 0; i < 16; ++i) zm = fminf(zm, fmaf(sacc[b][i], scale_log2e, -bias));
           zmin[qb] = zm;
         }
 #pragma unroll
-        for (int b = 0; b < kStreamKB; ++b) {
+        for (int b = 0; b < KB; ++b) {
           const int bk0 = wc0 + b * 32;
-          if (bk0 + 31 > row0 + qb * 32) {  // block reaches above the diagonal
+          if (bk0 + 31 > off + row0 + qb * 32) {  // block reaches above the diagonal
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
               const int key = bk0 + 8 * (i >> 2) + 4 * h + (i & 3);
               const float p = fast_exp2(fmaf(sacc[b][i], scale_log2e, -bias));
-              acc[b][i] += key > r ? 0.f : p;
+              acc[b][i] += key > off + r ? 0.f : p;
             }
           } else {
 #pragma unroll
@@ -1479,25 +1205,42 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_stream128_kernel(
       __syncthreads();
       const int wl = min(min(wave_lim[0], wave_lim[1]), min(wave_lim[2], wave_lim[3]));
       t_first = max(t_first, wl / kTile);
+      per_head = t_last - t_first + 1;
+      if (per_head <= 1) break;
     }
+    if (win.on && t <= t_first) break;
   }
   wait_vm<0>();  // tiles fetched ahead of the last one used: let them land
-  // sum over the 32 rows held by the lanes of one half
+  // sum over the 32 rows held by the lanes of one half, then over the two halves of the workgroup
 #pragma unroll
-  for (int b = 0; b < kStreamKB; ++b) {
+  for (int b = 0; b < KB; ++b) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[b][i] = group_sum<32>(acc[b][i]);
+  }
+  const auto each_key = [&](auto f) {  // by the lanes that hold the sums
     if (l32 == 0) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int key = wc0 + b * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
-        if (key < n) S[(size_t)g * n + key] = acc[b][i];
-      }
+      for (int b = 0; b < KB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) f(b * 32 + 8 * (i >> 2) + 4 * h + (i & 3), acc[b][i]);
     }
+  };
+  const int w0 = wave * 32 * KB;
+  if constexpr (RS > 1) {
+    if (part == 1) each_key([&](int key, float x) { other[w0 + key] = x; });
+    __syncthreads();
+    if (part == 1) return;
   }
+  each_key([&](int key, float x) {
+    if (RS > 1) x += other[w0 + key];
+    if (wc0 + key < nk) {
+      float* out = S + (size_t)g * s_stride + wc0 + key;
+      *out = accumulate ? fmaf(decay, *out, x) : x;
+    }
+  });
 }
 
-// Workgroups per head of col_scores_tail128_kernel: with fewer heads than the chip takes
+// Workgroups per head of col_scores_tail_kernel: with fewer heads than the chip takes
 // workgroups (two per compute unit), a head's keys are shared out, in steps of 256 keys.
 inline int tail_key_split(int G, int keys_per_head) {
   const int steps = (keys_per_head + kWaves * 32 * kTailKB - 1) / (kWaves * 32 * kTailKB);
@@ -1505,66 +1248,45 @@ inline int tail_key_split(int G, int keys_per_head) {
   return want < 1 ? 1 : (want > steps ? steps : want);
 }
 
-// col_scores_bf16_kernel for any head size and geometry
+// Rows split over the two halves of a workgroup of col_scores_stream_kernel: as for the attention rows, while
+// the workgroups are all resident at once (whole calls, alpha = 1, four waves / eight: 4 K/V heads x 8 query heads x 1000
+// 240 / 170 us, 64 x 600 behind a cache 125 / 82; alpha = 0.9, 16 x 5000 218 / 174); beyond that the halves only
+// wait for each other (kernel, 96 x 1777 with d = 64: 73 / 78 us; 32 x 4 x 3001: 41 / 54).
+constexpr unsigned kStreamSplitMaxBlocks = 256;
+
+// Column scores for any head size and geometry.
 template <int D>
-void launch_cols_rect(const void* q, const void* k, const float* lse2, int G, const AttnRect& rc,
-                      int keys_per_head, float alpha, const float* alpha_heads, float* scores,
-                      int s_stride, bool accumulate, float decay, hipStream_t st) {
+void launch_cols(const void* q, const void* k, const float* lse2, int G, const AttnRect& rc,
+                 int keys_per_head, float alpha, const float* alpha_heads, float tol, float* scores,
+                 int s_stride, bool accumulate, float decay, hipStream_t st) {
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)D);
   float l2a;
   const int first = first_contributing_row(rc.m, alpha, &l2a);
-  if constexpr (D == 128) {
-    // a row window of at most four tiles: staged once per head, every key streamed once
-    if (bf16_two_source_ok(D, rc, alpha)) {  // (also the only score kernel that reads a second key source)
-      const int ks = tail_key_split(G, keys_per_head);
-      hipLaunchKernelGGL(col_scores_tail128_kernel, dim3(G * ks), dim3(kThreads), 0, st, (const bf16_t*)q,
-                         (const bf16_t*)k, lse2, scores, rc, s_stride, accumulate, decay, first, l2a,
-                         alpha_heads, scale_log2e, 0.f, ks);
-      return;
-    }
+  // one query head per K/V head and a row window of at most four tiles: staged once per head,
+  // every key streamed once
+  if (rc.kv_group == 1 && rc.m - (first / kTile) * kTile <= kTailTiles * kTile) {
+    const int ks = tail_key_split(G, keys_per_head);
+    hipLaunchKernelGGL((col_scores_tail_kernel<D>), dim3(G * ks), dim3(kThreads), 0, st, (const bf16_t*)q,
+                       (const bf16_t*)k, lse2, scores, rc, s_stride, accumulate, decay, first, l2a,
+                       alpha_heads, scale_log2e, tol, ks);
+    return;
   }
-  const int ncb = (keys_per_head + kWaves * 32 - 1) / (kWaves * 32);
-  const long long total = (long long)G * ncb;
-  const unsigned grid = (unsigned)(((total + 7) / 8) * 8);
-  hipLaunchKernelGGL((col_scores_bf16_kernel<D>), dim3(grid), dim3(kThreads), 0, st, (const bf16_t*)q,
-                     (const bf16_t*)k, lse2, scores, rc, s_stride, accumulate, decay, G, ncb, first, l2a,
-                     alpha_heads, scale_log2e);
-}
-
-template <int D>
-void launch_cols(const void* q, const void* k, const float* lse2, int G, int n, float alpha,
-                 const float* alpha_heads, float tol, float* scores, hipStream_t st) {
-  const float scale_log2e = 1.4426950408889634f / sqrtf((float)D);
-  float l2a;
-  const int first = first_contributing_row(n, alpha, &l2a);
-  if constexpr (D == 128) {
-    if (n - (first / kTile) * kTile <= kTailTiles * kTile) {
-      const int ks = tail_key_split(G, n);
-      hipLaunchKernelGGL(col_scores_tail128_kernel, dim3(G * ks), dim3(kThreads), 0, st, (const bf16_t*)q,
-                         (const bf16_t*)k, lse2, scores, AttnRect{n, n, nullptr}, n, false, 0.f, first, l2a,
-                         alpha_heads, scale_log2e, tol, ks);
-      return;
-    }
-    constexpr int BC = kWaves * 32 * kStreamKB;
-    const int ncb = (n + BC - 1) / BC;
-    const unsigned grid = (unsigned)((((long long)G * ncb + 7) / 8) * 8);
-    hipLaunchKernelGGL(col_scores_stream128_kernel, dim3(grid), dim3(kThreads), 0, st,
-                       (const bf16_t*)q, (const bf16_t*)k, lse2, scores, n, G, ncb, first, l2a,
-                       alpha_heads, scale_log2e, tol);
-  } else {
-    launch_cols_rect<D>(q, k, lse2, G, AttnRect{n, n, nullptr}, n, alpha, alpha_heads, scores, n, false,
-                        0.f, st);
-  }
+#define A2SF_STREAM(KB, RS)                                                                           \
+  do {                                                                                                \
+    const int ncb = (keys_per_head + kWaves * 32 * KB - 1) / (kWaves * 32 * KB);                      \
+    const unsigned grid = (unsigned)((((long long)G * ncb + 7) / 8) * 8);                             \
+    hipLaunchKernelGGL((col_scores_stream_kernel<D, KB, RS>), dim3(grid), dim3(kThreads * RS), 0, st, \
+                       (const bf16_t*)q, (const bf16_t*)k, lse2, scores, rc, s_stride, accumulate, decay, G, ncb, \
+                       first, l2a, alpha_heads, scale_log2e, tol);                                    \
+  } while (0)
+  const long long blocks = (long long)G * ((keys_per_head + 255) / 256);
+  if (blocks <= kStreamSplitMaxBlocks && !(tol > 0.f)) A2SF_STREAM(2, 2);
+  else if constexpr (D == 64) A2SF_STREAM(1, 1);
+  else A2SF_STREAM(2, 1);
+#undef A2SF_STREAM
 }
 
 }  // namespace
-
-bool bf16_two_source_ok(int d, const AttnRect& rc, float alpha) {
-  if (d != 128 || rc.kv_group != 1) return false;
-  float l2a;
-  const int first = first_contributing_row(rc.m, alpha, &l2a);
-  return rc.m - (first / kTile) * kTile <= kTailTiles * kTile;  // the staged-window score kernel
-}
 
 void launch_attn_bf16(const void* q, const void* k, const void* v, int G, const AttnRect& rc, int d,
                       void* o, float* lse2, hipStream_t st) {
@@ -1579,31 +1301,33 @@ void launch_colscores_bf16(const void* q, const void* k, const float* lse2, int 
                            const AttnRect& rc, int keys_per_head, int d, float alpha, float* scores,
                            int s_stride, bool accumulate, float decay, hipStream_t st) {
   if (d == 64)
-    launch_cols_rect<64>(q, k, lse2, G, rc, keys_per_head, alpha, nullptr, scores, s_stride, accumulate, decay, st);
+    launch_cols<64>(q, k, lse2, G, rc, keys_per_head, alpha, nullptr, 0.f, scores, s_stride, accumulate, decay, st);
   else
-    launch_cols_rect<128>(q, k, lse2, G, rc, keys_per_head, alpha, nullptr, scores, s_stride, accumulate, decay, st);
+    launch_cols<128>(q, k, lse2, G, rc, keys_per_head, alpha, nullptr, 0.f, scores, s_stride, accumulate, decay, st);
 }
 
 void launch_prefill_bf16(const void* q, const void* k, const void* v, int G, int n, int d,
                          void* o, float* lse2, hipStream_t st, int first_row) {
-  if (d == 64) launch_fwd<64>(q, k, v, G, n, o, lse2, st);
+  if (d == 64) launch_fwd<64>(q, k, v, G, n, o, lse2, st, 1, first_row);
   else launch_fwd<128>(q, k, v, G, n, o, lse2, st, 1, first_row);
 }
 
-int bf16_first_lse_row(int n, int d, float alpha_max) {
-  if (d != 128) return 0;
+int bf16_first_lse_row(int n, float alpha_max) {
   float l2a;
-  // every score kernel walks the row tiles from the one that holds the first contributing row
-  // on (col_scores_tail128_kernel stages them, the others start their tile loop there; a tile
-  // they fetch below it is never used)
+  // the score kernels walk the row tiles from the one that holds the first contributing row
+  // on (col_scores_tail_kernel stages them, the other starts its tile loop there; a tile
+  // it fetches below that is never used)
   return (first_contributing_row(n, alpha_max, &l2a) / kTile) * kTile;
 }
 
 void launch_scores_bf16(const void* q, const void* k, const float* lse2, int G, int n, int d,
                         float alpha, const float* alpha_heads, float tol, float* scores,
                         hipStream_t st) {
-  if (d == 64) launch_cols<64>(q, k, lse2, G, n, alpha, alpha_heads, tol, scores, st);
-  else launch_cols<128>(q, k, lse2, G, n, alpha, alpha_heads, tol, scores, st);
+  const AttnRect rc{n, n, nullptr};
+  if (d == 64)  // (the tolerance is defined for d = 128 only)
+    launch_cols<64>(q, k, lse2, G, rc, n, alpha, alpha_heads, 0.f, scores, n, false, 0.f, st);
+  else
+    launch_cols<128>(q, k, lse2, G, rc, n, alpha, alpha_heads, tol, scores, n, false, 0.f, st);
 }
 
 }  // namespace a2sf

@@ -143,3 +143,53 @@ def test_gather_list_lengths(dtype, d, budget, n):
     of their own: both sides of the line, full lists and prompts shorter than the budget."""
     prompt_and_steps(variant(1 if dtype == "bf16" else 0, heads=3, d=d, dtype=dtype, n=n, T=1, select=budget // 2,
                              recent=budget - budget // 2, name="list lengths"), 0.8, steps=1)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,n", [(300, 1), (300, 63), (300, 65), (150, 130), (150, 200), (40, 700), (3, 64), (3, 449)])
+def test_bf16_prompt_tiles(G, n, d):
+    """Up to 256 row blocks of 128 the keys of a row are split between the two halves of a workgroup (few
+    heads: one to eight tiles, odd and even numbers of them), above that they are not; the streaming
+    score kernel (alpha = 1) likewise takes every other tile per half, or all of them."""
+    for alpha in (0.4, 1.0):
+        prompt_and_steps(variant(1, heads=G, d=d, n=n, T=1, select=min(11, n), recent=9, name="bf16 tiles"), alpha,
+                         sample=sorted({0, G // 2, G - 1}), steps=1)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,group,m", [(2, 1, 1), (2, 1, 130), (300, 1, 66), (2, 3, 70), (120, 3, 90), (2, 8, 300)])
+def test_bf16_chunk_tiles(G, group, m, d):
+    """Chunks whose keys lie half in the cache and half in the call's inputs, for every size class of
+    the attention and score kernels: tiles that straddle the two, chunks of less than a tile, groups."""
+    select, recent, alpha, L0 = 40, 37, np.float32(0.93), 101
+    gen = torch.Generator(device="cuda").manual_seed(m + d)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").bfloat16()
+    cache = a2sf.Cache(G, L0 + m + 3, d, torch.bfloat16)
+    cache.k[:, :L0], cache.v[:, :L0] = rnd(G, L0, d), rnd(G, L0, d)
+    cache.scores[:, :L0] = torch.rand(G, L0, generator=gen, device="cuda")
+    cache.pos[:, :L0] = torch.arange(L0, device="cuda").int()
+    lens = torch.randint(0, L0 + 1, (G,), generator=gen, device="cuda").int()
+    lens[0], lens[-1] = 64, L0
+    cache.len.copy_(lens)
+    q, k, v = rnd(G, group, m, d), rnd(G, m, d), rnd(G, m, d)
+    sample = sorted({0, G // 2, G - 1})
+    oc = {g: orc.HeadCache(*(parity.to_f64(x[g, : int(lens[g])]) for x in (cache.k, cache.v, cache.scores)),
+                           cache.pos[g, : int(lens[g])].cpu().numpy().astype(np.int64)) for g in sample}
+    ws = torch.empty(a2sf.a2sf_workspace_bytes(G * group, m, cache.capacity, d, a2sf.A2SF_BF16, select, recent),
+                     dtype=torch.uint8, device="cuda")
+    o = torch.full((G, group, m, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    if group == 1:
+        a2sf.a2sf_prefill_chunk(q, k, v, m, L0, float(alpha), select, recent, cache, o=o, workspace=ws)
+    else:
+        a2sf.a2sf_prefill_chunk_gqa(q, k, v, m, L0, group, float(alpha), select, recent, cache, o=o, workspace=ws)
+    torch.cuda.synchronize()
+    for g in sample:
+        kept = int(cache.len[g])
+        pos = cache.pos[g, :kept].cpu().numpy().astype(np.int64)
+        O, _, _ = orc.gqa_prefill_chunk(oc[g], parity.to_f64(q[g]), parity.to_f64(k[g]), parity.to_f64(v[g]), L0,
+                                        float(alpha), select, recent, forced_retained=pos.tolist(), margin=parity.MARGIN)
+        assert np.abs(parity.to_f64(o[g]) - O).max() <= parity.O_TOL["bf16"]
+        c = oc[g].sorted_by_pos()
+        assert np.array_equal(pos, c.pos)
+        assert np.array_equal(parity.to_f64(cache.k[g, :kept]), c.K) and np.array_equal(parity.to_f64(cache.v[g, :kept]), c.V)
+        parity.compare_scores(cache.scores[g, :kept].cpu().numpy(), c.S, f"head {g}")

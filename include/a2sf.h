@@ -299,7 +299,8 @@ a2sf_status a2sf_similarity_mean(const float* cos, int32_t steps, int32_t G, int
  * benchmarks and profiles that have to name the kernels they measure).  Any out pointer may
  * be NULL.
  *   nsplit          workgroups per head; 1 = one fused kernel, > 1 = the tokens of a head are
- *                   split over that many workgroups and a second kernel combines them.
+ *                   split over that many workgroups and a second kernel combines them (reported
+ *                   for bf16; few fp32 heads are split from fewer slots on).
  *   rows_per_split  cached tokens per workgroup when nsplit > 1.
  *   wave_slots      > 0: a wave works on a whole head (64 * wave_slots slots in registers).
  *   wave_heads      heads a wave works through in the fast eviction mode: 1, or more in the

@@ -170,7 +170,8 @@ a2sf_status decode_impl(const void* q, const void* k_new, const void* v_new, int
   if (t_pos < 0) return A2SF_EINVAL;
   if (mode != A2SF_EVICT_FAST && mode != A2SF_EVICT_STABLE) return A2SF_EINVAL;
   const WsLayout w = ws_layout(cache->G, 0, cache->capacity, cache->d, budget);
-  const DecodePlan plan = plan_decode(cache->G, cache->capacity, cache->d);
+  DecodePlan plan = plan_decode(cache->G, cache->capacity, cache->d);
+  plan.small = decode_small(cache->G, cache->capacity, cache->d, cache->dtype, mode == A2SF_EVICT_STABLE);
   const bool needs_ws = plan.ws_bytes > 0 || mode == A2SF_EVICT_STABLE;
   if (needs_ws && (!workspace || misaligned(workspace) || workspace_bytes < w.total))
     return A2SF_EWORKSPACE;
@@ -180,7 +181,7 @@ a2sf_status decode_impl(const void* q, const void* k_new, const void* v_new, int
   char* ws = (char*)workspace;
   launch_decode(q, k_new, v_new, t_pos, *cache, alpha, alpha_heads, budget.select, budget.recent,
                 mode == A2SF_EVICT_FAST, o, ws ? ws + w.split : nullptr, plan, st);
-  if (mode == A2SF_EVICT_STABLE) {
+  if (mode == A2SF_EVICT_STABLE && !plan.small) {
     int32_t* keep_idx = (int32_t*)(ws + w.keep_idx);
     int32_t* n_keep = (int32_t*)(ws + w.n_keep);
     launch_select(cache->scores, cache->pos, cache->len, cache->G, cache->capacity,
@@ -494,7 +495,11 @@ a2sf_status a2sf_decode_plan(int32_t G, int32_t capacity, int32_t d, int32_t* ns
                              int32_t* rows_per_split, int32_t* wave_slots, int32_t* wave_heads) {
   if (G < 1 || (d != 64 && d != 128)) return A2SF_ESHAPE;
   if (capacity < 1 || capacity > A2SF_MAX_CAPACITY) return A2SF_ECAPACITY;
-  const DecodePlan p = plan_decode(G, capacity, d);
+  DecodePlan p = plan_decode(G, capacity, d);
+  if (decode_small(G, capacity, d, A2SF_BF16, false)) {
+    p.nsplit = 1;
+    p.rows_per_split = (capacity + 63) / 64 * 64;
+  }
   if (nsplit) *nsplit = p.nsplit;
   if (rows_per_split) *rows_per_split = p.rows_per_split;
   if (wave_slots) *wave_slots = p.wave_slots;

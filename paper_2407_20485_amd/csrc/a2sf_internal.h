@@ -30,10 +30,12 @@ struct DecodePlan {
   int wave_slots;      // > 0: wave-per-head kernel holding 64*wave_slots slots in registers
   bool loop;           // wave-per-head path, fast mode: persistent workgroups, a wave works through several heads
   int wave_heads;      // ... that many (1 otherwise)
+  bool small;          // one large workgroup per head, all rows in registers; does the stable eviction itself
   bool stream;         // single-kernel paths: load the cache rows with the non-temporal hint
   size_t ws_bytes;     // split-K scratch
 };
 DecodePlan plan_decode(int G, int capacity, int d);
+bool decode_small(int G, int capacity, int d, int dtype, bool stable);  // whether DecodePlan::small applies
 void launch_decode(const void* q, const void* k_new, const void* v_new, int t_pos,
                    const a2sf_cache& c, float alpha, const float* alpha_heads, int select,
                    int recent, bool evict_here, void* o, void* ws, const DecodePlan& plan,

@@ -1446,6 +1446,224 @@ void decode_gqa_mfma_kernel(
                                   t_pos, alpha, select, recent, evict_here != 0, sms[wave]);
 }
 
+// ---- one large workgroup per head, the whole head in registers --------------------------
+// For few heads with short caches.  Such a step moves a few megabytes and is a chain of round trips:
+// decode_fused_kernel waits for the length, then for the K rows (two rounds of loads), then for
+// the V rows, and meets at a dozen barriers.  Here 16 waves request every K and V row of the
+// cache's capacity, the query, the new token's rows, the scores and the positions at once, before
+// the length is known (rows past it are read and ignored); each wave then forms the softmax
+// statistics of the whole head for itself from the logits in LDS, so the workgroup meets at two
+// barriers, and wave 0 alone does the bookkeeping (slot j = lane + 64 k).  In the stable mode every
+// row is already in a register when the victim is known: it is stored at its new slot, and no
+// selection or compaction kernel follows.
+// GPU time per step (steps replayed from a graph), bf16, d = 128, the kernels it replaced / here: 32 heads x 205
+// slots 7.2 / 6.4 us, 255 x 256 8.4 / 7.1, 100 x 257 10.2 / 9.0; d = 64, 255 x 300 13.1 / 7.4; stable mode
+// (fused step, selection, compaction / here): 320 x 410 42 / 29.8.
+constexpr int kSmallWaves = 16;
+constexpr int kSmallMaxSlots = 512;
+constexpr int kSmallMaxHeads = 255, kSmallMaxHeadsStable = 4095;
+template <typename T, int D>
+constexpr int kSmallRows = kSmallWaves * RowGeom<T, D>::RPW;  // rows of one pass
+
+template <typename T, int D, int NP>  // NP passes of kSmallRows rows each
+__global__ __launch_bounds__(kSmallWaves * 64) void decode_small_kernel(
+    const T* __restrict__ q, const T* __restrict__ k_new, const T* __restrict__ v_new, int t_pos,
+    T* K, T* V, float* S, int32_t* P, int32_t* len, int capacity, float alpha,
+    const float* __restrict__ alpha_heads, int select, int recent, int evict, T* __restrict__ o,
+    float scale_log2e) {
+  using Gm = RowGeom<T, D>;
+  constexpr int NJ = NP * kSmallRows<T, D> / 64;  // slots per lane of wave 0
+  static_assert(NJ >= 1 && NJ * 64 <= kSmallMaxSlots, "slots");
+  __shared__ float z[NJ * 64];
+  __shared__ float part[kSmallWaves][D];
+  __shared__ float sz[NJ * 64];
+  __shared__ int pz[NJ * 64], dst[NJ * 64];
+  __shared__ StepSmem sm;
+  const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int sub = lane % Gm::LPR, rgrp = lane / Gm::LPR;
+  T* Kg = K + (size_t)g * capacity * D;
+  T* Vg = V + (size_t)g * capacity * D;
+  float* Sg = S + (size_t)g * capacity;
+  int32_t* Pg = P + (size_t)g * capacity;
+  const T* knew = k_new + (size_t)g * D;
+  const T* vnew = v_new + (size_t)g * D;
+
+  const int n_old = len[g];
+  float qv[Gm::EPL];
+  const uint4 q_raw = load16(q + (size_t)g * D + sub * Gm::EPL);
+  uint4 kx[NP], vx[NP];
+  const int row0 = wave * Gm::RPW + rgrp;  // this lane's row of the first pass
+#pragma unroll
+  for (int p = 0; p < NP; ++p) kx[p] = load16(Kg + (size_t)min(row0 + p * kSmallRows<T, D>, capacity - 1) * D + sub * Gm::EPL);
+  const uint4 kn = load16(knew + sub * Gm::EPL), vn = load16(vnew + sub * Gm::EPL);
+#pragma unroll
+  for (int p = 0; p < NP; ++p) vx[p] = load16(Vg + (size_t)min(row0 + p * kSmallRows<T, D>, capacity - 1) * D + sub * Gm::EPL);
+  float s_old[NJ];
+  int pos[NJ];
+  if (wave == 0) {
+#pragma unroll
+    for (int k = 0; k < NJ; ++k) {
+      s_old[k] = Sg[min(lane + 64 * k, capacity - 1)];
+      pos[k] = Pg[min(lane + 64 * k, capacity - 1)];
+    }
+  }
+  if (alpha_heads) alpha = alpha_heads[g];
+  if (n_old < 0 || n_old >= capacity) {
+    flag_bad_head<T, D>(o + (size_t)g * D, tid, kSmallWaves * 64);
+    return;
+  }
+  const int L = n_old + 1;
+
+  Elem<T>::unpack(q_raw, qv);
+#pragma unroll
+  for (int e = 0; e < Gm::EPL; ++e) qv[e] *= scale_log2e;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int r = row0 + p * kSmallRows<T, D>;
+    if (r == n_old) { kx[p] = kn; vx[p] = vn; }
+    float f[Gm::EPL];
+    Elem<T>::unpack(kx[p], f);
+    float dot = 0.f;
+#pragma unroll
+    for (int e = 0; e < Gm::EPL; ++e) dot = fmaf(qv[e], f[e], dot);
+    dot = group_sum<Gm::LPR>(dot);
+    if (sub == 0) z[r] = r < L ? dot : -INFINITY;
+  }
+  __syncthreads();
+
+  // softmax statistics of the head, by every wave for itself
+  float pr[NJ];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < NJ; ++k) {
+    pr[k] = z[lane + 64 * k];
+    mx = fmaxf(mx, pr[k]);
+  }
+  mx = wave_max(mx);
+  float sum = 0.f;
+#pragma unroll
+  for (int k = 0; k < NJ; ++k) {
+    pr[k] = exp2f(pr[k] - mx);  // 0 for slots >= L
+    sum += pr[k];
+  }
+  const float inv = 1.0f / wave_sum(sum);
+  float acc[Gm::EPL];
+#pragma unroll
+  for (int e = 0; e < Gm::EPL; ++e) acc[e] = 0.f;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int r = row0 + p * kSmallRows<T, D>;
+    const float w = exp2f(z[r] - mx) * inv;
+    float f[Gm::EPL];
+    Elem<T>::unpack(vx[p], f);
+    if (r < L) {  // (rows past the length hold anything)
+#pragma unroll
+      for (int e = 0; e < Gm::EPL; ++e) acc[e] = fmaf(w, f[e], acc[e]);
+    }
+  }
+  v_fold_row_groups<T, D>(acc);
+  if (rgrp == 0) {
+#pragma unroll
+    for (int e = 0; e < Gm::EPL; ++e) part[wave][sub * Gm::EPL + e] = acc[e];
+  }
+  if (wave == 0) {
+#pragma unroll
+    for (int k = 0; k < NJ; ++k) {
+      const int j = lane + 64 * k;
+      pr[k] *= inv;
+      s_old[k] = j < n_old ? s_old[k] : 0.f;
+      pos[k] = j < n_old ? pos[k] : t_pos;
+    }
+    if (evict == kEvictShift) {
+      // where every row goes, -1: it leaves
+      float s_new[NJ];
+#pragma unroll
+      for (int k = 0; k < NJ; ++k) s_new[k] = fmaf(alpha, s_old[k], pr[k]);
+      const int excess = L - (select + recent);
+      bool gone[NJ];
+#pragma unroll
+      for (int k = 0; k < NJ; ++k) gone[k] = false;
+      if (excess > 0) {
+        // protected: the `recent` newest positions; exactly those > t_pos - recent in a cache that
+        // always kept them, otherwise by rank
+        int cnt = 0;
+        bool kept[NJ];
+#pragma unroll
+        for (int k = 0; k < NJ; ++k) {
+          kept[k] = lane + 64 * k >= L || pos[k] > t_pos - recent;
+          cnt += kept[k] && lane + 64 * k < L;
+        }
+        if (wave_sum_i(cnt) != recent) {
+#pragma unroll
+          for (int k = 0; k < NJ; ++k)
+            if (lane + 64 * k < L) pz[lane + 64 * k] = pos[k];
+          WaveGroup::sync();
+#pragma unroll
+          for (int k = 0; k < NJ; ++k) {
+            int newer = 0;
+            for (int i = 0; i < L; ++i) newer += pz[i] > pos[k];
+            kept[k] = lane + 64 * k >= L || newer < recent;
+          }
+          WaveGroup::sync();
+        }
+        for (int it = 0; it < excess; ++it) {  // the lowest score leaves; among equals the highest position
+          unsigned long long best = ~0ull;
+#pragma unroll
+          for (int k = 0; k < NJ; ++k) {
+            const unsigned long long key = kept[k] || gone[k] ? ~0ull : evict_key(s_new[k], pos[k]);
+            best = key < best ? key : best;
+          }
+          best = wave_min_u64(best);
+#pragma unroll
+          for (int k = 0; k < NJ; ++k)
+            gone[k] = gone[k] || (!kept[k] && best != ~0ull && evict_key(s_new[k], pos[k]) == best);
+        }
+      }
+      int before = 0;
+#pragma unroll
+      for (int k = 0; k < NJ; ++k) {
+        const int j = lane + 64 * k;
+        const unsigned long long left = __ballot(gone[k]);
+        const int to = j - before - (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(left >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)left, 0u));
+        before += __popcll(left);
+        dst[j] = gone[k] || j >= L ? -1 : to;
+        if (!gone[k] && j < L) { sz[to] = s_new[k]; pz[to] = pos[k]; }
+      }
+      WaveGroup::sync();
+#pragma unroll
+      for (int k = 0; k < NJ; ++k) {
+        const int j = lane + 64 * k;
+        if (j < L - before) { Sg[j] = sz[j]; Pg[j] = pz[j]; }
+      }
+      if (lane == 0) len[g] = L - before;
+    }
+  }
+  __syncthreads();
+  if (tid >= 64 && tid < 64 + D) {
+    const int c = tid - 64;
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; w += 4) t += (part[w][c] + part[w + 1][c]) + (part[w + 2][c] + part[w + 3][c]);
+    Elem<T>::store(o + (size_t)g * D + c, t);
+  }
+  if (evict == kEvictShift) {
+    // (every row was read before the first barrier: a store can only hit rows that are in registers)
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int r = row0 + p * kSmallRows<T, D>;
+      const int to = dst[r];
+      if (to >= 0 && (to != r || r == n_old)) {
+        store16(Kg + (size_t)to * D + sub * Gm::EPL, kx[p]);
+        store16(Vg + (size_t)to * D + sub * Gm::EPL, vx[p]);
+      }
+    }
+  } else if (wave == 0) {
+    wave_update_and_evict<T, D, NJ>(s_old, pr, pos, z, n_old, Kg, Vg, Sg, Pg, len + g, knew, vnew, t_pos, alpha,
+                                    select, recent, true, sm);
+  }
+}
+
 // ---- split over tokens ----------------------------------------------------------------
 // workspace layout (floats): z[G][capacity] | ml[G][nsplit][2] | po[G][nsplit][D]
 template <typename T, int D>
@@ -1587,6 +1805,18 @@ void launch_typed(const void* q, const void* k_new, const void* v_new, int t_pos
     else A2SF_WAVE(8);
 #undef A2SF_WAVE
 #undef A2SF_WAVE_
+    return;
+  }
+  if (plan.small) {
+    constexpr int kNP = kSmallMaxSlots / kSmallRows<T, D> < 8 ? kSmallMaxSlots / kSmallRows<T, D> : 8;  // most passes
+#define A2SF_SMALL(NP)                                                                                  \
+  hipLaunchKernelGGL((decode_small_kernel<T, D, NP>), dim3(c.G), dim3(kSmallWaves * 64), 0, st, (const T*)q, \
+                     (const T*)k_new, (const T*)v_new, t_pos, (T*)c.k, (T*)c.v, c.scores, c.pos, c.len, \
+                     c.capacity, alpha, alpha_heads, select, recent,                                    \
+                     evict_here ? kEvictInSlot : kEvictShift, (T*)o, scale_log2e)
+    if (c.capacity <= kNP / 2 * kSmallRows<T, D>) A2SF_SMALL(kNP / 2);
+    else A2SF_SMALL(kNP);
+#undef A2SF_SMALL
     return;
   }
   // the kernels that keep one float per slot in LDS may ask for more than the default 64 KB
@@ -1989,9 +2219,26 @@ DecodePlan plan_decode(int G, int capacity, int d) {
   // last-level cache from one step to the next anyway (320 heads x 410 slots, 69 MB, resident:
   // 17.2 us per step without the hint, 20.8 with it; 16384 x 201, 1.7 GB: 317 without, 291 with).
   p.stream = 4.0 * G * capacity * d > 512e6;   // K and V rows of >= 2 bytes per element
+  p.small = false;
   p.ws_bytes = ns <= 1 ? 0
                        : sizeof(float) * ((size_t)G * capacity + (size_t)G * ns * 2 + (size_t)G * ns * d);
   return p;
+}
+
+// Capacities that fit the registers of one large workgroup: eight passes of 16 waves, 1 KB per wave
+// and pass.
+// Fast mode: up to one head per compute unit -- a second one would wait for the first, and one 256-thread
+// workgroup per head overlaps more of them (bf16, d = 128, kernel here / decode_fused_kernel: 320 x 410
+// 22.1 / 15.3 us, 512 x 512 35.8 / 27.1) -- and, from the capacities on where the tokens of few heads are
+// split over workgroups, up to 96 KB of K rows per head (graph replay, here / split: 64 x 300 9.0 / 9.3 us,
+// 255 x 300 11.7 / 13.8, with d = 64 7.4 / 12.2; but 8 x 512 9.2 / 8.7, 255 x 512 17.0 / 16.4).
+// Stable mode, where it replaces three kernels: up to the heads that the wave-per-head kernel takes (us
+// per call, three kernels / here: 600 x 201 58 / 24, 1000 x 410 151 / 79, 3000 x 201 211 / 104,
+// 4000 x 512 with d = 64 327 / 170).
+bool decode_small(int G, int capacity, int d, int dtype, bool stable) {
+  const int row_bytes = d * (dtype == A2SF_BF16 ? 2 : 4);
+  if (capacity > (row_bytes >= 512 ? 256 : kSmallMaxSlots)) return false;
+  return stable ? G <= kSmallMaxHeadsStable : G <= kSmallMaxHeads && (capacity <= 256 || capacity * row_bytes <= 96 * 1024);
 }
 
 void launch_decode(const void* q, const void* k_new, const void* v_new, int t_pos,

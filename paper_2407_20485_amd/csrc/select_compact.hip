@@ -435,8 +435,8 @@ void launch_select_gather(const void* k, const void* v, const float* scores_full
   const int keep_stride = select + recent;
   // Short lists: the workgroup that selects also copies (up to 512 KB per head) -- one launch and one
   // round trip through the index list less (bf16, d = 128: 2048 heads keeping 200 of 2048 rows 28 + 69 us
-  // in two kernels, 77 in one; 32 heads keeping 204 of 1024: 7.7 + 4.3 and 11.9, a launch less; 64 heads
-  // keeping 177 of 1777, d = 64: 15 + 6 and 13).  A longer list is copied by more workgroups than one per
+  // in two kernels, 77 in one; 32 heads keeping 204 of 1024: 7.7 + 4.3 and 11.9, a launch less; 96 heads
+  // keeping 355 of 1777, d = 64: 15 + 6 and 13).  A longer list is copied by more workgroups than one per
   // head: 32 heads keeping 3276 of 32768 rows move 3.4 MB per head, 20 us with 205 workgroups per head.
   if (keep_stride <= kFusedKeep) {
     const GatherTo to = {(const u32x4_t*)k, (const u32x4_t*)v, (u32x4_t*)c.k, (u32x4_t*)c.v, c.scores, c.pos,

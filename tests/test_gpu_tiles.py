@@ -193,3 +193,24 @@ def test_bf16_chunk_tiles(G, group, m, d):
         assert np.array_equal(pos, c.pos)
         assert np.array_equal(parity.to_f64(cache.k[g, :kept]), c.K) and np.array_equal(parity.to_f64(cache.v[g, :kept]), c.V)
         parity.compare_scores(cache.scores[g, :kept].cpu().numpy(), c.S, f"head {g}")
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("budget", [1, 62, 63, 64, 127, 128, 254, 255, 300, 511])
+def test_small_step_capacities(dtype, d, budget):
+    """Generation steps whose head fits the registers of one workgroup: capacities around every number of
+    passes and slots, both eviction modes, caches that are still filling, several evictions at once."""
+    if dtype == "f32" and d == 128 and budget > 300:
+        budget = 255
+    recent = budget // 3
+    for mode in (a2sf.A2SF_EVICT_FAST, a2sf.A2SF_EVICT_STABLE):
+        w = variant(1 if dtype == "bf16" else 0, heads=5, d=d, dtype=dtype, n=max(1, budget - 2), T=7,
+                    select=budget - recent, recent=recent, name="small step")
+        ls = parity.LockStep(parity.Problem(w), 0.6)
+        ls.prefill()
+        for t in range(4):
+            ls.step(t, mode=mode)
+        if budget >= 62:  # a lower budget: several tokens leave in one step
+            ls.select, ls.recent = ls.select - 9, ls.recent - 8
+        for t in range(4, 7):
+            ls.step(t, mode=mode)

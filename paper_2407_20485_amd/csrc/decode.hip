@@ -61,6 +61,20 @@ struct BlockGroup {
     return block_min_u64(v, sm.red64);
   }
 };
+constexpr int kMergeThreads = 1024, kMergeWaves = kMergeThreads / kWave;
+struct MergeGroup {  // the large workgroups that merge a head's token splits
+  static constexpr int kSize = kMergeThreads, kNW = kMergeWaves;
+  __device__ static __forceinline__ int tid() { return threadIdx.x; }
+  __device__ static __forceinline__ void sync() { __syncthreads(); }
+  __device__ static __forceinline__ unsigned long long min_u64(unsigned long long v, StepSmem&) {
+    __shared__ unsigned long long red[kNW];
+    v = wave_min_u64(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return wave_min_u64((threadIdx.x & 63) < kNW ? red[threadIdx.x & 63] : ~0ull);
+  }
+};
 struct WaveGroup {
   static constexpr int kSize = kWave, kNW = 1;
   __device__ static __forceinline__ int tid() { return threadIdx.x & 63; }
@@ -1715,51 +1729,171 @@ __global__ __launch_bounds__(kThreads) void decode_partial_kernel(
   if (tid < D) poo[tid] = part[0][tid];
 }
 
+// The merge moves kilobytes and is one chain of round trips, so it runs with 1024 threads per head that
+// request everything -- per-split (max, sum) and outputs, logits, scores and positions of the first
+// 4096 slots, the new token's rows -- before the length is known (what lies past it is ignored);
+// every wave merges the splits' statistics for itself, the wave that owns the victim writes the new rows, and the
+// workgroup meets once (grouped queries: twice).  32 heads x 3277 slots: 8.5 us with 256 threads, 4.9 here; 64 K/V
+// heads x 4 queries x 1025 slots: 7.0 and 4.9.
+constexpr int kMergeBatch = 4;  // slots per thread and pass
+template <int NA>
+struct MergeBatch {             // slots tid + b * kMergeThreads from `base` on
+  float s[kMergeBatch], z[kMergeBatch][NA];
+  int p[kMergeBatch];
+  __device__ __forceinline__ void load(int base, const float* zg, const float* Sg, const int32_t* Pg, int capacity) {
+#pragma unroll
+    for (int b = 0; b < kMergeBatch; ++b) {
+      const int j = base + (int)threadIdx.x + b * kMergeThreads;
+      s[b] = 0.f;
+      p[b] = 0;
+#pragma unroll
+      for (int r = 0; r < NA; ++r) z[b][r] = 0.f;
+      if (j < capacity) {
+        s[b] = Sg[j];
+        p[b] = Pg[j];
+#pragma unroll
+        for (int r = 0; r < NA; ++r) z[b][r] = zg[(size_t)r * capacity + j];
+      }
+    }
+  }
+};
+template <int NOUT>
+struct MergeSmem {
+  float part[NOUT];  // the splits' outputs, summed by groups of threads
+  unsigned long long key[kMergeWaves];
+  int cnt[kMergeWaves];
+  float s_tok;
+};
+
+// Score update and eviction of one head, as update_and_evict.  `meet` runs right after the barrier.
+// prob(z): a slot's probability from its NA logits.
+template <typename T, int D, int NA, int NOUT, typename ProbFn, typename MeetFn>
+__device__ __forceinline__ void merge_update_and_evict(
+    MergeBatch<NA>& sb, ProbFn prob, MeetFn meet, uint4 row_new, MergeSmem<NOUT>& ms, float* a, int n_old, T* Kg,
+    T* Vg, const float* zg, float* Sg, int32_t* Pg, int32_t* len_g, const T* knew, const T* vnew, int t_pos,
+    float alpha, int select, int recent, bool evict_here, int capacity, StepSmem& sm) {
+  constexpr int LPR = RowGeom<T, D>::LPR, EPL = RowGeom<T, D>::EPL;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int L = n_old + 1;
+  const int excess = evict_here ? L - (select + recent) : 0;
+  const int thr = t_pos - recent;
+  int cnt = 0, best_slot = n_old;
+  unsigned long long best = ~0ull;
+  for (int base = 0; base < L; base += kMergeThreads * kMergeBatch) {
+    if (base > 0) sb.load(base, zg, Sg, Pg, capacity);
+#pragma unroll
+    for (int b = 0; b < kMergeBatch; ++b) {
+      const int j = base + tid + b * kMergeThreads;
+      if (j < L) {
+        const float s = fmaf(alpha, j < n_old ? sb.s[b] : 0.f, prob(sb.z[b]));  // the forgetting update
+        const int pos = j < n_old ? sb.p[b] : t_pos;
+        a[j] = s;
+        if (j == n_old) ms.s_tok = s;
+        if (pos > thr) {
+          ++cnt;
+        } else {
+          const unsigned long long key = evict_key(s, pos);
+          if (key < best) { best = key; best_slot = j; }
+        }
+      }
+    }
+  }
+  const int cnt_w = wave_sum_i(cnt);
+  const unsigned long long best_w = wave_min_u64(best);
+  if (lane == 0) { ms.cnt[wave] = cnt_w; ms.key[wave] = best_w; }
+  __syncthreads();
+  meet();
+  // stores the new token's rows (held by the first 2 * LPR lanes of every wave) in slot v
+  const auto put_rows = [&](int v) {
+    if (lane < LPR) store16(Kg + (size_t)v * D + lane * EPL, row_new);
+    else if (lane < 2 * LPR) store16(Vg + (size_t)v * D + (lane - LPR) * EPL, row_new);
+  };
+  if (excess <= 0) {  // room left: plain append
+    for (int j = tid; j < L; j += kMergeThreads) Sg[j] = a[j];
+    if (tid == 0) { Pg[n_old] = t_pos; *len_g = L; }
+    if (wave == kMergeWaves - 1) put_rows(n_old);
+    return;
+  }
+  const int in_window = wave_sum_i(lane < kMergeWaves ? ms.cnt[lane] : 0);
+  if (excess == 1 && in_window == recent) {  // steady state: one eviction, no row moves
+    const unsigned long long win = wave_min_u64(lane < kMergeWaves ? ms.key[lane] : ~0ull);
+    const bool own = best == win && best != ~0ull;  // keys are unique (positions are)
+    const float s_tok = ms.s_tok;
+    for (int j = tid; j < n_old; j += kMergeThreads) Sg[j] = own && j == best_slot ? s_tok : a[j];
+    const unsigned long long owner = __ballot(own);
+    if (owner) {
+      const int v = __builtin_amdgcn_readlane(best_slot, __builtin_ctzll(owner));
+      if (v != n_old) {
+        if (lane == 63) Pg[v] = t_pos;
+        put_rows(v);
+      }
+    }
+    return;  // len stays n_old (= select + recent)
+  }
+  evict_general<MergeGroup, T, D>(a, n_old, excess, Kg, Vg, Sg, Pg, len_g, knew, vnew, t_pos, recent, sm);
+}
+// The new token's K and V row in the first 2 * LPR lanes of a wave.
 template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void decode_combine_kernel(
+__device__ __forceinline__ uint4 load_new_rows(const T* knew, const T* vnew) {
+  constexpr int LPR = RowGeom<T, D>::LPR, EPL = RowGeom<T, D>::EPL;
+  const int lane = threadIdx.x & 63;
+  return load16(lane < LPR ? knew + lane * EPL : vnew + (lane - LPR) % LPR * EPL);
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(kMergeThreads) void decode_combine_kernel(
     const T* __restrict__ k_new, const T* __restrict__ v_new, int t_pos, T* K, T* V, float* S,
     int32_t* P, int32_t* len, int capacity, int nsplit, const float* __restrict__ zbuf,
     const float* __restrict__ ml, const float* __restrict__ po, float alpha,
     const float* __restrict__ alpha_heads, int select, int recent, int evict_here,
     T* __restrict__ o) {
+  constexpr int GR = kMergeThreads / D, PG = kWave / GR;  // thread groups of D, splits per group (nsplit <= 64)
   extern __shared__ float a[];  // [capacity]
   __shared__ StepSmem sm;
-  const int g = blockIdx.x, tid = threadIdx.x;
-  if (alpha_heads) alpha = alpha_heads[g];
+  __shared__ MergeSmem<GR * D> ms;
+  const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int n_old = len[g];
-  if (n_old < 0 || n_old >= capacity) { flag_bad_head<T, D>(o + (size_t)g * D, tid, kThreads); return; }
-  // everything the merge reads is requested at once: the per-split (max, sum), the first
-  // slots' logits, scores and positions, the per-split outputs
   const float* zg = zbuf + (size_t)g * capacity;
   float* Sg = S + (size_t)g * capacity;
   int32_t* Pg = P + (size_t)g * capacity;
+  const T* knew = k_new + (size_t)g * D;
+  const T* vnew = v_new + (size_t)g * D;
   const float* mlg = ml + (size_t)g * nsplit * 2;
-  const float mc = tid < nsplit ? mlg[2 * tid] : -INFINITY;       // nsplit <= 64
-  const float lc = tid < nsplit ? mlg[2 * tid + 1] : 0.f;
-  const auto logit = [&](int j) { return zg[j]; };
-  SlotBatch first;
-  load_slot_batch(first, logit, Sg, Pg, tid, n_old, t_pos);
-  __shared__ float wsplit[kWave];
-  if (tid < kWave) {  // one lane per split, wave reductions
-    const float mw = wave_max(mc);
-    const float w = exp2f(mc - mw);  // 0 for empty splits
-    const float sw = wave_sum(lc * w);
-    wsplit[tid] = w;
-    if (tid == 0) { sm.redf[6] = mw; sm.redf[7] = sw; }
+  const float mc = lane < nsplit ? mlg[2 * lane] : -INFINITY;
+  const float lc = lane < nsplit ? mlg[2 * lane + 1] : 0.f;
+  MergeBatch<1> sb;
+  sb.load(0, zg, Sg, Pg, capacity);
+  const int grp = __builtin_amdgcn_readfirstlane(tid / D), col = tid % D;
+  float pv[PG];
+#pragma unroll
+  for (int i = 0; i < PG; ++i) pv[i] = po[((size_t)g * nsplit + min(grp + i * GR, nsplit - 1)) * D + col];
+  const uint4 row_new = load_new_rows<T, D>(knew, vnew);
+  if (alpha_heads) alpha = alpha_heads[g];
+  if (n_old < 0 || n_old >= capacity) { flag_bad_head<T, D>(o + (size_t)g * D, tid, kMergeThreads); return; }
+
+  const float mx = wave_max(mc);
+  const float w = exp2f(mc - mx);  // 0 for empty splits, one lane per split
+  const float inv = 1.0f / wave_sum(lc * w);
+  float acc = 0.f;
+#pragma unroll
+  for (int i = 0; i < PG; ++i) {
+    const float wc = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), grp + i * GR));
+    if (grp + i * GR < nsplit) acc = fmaf(pv[i], wc, acc);
   }
-  __syncthreads();
-  const float mx = sm.redf[6];
-  const float inv = 1.0f / sm.redf[7];
-  if (tid < D) {
-    float acc = 0.f;
-#pragma unroll 4
-    for (int c = 0; c < nsplit; ++c) acc = fmaf(po[((size_t)g * nsplit + c) * D + tid], wsplit[c], acc);
-    Elem<T>::store(o + (size_t)g * D + tid, acc * inv);
-  }
-  update_and_evict<T, D, true>(logit, [&](int, float z) { return exp2f(z - mx) * inv; }, first, a, n_old,
-                               K + (size_t)g * capacity * D, V + (size_t)g * capacity * D, Sg, Pg,
-                               len + g, k_new + (size_t)g * D, v_new + (size_t)g * D, t_pos, alpha,
-                               select, recent, evict_here != 0, sm);
+  ms.part[tid] = acc;
+  merge_update_and_evict<T, D>(
+      sb, [&](const float (&z)[1]) { return exp2f(z[0] - mx) * inv; },
+      [&] {
+        if (tid < D) {
+          float t = 0.f;
+#pragma unroll
+          for (int h = 0; h < GR; h += 4)
+            t += (ms.part[h * D + tid] + ms.part[(h + 1) * D + tid]) + (ms.part[(h + 2) * D + tid] + ms.part[(h + 3) * D + tid]);
+          Elem<T>::store(o + (size_t)g * D + tid, t * inv);
+        }
+      },
+      row_new, ms, a, n_old, K + (size_t)g * capacity * D, V + (size_t)g * capacity * D, zg, Sg, Pg, len + g, knew,
+      vnew, t_pos, alpha, select, recent, evict_here != 0, capacity, sm);
 }
 
 template <typename T, int D>
@@ -1850,7 +1984,7 @@ void launch_typed(const void* q, const void* k_new, const void* v_new, int t_pos
   static const hipError_t raised = hipFuncSetAttribute(
       (const void*)decode_combine_kernel<T, D>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
   (void)raised;
-  hipLaunchKernelGGL((decode_combine_kernel<T, D>), dim3(c.G), dim3(kThreads),
+  hipLaunchKernelGGL((decode_combine_kernel<T, D>), dim3(c.G), dim3(kMergeThreads),
                      (size_t)c.capacity * sizeof(float), st, (const T*)k_new, (const T*)v_new,
                      t_pos, (T*)c.k, (T*)c.v, c.scores, c.pos, c.len, c.capacity, plan.nsplit,
                      zbuf, ml, po, alpha, alpha_heads, select, recent, (int)evict_here, (T*)o);
@@ -1990,73 +2124,95 @@ __global__ __launch_bounds__(kThreads) void decode_gqa_partial_kernel(
 }
 
 template <int R>
-__global__ __launch_bounds__(kThreads) void decode_gqa_combine_kernel(
+__global__ __launch_bounds__(kMergeThreads) void decode_gqa_combine_kernel(
     const bf16_t* __restrict__ k_new, const bf16_t* __restrict__ v_new, int t_pos, bf16_t* K, bf16_t* V,
     float* S, int32_t* P, int32_t* len, int capacity, int nsplit, const float* __restrict__ zbuf,
     const float* __restrict__ ml, const float* __restrict__ po, float alpha, int select, int recent,
     int evict_here, bf16_t* __restrict__ o) {
   using T = bf16_t;
-  constexpr int D = 128;
-  extern __shared__ float a[];  // [capacity]: the group's summed probability of each slot
+  constexpr int D = 128, GR = kMergeThreads / D;
+  extern __shared__ float a[];  // [capacity]
   __shared__ StepSmem sm;
+  __shared__ MergeSmem<GR * R * D> ms;
   __shared__ float wsplit[R][kWave];
   __shared__ float mx_s[R], inv_s[R];
-  const int g = blockIdx.x, tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_old = len[g];
-  if (n_old < 0 || n_old >= capacity) {
-    for (int r = 0; r < R; ++r) flag_bad_head<T, D>(o + ((size_t)g * R + r) * D, tid, kThreads);
-    return;
-  }
-  const int L = n_old + 1;
+  const float* zg = zbuf + (size_t)g * R * capacity;
   float* Sg = S + (size_t)g * capacity;
   int32_t* Pg = P + (size_t)g * capacity;
-  const auto no_aux = [](int) { return 0.f; };
-  SlotBatch first;
-  load_slot_batch(first, no_aux, Sg, Pg, tid, n_old, t_pos);
+  const T* knew = k_new + (size_t)g * D;
+  const T* vnew = v_new + (size_t)g * D;
   // per query head: the splits' (max, sum) merged by one wave, one lane per split (nsplit <= 64)
-  for (int r = wave; r < R; r += kWaves) {
-    const float* mlg = ml + ((size_t)g * R + r) * nsplit * 2;
-    const float mc = lane < nsplit ? mlg[2 * lane] : -INFINITY;
-    const float lc = lane < nsplit ? mlg[2 * lane + 1] : 0.f;
+  float mc = -INFINITY, lc = 0.f;
+  if (wave < R && lane < nsplit) {
+    const float* mlg = ml + ((size_t)g * R + wave) * nsplit * 2;
+    mc = mlg[2 * lane];
+    lc = mlg[2 * lane + 1];
+  }
+  // the first two splits of this thread's group, for all query heads
+  const int grp = tid / D, col = tid % D;
+  const float* pg = po + (size_t)g * R * nsplit * D + col;
+  float pv[R][2];
+  const auto request = [&](int c0) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) pv[r][i] = pg[((size_t)r * nsplit + min(c0 + grp + i * GR, nsplit - 1)) * D];
+  };
+  request(0);
+  MergeBatch<R> sb;
+  sb.load(0, zg, Sg, Pg, capacity);
+  const uint4 row_new = load_new_rows<T, D>(knew, vnew);
+  if (n_old < 0 || n_old >= capacity) {
+    for (int r = 0; r < R; ++r) flag_bad_head<T, D>(o + ((size_t)g * R + r) * D, tid, kMergeThreads);
+    return;
+  }
+  if (wave < R) {
     const float mw = wave_max(mc);
     const float w = exp2f(mc - mw);  // 0 for empty splits
     const float sw = wave_sum(lc * w);
-    wsplit[r][lane] = w;
-    if (lane == 0) { mx_s[r] = mw; inv_s[r] = 1.0f / sw; }
+    wsplit[wave][lane] = w;
+    if (lane == 0) { mx_s[wave] = mw; inv_s[wave] = 1.0f / sw; }
   }
   __syncthreads();
-  {
-    // a thread's R * D / kThreads outputs side by side, so that their loads are in flight together
-    constexpr int PER = (R * D + kThreads - 1) / kThreads;
-    float acc[PER];
+  float acc[R];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) acc[i] = 0.f;
-#pragma unroll 8
-    for (int c = 0; c < nsplit; ++c) {
+  for (int r = 0; r < R; ++r) acc[r] = 0.f;
+  for (int c0 = 0; c0 < nsplit; c0 += 2 * GR) {
+    if (c0 > 0) request(c0);
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const int idx = min(tid + i * kThreads, R * D - 1), r = idx / D, col = idx % D;
-        acc[i] = fmaf(po[(((size_t)g * R + r) * nsplit + c) * D + col], wsplit[r][c], acc[i]);
-      }
-    }
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int idx = tid + i * kThreads, r = idx / D, col = idx % D;
-      if (idx < R * D) Elem<T>::store(o + ((size_t)g * R + r) * D + col, acc[i] * inv_s[r]);
-    }
+      for (int i = 0; i < 2; ++i)
+        if (c0 + grp + i * GR < nsplit) acc[r] = fmaf(pv[r][i], wsplit[r][c0 + grp + i * GR], acc[r]);
   }
-  for (int j = tid; j < L; j += kThreads) {
-    float p = 0.f;
 #pragma unroll
-    for (int r = 0; r < R; ++r) p += exp2f(zbuf[((size_t)g * R + r) * capacity + j] - mx_s[r]) * inv_s[r];
-    a[j] = p;
-  }
-  __syncthreads();
-  update_and_evict<T, D, true>(no_aux, [&](int j, float) { return a[j]; }, first, a, n_old,
-                               K + (size_t)g * capacity * D, V + (size_t)g * capacity * D, Sg, Pg,
-                               len + g, k_new + (size_t)g * D, v_new + (size_t)g * D, t_pos, alpha,
-                               select, recent, evict_here != 0, sm);
+  for (int r = 0; r < R; ++r) ms.part[(grp * R + r) * D + col] = acc[r];
+  float mx[R], inv[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) { mx[r] = mx_s[r]; inv[r] = inv_s[r]; }
+  merge_update_and_evict<T, D>(
+      sb,
+      [&](const float (&z)[R]) {
+        float p = 0.f;
+#pragma unroll
+        for (int r = 0; r < R; ++r) p += exp2f(z[r] - mx[r]) * inv[r];
+        return p;
+      },
+      [&] {
+        for (int idx = tid; idx < R * D; idx += kMergeThreads) {
+          float t = 0.f;
+#pragma unroll
+          for (int h = 0; h < GR; h += 4)
+            t += (ms.part[h * R * D + idx] + ms.part[(h + 1) * R * D + idx]) +
+                 (ms.part[(h + 2) * R * D + idx] + ms.part[(h + 3) * R * D + idx]);
+          Elem<T>::store(o + (size_t)g * R * D + idx, t * inv_s[idx / D]);
+        }
+      },
+      row_new, ms, a, n_old, K + (size_t)g * capacity * D, V + (size_t)g * capacity * D, zg, Sg, Pg, len + g, knew,
+      vnew, t_pos, alpha, select, recent, evict_here != 0, capacity, sm);
 }
 
 // f(std::integral_constant<int, R>) for the run-time group size R = 2 .. 8
@@ -2099,17 +2255,17 @@ void launch_gqa_typed(const void* q, const void* k_new, const void* v_new, int t
         float* po = ml + heads * ns * 2;
         const size_t lds_p = (size_t)group * rows * sizeof(float);
         const size_t lds_c = (size_t)c.capacity * sizeof(float);
-        constexpr int kMaxLds = A2SF_MAX_CAPACITY * (int)sizeof(float);
         with_group(group, [&](auto rc) {
           constexpr int R = decltype(rc)::value;
           if constexpr (R >= 2) {
             static const hipError_t raised = hipFuncSetAttribute(
-                (const void*)decode_gqa_combine_kernel<R>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+                (const void*)decode_gqa_combine_kernel<R>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                A2SF_GQA_MAX_LOGITS / R * (int)sizeof(float));
             (void)raised;
             hipLaunchKernelGGL((decode_gqa_partial_kernel<R>), dim3((unsigned)c.G * ns), dim3(kThreads), lds_p,
                                st, (const T*)q, (const T*)k_new, (const T*)v_new, (const T*)c.k, (const T*)c.v,
                                c.len, c.capacity, ns, rows, zbuf, ml, po, scale_log2e);
-            hipLaunchKernelGGL((decode_gqa_combine_kernel<R>), dim3(c.G), dim3(kThreads), lds_c, st,
+            hipLaunchKernelGGL((decode_gqa_combine_kernel<R>), dim3(c.G), dim3(kMergeThreads), lds_c, st,
                                (const T*)k_new, (const T*)v_new, t_pos, (T*)c.k, (T*)c.v, c.scores, c.pos, c.len,
                                c.capacity, ns, zbuf, ml, po, alpha, select, recent, (int)evict_here, (T*)o);
           }
@@ -2196,8 +2352,8 @@ DecodePlan plan_decode(int G, int capacity, int d) {
   // never gets fewer than 64 rows.  It costs a second kernel (the combine), which only pays
   // when one workgroup per head would leave most of the chip idle for long.  Measured GPU
   // time per step (steps replayed from a HIP graph, bf16, d = 128), one kernel / split:
-  // 32 heads x 205 slots 8.1 / 8.7 us, 8 x 512 11.2 / 9.0, 128 x 512 14.7 / 12.2,
-  // 64 x 1024 23.0 / 13.3, 256 x 1024 28.0 / 27.4, 320 x 410 17.0 / 18.2, 512 x 512 23.8 / 27.1,
+  // 8 x 512 11.2 / 8.7, 128 x 512 14.7 / 12.1, 64 x 1024 23.0 / 11.7 us; with a merge that took 2 to 3 us
+  // longer than today's: 32 x 205 8.1 / 8.7, 256 x 1024 28.0 / 27.4, 320 x 410 17.0 / 18.2, 512 x 512 23.8 / 27.1,
   // 900 x 256 21.2 / 26.5, 700 x 4096 257 / 291.
   const bool one_kernel = capacity <= 256 || (G >= 256 && capacity <= 1024) || G >= 640;
   int want = one_kernel ? 1 : (1024 + G - 1) / G;

@@ -214,3 +214,51 @@ def test_small_step_capacities(dtype, d, budget):
             ls.select, ls.recent = ls.select - 9, ls.recent - 8
         for t in range(4, 7):
             ls.step(t, mode=mode)
+
+
+@pytest.mark.parametrize("dtype,d,group,B", [("bf16", 128, 1, 400), ("bf16", 128, 1, 1024), ("bf16", 128, 1, 4095),
+                                             ("bf16", 128, 1, 4096), ("bf16", 64, 1, 9001), ("f32", 128, 1, 5000),
+                                             ("f32", 64, 1, 1023), ("bf16", 128, 2, 5001), ("bf16", 128, 3, 1024),
+                                             ("bf16", 128, 5, 700), ("bf16", 128, 8, 2036)])
+def test_split_step_sizes(dtype, d, group, B):
+    """Steps whose tokens are split over workgroups: one to three passes of the merging workgroup over
+    the slots, every number of splits from a few to all, caches with gaps in the newest positions, a
+    cache still filling, several evictions at once."""
+    G, steps = 4, 3
+    gen = torch.Generator(device="cuda").manual_seed(B + d)
+    torch_dtype = torch.bfloat16 if dtype == "bf16" else torch.float32
+    code = a2sf.A2SF_BF16 if dtype == "bf16" else a2sf.A2SF_F32
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(torch_dtype)
+    cache = a2sf.Cache(G, B + 9, d, torch_dtype)
+    cache.k.copy_(rnd(*cache.k.shape)), cache.v.copy_(rnd(*cache.v.shape))
+    cache.scores.copy_(torch.rand(G, B + 9, generator=gen, device="cuda"))
+    lens = [B, B - 2, B + 5, B]                     # full, filling, too full, full with gaps
+    t0 = 2 * B + 10
+    for g, L in enumerate(lens):
+        pos = np.arange(t0 - L, t0) if g < 3 else np.sort(np.random.default_rng(B).permutation(t0 - 1)[:L])
+        cache.pos[g, :L] = torch.as_tensor(pos.astype(np.int32), device="cuda")
+        cache.len[g] = L
+    oc = [orc.HeadCache(*(parity.to_f64(x[g, :L]) for x in (cache.k, cache.v, cache.scores)),
+                        cache.pos[g, :L].cpu().numpy().astype(np.int64)) for g, L in enumerate(lens)]
+    select, recent, alpha = B - B // 3, B // 3, np.float32(0.7)
+    nbytes = a2sf.a2sf_workspace_bytes(G * group, 0, B + 9, d, code, select, recent)
+    ws = torch.full((nbytes + (4 * G * group * 64 * (d + 2) if group > 1 else 0),), 255, dtype=torch.uint8, device="cuda")
+    for t in range(t0, t0 + steps):
+        q, kn, vn = rnd(G, group, d), rnd(G, d), rnd(G, d)
+        o = torch.full((G, group, d), float("nan"), dtype=torch_dtype, device="cuda")
+        if group == 1:
+            a2sf.a2sf_decode_step(q, kn, vn, t, cache, float(alpha), select, recent, o, workspace=ws)
+        else:
+            a2sf.a2sf_decode_step_gqa(q, kn, vn, t, cache, group, float(alpha), select, recent, o, workspace=ws)
+        torch.cuda.synchronize()
+        for g in range(G):
+            kept = int(cache.len[g])
+            pos = cache.pos[g, :kept].cpu().numpy().astype(np.int64)
+            o_ref, _ = orc.gqa_attend_and_update(oc[g], parity.to_f64(q[g]), parity.to_f64(kn[g]), parity.to_f64(vn[g]), t, float(alpha))
+            orc.evict(oc[g], select, recent, forced_retained=pos.tolist(), margin=parity.MARGIN)
+            assert np.abs(parity.to_f64(o[g]) - o_ref).max() <= parity.O_TOL[dtype]
+            order = np.argsort(pos, kind="stable")
+            c = oc[g].sorted_by_pos()
+            assert np.array_equal(pos[order], c.pos)
+            assert np.array_equal(parity.to_f64(cache.k[g, :kept])[order], c.K) and np.array_equal(parity.to_f64(cache.v[g, :kept])[order], c.V)
+            parity.compare_scores(cache.scores[g, :kept].cpu().numpy()[order], c.S, f"head {g} step {t}")

@@ -106,18 +106,25 @@ class A2SFError(RuntimeError):
         super().__init__(f"a2sf status {status}: {a2sf_status_string(status)}")
 
 
+# The generation step of a few heads takes 7 us on the GPU: the marshalling below is on its critical
+# path (32 heads x 205 slots, calls back to back: 14.6 us per call before, 11.5 after).
+_Tensor = torch.Tensor
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # (absent in builds without a GPU backend)
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _ptr(x):
-    if x is None:
-        return None
-    if isinstance(x, torch.Tensor):
+    if type(x) is _Tensor or isinstance(x, _Tensor):
         return x.data_ptr()
-    return int(x)
+    return None if x is None else int(x)
 
 
 def _stream(stream):
-    if stream is None:
-        return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
-    return int(stream)
+    if stream is not None:
+        return int(stream)
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(_get_device())
+    return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
 
 
 def _check(status: int):
@@ -125,12 +132,14 @@ def _check(status: int):
         raise A2SFError(status)
 
 
+_DTYPE_CODES = {torch.float32: A2SF_F32, torch.bfloat16: A2SF_BF16}
+
+
 def dtype_code(t: torch.dtype) -> int:
-    if t == torch.float32:
-        return A2SF_F32
-    if t == torch.bfloat16:
-        return A2SF_BF16
-    raise A2SFError(A2SF_EDTYPE)
+    code = _DTYPE_CODES.get(t)
+    if code is None:
+        raise A2SFError(A2SF_EDTYPE)
+    return code
 
 
 class Cache:
@@ -176,7 +185,7 @@ def a2sf_prefill(q, k, v, n, alpha, select, recent, cache, o=None, scores_full=N
                  workspace=None, workspace_bytes=None, stream=None):
     cs = _cache_struct(cache)
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+        workspace_bytes = workspace.nbytes if workspace is not None else 0
     _check(lib().a2sf_prefill(_ptr(q), _ptr(k), _ptr(v), n, alpha, Budget(select, recent),
                               ctypes.byref(cs), _ptr(o), _ptr(scores_full), _ptr(workspace),
                               workspace_bytes, _stream(stream)))
@@ -186,7 +195,7 @@ def a2sf_prefill_windowed(q, k, v, n, alpha, score_rel_tol, select, recent, cach
                           workspace=None, workspace_bytes=None, stream=None):
     cs = _cache_struct(cache)
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+        workspace_bytes = workspace.nbytes if workspace is not None else 0
     _check(lib().a2sf_prefill_windowed(_ptr(q), _ptr(k), _ptr(v), n, alpha, score_rel_tol,
                                        Budget(select, recent), ctypes.byref(cs), _ptr(o), _ptr(scores_full),
                                        _ptr(workspace), workspace_bytes, _stream(stream)))
@@ -196,7 +205,7 @@ def a2sf_prefill_chunk(q, k, v, m, pos0, alpha, select, recent, cache, o=None, w
                        workspace_bytes=None, stream=None):
     cs = _cache_struct(cache)
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+        workspace_bytes = workspace.nbytes if workspace is not None else 0
     _check(lib().a2sf_prefill_chunk(_ptr(q), _ptr(k), _ptr(v), m, pos0, alpha, Budget(select, recent),
                                     ctypes.byref(cs), _ptr(o), _ptr(workspace), workspace_bytes,
                                     _stream(stream)))
@@ -206,7 +215,7 @@ def a2sf_prefill_chunk_gqa(q, k, v, m, pos0, group, alpha, select, recent, cache
                            workspace_bytes=None, stream=None):
     cs = _cache_struct(cache)
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+        workspace_bytes = workspace.nbytes if workspace is not None else 0
     _check(lib().a2sf_prefill_chunk_gqa(_ptr(q), _ptr(k), _ptr(v), m, pos0, group, alpha, Budget(select, recent),
                                         ctypes.byref(cs), _ptr(o), _ptr(workspace), workspace_bytes,
                                         _stream(stream)))
@@ -216,7 +225,7 @@ def a2sf_prefill_gqa(q, k, v, n, group, alpha, select, recent, cache, o=None, sc
                      workspace=None, workspace_bytes=None, stream=None):
     cs = _cache_struct(cache)
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+        workspace_bytes = workspace.nbytes if workspace is not None else 0
     _check(lib().a2sf_prefill_gqa(_ptr(q), _ptr(k), _ptr(v), n, group, alpha, Budget(select, recent),
                                   ctypes.byref(cs), _ptr(o), _ptr(scores_full), _ptr(workspace),
                                   workspace_bytes, _stream(stream)))
@@ -226,7 +235,7 @@ def a2sf_decode_step_gqa(q, k_new, v_new, t_pos, cache, group, alpha, select, re
                          mode=A2SF_EVICT_FAST, workspace=None, workspace_bytes=None, stream=None):
     cs = _cache_struct(cache)
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+        workspace_bytes = workspace.nbytes if workspace is not None else 0
     _check(lib().a2sf_decode_step_gqa(_ptr(q), _ptr(k_new), _ptr(v_new), t_pos, ctypes.byref(cs), group,
                                       alpha, Budget(select, recent), mode, _ptr(o), _ptr(workspace),
                                       workspace_bytes, _stream(stream)))
@@ -236,7 +245,7 @@ def a2sf_decode_step(q, k_new, v_new, t_pos, cache, alpha, select, recent, o,
                      mode=A2SF_EVICT_FAST, workspace=None, workspace_bytes=None, stream=None):
     cs = _cache_struct(cache)
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+        workspace_bytes = workspace.nbytes if workspace is not None else 0
     _check(lib().a2sf_decode_step(_ptr(q), _ptr(k_new), _ptr(v_new), t_pos, ctypes.byref(cs), alpha,
                                   Budget(select, recent), mode, _ptr(o), _ptr(workspace),
                                   workspace_bytes, _stream(stream)))
@@ -253,7 +262,7 @@ def a2sf_prefill_alpha_per_head(q, k, v, n, alpha_heads, alpha_max, select, rece
                                 scores_full=None, workspace=None, workspace_bytes=None, stream=None):
     cs = _cache_struct(cache)
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+        workspace_bytes = workspace.nbytes if workspace is not None else 0
     _check(lib().a2sf_prefill_alpha_per_head(_ptr(q), _ptr(k), _ptr(v), n, _ptr(alpha_heads), alpha_max,
                                              Budget(select, recent), ctypes.byref(cs), _ptr(o),
                                              _ptr(scores_full), _ptr(workspace), workspace_bytes,
@@ -265,7 +274,7 @@ def a2sf_decode_step_alpha_per_head(q, k_new, v_new, t_pos, cache, alpha_heads, 
                                     stream=None):
     cs = _cache_struct(cache)
     if workspace_bytes is None:
-        workspace_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+        workspace_bytes = workspace.nbytes if workspace is not None else 0
     _check(lib().a2sf_decode_step_alpha_per_head(_ptr(q), _ptr(k_new), _ptr(v_new), t_pos,
                                                  ctypes.byref(cs), _ptr(alpha_heads),
                                                  Budget(select, recent), mode, _ptr(o), _ptr(workspace),

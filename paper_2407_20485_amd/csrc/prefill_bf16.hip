@@ -45,6 +45,24 @@ __device__ __forceinline__ long long xcd_contiguous_id(long long total) {
   const long long per = (total + 7) / 8;
   return (long long)(blockIdx.x % 8) * per + blockIdx.x / 8;
 }
+// The order of the (head, block) items: that of ordered_item, or, for launches of up to RESIDENT blocks, head
+// after head.  kOneRound: launches that are resident at once, where nothing is left to be dealt out and
+// ordered_item costs half a microsecond.
+constexpr long long kOneRound = 1ll << 62;
+template <long long RESIDENT>
+__device__ __forceinline__ bool launch_item(int G, int nb, int& head, int& rank) {
+  const long long total = (long long)G * nb;
+  if (total > RESIDENT) return ordered_item(G, nb, head, rank);
+  const long long id = xcd_contiguous_id(total);
+  head = (int)(id / nb);
+  rank = (int)(id % nb);
+  return id < total;
+}
+template <long long RESIDENT>
+unsigned launch_grid(int G, int nb) {
+  const long long total = (long long)G * nb;
+  return total > RESIDENT ? ordered_grid(G, nb) : (unsigned)((total + 7) / 8 * 8);
+}
 
 // ---------------------------------------------------------------------------------------
 // Masked attention rows, d = 64 or 128, on two gfx950 features:
@@ -177,12 +195,10 @@ __global__ __launch_bounds__(kThreads * KS, !WITH_O ? 4 : 2 / KS) void attn_fwd_
   __shared__ __attribute__((aligned(1024))) char smem[KS * kLds];
   __shared__ float m_other[KS > 1 ? BM : 1], l_other[KS > 1 ? BM : 1];
 
-  const long long total = (long long)G * nqb;
-  const long long vid = xcd_contiguous_id(total);
-  if (vid >= total) return;
-  const int g = (int)(vid / nqb);
-  // longest rows first; the launch covers the nqb row blocks from the one that holds rc.first_row on
-  const int qb = rc.first_row / BM + nqb - 1 - (int)(vid % nqb);
+  int g, rank;
+  if (!launch_item<KS == 1 ? 0 : kOneRound>(G, nqb, g, rank)) return;
+  // the launch covers the nqb row blocks from the one that holds rc.first_row on
+  const int qb = rc.first_row / BM + nqb - 1 - rank;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % kWaves;  // wave-uniform: branches on it are scalar
@@ -743,12 +759,11 @@ void launch_fwd_rect(const void* q, const void* k, const void* v, int G, const A
   const int GQ = G * rc.kv_group;  // query heads
   constexpr int bm = kWaves * 32;
   const int nqb = (rc.m + bm - 1) / bm - (o ? 0 : rc.first_row / bm);  // row blocks to compute
-  const unsigned grid = (unsigned)((((long long)GQ * nqb + 7) / 8) * 8);
 #define A2SF_FWD(WITH_O, KS)                                                                          \
-  hipLaunchKernelGGL((attn_fwd_kernel<D, WITH_O, KS>), dim3(grid), dim3(kThreads * KS), 0, st, (const bf16_t*)q, \
+  hipLaunchKernelGGL((attn_fwd_kernel<D, WITH_O, KS>), dim3(launch_grid<KS == 1 ? 0 : kOneRound>(GQ, nqb)), dim3(kThreads * KS), 0, st, (const bf16_t*)q, \
                      (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, lse2, rc, GQ, nqb, scale_log2e)
   if (!o) A2SF_FWD(false, 1);
-  else if (grid <= kSplitKeysMaxBlocks) A2SF_FWD(true, 2);
+  else if ((long long)GQ * nqb <= kSplitKeysMaxBlocks) A2SF_FWD(true, 2);
   else A2SF_FWD(true, 1);
 #undef A2SF_FWD
 }
@@ -1040,6 +1055,9 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_tail_kernel(
 // accumulate: the column sums are added to decay * S[] (a chunk: the cached tokens' older scores
 // decayed by alpha^m) instead of replacing it.
 constexpr int kStreamStages = 4;
+// Workgroups up to which heads are launched one after the other: two per compute unit (45 heads x 1400 rows,
+// alpha = 0.9: 42 us, 46 in the order of ordered_item; 96 x 1777, d = 64, alpha = 1: 63.7 and 49.0).
+constexpr long long kStreamResident = 512;
 
 // RS = 2 (without a tolerance): eight waves, the second four take the odd tiles for the same keys, each
 // half with a ring of its own; their sums meet at the end.  For launches whose workgroups are all
@@ -1059,11 +1077,8 @@ __global__ __launch_bounds__(kThreads * RS, (D == 64 && KB == 1 ? 4 : 2) / RS) v
   __shared__ int wave_lim[kWaves];
   __shared__ float other[RS > 1 ? BC : 1];
 
-  const long long total = (long long)G * ncb;
-  const long long vid = xcd_contiguous_id(total);
-  if (vid >= total) return;
-  const int g = (int)(vid / ncb);
-  const int cb = (int)(vid % ncb);  // column block 0 has the most rows: first
+  int g, cb;  // column block 0 has the most rows
+  if (!launch_item<RS == 1 ? kStreamResident : kOneRound>(G, ncb, g, cb)) return;
   const int n = rc.m;
   const int off = rc.off_heads ? rc.off_heads[g] : 0;
   const int nk = off + n;  // keys of this head
@@ -1274,7 +1289,7 @@ void launch_cols(const void* q, const void* k, const float* lse2, int G, const A
 #define A2SF_STREAM(KB, RS)                                                                           \
   do {                                                                                                \
     const int ncb = (keys_per_head + kWaves * 32 * KB - 1) / (kWaves * 32 * KB);                      \
-    const unsigned grid = (unsigned)((((long long)G * ncb + 7) / 8) * 8);                             \
+    const unsigned grid = launch_grid<RS == 1 ? kStreamResident : kOneRound>(G, ncb);                 \
     hipLaunchKernelGGL((col_scores_stream_kernel<D, KB, RS>), dim3(grid), dim3(kThreads * RS), 0, st, \
                        (const bf16_t*)q, (const bf16_t*)k, lse2, scores, rc, s_stride, accumulate, decay, G, ncb, \
                        first, l2a, alpha_heads, scale_log2e, tol);                                    \

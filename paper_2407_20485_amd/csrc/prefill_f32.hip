@@ -23,8 +23,8 @@
 // (global_load_lds) and meets the other waves of its workgroup only at the end.  The four waves of a
 // workgroup share 32 query rows (attention) or 32 keys (scores) and take every fourth tile, which keeps
 // the chip full from a few hundred rows on and the longest row's chain short.
-// 32 heads x 1000 rows x 128: attention 117 us (8.2 GFLOP = 70 TFLOP/s of the 154 that a large fp32
-// matrix product reaches; matrix pipe busy 49 %), scores 23 us (window of 93 rows; vector form: 219).
+// 32 heads x 1000 rows x 128: attention 101 us (8.2 GFLOP = 81 TFLOP/s of the 154 that a large fp32
+// matrix product reaches), scores 23 us (window of 93 rows; vector form: 219).
 #include <math.h>
 
 #include "a2sf_dev.h"
@@ -71,17 +71,11 @@ __device__ __forceinline__ void fetch_tile(const float* __restrict__ Mg, int row
   }
 }
 
-// Workgroup id -> work id such that each of the 8 accelerator dies (which receive consecutive
-// workgroup ids round-robin) works on a contiguous range, i.e. on whole heads.
-__device__ __forceinline__ long long xcd_contiguous_id(long long total) {
-  const long long per = (total + 7) / 8;
-  return (long long)(blockIdx.x % 8) * per + blockIdx.x / 8;
-}
-
 // One workgroup per 32 query rows; wave w takes the key tiles w, w + 4, ...  A wave's strip holds
 // the K tile until its logits are formed, then the V tile: the wave waits for each, and the
 // second wave of the SIMD fills the gaps (two strips per wave, with the next tile fetched half a tile ahead,
-// leave room for one wave per SIMD only: 126 us instead of 117 at 32 heads x 1000 rows x 128; a workgroup of
+// leave room for one wave per SIMD only: 126 us instead of 117 at 32 heads x 1000 rows x 128 in the old launch order;
+// quarters of a tile fetched as the quarters before them are used up: no difference; a workgroup of
 // vector arithmetic per row, as this kernel used to be: 2187).
 template <int D, bool WITH_O>
 __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(
@@ -91,11 +85,9 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(
   __shared__ __attribute__((aligned(1024))) char smem[kWaves * kTileBytes];
   __shared__ float m_s[kWaves][kRows], l_s[kWaves][kRows];
 
-  const long long total = (long long)GQ * nqb;
-  const long long vid = xcd_contiguous_id(total);
-  if (vid >= total) return;
-  const int g = (int)(vid / nqb);
-  const int qb = rc.first_row / kRows + nqb - 1 - (int)(vid % nqb);  // longest rows first
+  int g, rank;
+  if (!ordered_item(GQ, nqb, g, rank)) return;
+  const int qb = rc.first_row / kRows + nqb - 1 - rank;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
@@ -250,10 +242,9 @@ __global__ __launch_bounds__(kThreads, 2) void scores_f32_kernel(
   constexpr int C8 = D / 8, kTileBytes = kRows * D * 4;
   __shared__ __attribute__((aligned(1024))) char smem[kWaves * kTileBytes];
   __shared__ float part[kWaves][kRows];
-  const long long total = (long long)G * ncb;
-  const long long vid = xcd_contiguous_id(total);
-  if (vid >= total) return;
-  const int g = (int)(vid / ncb), c0 = (int)(vid % ncb) * kRows;  // the oldest keys have the most rows: first
+  int g, rank;
+  if (!ordered_item(G, ncb, g, rank)) return;
+  const int c0 = rank * kRows;  // the oldest keys have the most rows
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
@@ -353,7 +344,7 @@ void launch_attn_f32(const float* q, const float* k, const float* v, int G, cons
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)d);
   const int GQ = G * rc.kv_group;
   const int nqb = (rc.m + kRows - 1) / kRows - rc.first_row / kRows;  // row blocks to compute
-  const unsigned grid = (unsigned)((((long long)GQ * nqb + 7) / 8) * 8);
+  const unsigned grid = ordered_grid(GQ, nqb);
 #define A2SF_ATTN_F32(D, WO)                                                                          \
   hipLaunchKernelGGL((attn_f32_kernel<D, WO>), dim3(grid), dim3(kThreads), 0, st, q, k, v, rc, GQ, nqb, o, \
                      lse2, scale_log2e)
@@ -373,7 +364,7 @@ void launch_colscores_f32(const float* q, const float* k, const float* lse2, int
   float l2a;
   const int first = first_contributing_row(rc.m, alpha, &l2a);
   const int ncb = (keys_per_head + kRows - 1) / kRows;
-  const unsigned grid = (unsigned)((((long long)G * ncb + 7) / 8) * 8);
+  const unsigned grid = ordered_grid(G, ncb);
   if (d == 64)
     hipLaunchKernelGGL(scores_f32_kernel<64>, dim3(grid), dim3(kThreads), 0, st, q, k, lse2, rc, G, ncb, first,
                        l2a, alpha_heads, scores, s_stride, accumulate, decay, scale_log2e);

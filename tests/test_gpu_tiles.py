@@ -262,3 +262,25 @@ def test_split_step_sizes(dtype, d, group, B):
             assert np.array_equal(pos[order], c.pos)
             assert np.array_equal(parity.to_f64(cache.k[g, :kept])[order], c.K) and np.array_equal(parity.to_f64(cache.v[g, :kept])[order], c.V)
             parity.compare_scores(cache.scores[g, :kept].cpu().numpy()[order], c.S, f"head {g} step {t}")
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("G,n", [(1, 700), (5, 400), (8, 97), (9, 33), (45, 300), (70, 260), (131, 129), (515, 140)])
+def test_launch_order_covers_every_block(dtype, d, G, n):
+    """Every head and row / column block of launches whose heads do and do not divide by 8, in one and
+    in several rounds of heads: outputs and scores of all heads against plain float64 arithmetic."""
+    torch_dtype = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(G + n)
+    q, k, v = (torch.randn(G, n, d, generator=gen, device="cuda").to(torch_dtype) for _ in range(3))
+    B = min(n, 24)
+    cache = a2sf.Cache(G, B + 1, d, torch_dtype)
+    o = torch.full_like(q, float("nan"))
+    full = torch.full((G, n), float("nan"), device="cuda")
+    ws = torch.empty(a2sf.a2sf_workspace_bytes(G, n, B + 1, d, a2sf.A2SF_BF16 if dtype == "bf16" else a2sf.A2SF_F32, B // 2, B - B // 2),
+                     dtype=torch.uint8, device="cuda")
+    a2sf.a2sf_prefill(q, k, v, n, 1.0, B // 2, B - B // 2, cache, o=o, scores_full=full, workspace=ws)
+    torch.cuda.synchronize()
+    p = torch.matmul(q.double().cpu(), k.double().cpu().transpose(1, 2).contiguous()) / d ** 0.5
+    p = torch.softmax(p.masked_fill(torch.ones(n, n, dtype=torch.bool).triu(1), float("-inf")), dim=-1)
+    assert (torch.matmul(p, v.double().cpu()) - o.double().cpu()).abs().max() <= parity.O_TOL[dtype]
+    parity.compare_scores(full.cpu().numpy(), p.sum(1).numpy(), f"{G} heads")

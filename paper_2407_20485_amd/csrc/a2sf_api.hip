@@ -186,7 +186,9 @@ a2sf_status decode_impl(const void* q, const void* k_new, const void* v_new, int
     int32_t* n_keep = (int32_t*)(ws + w.n_keep);
     launch_select(cache->scores, cache->pos, cache->len, cache->G, cache->capacity,
                   cache->capacity, budget.select, budget.recent, keep_idx, n_keep, st);
-    launch_compact(*cache, keep_idx, budget.select + budget.recent, n_keep, st);
+    // (the wave-per-head kernel has shifted the rows: heads that evict several tokens are left)
+    launch_compact(*cache, keep_idx, budget.select + budget.recent, n_keep, st, nullptr, nullptr, 0, nullptr,
+                   plan.wave_slots > 0);
   }
   return launch_status();
 }

@@ -17,7 +17,8 @@ void launch_select(const float* scores, const int32_t* pos, const int32_t* len, 
 // (a chunk whose rows were not copied into the cache)
 void launch_compact(const a2sf_cache& c, const int32_t* keep_idx, int keep_stride,
                     const int32_t* n_keep, hipStream_t st, const void* k2 = nullptr,
-                    const void* v2 = nullptr, int m2 = 0, const int32_t* off_heads = nullptr);
+                    const void* v2 = nullptr, int m2 = 0, const int32_t* off_heads = nullptr,
+                    bool mostly_done = false);  // hardly a head has rows to move
 // Selection on a prompt's scores [G, n] and gather of the surviving rows into the cache.
 void launch_select_gather(const void* k, const void* v, const float* scores_full, int n, int select,
                           int recent, int32_t* keep_idx, int32_t* n_keep, const a2sf_cache& c,

@@ -284,3 +284,17 @@ def test_launch_order_covers_every_block(dtype, d, G, n):
     p = torch.softmax(p.masked_fill(torch.ones(n, n, dtype=torch.bool).triu(1), float("-inf")), dim=-1)
     assert (torch.matmul(p, v.double().cpu()) - o.double().cpu()).abs().max() <= parity.O_TOL[dtype]
     parity.compare_scores(full.cpu().numpy(), p.sum(1).numpy(), f"{G} heads")
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+def test_stable_steps_of_many_heads(dtype, d):
+    """Stable steps whose kernel shifts the rows itself, then steps that evict several tokens at once, where
+    one compaction workgroup per head moves all slices of the rows."""
+    w = variant(1 if dtype == "bf16" else 0, heads=4097, d=d, dtype=dtype, n=70, T=5, select=40, recent=25, name="many heads")
+    ls = parity.LockStep(parity.Problem(w, sample=[0, 1, 2048, 4096]), 0.6)
+    ls.prefill()
+    for t in range(2):
+        ls.step(t, mode=a2sf.A2SF_EVICT_STABLE)
+    ls.select, ls.recent = 30, 11
+    for t in range(2, 5):
+        ls.step(t, mode=a2sf.A2SF_EVICT_STABLE)

@@ -71,6 +71,48 @@ __device__ __forceinline__ void fetch_tile(const float* __restrict__ Mg, int row
   }
 }
 
+// A matrix op multiplies a masked key's probability, 0, with its V row, and 0 times an infinity is not 0.
+// So the tiles that the mask cuts are looked over (D / 8 LDS reads of a lane beside the 4 D of the products) and their
+// infinities and NaN set to 0; add_nonfinite gives them to the rows that see them at the end.
+template <int D>
+__device__ __forceinline__ bool clear_nonfinite(lds_char* tile) {
+  lds_char* const mine = tile + (threadIdx.x & 63) * 16;
+  float zeros = 0.f;  // a NaN if some x is not finite
+#pragma unroll 8
+  for (int u = 0; u < D / 8; ++u) {
+    const f32x4 x = lds_read4(mine + u * 1024);
+    zeros = fmaf(x[0], 0.f, fmaf(x[1], 0.f, fmaf(x[2], 0.f, fmaf(x[3], 0.f, zeros))));
+  }
+  if (!__any(zeros != 0.f)) return false;
+#pragma unroll 1
+  for (int u = 0; u < D / 8; ++u) {
+    f32x4 x = lds_read4(mine + u * 1024);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = x[e] * 0.f == 0.f ? x[e] : 0.f;
+    *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(mine + u * 1024) = x;
+  }
+  return true;
+}
+// The terms p v of the keys [key0, last key of the row] whose v is not finite, onto the rows that a workgroup has
+// stored (such a sum is an infinity or NaN: adding a term again, or p's own rounding, does not change it).
+template <int D>
+__device__ __forceinline__ void add_nonfinite(const float* Qg, const float* Kg, const float* Vg, const float* lse2, float* Og,
+                                           int row0, int n, int off, int key0, float scale_log2e) {
+  for (int e = threadIdx.x; e < kRows * D; e += kThreads) {
+    const int r = row0 + e / D, c = e % D;
+    if (r >= n) break;
+    float x = Og[(size_t)r * D + c];
+    for (int j = key0; j <= off + r; ++j) {
+      const float v = Vg[(size_t)j * D + c];
+      if (v * 0.f == 0.f) continue;
+      float s = 0.f;
+      for (int i = 0; i < D; ++i) s = fmaf(Qg[(size_t)r * D + i], Kg[(size_t)j * D + i], s);
+      x += exp2f(fmaf(s, scale_log2e, -lse2[r])) * v;
+    }
+    Og[(size_t)r * D + c] = x;
+  }
+}
+
 // One workgroup per 32 query rows; wave w takes the key tiles w, w + 4, ...  A wave's strip holds
 // the K tile until its logits are formed, then the V tile: the wave waits for each, and the
 // second wave of the SIMD fills the gaps (two strips per wave, with the next tile fetched half a tile ahead,
@@ -78,12 +120,13 @@ __device__ __forceinline__ void fetch_tile(const float* __restrict__ Mg, int row
 // quarters of a tile fetched as the quarters before them are used up: no difference; a workgroup of
 // vector arithmetic per row, as this kernel used to be: 2187).
 template <int D, bool WITH_O>
-__global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     AttnRect rc, int GQ, int nqb, float* __restrict__ O, float* __restrict__ LSE2, float scale_log2e) {
   constexpr int C8 = D / 8, DB = D / 32, kTileBytes = kRows * D * 4;
   __shared__ __attribute__((aligned(1024))) char smem[kWaves * kTileBytes];
   __shared__ float m_s[kWaves][kRows], l_s[kWaves][kRows];
+  __shared__ bool odd_s[kWaves];
 
   int g, rank;
   if (!ordered_item(GQ, nqb, g, rank)) return;
@@ -128,6 +171,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
   float m = -INFINITY, l = 0.f;
+  bool odd = false;  // a V row of a masked tile holds an infinity or a NaN
   const int newest = off + row0 + l32;  // newest key this lane's row sees
 
   for (int t = wave; t < ntiles; t += kWaves) {
@@ -150,7 +194,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(
     wait_lds();
     if (WITH_O) fetch_tile<D, true>(Vg, key0, nk, strip);
     else fetch_tile<D, false>(Kg, next, nk, strip);
-    if (key0 + kRows - 1 > off + row0) {  // the tile reaches past the block's first row
+    const bool masked = key0 + kRows - 1 > off + row0;  // the tile reaches past the block's first row
+    if (masked) {
 #pragma unroll
       for (int i = 0; i < 16; ++i)
         if (key0 + 8 * (i >> 2) + 4 * h + (i & 3) > newest) s[i] = -INFINITY;
@@ -177,8 +222,12 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(
       s[i] = __builtin_amdgcn_exp2f(fmaf(s[i], scale_log2e, -m));
       l += s[i];
     }
-    if (WITH_O) {
+    if constexpr (WITH_O) {
       wait_vm<0>();  // V tile t
+      if (masked && clear_nonfinite<D>(strip)) {
+        odd = true;
+        wait_lds();
+      }
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
 #pragma unroll
@@ -196,6 +245,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(
   // ---- the four waves' parts of the 32 rows
   l = across_rows(l, OpAdd(), false, true);
   if (h == 0) { m_s[wave][l32] = m; l_s[wave][l32] = l; }
+  if (WITH_O && lane == 0) odd_s[wave] = odd;
   __syncthreads();
   float mall = m_s[0][l32];  // wave 0 has seen key 0: finite
 #pragma unroll
@@ -226,6 +276,11 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_kernel(
       const f32x4 a = (lds_read4(p) + lds_read4(p + kTileBytes)) +
                       (lds_read4(p + 2 * kTileBytes) + lds_read4(p + 3 * kTileBytes));
       *reinterpret_cast<f32x4*>(O + ((size_t)g * n + row0 + r) * D + c * 4) = a;
+    }
+    if (odd_s[0] || odd_s[1] || odd_s[2] || odd_s[3]) {
+      __syncthreads();
+      add_nonfinite<D>(Q + (size_t)g * n * D, Kg, Vg, LSE2 + (size_t)g * n, O + (size_t)g * n * D, row0, n, off,
+                       (off + row0) / kRows * kRows, scale_log2e);
     }
   }
 }

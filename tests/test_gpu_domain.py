@@ -1,0 +1,74 @@
+"""GPU results at the ends of the value range: infinities and NaN among the inputs, logits and
+values of extreme size.  Against plain float64 arithmetic over the keys that a row sees."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2407_20485_amd as a2sf
+import parity
+
+pytestmark = pytest.mark.gpu
+
+CODE = {torch.float32: a2sf.A2SF_F32, torch.bfloat16: a2sf.A2SF_BF16}
+
+
+def prefill(q, k, v, alpha=1.0, select=8, recent=8):
+    """q [G, group, n, d]; outputs and the score of every token."""
+    G, group, n, d = q.shape
+    cache = a2sf.Cache(G, select + recent + 1, d, q.dtype)
+    o, s = torch.full_like(q, 7.0), torch.full((G, n), 7.0, device="cuda")
+    ws = torch.empty(a2sf.a2sf_workspace_bytes(G * group, n, cache.capacity, d, CODE[q.dtype], select, recent),
+                     dtype=torch.uint8, device="cuda")
+    a2sf.a2sf_prefill_gqa(q, k, v, n, group, alpha, select, recent, cache, o=o, scores_full=s, workspace=ws)
+    torch.cuda.synchronize()
+    return o, s
+
+
+def chunk(q, k, v, cached, select=8, recent=8):
+    """The last rows of a prompt as a chunk behind its first `cached` ones."""
+    G, group, m, d = q.shape
+    cache = a2sf.Cache(G, cached + m + select + recent + 1, d, q.dtype)
+    cache.k[:, :cached], cache.v[:, :cached] = k[:, :cached], v[:, :cached]
+    cache.scores[:, :cached] = 1.0
+    cache.pos[:, :cached] = torch.arange(cached, device="cuda").int()
+    cache.len.fill_(cached)
+    o = torch.full_like(q, 7.0)
+    ws = torch.empty(a2sf.a2sf_workspace_bytes(G * group, m, cache.capacity, d, CODE[q.dtype], select, recent),
+                     dtype=torch.uint8, device="cuda")
+    a2sf.a2sf_prefill_chunk_gqa(q, k[:, cached:].contiguous(), v[:, cached:].contiguous(), m, cached, group, 0.5,
+                                select, recent, cache, o=o, workspace=ws)
+    torch.cuda.synchronize()
+    return o
+
+
+def rows_by_hand(q, k, v, off=0):
+    """float64 attention rows that read only the keys they see."""
+    q, k, v = parity.to_f64(q), parity.to_f64(k), parity.to_f64(v)
+    out = np.empty(q.shape)
+    for g in range(q.shape[0]):
+        for r in range(q.shape[1]):
+            for i in range(q.shape[2]):
+                z = k[g, : off + i + 1] @ q[g, r, i] / np.sqrt(q.shape[3])
+                p = np.exp(z - z.max())
+                with np.errstate(invalid="ignore"):
+                    out[g, r, i] = (p / p.sum()) @ v[g, : off + i + 1]
+    return out
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("group,n,cached", [(1, 100, 0), (3, 65, 0), (1, 45, 50), (2, 33, 31)])
+def test_fp32_infinities_reach_only_the_rows_that_see_them(d, group, n, cached):
+    """V rows with an infinity or a NaN, each in another tile: the rows before them share the tile and
+    stay finite, the rows after them get what float64 arithmetic gets."""
+    gen = torch.Generator(device="cuda").manual_seed(d + n)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    q, k, v = rnd(4, group, n, d), rnd(4, cached + n, d), rnd(4, cached + n, d)
+    at = cached + n - 20
+    v[0, at, 3], v[1, at, d - 1], v[2, at, 7] = float("inf"), float("nan"), -float("inf")
+    v[2, at + 5, 7] = float("inf")
+    o = chunk(q, k, v, cached) if cached else prefill(q, k, v)[0]
+    got, want = o.double().cpu().numpy(), rows_by_hand(q, k, v, cached)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(np.where(np.isinf(want), want, 0.0), np.where(np.isinf(got), got, 0.0))
+    finite = np.isfinite(want)
+    assert finite.mean() > 0.9 and np.abs(got[finite] - want[finite]).max() <= parity.O_TOL["f32"]

@@ -71,6 +71,12 @@ __device__ __forceinline__ void fetch_tile(const float* __restrict__ Mg, int row
   }
 }
 
+// The maximum that a row's exponents are taken against is that of the logits as they come from the products, before
+// they are scaled, so that the largest one's exponent is exactly 0 however large it is (s * scale rounded and s * scale in
+// an fma differ by more than an exponent's range from 2^31 on).  It starts here and not at -inf, which must not be
+// subtracted from a masked logit.
+constexpr float kLowest = -3.402823466e38f;
+
 // A matrix op multiplies a masked key's probability, 0, with its V row, and 0 times an infinity is not 0.
 // So the tiles that the mask cuts are looked over (D / 8 LDS reads of a lane beside the 4 D of the products) and their
 // infinities and NaN set to 0; add_nonfinite gives them to the rows that see them at the end.
@@ -78,7 +84,7 @@ template <int D>
 __device__ __forceinline__ bool clear_nonfinite(lds_char* tile) {
   lds_char* const mine = tile + (threadIdx.x & 63) * 16;
   float zeros = 0.f;  // a NaN if some x is not finite
-#pragma unroll 8
+#pragma unroll 4
   for (int u = 0; u < D / 8; ++u) {
     const f32x4 x = lds_read4(mine + u * 1024);
     zeros = fmaf(x[0], 0.f, fmaf(x[1], 0.f, fmaf(x[2], 0.f, fmaf(x[3], 0.f, zeros))));
@@ -170,7 +176,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_f32_kernel(
   for (int db = 0; db < (WITH_O ? DB : 1); ++db)
 #pragma unroll
     for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  float m = kLowest, l = 0.f;
   bool odd = false;  // a V row of a masked tile holds an infinity or a NaN
   const int newest = off + row0 + l32;  // newest key this lane's row sees
 
@@ -204,10 +210,9 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_f32_kernel(
 #pragma unroll
     for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
     mx = across_rows(mx, OpMax(), false, true);
-    // a tile can be fully masked for a row: the floor keeps m finite then
-    const float m_new = fmaxf(m, fmaxf(mx * scale_log2e, -1e30f));
+    const float m_new = fmaxf(m, mx);
     if (__any(m_new > m)) {
-      const float corr = exp2f(m - m_new);  // 0 on the first tile (m = -inf)
+      const float corr = exp2f((m - m_new) * scale_log2e);
       l *= corr;
       if (WITH_O) {
 #pragma unroll
@@ -219,7 +224,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_f32_kernel(
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      s[i] = __builtin_amdgcn_exp2f(fmaf(s[i], scale_log2e, -m));
+      s[i] = __builtin_amdgcn_exp2f((s[i] - m) * scale_log2e);
       l += s[i];
     }
     if constexpr (WITH_O) {
@@ -247,15 +252,16 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_f32_kernel(
   if (h == 0) { m_s[wave][l32] = m; l_s[wave][l32] = l; }
   if (WITH_O && lane == 0) odd_s[wave] = odd;
   __syncthreads();
-  float mall = m_s[0][l32];  // wave 0 has seen key 0: finite
+  float mall = m_s[0][l32];
 #pragma unroll
   for (int w = 1; w < kWaves; ++w) mall = fmaxf(mall, m_s[w][l32]);
   float lall = 0.f;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) lall += l_s[w][l32] * exp2f(m_s[w][l32] - mall);
-  if (wave == 0 && h == 0 && row0 + l32 < n) LSE2[(size_t)g * n + row0 + l32] = mall + log2f(lall);
+  for (int w = 0; w < kWaves; ++w) lall += l_s[w][l32] * exp2f((m_s[w][l32] - mall) * scale_log2e);
+  if (wave == 0 && h == 0 && row0 + l32 < n)
+    LSE2[(size_t)g * n + row0 + l32] = fmaf(mall, scale_log2e, log2f(lall));
   if constexpr (WITH_O) {
-    const float f = exp2f(m - mall) / lall;
+    const float f = exp2f((m - mall) * scale_log2e) / lall;
     // the strip now takes the wave's outputs, [query][d], chunks swizzled as in a tile
 #pragma unroll
     for (int db = 0; db < DB; ++db)

@@ -72,3 +72,23 @@ def test_fp32_infinities_reach_only_the_rows_that_see_them(d, group, n, cached):
     assert np.array_equal(np.where(np.isinf(want), want, 0.0), np.where(np.isinf(got), got, 0.0))
     finite = np.isfinite(want)
     assert finite.mean() > 0.9 and np.abs(got[finite] - want[finite]).max() <= parity.O_TOL["f32"]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("size", [1e6, 1e12, 1e30, 1e34])
+def test_fp32_logits_of_any_size(d, size):
+    """Rows whose logits are all far below (and above) the range of an exponent: with one key, with the same
+    logit for all keys, and with logits that rise or fall so steeply that one key has all the weight."""
+    n = 70
+    q, k = torch.zeros(6, 1, n, d, device="cuda"), torch.zeros(6, n, d, device="cuda")
+    v = torch.randn(6, n, d, generator=torch.Generator(device="cuda").manual_seed(d), device="cuda")
+    ramp = 1.0 + 0.01 * torch.arange(n, device="cuda")
+    q[..., 0] = 1.0
+    k[0, :, 0], k[1, :, 0], k[2, :, 0] = -size, -size * ramp, -size / ramp
+    k[3:, :, 0] = -k[:3, :, 0]
+    o = prefill(q, k, v)[0][:, 0].double()
+    same = v.double().cumsum(1) / torch.arange(1, n + 1, device="cuda").view(1, n, 1)
+    for g, want in ((0, same[0]), (1, v[1, :1].double()), (2, v[2].double()), (3, same[3]), (4, v[4].double()), (5, v[5, :1].double())):
+        if size < 1e12 and g in (2, 5):   # the last keys' logits lie a few hundred apart, still one key's weight
+            assert 1.0 / ramp[-2] - 1.0 / ramp[-1] > 100.0 * d ** 0.5 / size
+        assert (o[g] - want).abs().max() <= parity.O_TOL["f32"], g

@@ -192,7 +192,8 @@ def mask_full(base):
     return [f"v_mov_b32 {v(base + i)}, {v(NEGINF)}" for i in range(16)]
 
 
-RESCALE_AT = 0x4e800000  # 2^30
+def rescale_at():
+    return 0x43800000 if RAGGED else 0x4e800000  # 2^8, 2^30
 
 
 def softmax(out, b, s, p):
@@ -201,7 +202,8 @@ def softmax(out, b, s, p):
     intact, bf16 probabilities go to v[p..p+15]).  Floating point keeps full relative
     precision while p stays far from overflow, so m only has to move when the tile's sum
     passes 2^30 (or is not a number, which is how the first tile, with m = -inf, announces
-    itself); then the out-of-line slow path redoes the tile with a fresh maximum.  Returns
+    itself); then the out-of-line slow path redoes the tile with a fresh maximum.  The ragged
+    stream moves m from 2^8 on, which leaves values of up to 2^120 / (number of keys) room in O.  Returns
     (vector-op list, slow-path lines to be placed out of line)."""
     m, l, flag = M[b], L[b], FLAG[b]
     slow, back = out.label("slow"), out.label("back")
@@ -232,7 +234,7 @@ def softmax(out, b, s, p):
             o.append(add(i - 2))
             if (i - 2) & 1:
                 o.append(cvt((i - 2) // 2))
-    o += [f"v_cmp_nge_f32 vcc, {RESCALE_AT:#x}, {v(RS)}",
+    o += [f"v_cmp_nge_f32 vcc, {rescale_at():#x}, {v(RS)}",
           "s_cmp_lg_u64 vcc, 0",
           f"s_cbranch_scc1 {slow}",
           f"{back}:",
@@ -257,7 +259,8 @@ def softmax_slow(b, s, p):
           f"v_max_f32 {v(MX)}, {v(MX)}, {v(T1)}",
           f"v_mul_f32 {v(MX)}, %[scale], {v(MX)}",
           f"v_max_f32 {v(MX)}, 0xf149f2ca, {v(MX)}",          # -1e30 floor
-          f"v_add_f32 {v(T1)}, 0x41000000, {v(m)}",            # lazy rescale: only past m + 8
+          # lazy rescale: only past m + 8 (ragged: past m, or sums between 2^8 and 2^13 would come here again)
+          f"v_mov_b32 {v(T1)}, {v(m)}" if RAGGED else f"v_add_f32 {v(T1)}, 0x41000000, {v(m)}",
           f"v_cmp_gt_f32 vcc, {v(MX)}, {v(T1)}",
           "s_cmp_lg_u64 vcc, 0",
           f"s_cselect_b64 {sp(flag)}, -1, 0",

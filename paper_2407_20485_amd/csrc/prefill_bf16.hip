@@ -175,9 +175,10 @@ __device__ __forceinline__ void dma_full_tile(const bf16_t* __restrict__ Mg, int
 // interleaved in the instruction stream), then O += V(t)^T P(t).  K tiles are fetched two steps ahead,
 // V tiles one.  Exponentials are taken against the running maximum as it is, without looking for
 // the tile's own: floating point keeps their relative precision whatever their size, so the
-// maximum has to move (and O to be rescaled) only when a tile's sum leaves the range (>= 2^30, or not
-// a number: the first tile, whose running maximum is -inf).
-constexpr float kMoveMaximumAt = 1073741824.f;  // 2^30
+// maximum has to move (and O to be rescaled) only when a tile's sum leaves a range (or is not a number: the
+// first tile, whose running maximum is -inf).  Sums alone may grow to 2^30; with outputs a probability stays below
+// 2^8, so that O overflows for values above 2^120 / (number of keys) only.
+constexpr float kMoveMaximumAt = 1073741824.f, kMoveMaximumWithO = 256.f;
 
 // KS = 2 (with outputs): eight waves, the second four take the odd tiles of the same 128 rows and the
 // two halves are merged at the end -- for launches that do not fill the chip, where the chain of
@@ -447,7 +448,7 @@ __global__ __launch_bounds__(kThreads * KS, !WITH_O ? 4 : 2 / KS) void attn_fwd_
         __builtin_amdgcn_sched_barrier(0);
       });
       finish(15);
-      if (__any(!(rs < kMoveMaximumAt))) {
+      if (__any(!(rs < kMoveMaximumWithO))) {
         const float corr = move_maximum(s);
         lsum *= corr;
 #pragma unroll

@@ -92,3 +92,22 @@ def test_fp32_logits_of_any_size(d, size):
         if size < 1e12 and g in (2, 5):   # the last keys' logits lie a few hundred apart, still one key's weight
             assert 1.0 / ramp[-2] - 1.0 / ramp[-1] > 100.0 * d ** 0.5 / size
         assert (o[g] - want).abs().max() <= parity.O_TOL["f32"], g
+
+
+@pytest.mark.parametrize("G,n,d,cached", [(2, 200, 64, 0), (2, 200, 128, 0), (300, 200, 64, 0), (300, 200, 128, 0), (129, 1000, 128, 0),
+                                          (64, 2049, 128, 0), (2, 70, 64, 130), (2, 70, 128, 130)])
+def test_bf16_values_of_extreme_size(G, n, d, cached):
+    """Values of 1e34 whose later keys have logits 24 octaves above the earlier ones: a row's average is a value of
+    1e34 again, whatever its probabilities are taken relative to (bf16 rounds it by 2^-8 at most)."""
+    total = cached + n
+    q, k = torch.zeros(G, 1, n, d, device="cuda"), torch.zeros(G, total, d, device="cuda")
+    q[..., 0] = 4.0
+    k[:, total // 2:, 0] = 24 * np.log(2.0) * d ** 0.5 / 4
+    v = torch.full((G, total, d), 1e34, device="cuda")
+    v[:, ::2] *= -0.5
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    o = chunk(q, k, v, cached) if cached else prefill(q, k, v)[0]
+    want = rows_by_hand(q[:1], k[:1], v[:1], cached) / 1e34
+    got = o.double().cpu().numpy() / 1e34
+    assert np.isfinite(got).all()
+    assert np.abs(got - want).max() <= 2e-2

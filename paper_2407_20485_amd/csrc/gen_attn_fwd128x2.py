@@ -93,7 +93,7 @@ SGN, SQBN = 84, 85      # its head and row block
 SLO, SHI = 40, 99
 # ragged stream only
 TP, PT, LIM = 68, 70, 71      # tile from which the fetch is out of line; the partial tile; its largest lane offset
-NVALID = (72, 73)       # rows of block 0 / 1 that exist (from its first one on; may be negative)
+NVALID = (72, 73)       # rows of block 0 / 1 that exist (of its 32; may be negative)
 X0, X1, X2, X3 = 74, 75, 76, 77 # scratch
 QOF = (223, 224)        # per-lane offsets of the Q loads, per block
 
@@ -600,6 +600,7 @@ def q_clamp(b, row):
     return [f"s_sub_u32 s{X0}, s{row}, s{SHEAD}",            # first row in the head
             f"s_sub_u32 s{X1}, %[n], s{X0}",                 # rows that exist
             f"s_sub_u32 s{X1}, s{X1}, 1",
+            f"s_min_u32 s{X1}, s{X1}, 31",                   # (of the block's 32)
             f"s_lshl_b32 s{X1}, s{X1}, 8",
             f"s_add_u32 s{X1}, s{X1}, 16",
             f"s_add_u32 s{X2}, s{SHEAD}, %[n]",
@@ -731,6 +732,8 @@ def prologue(out):
     if RAGGED:
         out.e(f"s_sub_u32 s{NVALID[0]}, %[n], s{ST1}")
         out.e(f"s_sub_u32 s{NVALID[1]}, %[n], s{PAIR}")
+        for b in (0, 1):
+            out.e(f"s_min_i32 s{NVALID[b]}, s{NVALID[b]}, 32")
         # the head's last row block: tile n / 64 is partial (or the first one past the rows)
         out.e(f"s_lshr_b32 s{X0}, %[n], 6")
         out.e(f"s_and_b32 s{X1}, %[n], 63")

@@ -83,6 +83,16 @@ class RaggedWave(Wave):
                 return True
         return False
 
+    def s_min_u32(self, a):
+        x, y = self.val(a[1]) & M32, self.val(a[2]) & M32
+        self.put(a[0], min(x, y))
+        self.scc = int(x < y)
+
+    def s_min_i32(self, a):
+        x, y = signed(self.val(a[1]) & M32), signed(self.val(a[2]) & M32)
+        self.put(a[0], min(x, y) & M32)
+        self.scc = int(x < y)
+
     def global_load_lds_dwordx4(self, a):
         add, lim = self.reg[a[0]]
         off = self._offset(a)
@@ -249,6 +259,15 @@ def test_single_blocks(program, n):
         for qb in {0, nqb - 2, nqb - 1}:
             waves = run_workgroup(program, n, G, kvr, (g, qb), None, nqb)
             check_workgroup(waves, [(g, qb)], n, G, kvr)
+
+
+@pytest.mark.parametrize("n", [(1 << 23) - 1, (1 << 23) + 5, (1 << 24) + 77])
+def test_rows_beyond_the_range_of_a_byte_offset(program, n):
+    """Heads so long that 256 times the rows left to the end does not fit 31 bits."""
+    nqb = -(-n // 256)
+    for qb in (0, 1):
+        waves = run_workgroup(program, n, 2, 1, (1, qb), None, nqb)
+        check_workgroup(waves, [(1, qb)], n, 2, 1)
 
 
 @pytest.mark.parametrize("n,rounds,vid0,kvr", [(513, 4, 0, 1), (600, 6, 31, 2), (700, 4, 2, 1), (1000, 4, 33, 4), (1024, 4, 35, 1),

@@ -211,7 +211,8 @@ __global__ __launch_bounds__(T) void select_kernel(
     // kept, so that the cut is simply the B-th largest key), the ordered score of the others.
     const auto form_key = [&](int it, int j, uint32_t bits) -> uint32_t {
       const bool r = recent > 0 && (ps ? pos_key(it) > (uint32_t)p_recent : j >= p_recent);
-      return j < Lg ? (r ? 0xFFFFFFFFu : ordered_key(__uint_as_float(bits))) : 0u;
+      const uint32_t o = ordered_key(__uint_as_float(bits));  // (0 and all ones: NaN of all ones)
+      return j < Lg ? (r ? 0xFFFFFFFFu : min(max(o, 1u), 0xFFFFFFFEu)) : 0u;
     };
     if constexpr (IPT > 0) each([&](int it, int j) { key[it] = form_key(it, j, key[it]); });
     const auto key_of = [&](int it) -> uint32_t {

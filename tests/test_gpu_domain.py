@@ -111,3 +111,26 @@ def test_bf16_values_of_extreme_size(G, n, d, cached):
     got = o.double().cpu().numpy() / 1e34
     assert np.isfinite(got).all()
     assert np.abs(got - want).max() <= 2e-2
+
+
+@pytest.mark.parametrize("L", [150, 1000, 5000, 40000])
+def test_selection_among_nan_scores(L):
+    """Scores that are NaN of any sign and payload, all bits set among them: every head keeps as many slots as the
+    budget has, the recent ones among them, positive NaN before and negative ones after every number."""
+    rng = np.random.default_rng(L)
+    bits = rng.random((5, L)).astype(np.float32).view(np.uint32)
+    nan = np.array([0x7FFFFFFF, 0xFFFFFFFF, 0x7FC00000, 0xFFC00000, 0xFFFFFFFE], dtype=np.uint32)
+    bits[0, ::3] = rng.choice(nan, bits[0, ::3].shape)
+    bits[1, :], bits[2, :], bits[3, : L // 2] = 0xFFFFFFFF, 0x7FFFFFFF, 0xFFFFFFFF
+    scores = torch.from_numpy(bits.view(np.float32)).cuda()
+    select, recent = L // 3, L // 7
+    for pos in (None, torch.arange(L, device="cuda").int().expand(5, L).contiguous()):
+        keep = torch.full((5, select + recent), -1, dtype=torch.int32, device="cuda")
+        n_keep = torch.zeros(5, dtype=torch.int32, device="cuda")
+        a2sf.a2sf_select(scores, pos, None, 5, L, L, select, recent, keep, n_keep)
+        torch.cuda.synchronize()
+        order = np.where(bits >> 31, ~bits, bits | 0x80000000).clip(1, 0xFFFFFFFE)
+        order[:, L - recent:] = 0xFFFFFFFF
+        for g in range(5):
+            want = np.sort(np.lexsort((np.arange(L), -order[g].astype(np.int64)))[: select + recent])
+            assert int(n_keep[g]) == select + recent and np.array_equal(keep[g].cpu().numpy(), want), g

@@ -242,9 +242,15 @@ __device__ __forceinline__ uint4 load16_as(const void* p) {
 // to the compiler's wait counting: the kernel waits itself (wait_vm, wait_vm_barrier) before the data is
 // read, and makes sure that a stage's readers are done before it is filled again.  The compiler's
 // own waits stay correct, since loads return in order: it can only wait for more than it needs.
+// The statements keep the distances themselves that the hardware does not: one state between the M0
+// write and the load, and five between a vector instruction that writes a scalar register and a load that reads
+// it -- the compiler may have formed the base with one (v_readfirstlane) right before, so the load reads a copy
+// that a scalar move made.  M0 cannot be declared as clobbered: it is a reserved register, which the compiler
+// keeps no value in across a statement but writes right before each of its own uses.
 __device__ __forceinline__ void dma16(const void* base, uint32_t lane_off, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"(base) : "memory");
+  const void* copy;
+  asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+               : "=&s"(copy) : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"(base) : "memory");
 }
 // ... from an address per lane
 __device__ __forceinline__ void dma16_at(const void* p, uint32_t lds_addr) {
@@ -252,8 +258,9 @@ __device__ __forceinline__ void dma16_at(const void* p, uint32_t lds_addr) {
                :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(p) : "memory");
 }
 __device__ __forceinline__ void dma4(const void* base, uint32_t lane_off, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
-               :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"(base) : "memory");
+  const void* copy;
+  asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dword %2, %0"
+               : "=&s"(copy) : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"(base) : "memory");
 }
 // At most LEFT of this wave's loads and stores outstanding; LDS reads done.
 template <int LEFT>

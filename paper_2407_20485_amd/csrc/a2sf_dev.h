@@ -116,6 +116,9 @@ __device__ __forceinline__ uint32_t ordered_key(float s) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// The same without the keys 0 and all ones, which only a NaN of all bits set has: a selection marks slots with them.
+__device__ __forceinline__ uint32_t score_key(float s) { return min(max(ordered_key(s), 1u), 0xFFFFFFFEu); }
+
 // ---- wave / block reductions ------------------------------------------------------------
 __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, dpp_move<0xB1>(v));
@@ -198,6 +201,127 @@ __device__ __forceinline__ unsigned long long block_min_u64(unsigned long long v
   unsigned long long a = red[0] < red[1] ? red[0] : red[1];
   unsigned long long b = red[2] < red[3] ? red[2] : red[3];
   return a < b ? a : b;
+}
+
+// ---- selection by threshold counts --------------------------------------------------------
+// What the waves of a search share (one wave alone needs nothing).
+template <int NW>
+struct SelectSmem {
+  int cnt[2][NW * 8];  // per wave: counts of up to eight thresholds; two sets, so a round needs one barrier
+  int lo[NW], hi[NW];
+};
+template <>
+struct SelectSmem<1> {};
+
+// Sum over the waves of the counts that every wave has put into cnt[wave * 8 + i], i < 8: the
+// lanes i = lane % 8 get the total of threshold i.
+template <int NW>
+__device__ __forceinline__ int sum_counts(const int* cnt, int lane) {
+  uint32_t v = 0;
+  if (NW >= 8) {
+#pragma unroll
+    for (int w = 0; w < NW; w += 8) v += (uint32_t)cnt[w * 8 + lane];
+  } else {
+    v = lane < NW * 8 ? (uint32_t)cnt[lane] : 0u;
+  }
+  v += dpp_move_u32<0x128>(v);  // row_ror:8
+  u32x2_t r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = r[0] + r[1];
+  r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return (int)(r[0] + r[1]);
+}
+
+struct Cut {
+  uint32_t key;  // the k-th largest key
+  int above;     // keys > key, or -1: exactly k keys are >= key (no ties to break)
+};
+
+// k-th largest of the keys key_of(it), it in [0, n_it), of all threads of NW waves; key 0 marks what does
+// not take part, n_top < k keys are 0xFFFFFFFF.  With fewer than k others the result is key 0.  Must be reached
+// by all NW waves (a workgroup's, if more than one); every thread gets the result.
+template <int NW, int NT, int IPT, typename F>
+__device__ __forceinline__ Cut kth_largest(F key_of, int n_it, int k, int n_top, SelectSmem<NW>& sm) {
+  const int lane = threadIdx.x & 63, wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const auto each = [&](auto f) {
+    if constexpr (IPT > 0) {
+#pragma unroll
+      for (int it = 0; it < IPT; ++it)
+        if (it < n_it) f(it);
+    } else {
+      for (int it = 0; it < n_it; ++it) f(it);
+    }
+  };
+  // invariant: at least k keys are >= lo (`reach`, or fewer at first), fewer than k are >= hi, namely `above`
+  uint32_t lo = 1u, hi = 0xFFFFFFFFu;
+  int above = n_top, reach = 64 * NW * n_it;
+  // closes lo and hi in on the keys between them; false: there are none
+  const auto close_in = [&]() -> bool {
+    uint32_t below = 0xFFFFFFFFu, behind = 0xFFFFFFFFu;  // room at the ends (keys outside wrap to at least hi - lo)
+    each([&](int it) {
+      const uint32_t key = key_of(it);
+      below = min(below, key - lo);
+      behind = min(behind, hi - 1u - key);
+    });
+    int mb = wave_max_i((int)(~below ^ 0x80000000u)), mh = wave_max_i((int)(~behind ^ 0x80000000u));
+    if constexpr (NW > 1) {
+      __syncthreads();  // the scratch arrays are free
+      if (lane == 0) { sm.lo[wave] = mb; sm.hi[wave] = mh; }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < NW; ++w) { mb = max(mb, sm.lo[w]); mh = max(mh, sm.hi[w]); }
+    }
+    below = (uint32_t)__builtin_amdgcn_readfirstlane(~(mb ^ (int)0x80000000u));
+    behind = (uint32_t)__builtin_amdgcn_readfirstlane(~(mh ^ (int)0x80000000u));
+    if (below >= hi - lo) return false;
+    lo += below;
+    hi -= behind;
+    return true;
+  };
+  if (!close_in()) return {0u, n_top};  // nothing else takes part
+  // (the smallest key itself is never counted: fewer than k keys in all end at lo with above < k)
+  for (int round = 1; hi - lo > 1; ++round) {
+    const uint32_t w = hi - lo;
+    const uint32_t step = w > NT + 1 ? w / (NT + 1) : 1u;
+    uint32_t c[NT];
+    int n[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      c[i] = step * (i + 1) < w ? lo + step * (i + 1) : hi - 1;  // repeats of hi - 1 do no harm
+      n[i] = 0;
+    }
+    each([&](int it) {
+      const uint32_t key = key_of(it);
+#pragma unroll
+      for (int i = 0; i < NT; ++i) n[i] += __popcll(__ballot(key >= c[i]));
+    });
+    if constexpr (NW > 1) {
+      int mine = 0;
+#pragma unroll
+      for (int i = 0; i < NT; ++i) mine = lane == i ? n[i] : mine;
+      int* cnt = sm.cnt[round & 1];
+      if (lane < 8) cnt[wave * 8 + lane] = mine;
+      __syncthreads();
+      const int sum = sum_counts<NW>(cnt, lane);
+#pragma unroll
+      for (int i = 0; i < NT; ++i) n[i] = __builtin_amdgcn_readlane(sum, i);
+    }
+    uint32_t new_lo = lo, new_hi = hi;
+    const int inside = reach - above;
+#pragma unroll
+    for (int i = NT - 1; i >= 0; --i) {  // counts fall with i
+      if (n[i] == k) return {c[i], -1};
+      if (n[i] < k) { new_hi = c[i]; above = n[i]; }
+      else if (c[i] > new_lo) { new_lo = c[i]; reach = n[i]; }
+    }
+    lo = new_lo;
+    hi = new_hi;
+    // a range that shrank and lost few of its keys is mostly empty (ties, outliers, clusters): the rest is left at
+    // once.  (Not in the first round: scores fill the upper end of their range, an octave like the next.  Nor with
+    // 32 keys per thread, whose registers are all taken.)
+    if constexpr (IPT <= 16)
+      if (round > 1 && 8 * (long long)(reach - above) > 7 * (long long)inside && hi - lo > 1) close_in();
+  }
+  return {lo, above};
 }
 
 // Row window and exponent slope of one head's forgotten score (Section 3.3 Eq.5): rows before

@@ -5,13 +5,15 @@
 //
 // Selection: one workgroup per head.  A head's scores become order-preserving integer keys, held in
 // registers where they fit, and the cut (a key that exactly `select` tokens reach) is found by a
-// search over the key range: every round counts the keys at or above seven (three) thresholds at
+// search over the key range (kth_largest): every round counts the keys at or above three thresholds at
 // once, one compare and one scalar bit count per wave, key and threshold, and keeps the
 // subinterval that holds the cut.  It ends as soon as a threshold separates exactly `select`
-// tokens, after four to six rounds on real scores.  A histogram of digits (the usual radix
+// tokens, after six to nine rounds on real scores; where a subinterval keeps nearly all of its keys (ties, outliers,
+// clusters) the bounds close in on them.  A histogram of digits (the usual radix
 // select) sends most keys of a head to a few bins -- scores share their sign and most of
-// their exponent -- where the LDS atomics serialise: 32 heads x 32768 tokens took 221 us that way and take
-// 39 us here; 32 x 1024: 10.9 and 7.7 us.  Up to three searches run:
+// their exponent -- where the LDS atomics serialise (us per call, that way / here: 32 heads x 32768 tokens 195 / 47,
+// 32 x 1024 9.5 / 8.4, 2048 x 2048 27 / 24, the same with most scores 0 106 / 33, 8000 x 400 32 / 18).  Seven thresholds
+// need fewer rounds and more work per bit (8000 x 200: 12.0 and 15.1).  Up to three searches run:
 //   1. the `recent`-th largest position           -> who is in the recent window (only where the
 //      newest positions have gaps; otherwise the largest position tells)
 //   2. the `select`-th largest score of the rest  -> score threshold
@@ -23,108 +25,6 @@
 namespace a2sf {
 namespace {
 
-template <int NW>
-struct SelectSmem {
-  int cnt[2][NW * 8];  // per wave: counts of up to eight thresholds; two sets, so a round needs one barrier
-  int lo[NW], hi[NW];
-};
-
-// Sum over the waves of the counts that every wave has put into cnt[wave * 8 + i], i < 8: the
-// lanes i = lane % 8 get the total of threshold i.
-template <int NW>
-__device__ __forceinline__ int sum_counts(const int* cnt, int lane) {
-  uint32_t v = 0;
-  if (NW >= 8) {
-#pragma unroll
-    for (int w = 0; w < NW; w += 8) v += (uint32_t)cnt[w * 8 + lane];
-  } else {
-    v = lane < NW * 8 ? (uint32_t)cnt[lane] : 0u;
-  }
-  v += dpp_move_u32<0x128>(v);  // row_ror:8
-  u32x2_t r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  v = r[0] + r[1];
-  r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return (int)(r[0] + r[1]);
-}
-
-struct Cut {
-  uint32_t key;  // the k-th largest key
-  int above;     // keys > key, or -1: exactly k keys are >= key (no ties to break)
-};
-
-// k-th largest of the keys key_of(it), it in [0, n_it), of all threads; key 0 marks what does not take
-// part, n_top < k keys are 0xFFFFFFFF.  With fewer than k others the result is key 0.  Must be reached
-// by the whole workgroup; every thread gets the result.
-template <int NW, int NT, int IPT, typename F>
-__device__ __forceinline__ Cut kth_largest(F key_of, int n_it, int k, int n_top, SelectSmem<NW>& sm) {
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const auto each = [&](auto f) {
-    if constexpr (IPT > 0) {
-#pragma unroll
-      for (int it = 0; it < IPT; ++it)
-        if (it < n_it) f(it);
-    } else {
-      for (int it = 0; it < n_it; ++it) f(it);
-    }
-  };
-  // the range of the other keys (0xFFFFFFFF + 1 and 0 - 1 wrap out of the way)
-  uint32_t mn = 0xFFFFFFFFu, mx = 0u;
-  each([&](int it) {
-    const uint32_t key = key_of(it);
-    mx = max(mx, key + 1u);
-    mn = min(mn, key - 1u);
-  });
-  const int smx = wave_max_i((int)(mx ^ 0x80000000u)), smn = wave_max_i((int)(~mn ^ 0x80000000u));
-  __syncthreads();  // the scratch arrays are free
-  if (lane == 0) { sm.hi[wave] = smx; sm.lo[wave] = smn; }
-  __syncthreads();
-  int top = sm.hi[0], bot = sm.lo[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) { top = max(top, sm.hi[w]); bot = max(bot, sm.lo[w]); }
-  // invariant: at least k keys are >= lo, fewer than k are >= hi, namely `above`
-  unsigned long long hi = (uint32_t)__builtin_amdgcn_readfirstlane(top ^ (int)0x80000000u);
-  unsigned long long lo = (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane(~(bot ^ (int)0x80000000u)) + 1ull;
-  if (lo >= hi) return {0u, n_top};  // nothing else takes part
-  int above = n_top;
-  // (the smallest key itself is never counted: fewer than k keys in all end at lo with above < k)
-  for (int round = 0; hi - lo > 1; ++round) {
-    const unsigned long long w = hi - lo;
-    const uint32_t step = w > NT + 1 ? (uint32_t)(w / (NT + 1)) : 1u;
-    uint32_t c[NT];
-    int n[NT];
-#pragma unroll
-    for (int i = 0; i < NT; ++i) {
-      const unsigned long long x = lo + (unsigned long long)step * (i + 1);
-      c[i] = (uint32_t)(x < hi ? x : hi - 1);  // repeats of hi - 1 do no harm
-      n[i] = 0;
-    }
-    each([&](int it) {
-      const uint32_t key = key_of(it);
-#pragma unroll
-      for (int i = 0; i < NT; ++i) n[i] += __popcll(__ballot(key >= c[i]));
-    });
-    int mine = 0;
-#pragma unroll
-    for (int i = 0; i < NT; ++i) mine = lane == i ? n[i] : mine;
-    int* cnt = sm.cnt[round & 1];
-    if (lane < 8) cnt[wave * 8 + lane] = mine;
-    __syncthreads();
-    const int sum = sum_counts<NW>(cnt, lane);
-#pragma unroll
-    for (int i = 0; i < NT; ++i) n[i] = __builtin_amdgcn_readlane(sum, i);
-    unsigned long long new_lo = lo, new_hi = hi;
-#pragma unroll
-    for (int i = NT - 1; i >= 0; --i) {  // counts fall with i
-      if (n[i] == k) return {c[i], -1};
-      if (n[i] < k) { new_hi = c[i]; above = n[i]; }
-      else if (c[i] > new_lo) new_lo = c[i];
-    }
-    lo = new_lo;
-    hi = new_hi;
-  }
-  return {(uint32_t)lo, above};
-}
-
 // Where the kept rows of a prompt go: fused selection and gather.
 constexpr int kFusedKeep = 512;  // tokens kept per head, at most
 struct GatherTo {
@@ -135,20 +35,21 @@ struct GatherTo {
   int capacity, lg_units;    // log2 of the 16-byte units per row
 };
 
-// T threads per head; IPT > 0: up to T * IPT tokens, keys in registers; IPT = 0: any number, the
-// keys are formed again from memory in every round.  With `to` the kept indices stay in LDS and the
+// T threads per head.  SOLO: one of the waves does the search alone (up to 64 * IPT tokens, keys in registers), the others
+// only take part in the copy.  Otherwise all waves do: up to T * IPT tokens with keys in registers, or, with
+// IPT = 0, any number, the keys formed again from memory in every round.  With `to` the kept indices stay in LDS and the
 // workgroup copies the rows of its head at once (to.kin set: pos and len are null, B <= kFusedKeep).
-template <int T, int IPT>
+template <int T, int IPT, bool SOLO>
 __global__ __launch_bounds__(T) void select_kernel(
     const float* __restrict__ scores, const int32_t* __restrict__ pos,
     const int32_t* __restrict__ len, int L, int stride, int select, int recent,
     int32_t* __restrict__ keep_idx, int32_t* __restrict__ n_keep, GatherTo to) {
-  constexpr int NW = T / 64, NR = IPT > 0 ? IPT : 1;
-  constexpr int NT = IPT > 8 || IPT == 0 ? 3 : 7;  // thresholds per round: few keys per thread, more of them
+  constexpr int NW = SOLO ? 1 : T / 64, NR = IPT > 0 ? IPT : 1;  // waves that search
+  constexpr int NT = 3;  // thresholds per round
   __shared__ SelectSmem<NW> sm;
   __shared__ int list[kFusedKeep];
   const int g = blockIdx.x, tid = threadIdx.x;
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, wave = SOLO ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
   const int B = select + recent;
   int Lg = len ? len[g] : L;
   Lg = Lg < 0 ? 0 : (Lg > L ? L : Lg);
@@ -159,9 +60,9 @@ __global__ __launch_bounds__(T) void select_kernel(
 
   if (Lg <= B) {
     for (int j = tid; j < Lg; j += T) out[j] = j;
-  } else {
+  } else if (!SOLO || T == 64 || __builtin_amdgcn_readfirstlane(tid >> 6) == (int)(blockIdx.x / 8) % (T / 64)) {
     // a wave has 64 * n_it consecutive slots, iteration it its slots j0 + 64 it
-    const int n_it = (Lg + T - 1) / T;
+    const int n_it = (Lg + NW * 64 - 1) / (NW * 64);
     const int j0 = wave * 64 * n_it + lane;
     const auto each = [&](auto f) {
       if constexpr (IPT > 0) {
@@ -192,17 +93,20 @@ __global__ __launch_bounds__(T) void select_kernel(
         uint32_t newest = 0;
         int cnt = 0;
         each([&](int it, int) { newest = max(newest, pos_key(it)); });
-        const int most = wave_max_i((int)(newest ^ 0x80000000u));
-        if (lane == 0) sm.hi[wave] = most;
-        __syncthreads();
-        int all = sm.hi[0];
+        int most = wave_max_i((int)(newest ^ 0x80000000u));
+        if constexpr (NW > 1) {
+          if (lane == 0) sm.hi[wave] = most;
+          __syncthreads();
 #pragma unroll
-        for (int w = 1; w < NW; ++w) all = max(all, sm.hi[w]);
-        newest = (uint32_t)__builtin_amdgcn_readfirstlane(all) ^ 0x80000000u;
+          for (int w = 0; w < NW; ++w) most = max(most, sm.hi[w]);
+        }
+        newest = (uint32_t)__builtin_amdgcn_readfirstlane(most) ^ 0x80000000u;
         each([&](int it, int) { cnt += __popcll(__ballot(pos_key(it) > newest - (uint32_t)recent)); });
-        if (lane < 8) sm.cnt[0][wave * 8 + lane] = cnt;
-        __syncthreads();
-        cnt = __builtin_amdgcn_readfirstlane(sum_counts<NW>(sm.cnt[0], lane));
+        if constexpr (NW > 1) {
+          if (lane < 8) sm.cnt[0][wave * 8 + lane] = cnt;
+          __syncthreads();
+          cnt = __builtin_amdgcn_readfirstlane(sum_counts<NW>(sm.cnt[0], lane));
+        }
         if (cnt == recent) p_recent = (int)(newest - (uint32_t)recent);  // (newest is a position + 1)
         else p_recent = (int)(kth_largest<NW, NT, IPT>(pos_key, n_it, recent, 0, sm).key - 1u);
       }
@@ -211,8 +115,7 @@ __global__ __launch_bounds__(T) void select_kernel(
     // kept, so that the cut is simply the B-th largest key), the ordered score of the others.
     const auto form_key = [&](int it, int j, uint32_t bits) -> uint32_t {
       const bool r = recent > 0 && (ps ? pos_key(it) > (uint32_t)p_recent : j >= p_recent);
-      const uint32_t o = ordered_key(__uint_as_float(bits));  // (0 and all ones: NaN of all ones)
-      return j < Lg ? (r ? 0xFFFFFFFFu : min(max(o, 1u), 0xFFFFFFFEu)) : 0u;
+      return j < Lg ? (r ? 0xFFFFFFFFu : score_key(__uint_as_float(bits))) : 0u;
     };
     if constexpr (IPT > 0) each([&](int it, int j) { key[it] = form_key(it, j, key[it]); });
     const auto key_of = [&](int it) -> uint32_t {
@@ -235,15 +138,17 @@ __global__ __launch_bounds__(T) void select_kernel(
       if (cut.above < 0) return k >= cut.key;
       return k > cut.key || (k == cut.key && tie_key(it) >= tie_cut && tie_cut != 0u);
     };
-    int total = 0;
-    each([&](int it, int) { total += __popcll(__ballot(keeps(it))); });
-    __syncthreads();
-    if (lane == 0) sm.lo[wave] = total;
-    __syncthreads();
     int base = 0;
+    if constexpr (NW > 1) {
+      int total = 0;
+      each([&](int it, int) { total += __popcll(__ballot(keeps(it))); });
+      __syncthreads();
+      if (lane == 0) sm.lo[wave] = total;
+      __syncthreads();
 #pragma unroll
-    for (int w = 0; w < NW; ++w) base += w < wave ? sm.lo[w] : 0;
-    base = __builtin_amdgcn_readfirstlane(base);
+      for (int w = 0; w < NW; ++w) base += w < wave ? sm.lo[w] : 0;
+      base = __builtin_amdgcn_readfirstlane(base);
+    }
     each([&](int it, int j) {
       const bool k = keeps(it);
       const unsigned long long mask = __ballot(k);
@@ -289,18 +194,29 @@ __global__ __launch_bounds__(T) void select_kernel(
 void launch_select_kernel(const float* scores, const int32_t* pos, const int32_t* len, int G, int L,
                           int stride, int select, int recent, int32_t* keep_idx, int32_t* n_keep,
                           const GatherTo& to, hipStream_t st) {
-#define A2SF_SELECT(T, IPT)                                                                         \
-  hipLaunchKernelGGL((select_kernel<T, IPT>), dim3(G), dim3(T), 0, st, scores, pos, len, L, stride, \
+#define A2SF_SELECT(T, IPT, SOLO)                                                                         \
+  hipLaunchKernelGGL((select_kernel<T, IPT, SOLO>), dim3(G), dim3(T), 0, st, scores, pos, len, L, stride, \
                      select, recent, keep_idx, n_keep, to)
-  // With more heads than the chip takes large workgroups (two per compute unit) small ones with
-  // more keys per thread; otherwise a head is spread over up to 16 waves.
-  if (L <= 1024 && (G > 512 || !to.kin)) A2SF_SELECT(256, 4);
-  else if (L <= 2048 && G > 512) A2SF_SELECT(256, 8);
-  else if (L <= 4096) A2SF_SELECT(1024, 4);
-  else if (L <= 8192) A2SF_SELECT(1024, 8);
-  else if (L <= 16384) A2SF_SELECT(1024, 16);
-  else if (L <= 32768) A2SF_SELECT(1024, 32);
-  else A2SF_SELECT(1024, 0);
+  // A search by one wave has no barriers: short heads, and longer ones of which there are so many that the
+  // work counts and not the chain of rounds (us, one wave / four: 300 heads x 200 5.6 / 6.4, 8000 x 400 18.5 / 35.5,
+  // 8000 x 1000 34 / 48, but 1500 x 1024 16.7 / 14.3 and 300 x 1024 14.5 / 8.4).  Up to 2048 slots four waves, or eight where
+  // every head's workgroup has a compute unit (2048 slots, four / eight: 32 heads 12.0 / 10.2, 1500 heads 20.2 / 25.1; 16 of
+  // them: 12.3 and 58.7).  Copying workgroups have more waves while there are few heads.
+  const bool copies = to.kin != nullptr, few = G <= 512;
+  if (L <= 256 && !copies) A2SF_SELECT(64, 4, true);
+  else if (L <= 256 && few) A2SF_SELECT(512, 4, true);
+  else if (L <= 256) A2SF_SELECT(256, 4, true);
+  else if (L <= 512 && !copies && !few) A2SF_SELECT(64, 8, true);
+  else if (L <= 1024 && !copies && G > 2048) A2SF_SELECT(64, 16, true);
+  else if (L <= 1024 && !(copies && few)) A2SF_SELECT(256, 4, false);
+  else if (L <= 2048 && !few) A2SF_SELECT(256, 8, false);
+  else if (L <= 2048) A2SF_SELECT(512, 4, false);
+  else if (L <= 4096) A2SF_SELECT(1024, 4, false);
+  else if (L <= 8192) A2SF_SELECT(1024, 8, false);
+  else if (L <= 16384) A2SF_SELECT(1024, 16, false);
+  else if (L <= 32768) A2SF_SELECT(1024, 32, false);
+  else A2SF_SELECT(1024, 0, false);
+#undef A2SF_SELECT_SOLO
 #undef A2SF_SELECT
 }
 

@@ -298,3 +298,37 @@ def test_stable_steps_of_many_heads(dtype, d):
     ls.select, ls.recent = 30, 11
     for t in range(2, 5):
         ls.step(t, mode=a2sf.A2SF_EVICT_STABLE)
+
+
+@pytest.mark.parametrize("L,G", [(256, 6), (257, 6), (64, 520), (256, 520), (257, 520), (512, 520), (513, 520), (1024, 520), (1025, 520),
+                                 (512, 2100), (513, 2100), (1024, 2100), (1025, 2100), (2048, 6), (2049, 6), (3000, 520)])
+def test_selection_by_one_wave_and_by_several(L, G):
+    """The lines between searches by one wave, by four and by more, on both sides of every number of heads."""
+    for form in ("slots", "consecutive", "gaps"):
+        test_selection_sizes(L, G, form)
+
+
+@pytest.mark.parametrize("L", [200, 900, 3000])
+def test_selection_of_clustered_scores(L):
+    """Scores whose range is mostly empty: nearly all equal, two far outliers around a cluster of neighbouring
+    values, nested clusters -- the search has to close in on the keys between its bounds."""
+    G, select, recent = 6, L // 9, L // 11
+    rng = np.random.default_rng(L)
+    scores = np.zeros((G, L), dtype=np.float32)
+    scores[0, rng.permutation(L)[: L // 50]] = rng.random(L // 50)
+    scores[1] = 1 + np.float32(2.0 ** -23) * rng.integers(0, 6, L)
+    scores[1, 5], scores[1, 17] = 3e38, -3e38
+    scores[2] = 1 + np.float32(2.0 ** -23) * rng.permutation(L)
+    scores[2, 3] = 1e-38
+    scores[3] = np.where(rng.random(L) < 0.5, 1e-30, 1e30) * (1 + 2.0 ** -23 * rng.integers(0, L, L))
+    scores[4] = np.ldexp(1 + 2.0 ** -23 * rng.integers(0, 3, L), -(rng.integers(0, 3, L) * 40))
+    scores[5, : L // 2] = -np.inf
+    scores[5, L // 2:] = np.inf
+    dev = torch.from_numpy(scores).cuda()
+    keep = torch.full((G, select + recent), -1, dtype=torch.int32, device="cuda")
+    n_keep = torch.zeros(G, dtype=torch.int32, device="cuda")
+    a2sf.a2sf_select(dev, None, None, G, L, L, select, recent, keep, n_keep)
+    torch.cuda.synchronize()
+    for g in range(G):
+        want = orc.select_keep(scores[g].astype(np.float64), np.arange(L), select, recent)
+        assert np.array_equal(keep[g].cpu().numpy(), np.sort(want)), g

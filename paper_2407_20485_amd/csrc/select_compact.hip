@@ -307,26 +307,27 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(
 }
 
 // Where hardly a head has anything to move (the stable steps of many heads, whose kernel has moved the rows already):
-// a workgroup looks at eight heads at once, one lane each, and takes those that move one after the other, slice by
-// slice (16384 heads x 201 slots with nothing to move: 27 us with four workgroups per head, 4.9 here).
+// a workgroup looks at eight heads at once, one lane each, and moves its slice of those that do move, one after the other
+// (16384 heads x 201 slots with nothing to move: 27 us with four workgroups per head, 7.2 here; 4096 fp32 heads x 101 x
+// 128 that all move, because the newest positions have gaps: 147 us, 176 when one workgroup takes all slices of its eight).
 constexpr int kSparseHeads = 8;
 template <int ROW_UNITS>
 __global__ __launch_bounds__(kThreads) void compact_sparse_kernel(
     uint4* __restrict__ K, uint4* __restrict__ V, float* __restrict__ S, int32_t* __restrict__ P,
     int32_t* __restrict__ len, int G, int capacity, const int32_t* __restrict__ keep_idx, int keep_stride,
     const int32_t* __restrict__ n_keep) {
-  const int g0 = blockIdx.x * kSparseHeads, lane = threadIdx.x & 63;
+  constexpr int PER = 2 * ROW_UNITS / kSliceUnits;  // workgroups per eight heads
+  const int g0 = blockIdx.x / PER * kSparseHeads, part = blockIdx.x % PER, lane = threadIdx.x & 63;
   bool moves = false;
   if (lane < kSparseHeads && g0 + lane < G) {
     const int nk = rows_kept(n_keep[g0 + lane], capacity, keep_stride);
-    if (threadIdx.x < kSparseHeads) len[g0 + lane] = nk;
+    if (part == 0 && threadIdx.x < kSparseHeads) len[g0 + lane] = nk;
     moves = nk > 0 && keep_idx[(size_t)(g0 + lane) * keep_stride + nk - 1] != nk - 1;
   }
   for (unsigned long long left = __ballot(moves); left; left &= left - 1) {  // (every wave has the same)
     const int g = g0 + __builtin_ctzll(left), nk = rows_kept(n_keep[g], capacity, keep_stride);
-    for (int part = 0; part < 2 * ROW_UNITS / kSliceUnits; ++part)
-      move_slice<ROW_UNITS>(g, part, nk, capacity, K, V, S, P, capacity, keep_idx + (size_t)g * keep_stride, nullptr,
-                            nullptr, 0);
+    move_slice<ROW_UNITS>(g, part, nk, capacity, K, V, S, P, capacity, keep_idx + (size_t)g * keep_stride, nullptr,
+                          nullptr, 0);
   }
 }
 
@@ -372,7 +373,7 @@ void launch_compact(const a2sf_cache& c, const int32_t* keep_idx, int keep_strid
 #define A2SF_COMPACT(RU)                                                                        \
   do {                                                                                          \
     if (mostly_done)                                                                            \
-      hipLaunchKernelGGL(compact_sparse_kernel<RU>, dim3((unsigned)(c.G + kSparseHeads - 1) / kSparseHeads), \
+      hipLaunchKernelGGL(compact_sparse_kernel<RU>, dim3((unsigned)(c.G + kSparseHeads - 1) / kSparseHeads * (2 * RU / kSliceUnits)), \
                          dim3(kThreads), 0, st, (uint4*)c.k, (uint4*)c.v, c.scores, c.pos, c.len, c.G,      \
                          c.capacity, keep_idx, keep_stride, n_keep);                            \
     else                                                                                        \

@@ -289,7 +289,7 @@ def test_launch_order_covers_every_block(dtype, d, G, n):
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
 def test_stable_steps_of_many_heads(dtype, d):
     """Stable steps whose kernel shifts the rows itself, then steps that evict several tokens at once, where
-    one compaction workgroup per head moves all slices of the rows."""
+    a compaction workgroup moves one slice of the rows of eight heads in turn."""
     w = variant(1 if dtype == "bf16" else 0, heads=4097, d=d, dtype=dtype, n=70, T=5, select=40, recent=25, name="many heads")
     ls = parity.LockStep(parity.Problem(w, sample=[0, 1, 2048, 4096]), 0.6)
     ls.prefill()
@@ -332,3 +332,50 @@ def test_selection_of_clustered_scores(L):
     for g in range(G):
         want = orc.select_keep(scores[g].astype(np.float64), np.arange(L), select, recent)
         assert np.array_equal(keep[g].cpu().numpy(), np.sort(want)), g
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("B", [3, 64, 130, 255, 400])
+def test_small_steps_with_gaps_and_lowered_budgets(dtype, d, B):
+    """Steps in registers whose newest positions have gaps (the protected ones are found by rank), then a budget that is
+    lowered to a quarter, a half, the protected part alone and one token; equal scores across the cut."""
+    if dtype == "f32" and d == 128 and B > 255:
+        B = 250
+    G = 4
+    torch_dtype = torch.bfloat16 if dtype == "bf16" else torch.float32
+    code = a2sf.A2SF_BF16 if dtype == "bf16" else a2sf.A2SF_F32
+    for mode in (a2sf.A2SF_EVICT_FAST, a2sf.A2SF_EVICT_STABLE):
+        gen = torch.Generator(device="cuda").manual_seed(B + d)
+        rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(torch_dtype)
+        cache = a2sf.Cache(G, B + 1, d, torch_dtype)
+        cache.k.copy_(rnd(*cache.k.shape)), cache.v.copy_(rnd(*cache.v.shape))
+        cache.scores.copy_(torch.rand(G, B + 1, generator=gen, device="cuda"))
+        cache.scores[1] = 0.5        # tokens without weight in this step stay tied
+        cache.k[1] = cache.k[1, :1]
+        t = 5 * B + 7
+        pos = np.stack([np.sort(np.random.default_rng(B + g).permutation(t - 1)[:B]) for g in range(G)]).astype(np.int32)
+        pos[3] = np.arange(t - B, t)  # no gaps, but steps that skip positions
+        cache.pos[:, :B] = torch.as_tensor(pos, device="cuda")
+        cache.len.fill_(B)
+        oc = [orc.HeadCache(*(parity.to_f64(x[g, :B]) for x in (cache.k, cache.v, cache.scores)), pos[g].astype(np.int64)) for g in range(G)]
+        ws = torch.full((a2sf.a2sf_workspace_bytes(G, 0, B + 1, d, code, B, 0),), 255, dtype=torch.uint8, device="cuda")
+        r = B // 3
+        for select, recent in ((B - r, r), (B - r, r), (B - r - B // 4, r), (max(1, B // 4), B // 4), (0, max(1, B // 5)), (1, 0)):
+            q, kn, vn = rnd(G, d), rnd(G, d), rnd(G, d)
+            o = torch.full((G, d), float("nan"), dtype=torch_dtype, device="cuda")
+            a2sf.a2sf_decode_step(q, kn, vn, t, cache, 0.7, select, recent, o, mode=mode, workspace=ws)
+            torch.cuda.synchronize()
+            for g in range(G):
+                kept = int(cache.len[g])
+                got = cache.pos[g, :kept].cpu().numpy().astype(np.int64)
+                o_ref, _ = orc.attend_and_update(oc[g], parity.to_f64(q[g]), parity.to_f64(kn[g]), parity.to_f64(vn[g]), t, float(np.float32(0.7)))
+                orc.evict(oc[g], select, recent, forced_retained=got.tolist(), margin=parity.MARGIN)
+                assert kept == len(oc[g].pos) and np.abs(parity.to_f64(o[g]) - o_ref).max() <= parity.O_TOL[dtype]
+                order = np.argsort(got, kind="stable")
+                if mode == a2sf.A2SF_EVICT_STABLE:
+                    assert np.array_equal(order, np.arange(kept))
+                c = oc[g].sorted_by_pos()
+                assert np.array_equal(got[order], c.pos)
+                assert np.array_equal(parity.to_f64(cache.k[g, :kept])[order], c.K) and np.array_equal(parity.to_f64(cache.v[g, :kept])[order], c.V)
+                parity.compare_scores(cache.scores[g, :kept].cpu().numpy()[order], c.S, f"head {g}")
+            t += 3

@@ -47,12 +47,14 @@ __device__ __forceinline__ long long xcd_contiguous_id(long long total) {
 }
 // The order of the (head, block) items: that of ordered_item, or, for launches of up to RESIDENT blocks, head
 // after head.  kOneRound: launches that are resident at once, where nothing is left to be dealt out and
-// ordered_item costs half a microsecond.
-constexpr long long kOneRound = 1ll << 62;
+// ordered_item costs half a microsecond.  kOnePerUnit, kTwoPerUnit: up to one, two workgroups per compute unit (attention: 100
+// heads x 130, 200 blocks, 8.3 us and 10.4 in the order of ordered_item, 40 x 1000, 320 blocks, 26 and 23; scores: 45 x 1400,
+// alpha = 0.9, 42 and 46).  Nor is there an order in one block per head.
+constexpr long long kOneRound = 1ll << 62, kOnePerUnit = 256, kTwoPerUnit = 512;
 template <long long RESIDENT>
 __device__ __forceinline__ bool launch_item(int G, int nb, int& head, int& rank) {
   const long long total = (long long)G * nb;
-  if (total > RESIDENT) return ordered_item(G, nb, head, rank);
+  if (total > RESIDENT && nb > 1) return ordered_item(G, nb, head, rank);
   const long long id = xcd_contiguous_id(total);
   head = (int)(id / nb);
   rank = (int)(id % nb);
@@ -61,7 +63,7 @@ __device__ __forceinline__ bool launch_item(int G, int nb, int& head, int& rank)
 template <long long RESIDENT>
 unsigned launch_grid(int G, int nb) {
   const long long total = (long long)G * nb;
-  return total > RESIDENT ? ordered_grid(G, nb) : (unsigned)((total + 7) / 8 * 8);
+  return total > RESIDENT && nb > 1 ? ordered_grid(G, nb) : (unsigned)((total + 7) / 8 * 8);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -183,7 +185,9 @@ constexpr float kMoveMaximumAt = 1073741824.f, kMoveMaximumWithO = 256.f;
 // KS = 2 (with outputs): eight waves, the second four take the odd tiles of the same 128 rows and the
 // two halves are merged at the end -- for launches that do not fill the chip, where the chain of
 // tiles of a head's last rows is what the call waits for.
-template <int D, bool WITH_O, int KS>
+// PIPED = false (with outputs): a tile's logits, probabilities and products one after the other, no work for a tile that
+// is not there -- for rows of a few tiles, where the start of the pipeline is most of the time.
+template <int D, bool WITH_O, int KS, bool PIPED>
 __global__ __launch_bounds__(kThreads * KS, !WITH_O ? 4 : 2 / KS) void attn_fwd_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, float* __restrict__ LSE2, AttnRect rc, int G, int nqb, float scale_log2e) {
@@ -192,12 +196,12 @@ __global__ __launch_bounds__(kThreads * KS, !WITH_O ? 4 : 2 / KS) void attn_fwd_
   // two stages of K tiles, two of V tiles (none without outputs; a deeper ring was measured for
   // that pass and is slower: it costs occupancy)
   // (with outputs: and 4 KB that take the loads of a step that has nothing to fetch)
-  constexpr int kLds = WITH_O ? 4 * kTB + 4096 : 2 * kTB;
+  constexpr int kLds = !WITH_O ? 2 * kTB : 4 * kTB + (PIPED ? 4096 : 0);
   __shared__ __attribute__((aligned(1024))) char smem[KS * kLds];
   __shared__ float m_other[KS > 1 ? BM : 1], l_other[KS > 1 ? BM : 1];
 
   int g, rank;
-  if (!launch_item<KS == 1 ? 0 : kOneRound>(G, nqb, g, rank)) return;
+  if (!launch_item<KS == 1 ? kOnePerUnit : kOneRound>(G, nqb, g, rank)) return;
   // the launch covers the nqb row blocks from the one that holds rc.first_row on
   const int qb = rc.first_row / BM + nqb - 1 - rank;
 
@@ -270,7 +274,7 @@ __global__ __launch_bounds__(kThreads * KS, !WITH_O ? 4 : 2 / KS) void attn_fwd_
   if (part < ntiles) fetch_k(part, lds);
   if (WITH_O) {
     if (part < ntiles) fetch_v(part, vst);
-    if (part + KS < ntiles) fetch_k(part + KS, lds + kTB);
+    if (PIPED && part + KS < ntiles) fetch_k(part + KS, lds + kTB);
   }
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qf[kk].x));  // waited for here, not in the loop
@@ -322,18 +326,21 @@ __global__ __launch_bounds__(kThreads * KS, !WITH_O ? 4 : 2 / KS) void attn_fwd_
     return corr;
   };
 
+  const auto keep_reads_ahead = [] {  // in `logits`: kPrefetch reads up front, then one new read per matrix op
+    __builtin_amdgcn_sched_group_barrier(0x100, kPrefetch, 0);
+#pragma unroll
+    for (int i = 0; i < 2 * KK; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (i + kPrefetch < 2 * KK) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+  };
+
   if constexpr (!WITH_O) {
     auto tile_step = [&](int t, const lds_char* kt) {
       if (t >= nt_wave) return;
       f32x16 s[2];
       logits(kt, s, [](int) {});
-      // keep that order: kPrefetch reads up front, then one new read per matrix op
-      __builtin_amdgcn_sched_group_barrier(0x100, kPrefetch, 0);
-#pragma unroll
-      for (int i = 0; i < 2 * KK; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (i + kPrefetch < 2 * KK) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
+      keep_reads_ahead();
       mask(t, s);
       float rs = 0.f;
 #pragma unroll
@@ -369,101 +376,7 @@ __global__ __launch_bounds__(kThreads * KS, !WITH_O ? 4 : 2 / KS) void attn_fwd_
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
-    f32x16 sa[2], sb[2];
-    logits(lds, sa, [](int) {});
-    // every wave is done with K(0) before K(2) takes its place
-    wait_vm_barrier<0>();
-
-    // probabilities of tile t (logits in s) beside the logits of tile t + 1 (into s_next; past the
-    // wave's last tile they are formed from whatever the stage holds and not used), then O += V^T P
-    //
-    // The loads of a tile are issued one by one between the first matrix ops: a load of 1 KB keeps
-    // the compute unit's one address path busy for 16 cycles, and issued at once after the barrier the
-    // eight loads of all waves held every wave up for 700 of the 2800 cycles of a step.  So that the
-    // instruction stream is the same in every step, a step without a whole tile to fetch (none left;
-    // or a ragged or two-source tile, which was fetched before) sends its loads to the spare 4 KB.
-    // (all lanes then read the head's first 16 bytes of Q, which every head has.)
-    struct Fetch {
-      const char* from;
-      uint32_t to, stride, lanes;  // lanes: mask of the per-lane offsets
-    };
-    const uint32_t spare = (uint32_t)(size_t)(lds + 4 * kTB) + wave * 1024;
-    const auto whole_k = [&](int t, lds_char* buf) -> Fetch {
-      const uint32_t to = (uint32_t)(size_t)buf + wave * 1024;
-      if (t < ntiles) {
-        if (K2g && (t + 1) * kTile > off) {
-          if (t * kTile >= off && (t + 1) * kTile <= nk)
-            return {reinterpret_cast<const char*>(K2g + (size_t)(t * kTile - off) * D), to, 4096u, ~0u};
-          dma_tile2<D, false>(Kg, K2g, off, t * kTile, nk, buf);
-        } else if ((t + 1) * kTile <= nk) {
-          return {reinterpret_cast<const char*>(Kg + (size_t)t * kTile * D), to, 4096u, ~0u};
-        } else {
-          dma_tile<D, false>(Kg, t * kTile, nk, buf);
-        }
-      }
-      return {reinterpret_cast<const char*>(Qg), spare, 0u, 0u};
-    };
-    const auto whole_v = [&](int t, lds_char* buf) -> Fetch {
-      const uint32_t to = (uint32_t)(size_t)buf + wave * 1024;
-      if (t < ntiles) {
-        if (K2g && (t + 1) * kTile > off) {
-          if (t * kTile >= off && (t + 1) * kTile <= nk)
-            return {reinterpret_cast<const char*>(V2g + (size_t)(t * kTile - off) * D), to, 4096u, ~0u};
-          dma_tile2<D, true>(Vg, V2g, off, t * kTile, nk, buf);
-        } else if ((t + 1) * kTile <= nk) {
-          return {reinterpret_cast<const char*>(Vg + (size_t)t * kTile * D), to, 4096u, ~0u};
-        } else {
-          dma_tile<D, true>(Vg, t * kTile, nk, buf);
-        }
-      }
-      return {reinterpret_cast<const char*>(Qg), spare, 0u, 0u};
-    };
-    auto tile_step = [&](int t, const lds_char* kt_next, const lds_char* vt, f32x16 (&s)[2], f32x16 (&s_next)[2],
-                         const Fetch& fk, const Fetch& fv) {
-      const auto piece = [&](int i) {
-        if (i < NL) dma16(fk.from, (uint32_t)k_loff[i] & fk.lanes, fk.to + i * fk.stride);
-        else if (i < 2 * NL) dma16(fv.from, (uint32_t)v_loff[i - NL] & fv.lanes, fv.to + (i - NL) * fv.stride);
-      };
-      mask(t, s);
-      float rs = 0.f, e0 = 0.f, e1 = 0.f;
-      uint32_t pf[16];  // bf16 probabilities 2j, 2j + 1 (of the lane's 32, key block by key block)
-      const auto finish = [&](int j) {  // the pair whose exponentials were requested last
-        rs += e0;
-        rs += e1;
-        pf[j] = pack_bf16(e0, e1);
-      };
-      // between two matrix ops: a load, and the lane's share of the probabilities -- no result is used
-      // right behind the instruction that forms it
-      logits(kt_next, s_next, [&](int i) {
-        if (i < 2 * NL) piece(i);
-        constexpr int PAIRS = 16 / (2 * KK);
-#pragma unroll
-        for (int jj = 0; jj < PAIRS; ++jj) {
-          const int j = PAIRS * i + jj;
-          const float x0 = fmaf(s[j >> 3][(2 * j) & 15], scale_log2e, -m), x1 = fmaf(s[j >> 3][(2 * j + 1) & 15], scale_log2e, -m);
-          if (j > 0) finish(j - 1);
-          e0 = fast_exp2(x0);
-          e1 = fast_exp2(x1);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      });
-      finish(15);
-      if (__any(!(rs < kMoveMaximumWithO))) {
-        const float corr = move_maximum(s);
-        lsum *= corr;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) oacc[db][i] *= corr;
-        rs = 0.f;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          e0 = fast_exp2(fmaf(s[j >> 3][(2 * j) & 15], scale_log2e, -m));
-          e1 = fast_exp2(fmaf(s[j >> 3][(2 * j + 1) & 15], scale_log2e, -m));
-          finish(j);
-        }
-      }
-      lsum += rs;
+    const auto add_values = [&](const lds_char* vt, const uint32_t (&pf)[16]) {  // O += V^T P
       constexpr int NF = DB * 4;  // fragment i = (kb, tt, db), db fastest
       uint2 lo[NF], hi[NF];
       auto vread = [&](int i, uint2& a, uint2& b) {
@@ -487,27 +400,172 @@ __global__ __launch_bounds__(kThreads * KS, !WITH_O ? 4 : 2 / KS) void attn_fwd_
         if (i + kPrefetch < NF) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
       }
     };
-
-    for (int u0 = 0; u0 < steps_wave; u0 += 2) {
+    if constexpr (!PIPED) {
+      for (int t0 = 0; t0 < ntiles; t0 += 2) {
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {  // stage u % 2: LDS offsets are immediates
-        if (u0 + b >= steps_wave) break;
-        const int t = part + KS * (u0 + b);
-        // free since the last barrier: the stages of K(u), whose logits are formed, and of V(u-1)
-        const Fetch fk = whole_k(t + 2 * KS, lds + b * kTB), fv = whole_v(t + KS, vst + (1 - b) * kTB);
-        if (b == 0) tile_step(t, lds + kTB, vst, sa, sb, fk, fv);
-        else tile_step(t, lds, vst + kTB, sb, sa, fk, fv);
-        wait_vm_barrier<0>();  // K(u+2) and V(u+1) for every wave of the workgroup
+        for (int b = 0; b < 2; ++b) {  // stage t % 2: LDS offsets are immediates
+          const int t = t0 + b;
+          if (t >= ntiles) break;
+          // the stages of tile t - 1 are free: every wave passed the barrier that ended its step
+          if (t + 1 < ntiles) {
+            fetch_k(t + 1, lds + (1 - b) * kTB);
+            fetch_v(t + 1, vst + (1 - b) * kTB);
+          }
+          if (t < nt_wave) {
+            f32x16 s[2];
+            logits(lds + b * kTB, s, [](int) {});
+            keep_reads_ahead();
+            mask(t, s);
+            float mx = s[0][0];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+              for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kb][i]);
+            mx = fmaxf(across_rows(mx, OpMax(), false, true) * scale_log2e, -1e30f);
+            if (__any(mx > m + 8.f)) {  // (kMoveMaximumWithO is 2^8)
+              const float m_new = fmaxf(m, mx), corr = fast_exp2(m - m_new);
+              lsum *= corr;
+#pragma unroll
+              for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) oacc[db][i] *= corr;
+              m = m_new;
+            }
+            uint32_t pf[16];
+            float rs = 0.f;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+              const float e0 = fast_exp2(fmaf(s[j >> 3][(2 * j) & 15], scale_log2e, -m));
+              const float e1 = fast_exp2(fmaf(s[j >> 3][(2 * j + 1) & 15], scale_log2e, -m));
+              rs += e0;
+              rs += e1;
+              pf[j] = pack_bf16(e0, e1);
+            }
+            lsum += rs;
+            add_values(vst + b * kTB, pf);
+          }
+          wait_vm_barrier<0>();  // tile t + 1 for every wave of the workgroup
+        }
+      }
+    } else {
+      f32x16 sa[2], sb[2];
+      logits(lds, sa, [](int) {});
+      // every wave is done with K(0) before K(2) takes its place
+      wait_vm_barrier<0>();
+
+      // probabilities of tile t (logits in s) beside the logits of tile t + 1 (into s_next; past the
+      // wave's last tile they are formed from whatever the stage holds and not used), then O += V^T P
+      //
+      // The loads of a tile are issued one by one between the first matrix ops: a load of 1 KB keeps
+      // the compute unit's one address path busy for 16 cycles, and issued at once after the barrier the
+      // eight loads of all waves held every wave up for 700 of the 2800 cycles of a step.  So that the
+      // instruction stream is the same in every step, a step without a whole tile to fetch (none left;
+      // or a ragged or two-source tile, which was fetched before) sends its loads to the spare 4 KB.
+      // (all lanes then read the head's first 16 bytes of Q, which every head has.)
+      struct Fetch {
+        const char* from;
+        uint32_t to, stride, lanes;  // lanes: mask of the per-lane offsets
+      };
+      const uint32_t spare = (uint32_t)(size_t)(lds + 4 * kTB) + wave * 1024;
+      const auto whole_k = [&](int t, lds_char* buf) -> Fetch {
+        const uint32_t to = (uint32_t)(size_t)buf + wave * 1024;
+        if (t < ntiles) {
+          if (K2g && (t + 1) * kTile > off) {
+            if (t * kTile >= off && (t + 1) * kTile <= nk)
+              return {reinterpret_cast<const char*>(K2g + (size_t)(t * kTile - off) * D), to, 4096u, ~0u};
+            dma_tile2<D, false>(Kg, K2g, off, t * kTile, nk, buf);
+          } else if ((t + 1) * kTile <= nk) {
+            return {reinterpret_cast<const char*>(Kg + (size_t)t * kTile * D), to, 4096u, ~0u};
+          } else {
+            dma_tile<D, false>(Kg, t * kTile, nk, buf);
+          }
+        }
+        return {reinterpret_cast<const char*>(Qg), spare, 0u, 0u};
+      };
+      const auto whole_v = [&](int t, lds_char* buf) -> Fetch {
+        const uint32_t to = (uint32_t)(size_t)buf + wave * 1024;
+        if (t < ntiles) {
+          if (K2g && (t + 1) * kTile > off) {
+            if (t * kTile >= off && (t + 1) * kTile <= nk)
+              return {reinterpret_cast<const char*>(V2g + (size_t)(t * kTile - off) * D), to, 4096u, ~0u};
+            dma_tile2<D, true>(Vg, V2g, off, t * kTile, nk, buf);
+          } else if ((t + 1) * kTile <= nk) {
+            return {reinterpret_cast<const char*>(Vg + (size_t)t * kTile * D), to, 4096u, ~0u};
+          } else {
+            dma_tile<D, true>(Vg, t * kTile, nk, buf);
+          }
+        }
+        return {reinterpret_cast<const char*>(Qg), spare, 0u, 0u};
+      };
+      auto tile_step = [&](int t, const lds_char* kt_next, const lds_char* vt, f32x16 (&s)[2], f32x16 (&s_next)[2],
+                           const Fetch& fk, const Fetch& fv) {
+        const auto piece = [&](int i) {
+          if (i < NL) dma16(fk.from, (uint32_t)k_loff[i] & fk.lanes, fk.to + i * fk.stride);
+          else if (i < 2 * NL) dma16(fv.from, (uint32_t)v_loff[i - NL] & fv.lanes, fv.to + (i - NL) * fv.stride);
+        };
+        mask(t, s);
+        float rs = 0.f, e0 = 0.f, e1 = 0.f;
+        uint32_t pf[16];  // bf16 probabilities 2j, 2j + 1 (of the lane's 32, key block by key block)
+        const auto finish = [&](int j) {  // the pair whose exponentials were requested last
+          rs += e0;
+          rs += e1;
+          pf[j] = pack_bf16(e0, e1);
+        };
+        // between two matrix ops: a load, and the lane's share of the probabilities -- no result is used
+        // right behind the instruction that forms it
+        logits(kt_next, s_next, [&](int i) {
+          if (i < 2 * NL) piece(i);
+          constexpr int PAIRS = 16 / (2 * KK);
+#pragma unroll
+          for (int jj = 0; jj < PAIRS; ++jj) {
+            const int j = PAIRS * i + jj;
+            const float x0 = fmaf(s[j >> 3][(2 * j) & 15], scale_log2e, -m), x1 = fmaf(s[j >> 3][(2 * j + 1) & 15], scale_log2e, -m);
+            if (j > 0) finish(j - 1);
+            e0 = fast_exp2(x0);
+            e1 = fast_exp2(x1);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        finish(15);
+        if (__any(!(rs < kMoveMaximumWithO))) {
+          const float corr = move_maximum(s);
+          lsum *= corr;
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) oacc[db][i] *= corr;
+          rs = 0.f;
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            e0 = fast_exp2(fmaf(s[j >> 3][(2 * j) & 15], scale_log2e, -m));
+            e1 = fast_exp2(fmaf(s[j >> 3][(2 * j + 1) & 15], scale_log2e, -m));
+            finish(j);
+          }
+        }
+        lsum += rs;
+        add_values(vt, pf);
+      };
+
+      for (int u0 = 0; u0 < steps_wave; u0 += 2) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {  // stage u % 2: LDS offsets are immediates
+          if (u0 + b >= steps_wave) break;
+          const int t = part + KS * (u0 + b);
+          // free since the last barrier: the stages of K(u), whose logits are formed, and of V(u-1)
+          const Fetch fk = whole_k(t + 2 * KS, lds + b * kTB), fv = whole_v(t + KS, vst + (1 - b) * kTB);
+          if (b == 0) tile_step(t, lds + kTB, vst, sa, sb, fk, fv);
+          else tile_step(t, lds, vst + kTB, sb, sa, fk, fv);
+          wait_vm_barrier<0>();  // K(u+2) and V(u+1) for every wave of the workgroup
+        }
+      }
+      // tiles that only the workgroup's later rows see: the wave still fetches its quarter
+      for (int u = steps_wave; u < steps; ++u) {
+        const int t = part + KS * u;
+        if (t + 2 * KS < ntiles) fetch_k(t + 2 * KS, lds + (u & 1) * kTB);
+        if (t + KS < ntiles) fetch_v(t + KS, vst + (1 - (u & 1)) * kTB);
+        wait_vm_barrier<0>();
       }
     }
-    // tiles that only the workgroup's later rows see: the wave still fetches its quarter
-    for (int u = steps_wave; u < steps; ++u) {
-      const int t = part + KS * u;
-      if (t + 2 * KS < ntiles) fetch_k(t + 2 * KS, lds + (u & 1) * kTB);
-      if (t + KS < ntiles) fetch_v(t + KS, vst + (1 - (u & 1)) * kTB);
-      wait_vm_barrier<0>();
-    }
-
     // ---- epilogue.  The accumulator layout gives a lane 4 consecutive d of one row at a time:
     // written straight to memory that is 32 rows x 16 bytes per instruction.  Instead each wave
     // transposes its 32 x D output block through its own strip of LDS (free after the
@@ -580,8 +638,7 @@ __global__ __launch_bounds__(kThreads * KS, !WITH_O ? 4 : 2 / KS) void attn_fwd_
 constexpr int kX2Rows = 256;             // query rows per workgroup and block
 constexpr int kX2RingBytes = 4 * 32768;  // four stages of one K tile + one V tile
 constexpr int kX2LdsBytes = kX2RingBytes + 4 * 8192;  // + one 8 KB output strip per wave
-constexpr int kX2MinRows = 2048;
-constexpr int kX2MinRowsPersistent = 512;
+constexpr int kX2MinRows = 512;
 constexpr int kX2Slots = 32;             // persistent launch: workgroups per XCD (one per CU)
 
 // rounds == 1: one workgroup per (head, 256-row block), ids mapped as in the other kernels.
@@ -751,8 +808,15 @@ __global__ __launch_bounds__(kThreads, 1) void attn_fwd128x2r_kernel(
 // itself, the launch lasts as long as a head's last rows and half the chain is nearly half the time (one
 // head x 2000, whole call: 65 -> 43 us; 32 x 1024: 25.0 -> 22.7 in the kernel).  Beyond that, two workgroups
 // of four waves per unit share it better (kernel, KS = 1 / 2: 40 heads x 1024 32.1 / 35.4 us, 64 x 1000 34.9 / 42.0,
-// 300 x 200 22.4 / 32.3).
+// 300 x 200 22.4 / 32.3).  Nor for short chains, where the start of the pipeline and the merge cost more (kernel, in turn /
+// split: 8 heads x 130 8.1 / 10.4, 8 x 512 13.9 / 13.9, 8 x 900 19.8 / 18.0; d = 64 8 x 130 6.0 / 6.5, 8 x 900 15.6 / 13.4).
 constexpr unsigned kSplitKeysMaxBlocks = 256;
+constexpr int kSplitKeysMinTiles = 10;
+// With d = 128 the pipelined form pays from about 20 tiles on (kernel, in turn / pipelined: 1500 heads x 130 47.8 / 54.8, 300 x
+// 900 103 / 104, 96 x 1777 94.3 / 91.9, 600 x 2500 1092 / 1045); with d = 64, where fewer registers let four workgroups
+// onto a compute unit, only for the longest (1500 x 130 27.4 / 38.1, 1500 x 900 258 / 325, 96 x 1777 57.3 / 60.1, 40 x 6000 238 /
+// 238, 40 x 9000 533 / 513).
+template <int D> constexpr int kPipedMinTiles = D == 128 ? 20 : 128;
 template <int D>
 void launch_fwd_rect(const void* q, const void* k, const void* v, int G, const AttnRect& rc, void* o,
                      float* lse2, hipStream_t st) {
@@ -760,12 +824,15 @@ void launch_fwd_rect(const void* q, const void* k, const void* v, int G, const A
   const int GQ = G * rc.kv_group;  // query heads
   constexpr int bm = kWaves * 32;
   const int nqb = (rc.m + bm - 1) / bm - (o ? 0 : rc.first_row / bm);  // row blocks to compute
-#define A2SF_FWD(WITH_O, KS)                                                                          \
-  hipLaunchKernelGGL((attn_fwd_kernel<D, WITH_O, KS>), dim3(launch_grid<KS == 1 ? 0 : kOneRound>(GQ, nqb)), dim3(kThreads * KS), 0, st, (const bf16_t*)q, \
-                     (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, lse2, rc, GQ, nqb, scale_log2e)
-  if (!o) A2SF_FWD(false, 1);
-  else if ((long long)GQ * nqb <= kSplitKeysMaxBlocks) A2SF_FWD(true, 2);
-  else A2SF_FWD(true, 1);
+  const int tiles = ((rc.off_heads ? rc.kv_stride : rc.m) + kTile - 1) / kTile;  // of the newest row, at most
+#define A2SF_FWD(WITH_O, KS, PIPED)                                                                   \
+  hipLaunchKernelGGL((attn_fwd_kernel<D, WITH_O, KS, PIPED>), dim3(launch_grid<KS == 1 ? kOnePerUnit : kOneRound>(GQ, nqb)), \
+                     dim3(kThreads * KS), 0, st, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, lse2, rc, \
+                     GQ, nqb, scale_log2e)
+  if (!o) A2SF_FWD(false, 1, false);
+  else if ((long long)GQ * nqb <= kSplitKeysMaxBlocks && tiles >= kSplitKeysMinTiles) A2SF_FWD(true, 2, true);
+  else if (tiles >= kPipedMinTiles<D>) A2SF_FWD(true, 1, true);
+  else A2SF_FWD(true, 1, false);
 #undef A2SF_FWD
 }
 
@@ -783,13 +850,12 @@ void launch_fwd(const void* q, const void* k, const void* v, int G_kv, int n, vo
     kv_magic = (unsigned)((1ull << 32) / (unsigned)kv_group) + 1u;
   }
   if constexpr (D == 128) {
-    // Two query blocks per wave pay off once a workgroup streams enough key tiles to amortise
-    // the start and end of a row block: from n = 2048 with one workgroup per block, from
-    // n = 512 in the persistent form, which overlaps them with the neighbouring blocks.
+    // Two query blocks per wave pay off from n = 512 on in the persistent form, which overlaps the start and the
+    // end of a row block with its neighbours.
     // Few row blocks: the split keys of attn_fwd_kernel<.., 2> shorten the longest chain of tiles
     // (8 heads x 4096, whole call: 122.6 us here, 73.5 there).
     const bool few = (long long)G * ((n + kWaves * 32 - 1) / (kWaves * 32)) <= kSplitKeysMaxBlocks;
-    if (o && !few && n >= kX2MinRowsPersistent && (long long)G * n < (1ll << 31)) {
+    if (o && !few && n >= kX2MinRows && (long long)G * n < (1ll << 31)) {
       const int nqb2 = (n + kX2Rows - 1) / kX2Rows;
       const long long items = (long long)G * nqb2;
       const int chunk = 2 * 8 * kX2Slots;  // items of two rounds of the persistent launch
@@ -810,7 +876,7 @@ void launch_fwd(const void* q, const void* k, const void* v, int G_kv, int n, vo
         if (items > main_ids) launch(main_ids, (int)(items - main_ids), 1);
         return;
       }
-      if (n >= kX2MinRows || persistent) {
+      if (n >= 2048 || persistent) {
         const unsigned nqm = (unsigned)((1ull << 32) / (unsigned)nqb2) + 1u;  // exact below 2^32 / nqb2
         const int all = (G / 2) * nqb2, odd = (G % 2) * nqb2;
         auto launch = [&](int odd_blocks, int base, int pairs, int rounds) {
@@ -1046,40 +1112,37 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_tail_kernel(
 }
 
 // ---------------------------------------------------------------------------------------
-// col_scores for a long row window (alpha close to 1) and for grouped-query heads: the
-// streaming form of col_scores_tail_kernel.  A workgroup owns 256 key columns (a wave two blocks of 32
-// keys, their K fragments resident in registers for the whole kernel) and walks down the rows that
+// col_scores for a long row window (alpha close to 1), for grouped-query heads and for few keys: the
+// streaming form of col_scores_tail_kernel.  A workgroup owns 128 key columns (a wave KB = 1 block of 32
+// keys, or 256 columns and KB = 2, the K fragments resident in registers for the whole kernel) and walks down the rows that
 // see them, one query head of the group after the other; Q tiles of 64 rows arrive by direct
-// global-to-LDS loads in a ring of four stages, three tiles ahead of the one being used.  One barrier
+// global-to-LDS loads in a ring, one tile (KB = 2: three tiles) ahead of the one being used.  One barrier
 // per tile publishes the tile that has landed and frees the stage of the previous one for the next fetch.
+// One block and two stages leave room for four workgroups per compute unit, which hide the loads and the vector work (the
+// exponentials) better than two blocks that share a Q fragment and a ring of four (us, alpha = 1, KB = 2 / 1: 300 heads x 260
+// 25 / 16, 300 x 1000 82 / 66, 96 x 1777 63 / 57, 300 x 4000 796 / 774; d = 64, 96 x 1777 52 / 42).  But they read the rows twice as
+// often, and from about 8000 rows on a die's heads do not stay in its L2 (64 x 9000 749 / 783; d = 64 never minds).
 // Geometry as in AttnRect (n = rc.m rows, keys 0 .. off + n - 1, row i sees keys <= off + i).
 // accumulate: the column sums are added to decay * S[] (a chunk: the cached tokens' older scores
 // decayed by alpha^m) instead of replacing it.
-constexpr int kStreamStages = 4;
-// Workgroups up to which heads are launched one after the other: two per compute unit (45 heads x 1400 rows,
-// alpha = 0.9: 42 us, 46 in the order of ordered_item; 96 x 1777, d = 64, alpha = 1: 63.7 and 49.0).
-constexpr long long kStreamResident = 512;
-
 // RS = 2 (without a tolerance): eight waves, the second four take the odd tiles for the same keys, each
 // half with a ring of its own; their sums meet at the end.  For launches whose workgroups are all
 // resident at once, which last as long as the column block with the most rows.
-// KB: 32-key blocks per wave.  Two share every Q fragment read from LDS; with d = 64, where the matrix work per
-// logit is half, more waves with one block each hide the vector work better (96 x 1777, alpha = 1: 74 -> 63 us).
 template <int D, int KB, int RS>
-__global__ __launch_bounds__(kThreads * RS, (D == 64 && KB == 1 ? 4 : 2) / RS) void col_scores_stream_kernel(
+__global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_scores_stream_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const float* __restrict__ LSE2,
     float* __restrict__ S, AttnRect rc, int s_stride, bool accumulate, float decay, int G, int ncb, int first_row,
     float log2_alpha, const float* __restrict__ alpha_heads, float scale_log2e, float tol) {
-  constexpr int KK = D / 16, BC = kWaves * 32 * KB, kTB = kTileBytesOf<D>;
+  constexpr int KK = D / 16, BC = kWaves * 32 * KB, kTB = kTileBytesOf<D>, kStages = KB == 1 ? 2 : 4;
   constexpr int NL = kLoadsPerWave<D>, kLoads = NL + 1;  // loads of a wave per tile
   // Q tiles, then per wave and stage the 64 log-sum-exp values of the tile's rows
-  constexpr int kLds = kStreamStages * kTB + kWaves * kStreamStages * 256;
+  constexpr int kLds = kStages * kTB + kWaves * kStages * 256;
   __shared__ __attribute__((aligned(1024))) char smem[RS * kLds];
   __shared__ int wave_lim[kWaves];
   __shared__ float other[RS > 1 ? BC : 1];
 
   int g, cb;  // column block 0 has the most rows
-  if (!launch_item<RS == 1 ? kStreamResident : kOneRound>(G, ncb, g, cb)) return;
+  if (!launch_item<RS == 1 ? kTwoPerUnit : kOneRound>(G, ncb, g, cb)) return;
   const int n = rc.m;
   const int off = rc.off_heads ? rc.off_heads[g] : 0;
   const int nk = off + n;  // keys of this head
@@ -1103,7 +1166,7 @@ __global__ __launch_bounds__(kThreads * RS, (D == 64 && KB == 1 ? 4 : 2) / RS) v
   // does not matter.
   const int t_last = (n + kTile - 1) / kTile - 1;
   int t_first = max(max(c0 - off, first_row), 0) / kTile;  // oldest tile any wave of the workgroup needs
-  lds_char* const lse_s = qs + kStreamStages * kTB + wave * (kStreamStages * 256);
+  lds_char* const lse_s = qs + kStages * kTB + wave * (kStages * 256);
   // tile f of the sequence is tile t_last - f % per_head of query head f / per_head; this half takes
   // the tiles part, part + RS, ...
   int per_head = t_last - t_first + 1;
@@ -1123,12 +1186,11 @@ __global__ __launch_bounds__(kThreads * RS, (D == 64 && KB == 1 ? 4 : 2) / RS) v
     if (row0 + kTile <= n) dma_full_tile<D>(Qg + head * D, row0, f_loff, qs + f_stage * kTB);
     else dma_tile<D, false>(Qg + head * D, row0, n, qs + f_stage * kTB);
     dma4(lse + head + row0, (uint32_t)(min(lane, n - 1 - row0) * 4), (uint32_t)(size_t)(lse_s + f_stage * 256));
-    f_stage = (f_stage + 1) % kStreamStages;
+    f_stage = (f_stage + 1) % kStages;
     f_i += RS;
   };
-  fetch();
-  fetch();
-  fetch();
+#pragma unroll
+  for (int i = 1; i < kStages; ++i) fetch();
 
   // K fragments (A operand): lane (key l32, half h) holds K[key][16kk + 8h .. +7]
   uint4 kf[KB][KK];
@@ -1156,12 +1218,12 @@ __global__ __launch_bounds__(kThreads * RS, (D == 64 && KB == 1 ? 4 : 2) / RS) v
   int lim = max(wc0 - off, first_row);   // rows before `lim` add nothing to this wave's keys
   int stage = 0, i_seq = part;
   const int steps = (rc.kv_group * per_head + RS - 1) / RS;
-  for (int u = 0; u < steps; ++u, stage = (stage + 1) % kStreamStages, i_seq += RS) {
+  for (int u = 0; u < steps; ++u, stage = (stage + 1) % kStages, i_seq += RS) {
     while (i_seq >= per_head) i_seq -= per_head;
     const int t = t_last - i_seq;
     const bool own = RS == 1 || u * RS + part < rc.kv_group * per_head;  // (the second half may be one tile short)
-    // this tile has landed: of this wave's fetches only those of the next two may still be under way
-    wait_vm_barrier<2 * kLoads>();
+    // this tile has landed: of this wave's fetches only those of the tiles behind it may still be under way
+    wait_vm_barrier<(kStages - 2) * kLoads>();
     fetch();  // into the stage of the previous tile, which every wave has left
     const int row0 = t * kTile;
     if (own && row0 + kTile - 1 >= lim) {  // some row of the tile counts for a key of this wave
@@ -1229,10 +1291,9 @@ __global__ __launch_bounds__(kThreads * RS, (D == 64 && KB == 1 ? 4 : 2) / RS) v
   wait_vm<0>();  // tiles fetched ahead of the last one used: let them land
   // sum over the 32 rows held by the lanes of one half, then over the two halves of the workgroup
 #pragma unroll
-  for (int b = 0; b < KB; ++b) {
+  for (int b = 0; b < KB; ++b)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[b][i] = group_sum<32>(acc[b][i]);
-  }
   const auto each_key = [&](auto f) {  // by the lanes that hold the sums
     if (l32 == 0) {
 #pragma unroll
@@ -1264,11 +1325,17 @@ inline int tail_key_split(int G, int keys_per_head) {
   return want < 1 ? 1 : (want > steps ? steps : want);
 }
 
-// Rows split over the two halves of a workgroup of col_scores_stream_kernel: as for the attention rows, while
-// the workgroups are all resident at once (whole calls, alpha = 1, four waves / eight: 4 K/V heads x 8 query heads x 1000
-// 240 / 170 us, 64 x 600 behind a cache 125 / 82; alpha = 0.9, 16 x 5000 218 / 174); beyond that the halves only
-// wait for each other (kernel, 96 x 1777 with d = 64: 73 / 78 us; 32 x 4 x 3001: 41 / 54).
+// Rows split over the two halves of a workgroup of col_scores_stream_kernel: while every workgroup has a compute unit to
+// itself and at least four tiles, or half a unit and sixteen (us, alpha = 1, four waves / eight: one head x 1000 20.8 /
+// 15.2, 40 x 640 15.5 / 12.9, 100 groups of 4 x 130 18.9 / 15.2, 40 x 1000, 320 blocks, 26.2 / 24.9, but 100 x 130, three
+// tiles, 8.3 / 9.4 and 100 x 400, 400 blocks, 15.1 / 19.9); beyond that the halves wait for each other (300 x 1000 66 / 113).
 constexpr unsigned kStreamSplitMaxBlocks = 256;
+constexpr int kStreamSplitMinTiles = 4;
+// KB = 2, d = 128: see above, and with two wide blocks per unit (8 x 9000, KB = 2 / 1: 223 / 173, 16 x 16000 588 / 617).
+constexpr int kStreamWideMinTiles = 128, kStreamWideMinBlocks = 1024;
+// Up to one block of keys the staging of col_scores_tail_kernel does not pay (1000 heads x 100, streamed / staged: 13.7 / 19.2 us,
+// d = 64 10.2 / 13.1; 200 keys: 25 / 28, 20.6 / 18.7).
+constexpr int kTailMinKeys = 128;
 
 // Column scores for any head size and geometry.
 template <int D>
@@ -1280,7 +1347,7 @@ void launch_cols(const void* q, const void* k, const float* lse2, int G, const A
   const int first = first_contributing_row(rc.m, alpha, &l2a);
   // one query head per K/V head and a row window of at most four tiles: staged once per head,
   // every key streamed once
-  if (rc.kv_group == 1 && rc.m - (first / kTile) * kTile <= kTailTiles * kTile) {
+  if (rc.kv_group == 1 && keys_per_head > kTailMinKeys && rc.m - (first / kTile) * kTile <= kTailTiles * kTile) {
     const int ks = tail_key_split(G, keys_per_head);
     hipLaunchKernelGGL((col_scores_tail_kernel<D>), dim3(G * ks), dim3(kThreads), 0, st, (const bf16_t*)q,
                        (const bf16_t*)k, lse2, scores, rc, s_stride, accumulate, decay, first, l2a,
@@ -1290,15 +1357,16 @@ void launch_cols(const void* q, const void* k, const float* lse2, int G, const A
 #define A2SF_STREAM(KB, RS)                                                                           \
   do {                                                                                                \
     const int ncb = (keys_per_head + kWaves * 32 * KB - 1) / (kWaves * 32 * KB);                      \
-    const unsigned grid = launch_grid<RS == 1 ? kStreamResident : kOneRound>(G, ncb);                 \
-    hipLaunchKernelGGL((col_scores_stream_kernel<D, KB, RS>), dim3(grid), dim3(kThreads * RS), 0, st, \
-                       (const bf16_t*)q, (const bf16_t*)k, lse2, scores, rc, s_stride, accumulate, decay, G, ncb, \
-                       first, l2a, alpha_heads, scale_log2e, tol);                                    \
+    hipLaunchKernelGGL((col_scores_stream_kernel<D, KB, RS>), dim3(launch_grid<RS == 1 ? kTwoPerUnit : kOneRound>(G, ncb)), \
+                       dim3(kThreads * RS), 0, st, (const bf16_t*)q, (const bf16_t*)k, lse2, scores, rc, s_stride, \
+                       accumulate, decay, G, ncb, first, l2a, alpha_heads, scale_log2e, tol);         \
   } while (0)
-  const long long blocks = (long long)G * ((keys_per_head + 255) / 256);
-  if (blocks <= kStreamSplitMaxBlocks && !(tol > 0.f)) A2SF_STREAM(2, 2);
-  else if constexpr (D == 64) A2SF_STREAM(1, 1);
-  else A2SF_STREAM(2, 1);
+  const int tiles = (rc.m + kTile - 1) / kTile - first / kTile;  // per query head, at most
+  const long long blocks = (long long)G * ((keys_per_head + kWaves * 32 - 1) / (kWaves * 32));
+  const int split_tiles = blocks <= kStreamSplitMaxBlocks ? kStreamSplitMinTiles : 4 * kStreamSplitMinTiles;
+  if (blocks <= 2 * kStreamSplitMaxBlocks && tiles * rc.kv_group >= split_tiles && !(tol > 0.f)) A2SF_STREAM(1, 2);
+  else if (D == 128 && tiles >= kStreamWideMinTiles && blocks >= kStreamWideMinBlocks) A2SF_STREAM((D == 128 ? 2 : 1), 1);
+  else A2SF_STREAM(1, 1);
 #undef A2SF_STREAM
 }
 

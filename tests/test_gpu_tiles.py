@@ -379,3 +379,43 @@ def test_small_steps_with_gaps_and_lowered_budgets(dtype, d, B):
                 assert np.array_equal(parity.to_f64(cache.k[g, :kept])[order], c.K) and np.array_equal(parity.to_f64(cache.v[g, :kept])[order], c.V)
                 parity.compare_scores(cache.scores[g, :kept].cpu().numpy()[order], c.S, f"head {g}")
             t += 3
+
+
+def plain_attention_rows(q, k, v, heads, rows):
+    """float64 outputs of some rows and, with alpha = 1, the scores of all keys, for q [G, n, d]."""
+    out, scores = {}, {}
+    for g in heads:
+        qd, kd, vd = (x[g].double() for x in (q, k, v))
+        n, d = qd.shape
+        s, o = torch.zeros(n, dtype=torch.float64, device="cuda"), torch.empty_like(qd)
+        for r0 in range(0, n, 1024):
+            z = qd[r0:r0 + 1024] @ kd.T / d ** 0.5
+            z.masked_fill_(torch.arange(n, device="cuda") > torch.arange(r0, min(n, r0 + 1024), device="cuda")[:, None], float("-inf"))
+            p = torch.softmax(z, dim=1)
+            s += p.sum(0)
+            o[r0:r0 + 1024] = p @ vd
+        out[g], scores[g] = o[rows], s
+    return out, scores
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,n", [(51, 576), (51, 577), (52, 577), (30, 1216), (30, 1217), (5, 8128), (5, 8129), (4, 8129), (2, 128), (2, 129),
+                                 (300, 128), (64, 193), (85, 300), (86, 300), (51, 1024), (52, 1025)])
+def test_bf16_forms_of_the_prompt_kernels(G, n, d):
+    """Both sides of the lines between the forms of the attention kernel (tiles in turn, pipelined, split keys: 256 row
+    blocks, 10 and 20 or 128 tiles) and of the score kernel (one or two key blocks per wave, split rows: 256 and 512
+    column blocks, 4, 16 and 128 tiles; 128 keys)."""
+    gen = torch.Generator(device="cuda").manual_seed(G + n)
+    q, k, v = (torch.randn(G, n, d, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    cache = a2sf.Cache(G, 25, d, torch.bfloat16)
+    o, full = torch.full_like(q, float("nan")), torch.full((G, n), float("nan"), device="cuda")
+    ws = torch.empty(a2sf.a2sf_workspace_bytes(G, n, 25, d, a2sf.A2SF_BF16, 12, 12), dtype=torch.uint8, device="cuda")
+    a2sf.a2sf_prefill(q, k, v, n, 1.0, 12, 12, cache, o=o, scores_full=full, workspace=ws)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(o.float()).all()) and bool(torch.isfinite(full).all())
+    assert torch.allclose(full.sum(1), torch.full_like(full[:, 0], float(n)), rtol=1e-4)   # every row's probabilities add up to 1
+    rows = torch.arange(n, device="cuda")
+    want, scores = plain_attention_rows(q, k, v, sorted({0, G // 2, G - 1}), rows)
+    for g in want:
+        assert (o[g].double() - want[g]).abs().max() <= parity.O_TOL["bf16"]
+        parity.compare_scores(full[g].cpu().numpy(), scores[g].cpu().numpy(), f"head {g}")

@@ -836,6 +836,22 @@ void launch_fwd_rect(const void* q, const void* k, const void* v, int G, const A
 #undef A2SF_FWD
 }
 
+// Whether attn_fwd128x2r_kernel is the faster one for G heads of n rows.  Both are counted in steps of 256 rows against one
+// tile: the pairs of whole double rounds cost every compute unit the same, what is left over lasts as long as one more
+// pair (a head's last block and its start, or a longer and a shorter block); a step of the compiled kernel takes 1.2 times
+// as long, spread evenly but for its last blocks.  Rows that the last block does not have count in full, so that prompts just
+// past a multiple of 256 rows stay with the compiled kernel's blocks of 128 (us, compiled / stream, steps by this count: 1500 heads
+// x 513 242 / 312, 107 / 144; 300 x 700 69 / 77, 31 / 32; 1500 x 700 351 / 330, 149 / 144; 1500 x 1000 560 / 514, 255 / 240; 100 x
+// 1500 76 / 91, 39 / 56; 300 x 1500 214 / 196, 112 / 112; 50 x 3001 130 / 158, 75 / 104; 128 x 3001 302 / 243, 185 / 156; 100 x 4097
+// 435 / 456, 270 / 288; 300 x 4097 1323 / 1275, 796 / 720).
+inline bool pair_stream_pays(long long G, int n) {
+  const long long nq = (n + kX2Rows - 1) / kX2Rows, nb = (n + kWaves * 32 - 1) / (kWaves * 32), units = 8 * kX2Slots;
+  const long long pairs = G / 2 * nq, rest = pairs % units + G % 2 * nq;
+  const double stream = (double)((pairs / units + (rest > 0)) * 4 * (nq + 1));
+  const double compiled = 1.2 * (double)G * (double)nb * (double)(nb + 1) / (2.0 * (double)units) + 0.2 * (double)nb;
+  return stream < compiled;
+}
+
 // Square geometry (a whole prompt): G K/V heads, kv_group query heads each.
 template <int D>
 void launch_fwd(const void* q, const void* k, const void* v, int G_kv, int n, void* o, float* lse2,
@@ -876,7 +892,7 @@ void launch_fwd(const void* q, const void* k, const void* v, int G_kv, int n, vo
         if (items > main_ids) launch(main_ids, (int)(items - main_ids), 1);
         return;
       }
-      if (n >= 2048 || persistent) {
+      if (pair_stream_pays(G, n)) {
         const unsigned nqm = (unsigned)((1ull << 32) / (unsigned)nqb2) + 1u;  // exact below 2^32 / nqb2
         const int all = (G / 2) * nqb2, odd = (G % 2) * nqb2;
         auto launch = [&](int odd_blocks, int base, int pairs, int rounds) {

@@ -419,3 +419,24 @@ def test_bf16_forms_of_the_prompt_kernels(G, n, d):
     for g in want:
         assert (o[g].double() - want[g]).abs().max() <= parity.O_TOL["bf16"]
         parity.compare_scores(full[g].cpu().numpy(), scores[g].cpu().numpy(), f"head {g}")
+
+
+@pytest.mark.parametrize("G,n", [(84, 1281), (85, 1320), (84, 1344), (85, 1345), (70, 1664), (151, 641), (152, 704), (111, 1023), (111, 1024),
+                                 (128, 3001), (301, 1500)])
+def test_ragged_stream_where_it_pays(G, n):
+    """The ragged attention stream where the count of steps chooses it: last row blocks of 1 to 256 rows, odd and even
+    numbers of heads, one or more double rounds and a rest."""
+    gen = torch.Generator(device="cuda").manual_seed(G + n)
+    q, k, v = (torch.randn(G, n, 128, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    cache = a2sf.Cache(G, 25, 128, torch.bfloat16)
+    guard = torch.full((G * n * 128 + 4096,), 7.0, dtype=torch.bfloat16, device="cuda")
+    o, full = guard[: G * n * 128].view(G, n, 128), torch.empty((G, n), device="cuda")
+    ws = torch.empty(a2sf.a2sf_workspace_bytes(G, n, 25, 128, a2sf.A2SF_BF16, 12, 12), dtype=torch.uint8, device="cuda")
+    a2sf.a2sf_prefill(q, k, v, n, 1.0, 12, 12, cache, o=o, scores_full=full, workspace=ws)
+    torch.cuda.synchronize()
+    assert bool((guard[G * n * 128:] == 7.0).all())          # nothing stored past the last row
+    assert torch.allclose(full.sum(1), torch.full_like(full[:, 0], float(n)), rtol=1e-4)
+    want, scores = plain_attention_rows(q, k, v, sorted({0, 1, G // 2, G - 2, G - 1}), torch.arange(n, device="cuda"))
+    for g in want:
+        assert (o[g].double() - want[g]).abs().max() <= parity.O_TOL["bf16"]
+        parity.compare_scores(full[g].cpu().numpy(), scores[g].cpu().numpy(), f"head {g}")

@@ -4,7 +4,9 @@
 // instruction multiplies and accumulates in fp32); the probability matrix is recomputed, never
 // stored.  The bf16 path lives in prefill_bf16.hip.
 //
-// Both kernels take the geometry of a2sf_internal.h's AttnRect: m query rows per head against
+// Short prompts of few heads go through kernels of plain vector arithmetic instead (below).
+//
+// Both matrix kernels take the geometry of a2sf_internal.h's AttnRect: m query rows per head against
 // keys that lie kv_stride rows apart from head to head; row i sees keys 0 .. off + i, where
 // off (per head, or 0) is the number of older tokens in front of the rows' own.  The prompt
 // phase is the square case (off = 0, kv_stride = m); a chunk of a prompt runs against the
@@ -386,6 +388,90 @@ __global__ __launch_bounds__(kThreads, 2) void scores_f32_kernel(
   }
 }
 
+// ---- short prompts -------------------------------------------------------------------------
+// A matrix op of 64 cycles per two elements makes a tile of 32 rows a chain of 8000 cycles and more, whatever the
+// prompt has of it.  A short prompt of few heads is done sooner by plain arithmetic: a workgroup per attention row, then one
+// per key (square geometry only).
+constexpr int kShortRows = 512;  // of a prompt, at most
+
+template <int D>
+__device__ __forceinline__ float dot_row(const float* __restrict__ a, const float* __restrict__ b) {
+  float acc = 0.f;
+#pragma unroll
+  for (int c = 0; c < D; c += 4) {
+    const float4 x = *reinterpret_cast<const float4*>(a + c);
+    const float4 y = *reinterpret_cast<const float4*>(b + c);
+    acc = fmaf(x.x, y.x, acc); acc = fmaf(x.y, y.y, acc);
+    acc = fmaf(x.z, y.z, acc); acc = fmaf(x.w, y.w, acc);
+  }
+  return acc;
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads) void attn_rows_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    AttnRect rc, float* __restrict__ o, float* __restrict__ lse2, float scale_log2e) {
+  __shared__ float z[kShortRows];
+  __shared__ float part[kThreads / D][D];
+  __shared__ float red[8];
+  const int n = rc.m, rows = n - rc.first_row;
+  const int g = blockIdx.x / rows, i = rc.first_row + blockIdx.x % rows, tid = threadIdx.x;
+  const int gk = g / rc.kv_group;  // the K/V head this query head reads
+  const float* qi = q + ((size_t)g * n + i) * D;
+  const float* kg = k + (size_t)gk * rc.kv_stride * D;
+  const float* vg = v + (size_t)gk * rc.kv_stride * D;
+  constexpr int PARTS = kThreads / D;
+  const int c = tid % D, part_id = tid / D;
+
+  float m = -INFINITY, l = 0.f, acc = 0.f;
+  for (int j = tid; j <= i; j += kThreads) {
+    z[j] = dot_row<D>(qi, kg + (size_t)j * D) * scale_log2e;
+    m = fmaxf(m, z[j]);
+  }
+  m = block_max(m, red);
+  for (int j = tid; j <= i; j += kThreads) {
+    z[j] = exp2f(z[j] - m);
+    l += z[j];
+  }
+  l = block_sum(l, red);
+  if (o) {
+    for (int j = part_id; j <= i; j += PARTS) acc = fmaf(z[j], vg[(size_t)j * D + c], acc);
+    part[part_id][c] = acc;
+    __syncthreads();
+    if (tid < D) {
+      float t = 0.f;
+#pragma unroll
+      for (int p = 0; p < PARTS; ++p) t += part[p][tid];
+      o[((size_t)g * n + i) * D + tid] = t / l;
+    }
+  }
+  if (tid == 0) lse2[(size_t)g * n + i] = m + log2f(l);
+}
+
+// Column scores, one workgroup per key.
+template <int D>
+__global__ __launch_bounds__(kThreads) void scores_rows_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ lse2,
+    AttnRect rc, int first_row, float log2_alpha, const float* __restrict__ alpha_heads,
+    float* __restrict__ scores, int s_stride, float scale_log2e) {
+  __shared__ float red[8];
+  const int n = rc.m;
+  const int g = blockIdx.x / n, j = blockIdx.x % n, tid = threadIdx.x;
+  head_window(alpha_heads, g, n, first_row, log2_alpha);
+  const float* kj = k + ((size_t)g * rc.kv_stride + j) * D;
+  float sum = 0.f;
+  for (int hq = 0; hq < rc.kv_group; ++hq) {  // the query heads that share this K/V head
+    const float* qg = q + ((size_t)g * rc.kv_group + hq) * n * D;
+    const float* lg = lse2 + ((size_t)g * rc.kv_group + hq) * n;
+    for (int i = max(j, first_row) + tid; i < n; i += kThreads) {
+      const float s = dot_row<D>(qg + (size_t)i * D, kj) * scale_log2e;
+      sum += exp2f(s - lg[i] + (float)(n - 1 - i) * log2_alpha);
+    }
+  }
+  sum = block_sum(sum, red);
+  if (tid == 0) scores[(size_t)g * s_stride + j] = sum;
+}
+
 }  // namespace
 
 int first_contributing_row(int n, float alpha, float* log2_alpha) {
@@ -400,10 +486,25 @@ int first_contributing_row(int n, float alpha, float* log2_alpha) {
   return n - w < 0 ? 0 : n - w;
 }
 
+// The kernels by rows cost G n workgroups of up to n keys, those by tiles a chain of n / 128: they meet where G n^1.5 is
+// about constant (us, attention and scores, rows / tiles: d = 128, 1 head x 200 21 / 23, x 300 30 / 30, 8 x 64 13 / 19, 8
+// x 130 28 / 23, 40 x 20 13 / 18, 40 x 48 26 / 20, 300 x 5 14 / 19, 300 x 12 32 / 20; d = 64, 1 x 420 23 / 26, 8 x 96 11 /
+// 14, 40 x 32 9 / 14, 40 x 64 18 / 14, 300 x 5 8 / 14, 300 x 20 23 / 15).
+static bool short_prompt(int G, const AttnRect& rc, int d) {
+  const double rows = (double)G * rc.kv_group * rc.m;
+  return !rc.off_heads && rc.m <= kShortRows && rows * rows * rc.m <= (d == 64 ? 90e6 : 27e6);
+}
+
 void launch_attn_f32(const float* q, const float* k, const float* v, int G, const AttnRect& rc,
                      int d, float* o, float* lse2, hipStream_t st) {
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)d);
   const int GQ = G * rc.kv_group;
+  if (short_prompt(G, rc, d)) {
+    const dim3 rows((unsigned)GQ * (unsigned)(rc.m - rc.first_row));
+    if (d == 64) hipLaunchKernelGGL(attn_rows_f32_kernel<64>, rows, dim3(kThreads), 0, st, q, k, v, rc, o, lse2, scale_log2e);
+    else hipLaunchKernelGGL(attn_rows_f32_kernel<128>, rows, dim3(kThreads), 0, st, q, k, v, rc, o, lse2, scale_log2e);
+    return;
+  }
   const int nqb = (rc.m + kRows - 1) / kRows - rc.first_row / kRows;  // row blocks to compute
   const unsigned grid = ordered_grid(GQ, nqb);
 #define A2SF_ATTN_F32(D, WO)                                                                          \
@@ -424,6 +525,16 @@ void launch_colscores_f32(const float* q, const float* k, const float* lse2, int
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)d);
   float l2a;
   const int first = first_contributing_row(rc.m, alpha, &l2a);
+  if (short_prompt(G, rc, d)) {
+    const dim3 keys((unsigned)G * (unsigned)rc.m);
+    if (d == 64)
+      hipLaunchKernelGGL(scores_rows_f32_kernel<64>, keys, dim3(kThreads), 0, st, q, k, lse2, rc, first, l2a, alpha_heads,
+                         scores, s_stride, scale_log2e);
+    else
+      hipLaunchKernelGGL(scores_rows_f32_kernel<128>, keys, dim3(kThreads), 0, st, q, k, lse2, rc, first, l2a, alpha_heads,
+                         scores, s_stride, scale_log2e);
+    return;
+  }
   const int ncb = (keys_per_head + kRows - 1) / kRows;
   const unsigned grid = ordered_grid(G, ncb);
   if (d == 64)

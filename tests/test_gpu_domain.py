@@ -56,7 +56,7 @@ def rows_by_hand(q, k, v, off=0):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("group,n,cached", [(1, 100, 0), (3, 65, 0), (1, 45, 50), (2, 33, 31)])
+@pytest.mark.parametrize("group,n,cached", [(1, 100, 0), (1, 200, 0), (3, 75, 0), (5, 97, 0), (1, 45, 50), (2, 33, 31)])
 def test_fp32_infinities_reach_only_the_rows_that_see_them(d, group, n, cached):
     """V rows with an infinity or a NaN, each in another tile: the rows before them share the tile and
     stay finite, the rows after them get what float64 arithmetic gets."""
@@ -79,7 +79,7 @@ def test_fp32_infinities_reach_only_the_rows_that_see_them(d, group, n, cached):
 def test_fp32_logits_of_any_size(d, size):
     """Rows whose logits are all far below (and above) the range of an exponent: with one key, with the same
     logit for all keys, and with logits that rise or fall so steeply that one key has all the weight."""
-    n = 70
+    n = 160  # (beyond the prompts that go row by row)
     q, k = torch.zeros(6, 1, n, d, device="cuda"), torch.zeros(6, n, d, device="cuda")
     v = torch.randn(6, n, d, generator=torch.Generator(device="cuda").manual_seed(d), device="cuda")
     ramp = 1.0 + 0.01 * torch.arange(n, device="cuda")

@@ -440,3 +440,13 @@ def test_ragged_stream_where_it_pays(G, n):
     for g in want:
         assert (o[g].double() - want[g]).abs().max() <= parity.O_TOL["bf16"]
         parity.compare_scores(full[g].cpu().numpy(), scores[g].cpu().numpy(), f"head {g}")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n,G", [(4, 1300), (31, 70), (32, 70), (33, 55), (97, 11), (128, 8), (129, 8), (161, 5), (300, 1), (2, 1), (5, 300), (6, 300),
+                                 (8, 419), (9, 421), (64, 10), (64, 11), (299, 1), (450, 1)])
+def test_fp32_prompts_by_rows_and_by_tiles(n, G, d):
+    """Both sides of the line between the kernels by rows and those by tiles; tile edges on the far side of it."""
+    for alpha in (0.0, 0.7, 1.0):
+        prompt_and_steps(variant(0, heads=G, d=d, n=n, T=1, select=min(9, n), recent=4, name="fp32 forms"), alpha,
+                         sample=sorted({0, G // 2, G - 1}), steps=1)

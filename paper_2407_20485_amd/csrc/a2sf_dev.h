@@ -8,7 +8,7 @@ namespace a2sf {
 typedef uint16_t bf16_t;  // storage type of bf16 elements (bit pattern)
 
 constexpr int kWave = 64;
-constexpr int kThreads = 256;  // every kernel here runs 4 waves per workgroup
+constexpr int kThreads = 256;  // threads per workgroup, where a kernel does not name its own number
 constexpr int kWaves = kThreads / kWave;
 
 // ---- element conversion ----------------------------------------------------------------
@@ -386,7 +386,8 @@ __device__ __forceinline__ void dma4(const void* base, uint32_t lane_off, uint32
   asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dword %2, %0"
                : "=&s"(copy) : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane_off), "s"(base) : "memory");
 }
-// At most LEFT of this wave's loads and stores outstanding; LDS reads done.
+// At most LEFT of this wave's loads and stores outstanding.  LDS reads are another matter: before a tile is filled again
+// its readers need wait_lds too (or wait_vm_barrier, which waits for both).
 template <int LEFT>
 __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(LEFT) : "memory"); }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }

@@ -381,7 +381,7 @@ __device__ __forceinline__ void load_query(const T* qg, float scale_log2e, float
 // What a kernel does when the step overfills the budget.
 constexpr int kEvictNone = 0;   // nothing: the token is appended (selection / compaction kernels follow)
 constexpr int kEvictInSlot = 1; // fast mode: the new token's rows go into the evicted slot
-constexpr int kEvictShift = 2;  // stable mode, one-wave-per-head kernel: the slots behind the victim move down
+constexpr int kEvictShift = 2;  // stable mode, wave-per-head and small-step kernels: the slots behind the victim move down
 
 constexpr int kBlockUnroll = 8;  // loads in flight per lane, workgroup-per-head kernels
 constexpr int kWaveUnroll = 8;   // loads in flight per lane, wave-per-head kernel
@@ -1456,7 +1456,7 @@ void decode_gqa_mfma_kernel(
                                   t_pos, alpha, select, recent, evict_here != 0, sms[wave]);
 }
 
-// ---- one large workgroup per head, the whole head in registers --------------------------
+// ---- one large workgroup per head, its K and V rows in registers -------------------------
 // For few heads with short caches.  Such a step moves a few megabytes and is a chain of round trips:
 // decode_fused_kernel waits for the length, then for the K rows (two rounds of loads), then for
 // the V rows, and meets at a dozen barriers.  Here 16 waves request every K and V row of the
@@ -1465,10 +1465,12 @@ void decode_gqa_mfma_kernel(
 // statistics of the whole head for itself from the logits in LDS, so the workgroup meets at two
 // barriers, and wave 0 alone does the bookkeeping (slot j = lane + 64 k).  In the stable mode every
 // row is already in a register when the victim is known: it is stored at its new slot, and no
-// selection or compaction kernel follows.
+// selection or compaction kernel follows.  1024 threads leave 128 registers each; the forms of 64 KB of K per head
+// (<bf16, 128, 8> and <float, 64, 8>) hold 64 of them as rows and spill eight, 36 bytes per lane, into scratch.
 // GPU time per step (steps replayed from a graph), bf16, d = 128, the kernels it replaced / here: 32 heads x 205
 // slots 7.2 / 6.4 us, 255 x 256 8.4 / 7.1, 100 x 257 10.2 / 9.0; d = 64, 255 x 300 13.1 / 7.4; stable mode
-// (fused step, selection, compaction / here): 320 x 410 42 / 29.8.
+// (fused step, selection, compaction / here): 320 x 410 42 / 29.2, each kernel traced by itself; calls back to back
+// take 26.5, as their 69 MB stay in the memory-side cache.
 constexpr int kSmallWaves = 16;
 constexpr int kSmallMaxSlots = 512;
 constexpr int kSmallMaxHeads = 255, kSmallMaxHeadsStable = 4095;

@@ -1023,8 +1023,7 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_tail_kernel(
   };
   uint4 kf[kTailKB][KK];
   load_keys(c_begin, kf);
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
+  wait_vm_barrier<0>();  // the staged rows of every wave
 
   const RowWindow win(tol, log2_alpha);
   const int rb_last = (n - 1 - r_lo) >> 5;   // the row block that holds the newest row

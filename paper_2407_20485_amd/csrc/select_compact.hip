@@ -392,11 +392,11 @@ void launch_select_gather(const void* k, const void* v, const float* scores_full
                           hipStream_t st) {
   const int ru = row_units(c.d, c.dtype);
   const int keep_stride = select + recent;
-  // Short lists: the workgroup that selects also copies (up to 512 KB per head) -- one launch and one
-  // round trip through the index list less (bf16, d = 128: 2048 heads keeping 200 of 2048 rows 28 + 69 us
-  // in two kernels, 77 in one; 32 heads keeping 204 of 1024: 7.7 + 4.3 and 11.9, a launch less; 96 heads
-  // keeping 355 of 1777, d = 64: 15 + 6 and 13).  A longer list is copied by more workgroups than one per
-  // head: 32 heads keeping 3276 of 32768 rows move 3.4 MB per head, 20 us with 205 workgroups per head.
+  // Short lists: the workgroup that selects also copies (up to 512 KB per head) -- one launch and one round
+  // trip through the index list less.  Kernel times in two / in one, bf16: 2048 heads keeping 200 of 2048 rows,
+  // d = 128, 95 / 84 us; 96 heads keeping 355 of 1777, d = 64, 15.0 / 12.3; 32 heads keeping 204 of 1024, d = 128,
+  // 11.2 / 11.1.  A longer list is copied by more workgroups than one per head: 32 heads keeping 3276 of 32768
+  // rows move 3.4 MB per head, 21 us with 205 workgroups per head.
   if (keep_stride <= kFusedKeep) {
     const GatherTo to = {(const u32x4_t*)k, (const u32x4_t*)v, (u32x4_t*)c.k, (u32x4_t*)c.v, c.scores, c.pos,
                          c.len, c.capacity, ru == 8 ? 3 : (ru == 16 ? 4 : 5)};

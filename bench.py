@@ -487,7 +487,11 @@ def main():
     else:
         nsplit_note = "one fused kernel, " + ("one wave per head" if wave_slots else "one workgroup per head")
     if args.mode == "stable":
-        nsplit_note += ", then select + in-place compaction"
+        # few heads of few slots take one kernel that also moves the rows (limits: a2sf_decode_plan in include/a2sf.h)
+        if G <= 4095 and capacity <= (256 if d * e >= 512 else 512):
+            nsplit_note = "one kernel, a workgroup of 16 waves per head, rows moved from registers"
+        else:
+            nsplit_note += ", then select + in-place compaction"
 
     out = {
         "metric": "decode steps/s (fused attn+A2SF+evict) & HBM GB/s; prefill score TFLOP/s",

@@ -108,7 +108,11 @@ size_t a2sf_workspace_bytes(int32_t G, int32_t n_max, int32_t capacity, int32_t 
  *                work is done, and rows whose weight alpha^(n-1-i) is
  *                exactly 0 in fp32 are not visited at all where the scores do not need them.
  *   scores_full  out [G, n] fp32: the Eq.5 score of every prompt token; may be NULL.
- * The n x n probability matrix is never written to memory. */
+ * The n x n probability matrix is never written to memory.
+ * Range of values: fp32 logits may take any finite value, and an infinity or NaN in a row of V
+ * reaches only the rows that see it.  bf16 works on tiles of 64 keys: an infinity or NaN in a row
+ * of V may also reach earlier rows of its tile, as NaN, and a row whose logits (q . k / sqrt(d)) all
+ * lie below about -7e29 comes out as NaN.  The same holds for a2sf_prefill_chunk. */
 a2sf_status a2sf_prefill(const void* q, const void* k, const void* v, int32_t n, float alpha,
                          a2sf_budget budget, const a2sf_cache* cache, void* o,
                          float* scores_full, void* workspace, size_t workspace_bytes,
@@ -305,7 +309,10 @@ a2sf_status a2sf_similarity_mean(const float* cos, int32_t steps, int32_t G, int
  *   wave_slots      > 0: a wave works on a whole head (64 * wave_slots slots in registers).
  *   wave_heads      heads a wave works through in the fast eviction mode: 1, or more in the
  *                   form for launches with several times more heads than the chip holds waves
- *                   (persistent workgroups; a step's small writes are held back in LDS). */
+ *                   (persistent workgroups; a step's small writes are held back in LDS).
+ * This is the fast eviction mode.  A step in A2SF_EVICT_STABLE differs: up to 4095 heads of at
+ * most 512 slots (256 where a row has 512 bytes) take one kernel, whatever nsplit says; every
+ * other step is the kernels reported here, one head per wave, and then selects and compacts. */
 a2sf_status a2sf_decode_plan(int32_t G, int32_t capacity, int32_t d, int32_t* nsplit,
                              int32_t* rows_per_split, int32_t* wave_slots, int32_t* wave_heads);
 

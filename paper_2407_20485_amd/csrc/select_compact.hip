@@ -216,7 +216,6 @@ void launch_select_kernel(const float* scores, const int32_t* pos, const int32_t
   else if (L <= 16384) A2SF_SELECT(1024, 16, false);
   else if (L <= 32768) A2SF_SELECT(1024, 32, false);
   else A2SF_SELECT(1024, 0, false);
-#undef A2SF_SELECT_SOLO
 #undef A2SF_SELECT
 }
 

@@ -157,6 +157,17 @@ a2sf_status prefill_impl(const void* q, const void* k, const void* v, int32_t n,
   return launch_status();
 }
 
+// The eviction of a step whose kernel has appended the new token.
+void evict_stable(const a2sf_cache& c, a2sf_budget b, int32_t* keep_idx, int32_t* n_keep, bool mostly_done,
+                  hipStream_t st) {
+  if (!mostly_done && selects_in_place(c, b.select, b.recent, false)) {
+    launch_select_compact(c, b.select, b.recent, st);
+    return;
+  }
+  launch_select(c.scores, c.pos, c.len, c.G, c.capacity, c.capacity, b.select, b.recent, keep_idx, n_keep, st);
+  launch_compact(c, keep_idx, b.select + b.recent, n_keep, st, nullptr, nullptr, 0, nullptr, mostly_done);
+}
+
 a2sf_status decode_impl(const void* q, const void* k_new, const void* v_new, int32_t t_pos,
                         const a2sf_cache* cache, float alpha, const float* alpha_heads,
                         a2sf_budget budget, int32_t mode, void* o, void* workspace,
@@ -182,13 +193,9 @@ a2sf_status decode_impl(const void* q, const void* k_new, const void* v_new, int
   launch_decode(q, k_new, v_new, t_pos, *cache, alpha, alpha_heads, budget.select, budget.recent,
                 mode == A2SF_EVICT_FAST, o, ws ? ws + w.split : nullptr, plan, st);
   if (mode == A2SF_EVICT_STABLE && !plan.small) {
-    int32_t* keep_idx = (int32_t*)(ws + w.keep_idx);
-    int32_t* n_keep = (int32_t*)(ws + w.n_keep);
-    launch_select(cache->scores, cache->pos, cache->len, cache->G, cache->capacity,
-                  cache->capacity, budget.select, budget.recent, keep_idx, n_keep, st);
-    // (the wave-per-head kernel has shifted the rows: heads that evict several tokens are left)
-    launch_compact(*cache, keep_idx, budget.select + budget.recent, n_keep, st, nullptr, nullptr, 0, nullptr,
-                   plan.wave_slots > 0);
+    // (the wave-per-head kernel has shifted the rows: only heads that evict several tokens are left)
+    const bool mostly_done = plan.wave_slots > 0;
+    evict_stable(*cache, budget, (int32_t*)(ws + w.keep_idx), (int32_t*)(ws + w.n_keep), mostly_done, st);
   }
   return launch_status();
 }
@@ -257,9 +264,18 @@ a2sf_status chunk_impl(const void* q, const void* k, const void* v, int32_t m, i
   // The bf16 kernels read the chunk's K/V rows from the call's inputs: the rows are not copied
   // behind the cached ones first, the compaction copies in those that are kept.
   const bool two_source = cache->dtype == A2SF_BF16;
+  const bool in_place = selects_in_place(*cache, budget.select, budget.recent, two_source);
+  // Then nothing is left for a kernel that appends, either: the lengths stay the old ones until the last kernel, and
+  // the score kernel, which forms the new tokens' scores, writes their positions beside them.
+  const bool append = !(two_source && in_place);
   if (two_source) { rc.k2 = k; rc.v2 = v; }
-
-  launch_chunk_append(k, v, m, pos0, *cache, len_old, !two_source, st);
+  if (append) {
+    launch_chunk_append(k, v, m, pos0, *cache, len_old, !two_source, st);
+  } else {
+    rc.off_heads = cache->len;
+    rc.pos = cache->pos;
+    rc.pos0 = pos0;
+  }
   if (cache->dtype == A2SF_F32) {
     launch_attn_f32((const float*)q, (const float*)cache->k, (const float*)cache->v, G, rc, d,
                     (float*)o, lse2, st);
@@ -269,12 +285,16 @@ a2sf_status chunk_impl(const void* q, const void* k, const void* v, int32_t m, i
     launch_attn_bf16(q, cache->k, cache->v, G, rc, d, o, lse2, st);
     launch_colscores_bf16(q, cache->k, lse2, G, rc, C, d, alpha, cache->scores, C, true, decay, st);
   }
-  launch_select(cache->scores, cache->pos, cache->len, G, C, C, budget.select, budget.recent,
-                keep_idx, n_keep, st);
-  if (two_source)
-    launch_compact(*cache, keep_idx, budget.select + budget.recent, n_keep, st, k, v, m, len_old);
-  else
-    launch_compact(*cache, keep_idx, budget.select + budget.recent, n_keep, st);
+  if (!append) {
+    launch_select_compact(*cache, budget.select, budget.recent, st, k, v, m);
+  } else if (in_place) {
+    launch_select_compact(*cache, budget.select, budget.recent, st, nullptr, nullptr, 0, len_old);
+  } else {
+    launch_select(cache->scores, cache->pos, cache->len, G, C, C, budget.select, budget.recent,
+                  keep_idx, n_keep, st);
+    launch_compact(*cache, keep_idx, budget.select + budget.recent, n_keep, st, two_source ? k : nullptr,
+                   two_source ? v : nullptr, m, len_old);
+  }
   return launch_status();
 }
 }  // namespace
@@ -387,11 +407,7 @@ a2sf_status a2sf_decode_step_gqa(const void* q, const void* k_new, const void* v
                     has_split ? workspace_bytes - w.split : 0, st);
   if (mode == A2SF_EVICT_STABLE) {
     char* ws = (char*)workspace;
-    int32_t* keep_idx = (int32_t*)(ws + w.keep_idx);
-    int32_t* n_keep = (int32_t*)(ws + w.n_keep);
-    launch_select(cache->scores, cache->pos, cache->len, cache->G, cache->capacity, cache->capacity,
-                  budget.select, budget.recent, keep_idx, n_keep, st);
-    launch_compact(*cache, keep_idx, budget.select + budget.recent, n_keep, st);
+    evict_stable(*cache, budget, (int32_t*)(ws + w.keep_idx), (int32_t*)(ws + w.n_keep), false, st);
   }
   return launch_status();
 }

@@ -14,11 +14,17 @@ void launch_select(const float* scores, const int32_t* pos, const int32_t* len, 
                    int stride, int select, int recent, int32_t* keep_idx, int32_t* n_keep,
                    hipStream_t st);
 // k2 / v2 [G, m2, d] set: the rows of the slots from off_heads[g] on are taken from there
-// (a chunk whose rows were not copied into the cache)
+// (a chunk whose rows were not copied into the cache); heads with a negative entry there are left alone
 void launch_compact(const a2sf_cache& c, const int32_t* keep_idx, int keep_stride,
                     const int32_t* n_keep, hipStream_t st, const void* k2 = nullptr,
                     const void* v2 = nullptr, int m2 = 0, const int32_t* off_heads = nullptr,
                     bool mostly_done = false);  // hardly a head has rows to move
+// Selection on the cache's scores and compaction in one kernel, for budgets it takes (selects_in_place).  k2 / v2 [G, m2, d]
+// set: every head's last m2 tokens, still to be counted into its length, have their rows there; a head that has
+// no room for them is left alone.  off_heads (may be null): heads with a negative entry are left alone.
+bool selects_in_place(const a2sf_cache& c, int select, int recent, bool appends);
+void launch_select_compact(const a2sf_cache& c, int select, int recent, hipStream_t st, const void* k2 = nullptr,
+                           const void* v2 = nullptr, int m2 = 0, const int32_t* off_heads = nullptr);
 // Selection on a prompt's scores [G, n] and gather of the surviving rows into the cache.
 void launch_select_gather(const void* k, const void* v, const float* scores_full, int n, int select,
                           int recent, int32_t* keep_idx, int32_t* n_keep, const a2sf_cache& c,
@@ -65,7 +71,7 @@ void launch_similarity_mean(const float* cos, long long begin, long long end, fl
 // Geometry of one attention call: m query rows per head against keys that lie kv_stride rows
 // apart from head to head; row i sees keys 0 .. off + i.  The prompt phase is the square case
 // (off = 0, kv_stride = m); a chunk of a prompt runs against the head's cache, off = the tokens
-// cached before the chunk (off_heads[g] < 0 marks a head to be skipped).
+// cached before the chunk (a head with off_heads[g] < 0, or without room for m more, is skipped).
 // kv_group > 1: grouped-query heads.  The attention kernels then run over G * kv_group query
 // heads, query head g reading the K/V rows of head g / kv_group; the column-score kernels run
 // over the G K/V heads and sum the scores of each head's kv_group query heads.
@@ -79,6 +85,9 @@ struct AttnRect {
   // k2 / v2 -- a chunk whose rows have not been copied behind the cached ones.
   const void* k2 = nullptr;
   const void* v2 = nullptr;
+  // Column scores with two sources: the positions pos0 + i of the keys off + i are written here, [G, kv_stride]
+  int32_t* pos = nullptr;
+  int pos0 = 0;
   // Calls without outputs: the log-sum-exp of the rows before first_row is not needed (the score
   // kernel that follows skips them), so their row blocks are not computed.
   int first_row = 0;

@@ -36,6 +36,12 @@ __device__ __forceinline__ f32x16 mfma_bf16(const uint4& a, const uint4& b, cons
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
+// Older tokens in front of head gk's own keys; negative: the head is to be skipped.
+__device__ __forceinline__ int rect_off(const AttnRect& rc, int gk) {
+  if (!rc.off_heads) return 0;
+  const int off = rc.off_heads[gk];
+  return off <= rc.kv_stride - rc.m ? off : -1;
+}
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Workgroup id -> flat work id such that each of the 8 accelerator dies (which receive
@@ -212,7 +218,7 @@ __global__ __launch_bounds__(kThreads * KS, !WITH_O ? 4 : 2 / KS) void attn_fwd_
   const int l32 = lane & 31, h = lane >> 5;
   const int n = rc.m;
   const int gk = g / rc.kv_group;  // the K/V head this query head reads
-  const int off = rc.off_heads ? rc.off_heads[gk] : 0;  // older tokens in front of the rows' own
+  const int off = rect_off(rc, gk);
   const int row0 = qb * BM;
   if (off < 0) {  // a head the caller's precondition excludes: its rows are flagged with NaN
     if (WITH_O)
@@ -973,7 +979,7 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_tail_kernel(
   // n query rows; row i sees keys 0 .. off + i of the head's nk = off + n keys (the prompt
   // phase: off = 0; a chunk of a prompt: off = tokens cached before it)
   const int n = rc.m;
-  const int off = rc.off_heads ? rc.off_heads[g] : 0;
+  const int off = rect_off(rc, g);
   if (off < 0) return;  // a head the caller's precondition excludes
   const int nk = off + n;
   constexpr int STEP = BC * kTailKB;  // keys per workgroup step
@@ -1106,19 +1112,27 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_tail_kernel(
       const int key = wc0 + 4 * lane;
       float4 v = *reinterpret_cast<const float4*>(&strip[wave][4 * lane]);
       float* out = Sg + key;
-      // `accumulate`: on top of `decay` times the older score (a chunk: alpha^n)
+      // `accumulate`: on top of `decay` times the older score (a chunk: alpha^n); the chunk's own keys have none
+      const float vv[4] = {v.x, v.y, v.z, v.w};
       if (key + 3 < nk && (reinterpret_cast<size_t>(out) & 15) == 0) {
         if (accumulate) {
           const float4 old = *reinterpret_cast<const float4*>(out);
-          v = make_float4(fmaf(decay, old.x, v.x), fmaf(decay, old.y, v.y), fmaf(decay, old.z, v.z),
-                          fmaf(decay, old.w, v.w));
+          const float ov[4] = {old.x, old.y, old.z, old.w};
+          float sum[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum[e] = key + e < off ? fmaf(decay, ov[e], vv[e]) : vv[e];
+          v = make_float4(sum[0], sum[1], sum[2], sum[3]);
         }
         *reinterpret_cast<float4*>(out) = v;
       } else {
-        const float vv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (key + e < nk) out[e] = accumulate ? fmaf(decay, out[e], vv[e]) : vv[e];
+          if (key + e < nk) out[e] = accumulate && key + e < off ? fmaf(decay, out[e], vv[e]) : vv[e];
+      }
+      if (rc.pos) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (key + e >= off && key + e < nk) rc.pos[(size_t)g * rc.kv_stride + key + e] = rc.pos0 + key + e - off;
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
@@ -1138,8 +1152,8 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_tail_kernel(
 // 25 / 16, 300 x 1000 82 / 66, 96 x 1777 63 / 57, 300 x 4000 796 / 774; d = 64, 96 x 1777 52 / 42).  But they read the rows twice as
 // often, and from about 8000 rows on a die's heads do not stay in its L2 (64 x 9000 749 / 783; d = 64 never minds).
 // Geometry as in AttnRect (n = rc.m rows, keys 0 .. off + n - 1, row i sees keys <= off + i).
-// accumulate: the column sums are added to decay * S[] (a chunk: the cached tokens' older scores
-// decayed by alpha^m) instead of replacing it.
+// accumulate: the column sums are added to decay * S[] for the keys before off (a chunk: the cached tokens' older
+// scores decayed by alpha^m) instead of replacing it.
 // RS = 2 (without a tolerance): eight waves, the second four take the odd tiles for the same keys, each
 // half with a ring of its own; their sums meet at the end.  For launches whose workgroups are all
 // resident at once, which last as long as the column block with the most rows.
@@ -1159,7 +1173,7 @@ __global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_sco
   int g, cb;  // column block 0 has the most rows
   if (!launch_item<RS == 1 ? kTwoPerUnit : kOneRound>(G, ncb, g, cb)) return;
   const int n = rc.m;
-  const int off = rc.off_heads ? rc.off_heads[g] : 0;
+  const int off = rect_off(rc, g);
   const int nk = off + n;  // keys of this head
   const int c0 = cb * BC;
   if (off < 0 || c0 >= nk) return;
@@ -1327,7 +1341,8 @@ __global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_sco
     if (RS > 1) x += other[w0 + key];
     if (wc0 + key < nk) {
       float* out = S + (size_t)g * s_stride + wc0 + key;
-      *out = accumulate ? fmaf(decay, *out, x) : x;
+      *out = accumulate && wc0 + key < off ? fmaf(decay, *out, x) : x;
+      if (rc.pos && wc0 + key >= off) rc.pos[(size_t)g * rc.kv_stride + wc0 + key] = rc.pos0 + wc0 + key - off;
     }
   });
 }

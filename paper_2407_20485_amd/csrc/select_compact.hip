@@ -25,25 +25,29 @@
 namespace a2sf {
 namespace {
 
-// Where the kept rows of a prompt go: fused selection and gather.
+// Where the kept rows go, for kernels that select and move them.
 constexpr int kFusedKeep = 512;  // tokens kept per head, at most
-struct GatherTo {
-  const u32x4_t *kin, *vin;  // [G, L, row]; null: selection only
+struct MoveTo {
+  const u32x4_t *kin, *vin;  // a prompt's rows [G, L, row]; a chunk's [G, m, row], or null
   u32x4_t *k, *v;            // [G, capacity, row]
   float* s;
   int32_t *p, *len;
   int capacity, lg_units;    // log2 of the 16-byte units per row
+  int m;                     // in place: tokens of the chunk
+  const int32_t* off_heads;  // in place, may be null: negative entries mark heads to be left alone
 };
+constexpr int kSelectOnly = 0, kGather = 1, kInPlace = 2;
 
 // T threads per head.  SOLO: one of the waves does the search alone (up to 64 * IPT tokens, keys in registers), the others
 // only take part in the copy.  Otherwise all waves do: up to T * IPT tokens with keys in registers, or, with
-// IPT = 0, any number, the keys formed again from memory in every round.  With `to` the kept indices stay in LDS and the
-// workgroup copies the rows of its head at once (to.kin set: pos and len are null, B <= kFusedKeep).
-template <int T, int IPT, bool SOLO>
+// IPT = 0, any number, the keys formed again from memory in every round.
+// MOVE: the kept indices stay in LDS (B <= kFusedKeep) and the workgroup moves the rows of its head at once.
+// kGather: from a prompt into the cache (pos and len are null).  kInPlace: in the cache, see move_slice for why rows may
+// move in ascending order; a chunk's tokens (to.kin) are the last to.m, in front of them len[g] others.
+template <int T, int IPT, bool SOLO, int MOVE>
 __global__ __launch_bounds__(T) void select_kernel(
-    const float* __restrict__ scores, const int32_t* __restrict__ pos,
-    const int32_t* __restrict__ len, int L, int stride, int select, int recent,
-    int32_t* __restrict__ keep_idx, int32_t* __restrict__ n_keep, GatherTo to) {
+    const float* scores, const int32_t* pos, const int32_t* len, int L, int stride, int select, int recent,
+    int32_t* __restrict__ keep_idx, int32_t* __restrict__ n_keep, MoveTo to) {
   constexpr int NW = SOLO ? 1 : T / 64, NR = IPT > 0 ? IPT : 1;  // waves that search
   constexpr int NT = 3;  // thresholds per round
   __shared__ SelectSmem<NW> sm;
@@ -52,10 +56,19 @@ __global__ __launch_bounds__(T) void select_kernel(
   const int lane = tid & 63, wave = SOLO ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
   const int B = select + recent;
   int Lg = len ? len[g] : L;
+  int off = to.capacity;  // in place: slots from here on have their rows in the second source
+  if constexpr (MOVE == kInPlace) {
+    if (to.off_heads && to.off_heads[g] < 0) return;
+    if (to.kin) {
+      if (Lg < 0 || Lg > to.capacity - to.m) return;
+      off = Lg;
+      Lg += to.m;
+    }
+  }
   Lg = Lg < 0 ? 0 : (Lg > L ? L : Lg);
   const float* sc = scores + (size_t)g * stride;
   const int32_t* ps = pos ? pos + (size_t)g * stride : nullptr;
-  int32_t* out = to.kin ? list : keep_idx + (size_t)g * B;
+  int32_t* out = MOVE ? list : keep_idx + (size_t)g * B;
   const int kept = min(Lg, B);
 
   if (Lg <= B) {
@@ -157,11 +170,52 @@ __global__ __launch_bounds__(T) void select_kernel(
       base += __popcll(mask);
     });
   }
-  if (!to.kin) {
+  if constexpr (MOVE == kSelectOnly) {
     if (tid == 0) n_keep[g] = kept;
     return;
   }
   __syncthreads();
+  if constexpr (MOVE == kInPlace) {
+    if (tid == 0) to.len[g] = kept;
+    if (kept == 0 || (list[kept - 1] == kept - 1 && kept <= off)) return;  // nothing moves (the list ascends)
+    constexpr int U = 4;  // units of K and of V per thread and round
+    const int lg = to.lg_units, rows = U * T >> lg;
+    u32x4_t* const Kg = to.k + (((size_t)g * to.capacity) << lg);
+    u32x4_t* const Vg = to.v + (((size_t)g * to.capacity) << lg);
+    const u32x4_t* const kin = to.kin + (((size_t)g * to.m) << lg);
+    const u32x4_t* const vin = to.vin + (((size_t)g * to.m) << lg);
+    float* const Sg = to.s + (size_t)g * to.capacity;
+    int32_t* const Pg = to.p + (size_t)g * to.capacity;
+    for (int r0 = 0; r0 < kept; r0 += rows) {
+      u32x4_t kx[U], vx[U];
+      bool moves[U];
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        const int u = tid + i * T, r = r0 + (u >> lg), c = u & ((1 << lg) - 1);
+        const int src = r < kept ? min(max(list[r], 0), to.capacity - 1) : r;
+        moves[i] = r < kept && (src != r || src >= off);
+        if (moves[i]) {
+          const int at = (src >= off ? min(src - off, to.m - 1) : src) << lg | c;
+          kx[i] = src >= off ? kin[at] : Kg[at];
+          vx[i] = src >= off ? vin[at] : Vg[at];
+        }
+      }
+      float s_val = 0.f;
+      int p_val = 0, dst = -1;
+      if (tid < rows && r0 + tid < kept) {
+        const int src = min(max(list[r0 + tid], 0), to.capacity - 1);
+        if (src != r0 + tid) { dst = r0 + tid; s_val = Sg[src]; p_val = Pg[src]; }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        const int u = tid + i * T;
+        if (moves[i]) { Kg[(r0 << lg) + u] = kx[i]; Vg[(r0 << lg) + u] = vx[i]; }
+      }
+      if (dst >= 0) { Sg[dst] = s_val; Pg[dst] = p_val; }
+    }
+    return;
+  }
   // the kept rows: K, V in 16-byte units, four rows' units of each under way per thread
   const int units = kept << to.lg_units, mask = (1 << to.lg_units) - 1;
   const size_t in0 = ((size_t)g * L) << to.lg_units, out0 = ((size_t)g * to.capacity) << to.lg_units;
@@ -191,18 +245,19 @@ __global__ __launch_bounds__(T) void select_kernel(
   if (tid == 0) to.len[g] = kept;
 }
 
+template <int MOVE>
 void launch_select_kernel(const float* scores, const int32_t* pos, const int32_t* len, int G, int L,
                           int stride, int select, int recent, int32_t* keep_idx, int32_t* n_keep,
-                          const GatherTo& to, hipStream_t st) {
+                          const MoveTo& to, hipStream_t st) {
 #define A2SF_SELECT(T, IPT, SOLO)                                                                         \
-  hipLaunchKernelGGL((select_kernel<T, IPT, SOLO>), dim3(G), dim3(T), 0, st, scores, pos, len, L, stride, \
+  hipLaunchKernelGGL((select_kernel<T, IPT, SOLO, MOVE>), dim3(G), dim3(T), 0, st, scores, pos, len, L, stride, \
                      select, recent, keep_idx, n_keep, to)
   // A search by one wave has no barriers: short heads, and longer ones of which there are so many that the
   // work counts and not the chain of rounds (us, one wave / four: 300 heads x 200 5.6 / 6.4, 8000 x 400 18.5 / 35.5,
   // 8000 x 1000 34 / 48, but 1500 x 1024 16.7 / 14.3 and 300 x 1024 14.5 / 8.4).  Up to 2048 slots four waves, or eight where
   // every head's workgroup has a compute unit (2048 slots, four / eight: 32 heads 12.0 / 10.2, 1500 heads 20.2 / 25.1; 16 of
   // them: 12.3 and 58.7).  Copying workgroups have more waves while there are few heads.
-  const bool copies = to.kin != nullptr, few = G <= 512;
+  const bool copies = MOVE != kSelectOnly, few = G <= 512;
   if (L <= 256 && !copies) A2SF_SELECT(64, 4, true);
   else if (L <= 256 && few) A2SF_SELECT(512, 4, true);
   else if (L <= 256) A2SF_SELECT(256, 4, true);
@@ -296,8 +351,8 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(
   constexpr int PER = 2 * ROW_UNITS / kSliceUnits;  // workgroups per head
   const int g = blockIdx.x / PER, part = blockIdx.x % PER;
   const int nk = rows_kept(n_keep[g], capacity, keep_stride);
+  if (off_heads && off_heads[g] < 0) return;      // a head the chunk did not fit into: untouched
   const int off = kin ? off_heads[g] : capacity;  // slots from here on live in the second source
-  if (off < 0) return;                            // a head the chunk did not fit into: untouched
   const int32_t* keep = keep_idx + (size_t)g * keep_stride;
   if (part == 0 && threadIdx.x == 0) len[g] = nk;  // (no other workgroup reads it)
   // strictly ascending indices: the identity if the last one is in its own slot
@@ -356,13 +411,14 @@ __global__ __launch_bounds__(kThreads) void gather_prompt_kernel(
 }
 
 inline int row_units(int d, int dtype) { return d * (dtype == A2SF_BF16 ? 2 : 4) / 16; }
+inline int lg_units(int ru) { return ru == 8 ? 3 : (ru == 16 ? 4 : 5); }
 
 }  // namespace
 
 void launch_select(const float* scores, const int32_t* pos, const int32_t* len, int G, int L,
                    int stride, int select, int recent, int32_t* keep_idx, int32_t* n_keep,
                    hipStream_t st) {
-  launch_select_kernel(scores, pos, len, G, L, stride, select, recent, keep_idx, n_keep, GatherTo{}, st);
+  launch_select_kernel<kSelectOnly>(scores, pos, len, G, L, stride, select, recent, keep_idx, n_keep, MoveTo{}, st);
 }
 
 void launch_compact(const a2sf_cache& c, const int32_t* keep_idx, int keep_stride,
@@ -386,6 +442,26 @@ void launch_compact(const a2sf_cache& c, const int32_t* keep_idx, int keep_strid
 #undef A2SF_COMPACT
 }
 
+// One workgroup moves a head's rows, up to 128 KB of K: a launch and a round trip through the index list less (us per call,
+// two kernels / this one, bf16, d = 128: chunk of 111 rows, 3 heads keeping 45, 25.4 / 21.2; 512 heads keeping 512,
+// 230 / 221; stable step of 243 heads x 8 queries, 174 slots, 34.4 / 28.6; 4 x 4, 500 slots, 23.2 / 22.6).  More is moved
+// sooner by a workgroup per slice (fp32, 500 slots, 256 KB: 30 heads 28 / 35, 600 heads 136 / 151), and with many heads the
+// launch does not count (stable step of 3000 x 4, 500 slots, 351 / 355; fp32 chunk of 30 rows, 2000 heads, 226 / 229) unless
+// `appends`, the kernel that would append the chunk is saved with it (2048 heads, 40 rows, 410 / 402).
+constexpr int kInPlaceHeads = 1024;
+bool selects_in_place(const a2sf_cache& c, int select, int recent, bool appends) {
+  return select + recent <= kFusedKeep && (select + recent) * row_units(c.d, c.dtype) <= 8192 &&
+         (appends || c.G <= kInPlaceHeads);
+}
+
+void launch_select_compact(const a2sf_cache& c, int select, int recent, hipStream_t st, const void* k2, const void* v2,
+                           int m2, const int32_t* off_heads) {
+  const MoveTo to = {(const u32x4_t*)k2, (const u32x4_t*)v2, (u32x4_t*)c.k, (u32x4_t*)c.v, c.scores, c.pos, c.len,
+                     c.capacity, lg_units(row_units(c.d, c.dtype)), m2, off_heads};
+  launch_select_kernel<kInPlace>(c.scores, c.pos, c.len, c.G, c.capacity, c.capacity, select, recent, nullptr, nullptr,
+                                 to, st);
+}
+
 void launch_select_gather(const void* k, const void* v, const float* scores_full, int n, int select,
                           int recent, int32_t* keep_idx, int32_t* n_keep, const a2sf_cache& c,
                           hipStream_t st) {
@@ -397,9 +473,9 @@ void launch_select_gather(const void* k, const void* v, const float* scores_full
   // 11.2 / 11.1.  A longer list is copied by more workgroups than one per head: 32 heads keeping 3276 of 32768
   // rows move 3.4 MB per head, 21 us with 205 workgroups per head.
   if (keep_stride <= kFusedKeep) {
-    const GatherTo to = {(const u32x4_t*)k, (const u32x4_t*)v, (u32x4_t*)c.k, (u32x4_t*)c.v, c.scores, c.pos,
-                         c.len, c.capacity, ru == 8 ? 3 : (ru == 16 ? 4 : 5)};
-    launch_select_kernel(scores_full, nullptr, nullptr, c.G, n, n, select, recent, nullptr, nullptr, to, st);
+    const MoveTo to = {(const u32x4_t*)k, (const u32x4_t*)v, (u32x4_t*)c.k, (u32x4_t*)c.v, c.scores, c.pos,
+                       c.len, c.capacity, lg_units(ru), 0, nullptr};
+    launch_select_kernel<kGather>(scores_full, nullptr, nullptr, c.G, n, n, select, recent, nullptr, nullptr, to, st);
     return;
   }
   launch_select(scores_full, nullptr, nullptr, c.G, n, n, select, recent, keep_idx, n_keep, st);

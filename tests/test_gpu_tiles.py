@@ -450,3 +450,93 @@ def test_fp32_prompts_by_rows_and_by_tiles(n, G, d):
     for alpha in (0.0, 0.7, 1.0):
         prompt_and_steps(variant(0, heads=G, d=d, n=n, T=1, select=min(9, n), recent=4, name="fp32 forms"), alpha,
                          sample=sorted({0, G // 2, G - 1}), steps=1)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("budget,m,G", [(1, 40, 6), (64, 70, 6), (129, 3, 520), (255, 300, 6), (256, 1, 6), (257, 90, 6),
+                                        (512, 200, 6), (512, 60, 520), (513, 130, 6)])
+def test_chunk_evicts_in_place(dtype, d, budget, m, G):
+    """Selection and moves of a chunk in one kernel, on both sides of the sizes where two kernels follow: the same
+    cache, bit for bit, as a chunk that evicts nothing followed by a2sf_select and a2sf_compact.  Lengths from an
+    empty cache to one without room, which stays as it is."""
+    tdt = parity.torch_dtype(dtype)
+    gen = torch.Generator(device="cuda").manual_seed(budget + d)
+    cap = max(budget, 512) + m + 3  # (a budget of all slots but one: two kernels)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(tdt)
+    lens = torch.randint(0, budget + 1, (G,), generator=gen, device="cuda").int()
+    lens[:5] = torch.tensor([budget, 0, budget // 2, cap - m + 1, -1])
+    lens[-1] = budget
+    small, large = a2sf.Cache(G, cap, d, tdt), a2sf.Cache(G, cap, d, tdt)
+    for x in (small, large):
+        x.len.copy_(lens)
+    for x, y in zip(small.tensors()[:4], large.tensors()[:4]):
+        x.copy_(torch.rand(x.shape, generator=gen, device="cuda"))
+        y.copy_(x)
+    small.pos.copy_(torch.arange(cap, device="cuda").int().expand(G, cap) * 2)
+    large.pos.copy_(small.pos)
+    before = small.snapshot()
+    q, k, v = rnd(G, m, d), rnd(G, m, d), rnd(G, m, d)
+    select = budget * 2 // 3
+    recent = budget - select
+    code = a2sf.A2SF_F32 if dtype == "f32" else a2sf.A2SF_BF16
+    o, o2 = torch.empty_like(q), torch.empty_like(q)
+    ws = torch.empty(a2sf.a2sf_workspace_bytes(G, m, cap, d, code, cap - 1, 0), dtype=torch.uint8, device="cuda")
+    a2sf.a2sf_prefill_chunk(q, k, v, m, 2 * cap, 0.9, select, recent, small, o=o, workspace=ws)
+    a2sf.a2sf_prefill_chunk(q, k, v, m, 2 * cap, 0.9, cap - 1, 0, large, o=o2, workspace=ws)
+    keep = torch.zeros((G, budget), dtype=torch.int32, device="cuda")
+    n_keep = torch.zeros(G, dtype=torch.int32, device="cuda")
+    a2sf.a2sf_select(large.scores, large.pos, large.len, G, cap, cap, select, recent, keep, n_keep)
+    a2sf.a2sf_compact(large, keep, budget, n_keep)
+    torch.cuda.synchronize()
+    for g in range(G):
+        if g in (3, 4):  # no room; an invalid length
+            assert torch.isnan(o[g]).all()
+            assert all(torch.equal(x[g], y[g]) for x, y in zip(small.tensors(), before))
+            continue
+        kept = min(int(lens[g]) + m, budget)
+        assert int(small.len[g]) == int(large.len[g]) == kept
+        assert torch.equal(o[g], o2[g])
+        for x, y in zip(small.tensors()[:4], large.tensors()[:4]):
+            assert torch.equal(x[g, :kept], y[g, :kept]), g
+
+
+@pytest.mark.parametrize("dtype,d,group", [("bf16", 64, 1), ("bf16", 128, 2), ("f32", 64, 3), ("f32", 128, 1)])
+@pytest.mark.parametrize("budget", [40, 256, 257, 511, 512, 513])
+def test_stable_step_evicts_in_place(dtype, d, group, budget):
+    """The same for a stable step whose kernel appends the new token: against a step that evicts nothing."""
+    G, tdt = 5, parity.torch_dtype(dtype)
+    gen = torch.Generator(device="cuda").manual_seed(budget)
+    cap = max(budget, 512) + 5
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(tdt)
+    small, large = a2sf.Cache(G, cap, d, tdt), a2sf.Cache(G, cap, d, tdt)
+    lens = torch.randint(0, budget + 4, (G,), generator=gen, device="cuda").int()  # up to four tokens leave at once
+    lens[:3] = torch.tensor([budget, budget - 1, budget + 3])
+    for x, y in zip(small.tensors()[:4], large.tensors()[:4]):
+        x.copy_(torch.rand(x.shape, generator=gen, device="cuda"))
+        y.copy_(x)
+    small.pos.copy_(torch.arange(cap, device="cuda").int().expand(G, cap) * 2)
+    large.pos.copy_(small.pos)
+    for x in (small, large):
+        x.len.copy_(lens)
+    shape = (G, d) if group == 1 else (G, group, d)
+    q, k, v, o, o2 = rnd(*shape), rnd(G, d), rnd(G, d), rnd(*shape), rnd(*shape)
+    code = a2sf.A2SF_F32 if dtype == "f32" else a2sf.A2SF_BF16
+    select = budget * 2 // 3
+    ws = torch.empty(a2sf.a2sf_workspace_bytes(G, 0, cap, d, code, cap - 1, 0), dtype=torch.uint8, device="cuda")
+    for c, s, r, out in ((small, select, budget - select, o), (large, cap - 1, 0, o2)):
+        if group == 1:
+            a2sf.a2sf_decode_step(q, k, v, 2 * cap, c, 0.9, s, r, out, mode=a2sf.A2SF_EVICT_STABLE, workspace=ws)
+        else:
+            a2sf.a2sf_decode_step_gqa(q, k, v, 2 * cap, c, group, 0.9, s, r, out, mode=a2sf.A2SF_EVICT_STABLE, workspace=ws)
+    keep = torch.zeros((G, budget), dtype=torch.int32, device="cuda")
+    n_keep = torch.zeros(G, dtype=torch.int32, device="cuda")
+    a2sf.a2sf_select(large.scores, large.pos, large.len, G, cap, cap, select, budget - select, keep, n_keep)
+    a2sf.a2sf_compact(large, keep, budget, n_keep)
+    torch.cuda.synchronize()
+    assert torch.equal(small.len, large.len) and torch.equal(small.len, (lens + 1).clamp(max=budget))
+    live = torch.arange(cap, device="cuda")[None, :] < small.len[:, None]
+    assert torch.equal(small.pos[live], large.pos[live])
+    assert torch.equal(small.k[live], large.k[live]) and torch.equal(small.v[live], large.v[live])
+    # (the budget takes its part of the workspace, which decides how many workgroups share a head: fp32 summation order)
+    assert torch.allclose(small.scores[live], large.scores[live], rtol=1e-5, atol=0.0)
+    assert (o.float() - o2.float()).abs().max().item() <= parity.O_TOL[dtype]

@@ -1,7 +1,6 @@
-// fp32 prompt phase on the fp32 matrix instructions: masked attention rows with their
+// fp32 prompt phase on the matrix cores, to the precision of fp32: masked attention rows with their
 // log-sum-exp (Section 3.1 Eq.3 of the paper) and the forgotten column scores of Section 3.3
-// Eq.5,  S_j = sum_{i>=j} alpha^(n-1-i) * exp(s_ij - lse_i).  Every product and sum is fp32 (the
-// instruction multiplies and accumulates in fp32); the probability matrix is recomputed, never
+// Eq.5,  S_j = sum_{i>=j} alpha^(n-1-i) * exp(s_ij - lse_i).  The probability matrix is recomputed, never
 // stored.  The bf16 path lives in prefill_bf16.hip.
 //
 // Short prompts of few heads go through kernels of plain vector arithmetic instead (below).
@@ -12,21 +11,25 @@
 // phase is the square case (off = 0, kv_stride = m); a chunk of a prompt runs against the
 // head's cache (off = tokens cached before the chunk).
 //
-// Operand layouts of v_mfma_f32_32x32x2_f32: lane (x = lane % 32, h = lane / 32) brings A[x][k = h]
-// and B[k = h][x]; accumulator register i of the lane is row 8 (i/4) + 4 h + i % 4, column x.
-// Both kernels form the transposed logit tile (keys = rows, queries = columns), so a lane owns
-// one query, and register i of the tile is at once the B operand of the i-th step of
-// O^T = V^T P^T (its two halves bring the keys 8 (i/4) + i % 4 and + 4).  The order in which a
-// sum over d runs is free: lane half h takes the elements 8c + 4h .. + 3 in the steps 4c .. 4c+3,
-// so operands come as 16-byte pieces.
+// Products run on v_mfma_f32_32x32x16_bf16, which does sixteen times the multiplications of the fp32 instruction per
+// cycle: every fp32 operand is cut into three bf16 parts of eight bits each, high + middle + low, which together are
+// the number itself, and of the nine products of parts the six above 2^-24 of the whole are summed in fp32
+// (the instruction multiplies exactly).  Sums of corrections are kept apart from the sums of high parts, which makes the
+// result more exact than a chain of fp32 multiply-adds: relative error of products of 128 normal
+// values 8.5e-8, of the fp32 instruction with two chains 1.43e-7, with one 2.04e-7 (1024 values: 1.9e-7, 3.8e-7, 5.7e-7).
+// An infinity has no parts: it makes the sums NaN, and rows whose result is not finite are done again in
+// plain fp32 arithmetic.
 //
-// One matrix op takes 64 cycles of its pipe for two operand floats per lane, so tiles need not
-// be shared: a wave fetches its own 32-row tiles straight into its own LDS strip
-// (global_load_lds) and meets the other waves of its workgroup only at the end.  The four waves of a
-// workgroup share 32 query rows (attention) or 32 keys (scores) and take every fourth tile, which keeps
-// the chip full from a few hundred rows on and the longest row's chain short.
-// 32 heads x 1000 rows x 128: attention 101 us (8.2 GFLOP = 81 TFLOP/s of the 154 that a large fp32
-// matrix product reaches), scores 23 us (window of 93 rows; vector form: 219).
+// Operand layouts: lane (x = lane % 32, h = lane / 32) brings A[x][k] and B[k][x] for the eight k of its half;
+// accumulator register i of the lane is row 8 (i/4) + 4 h + i % 4, column x.  Both kernels form the transposed logit
+// tile (keys = rows, queries = columns), so a lane owns one query, and the registers 8j .. 8j+7 of the tile
+// are at once the B operand of step j of O^T = V^T P^T (a half brings the keys 16j + 4h .. +3 and 16j + 8 + 4h .. +3).
+// A sum over d runs in steps of 16 elements, eight to a half, so operands come as 16-byte pieces.
+//
+// Waves fetch 32-row tiles straight into LDS (global_load_lds) and cut what they read from there.  The waves of
+// a workgroup share 32 or 64 query rows (attention) or 32 keys (scores) and take the tiles in turn, which keeps
+// the chip full from a few hundred rows on and the longest row's chain short; they add up at the end.
+// Scores of 32 heads x 1000 rows (window of 93 rows): 22 us.
 #include <math.h>
 
 #include "a2sf_dev.h"
@@ -41,8 +44,44 @@ typedef __attribute__((address_space(3))) char lds_char;
 
 constexpr int kRows = 32;  // query rows (attention) / keys (scores) per workgroup, and rows of a tile
 
-__device__ __forceinline__ f32x16 mfma_f32(float a, float b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ f32x16 mfma_bf16(const uint4& a, const uint4& b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// Eight numbers as three bf16 operands whose sum they are: 24 bits in three times eight, cut and not rounded, so that
+// every difference is exact and no part of a finite number is infinite.
+struct Parts {
+  uint4 high, middle, low;
+};
+__device__ __forceinline__ Parts cut(const float (&x)[8]) {
+  uint32_t hi[4], mi[4], lo[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float r[2], rr[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      r[e] = x[2 * i + e] - __uint_as_float(__float_as_uint(x[2 * i + e]) & 0xFFFF0000u);
+      rr[e] = r[e] - __uint_as_float(__float_as_uint(r[e]) & 0xFFFF0000u);
+    }
+    const auto upper = [](float a, float b) { return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u); };
+    hi[i] = upper(x[2 * i], x[2 * i + 1]);
+    mi[i] = upper(r[0], r[1]);
+    lo[i] = upper(rr[0], rr[1]);
+  }
+  return {make_uint4(hi[0], hi[1], hi[2], hi[3]), make_uint4(mi[0], mi[1], mi[2], mi[3]), make_uint4(lo[0], lo[1], lo[2], lo[3])};
+}
+__device__ __forceinline__ Parts cut(const f32x4& a, const f32x4& b) {
+  const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  return cut(x);
+}
+// sum += the product of the high parts, rest += the five next largest ones
+__device__ __forceinline__ void multiply(const Parts& a, const Parts& b, f32x16& sum, f32x16& rest) {
+  rest = mfma_bf16(a.low, b.high, rest);
+  sum = mfma_bf16(a.high, b.high, sum);
+  rest = mfma_bf16(a.high, b.low, rest);
+  rest = mfma_bf16(a.middle, b.middle, rest);
+  rest = mfma_bf16(a.middle, b.high, rest);
+  rest = mfma_bf16(a.high, b.middle, rest);
 }
 __device__ __forceinline__ f32x4 lds_read4(const lds_char* p) {
   return *reinterpret_cast<const __attribute__((address_space(3))) f32x4*>(p);
@@ -58,18 +97,29 @@ __device__ __forceinline__ float lds_read1(const lds_char* p) {
 template <bool V_LAYOUT>
 __device__ __forceinline__ int tile_swizzle(int row) { return V_LAYOUT ? ((row >> 2) & 1) * 8 : (row & 15); }
 
-// Rows row0 .. row0 + 31 of Mg (clamped to n rows) into this wave's LDS tile: D / 8 loads.
+// Rows row0 .. row0 + 31 of Mg (clamped to n rows) into an LDS tile, the loads first, first + step, ... of its D / 8.
+// In a tile that lies inside the matrix a load's lane offsets differ from the first one's by an exclusive or (the
+// rows of a load have the bits below its own first row) and by whole loads, which the scalar base takes.
 template <int D, bool V_LAYOUT>
-__device__ __forceinline__ void fetch_tile(const float* __restrict__ Mg, int row0, int n, lds_char* tile) {
+__device__ __forceinline__ void fetch_tile(const float* __restrict__ Mg, int row0, int n, lds_char* tile, int first = 0,
+                                           int step = 1) {
   constexpr int CPR = D / 4, RPL = 64 / CPR;  // chunks per row, rows per load
   const int lane = threadIdx.x & 63;
   const float* base = Mg + (size_t)row0 * D;
   const int most = n - 1 - row0;
+  if (most >= kRows - 1) {
+    const uint32_t lane0 = (uint32_t)((lane % CPR ^ tile_swizzle<V_LAYOUT>(lane / CPR)) * 16 + lane / CPR * D * 4);
 #pragma unroll
-  for (int u = 0; u < kRows / RPL; ++u) {
-    const int lrow = u * RPL + lane / CPR, pc = lane % CPR;
-    const int c = pc ^ tile_swizzle<V_LAYOUT>(lrow);
-    dma16(base, (uint32_t)(min(lrow, most) * D * 4 + c * 16), (uint32_t)(size_t)(tile + u * 1024));
+    for (int u = 0; u < kRows / RPL; ++u)
+      if (u % step == first)
+        dma16(base + u * RPL * D, lane0 ^ (uint32_t)(tile_swizzle<V_LAYOUT>(u * RPL) * 16), (uint32_t)(size_t)(tile + u * 1024));
+  } else {
+#pragma unroll
+    for (int u = 0; u < kRows / RPL; ++u) {
+      const int lrow = u * RPL + lane / CPR, pc = lane % CPR;
+      const int c = pc ^ tile_swizzle<V_LAYOUT>(lrow);
+      if (u % step == first) dma16(base, (uint32_t)(min(lrow, most) * D * 4 + c * 16), (uint32_t)(size_t)(tile + u * 1024));
+    }
   }
 }
 
@@ -79,98 +129,122 @@ __device__ __forceinline__ void fetch_tile(const float* __restrict__ Mg, int row
 // subtracted from a masked logit.
 constexpr float kLowest = -3.402823466e38f;
 
-// A matrix op multiplies a masked key's probability, 0, with its V row, and 0 times an infinity is not 0.
-// So the tiles that the mask cuts are looked over (D / 8 LDS reads of a lane beside the 4 D of the products) and their
-// infinities and NaN set to 0; add_nonfinite gives them to the rows that see them at the end.
 template <int D>
-__device__ __forceinline__ bool clear_nonfinite(lds_char* tile) {
-  lds_char* const mine = tile + (threadIdx.x & 63) * 16;
-  float zeros = 0.f;  // a NaN if some x is not finite
-#pragma unroll 4
-  for (int u = 0; u < D / 8; ++u) {
-    const f32x4 x = lds_read4(mine + u * 1024);
-    zeros = fmaf(x[0], 0.f, fmaf(x[1], 0.f, fmaf(x[2], 0.f, fmaf(x[3], 0.f, zeros))));
-  }
-  if (!__any(zeros != 0.f)) return false;
-#pragma unroll 1
-  for (int u = 0; u < D / 8; ++u) {
-    f32x4 x = lds_read4(mine + u * 1024);
+__device__ __forceinline__ float dot_row(const float* __restrict__ a, const float* __restrict__ b) {
+  float acc = 0.f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = x[e] * 0.f == 0.f ? x[e] : 0.f;
-    *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(mine + u * 1024) = x;
+  for (int c = 0; c < D; c += 4) {
+    const float4 x = *reinterpret_cast<const float4*>(a + c);
+    const float4 y = *reinterpret_cast<const float4*>(b + c);
+    acc = fmaf(x.x, y.x, acc); acc = fmaf(x.y, y.y, acc);
+    acc = fmaf(x.z, y.z, acc); acc = fmaf(x.w, y.w, acc);
   }
-  return true;
+  return acc;
 }
-// The terms p v of the keys [key0, last key of the row] whose v is not finite, onto the rows that a workgroup has
-// stored (such a sum is an infinity or NaN: adding a term again, or p's own rounding, does not change it).
-template <int D>
-__device__ __forceinline__ void add_nonfinite(const float* Qg, const float* Kg, const float* Vg, const float* lse2, float* Og,
-                                           int row0, int n, int off, int key0, float scale_log2e) {
-  for (int e = threadIdx.x; e < kRows * D; e += kThreads) {
-    const int r = row0 + e / D, c = e % D;
-    if (r >= n) break;
-    float x = Og[(size_t)r * D + c];
-    for (int j = key0; j <= off + r; ++j) {
-      const float v = Vg[(size_t)j * D + c];
-      if (v * 0.f == 0.f) continue;
-      float s = 0.f;
-      for (int i = 0; i < D; ++i) s = fmaf(Qg[(size_t)r * D + i], Kg[(size_t)j * D + i], s);
-      x += exp2f(fmaf(s, scale_log2e, -lse2[r])) * v;
+
+// The rows row0 .. end - 1 of a workgroup once more in plain arithmetic, which the matrix ops cannot replace where infinities are
+// about (an infinity cut into parts is NaN, and so is a masked key's probability, 0, times an infinite V element).  Every
+// row reads only the keys it sees.  lds: kThreads + 8 floats.
+template <int D, bool WITH_O>
+__device__ __forceinline__ void rows_again(const float* Qg, const float* Kg, const float* Vg, float* lse2, float* Og, int row0,
+                                           int end, int off, float scale_log2e, float* lds) {
+  const int tid = threadIdx.x, c = tid % D;
+  float* const red = lds + kThreads;
+#pragma unroll 1
+  for (int r = row0; r < end; ++r) {
+    const int nk = off + r + 1;
+    const float* q = Qg + (size_t)r * D;
+    float m = kLowest, l = 0.f;
+#pragma unroll 1
+    for (int j = tid; j < nk; j += kThreads) {
+      const float s = dot_row<D>(q, Kg + (size_t)j * D), up = fmaxf(m, s);
+      l = l * exp2f((m - up) * scale_log2e) + exp2f((s - up) * scale_log2e);
+      m = up;
     }
-    Og[(size_t)r * D + c] = x;
+    const float all = block_max(m, red);
+    l = block_sum(l * exp2f((m - all) * scale_log2e), red);
+    if (tid == 0) lse2[r] = fmaf(all, scale_log2e, log2f(l));
+    if (!WITH_O) continue;
+    float acc = 0.f;
+#pragma unroll 1
+    for (int j0 = 0; j0 < nk; j0 += kThreads) {
+      __syncthreads();
+      if (j0 + tid < nk) lds[tid] = exp2f((dot_row<D>(q, Kg + (size_t)(j0 + tid) * D) - all) * scale_log2e);
+      __syncthreads();
+      for (int j = tid / D; j < min(kThreads, nk - j0); j += kThreads / D) acc = fmaf(lds[j], Vg[(size_t)(j0 + j) * D + c], acc);
+    }
+    __syncthreads();
+    lds[tid] = acc;
+    __syncthreads();
+    if (tid < D) {
+      float t = 0.f;
+#pragma unroll
+      for (int p = 0; p < kThreads / D; ++p) t += lds[p * D + tid];
+      Og[(size_t)r * D + tid] = t / l;
+    }
+    __syncthreads();
   }
 }
 
-// One workgroup per 32 query rows; wave w takes the key tiles w, w + 4, ...  A wave's strip holds
-// the K tile until its logits are formed, then the V tile: the wave waits for each, and the
-// second wave of the SIMD fills the gaps (two strips per wave, with the next tile fetched half a tile ahead,
-// leave room for one wave per SIMD only: 126 us instead of 117 at 32 heads x 1000 rows x 128 in the old launch order;
-// quarters of a tile fetched as the quarters before them are used up: no difference; a workgroup of
-// vector arithmetic per row, as this kernel used to be: 2187).
-template <int D, bool WITH_O>
-__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_f32_kernel(
+// NW waves per workgroup, which has 32 RB query rows: wave w takes the rows 32 (w % RB) .. and every P-th key tile from
+// w / RB on.  The RB waves of a part share its K and its V tile, in buffers of their own: V(t) is under way while the
+// logits of tile t and their exponentials are formed, K(t + P) during the products with V(t).  A tile takes a wave 96 matrix ops
+// (d = 128) of 32 cycles and about a thousand vector instructions, most of them for cutting K and V.  A wave alone on its SIMD
+// issues a vector instruction every six cycles, two of them one every three, so registers are held to what two waves can have.
+// 32 heads x 1000 rows x 128: 80 us (8.2 GFLOP = 102 TFLOP/s of fp32 products, of which a large fp32 matrix product reaches
+// 154; on the fp32 instruction 103 us); 849 x 210: 152 (217).
+template <int D, bool WITH_O, int RB, int NW>
+__global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW == 4 ? 1 : 2)) void attn_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     AttnRect rc, int GQ, int nqb, float* __restrict__ O, float* __restrict__ LSE2, float scale_log2e) {
-  constexpr int C8 = D / 8, DB = D / 32, kTileBytes = kRows * D * 4;
-  __shared__ __attribute__((aligned(1024))) char smem[kWaves * kTileBytes];
-  __shared__ float m_s[kWaves][kRows], l_s[kWaves][kRows];
-  __shared__ bool odd_s[kWaves];
+  constexpr int C16 = D / 16, DB = D / 32, kTileBytes = kRows * D * 4, P = NW / RB, BM = kRows * RB, NT = NW * 64;
+  __shared__ __attribute__((aligned(1024))) char smem[2 * P * kTileBytes];
+  __shared__ float m_s[NW][kRows], l_s[NW][kRows];
+  __shared__ bool again;
+  const auto arrived = [] {  // this wave's loads, and those of the waves it shares tiles with
+    if (RB == 1) { wait_vm<0>(); wait_lds(); }
+    else wait_vm_barrier<0>();
+  };
 
   int g, rank;
   if (!ordered_item(GQ, nqb, g, rank)) return;
-  const int qb = rc.first_row / kRows + nqb - 1 - rank;
+  const int qb = rc.first_row / BM + nqb - 1 - rank;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), block = wave % RB, part = wave / RB;
   const int l32 = lane & 31, h = lane >> 5;
-  const int n = rc.m, row0 = qb * kRows;
+  const int n = rc.m, row0 = qb * BM, wrow0 = row0 + kRows * block;
   const int gk = g / rc.kv_group;  // the K/V head this query head reads
   const int off = rc.off_heads ? rc.off_heads[gk] : 0;
   if (off < 0) {  // a head the caller's precondition excludes: its rows are flagged
     if (WITH_O)
-      for (int e = tid; e < min(kRows, n - row0) * D; e += kThreads)
+      for (int e = tid; e < min(BM, n - row0) * D; e += NT)
         O[((size_t)g * n + row0) * D + e] = __int_as_float(0x7FC00000);
     return;
   }
   const int nk = off + n;
   const float* Kg = K + (size_t)gk * rc.kv_stride * D;
   const float* Vg = V + (size_t)gk * rc.kv_stride * D;
-  lds_char* const strip = (lds_char*)smem + wave * kTileBytes;
+  lds_char* const kbuf = (lds_char*)smem + part * 2 * kTileBytes;
+  lds_char* const vbuf = kbuf + kTileBytes;  // (without outputs: a second K buffer)
 
-  const int last_key = off + min(n, row0 + kRows) - 1;
-  const int ntiles = last_key / kRows + 1;
-  if (wave < ntiles) fetch_tile<D, false>(Kg, wave * kRows, nk, strip);
-  // Q (B operand): lane (query l32, half h) holds the elements 8c + 4h .. + 3
-  f32x4 qf[C8];
+  const int ntiles = (off + min(n, row0 + BM) - 1) / kRows + 1;
+  const int nt_wave = wrow0 < n ? (off + min(n, wrow0 + kRows) - 1) / kRows + 1 : 0;  // tiles this wave's rows see
+  if (part < ntiles) fetch_tile<D, false>(Kg, part * kRows, nk, kbuf, block, RB);
+  // Q (B operand): lane (query l32, half h) holds the elements 16c + 8h .. + 7
+  Parts qf[C16];
   {
-    const float* qr = Q + ((size_t)g * n + min(row0 + l32, n - 1)) * D + 4 * h;
+    const float* qr = Q + ((size_t)g * n + min(wrow0 + l32, n - 1)) * D + 8 * h;
+    f32x4 raw[2 * C16];
 #pragma unroll
-    for (int c = 0; c < C8; ++c) qf[c] = *reinterpret_cast<const f32x4*>(qr + 8 * c);
+    for (int c = 0; c < 2 * C16; ++c) raw[c] = *reinterpret_cast<const f32x4*>(qr + 16 * (c >> 1) + 4 * (c & 1));
+#pragma unroll
+    for (int c = 0; c < C16; ++c) qf[c] = cut(raw[2 * c], raw[2 * c + 1]);
+#pragma unroll
+    for (int c = 0; c < C16; ++c) asm volatile("" : "+v"(qf[c].high.x));  // formed here, not in every round of the loop
   }
+  int koff[8];  // chunk 4c + 2h + e of row l32: the swizzle reaches the low four chunk bits
 #pragma unroll
-  for (int c = 0; c < C8; ++c) asm volatile("" : "+v"(qf[c]));  // waited for here, not in every round of the loop
-  int koff[C8 < 8 ? C8 : 8];  // chunk 2c + h of row l32: the swizzle reaches the low four chunk bits
-#pragma unroll
-  for (int c = 0; c < 8 && c < C8; ++c) koff[c] = l32 * D * 4 + (((2 * c + h) ^ tile_swizzle<false>(l32)) << 4);
+  for (int i = 0; i < 8; ++i) koff[i] = l32 * D * 4 + (((4 * (i >> 1) + 2 * h + (i & 1)) ^ tile_swizzle<false>(l32)) << 4);
   const int voff[2] = {4 * h * D * 4 + l32 * 4 + h * 128, 4 * h * D * 4 + l32 * 4 + (1 - h) * 128};
 
   f32x16 oacc[WITH_O ? DB : 1];
@@ -179,92 +253,125 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_f32_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
   float m = kLowest, l = 0.f;
-  bool odd = false;  // a V row of a masked tile holds an infinity or a NaN
-  const int newest = off + row0 + l32;  // newest key this lane's row sees
+  const int newest = off + wrow0 + l32;  // newest key this lane's row sees
+  if (tid == 0) again = false;
 
-  for (int t = wave; t < ntiles; t += kWaves) {
-    const int key0 = t * kRows, next = min(t + kWaves, ntiles - 1) * kRows;
-    wait_vm<0>();  // K tile t
-    f32x16 s, s2;  // two sums: no matrix op waits for the one before it, and each rounds half as often
+  for (int t = part, step = 0; t < ntiles + part; t += P, ++step) {  // (the parts take the same number of steps)
+    const int key0 = t * kRows;
+    const bool mine = t < nt_wave;
+    lds_char* const kt = WITH_O || step % 2 == 0 ? kbuf : vbuf;
+    arrived();  // K tile t; the other buffer is free
+    if (WITH_O && t < ntiles) fetch_tile<D, true>(Vg, key0, nk, vbuf, block, RB);
+    if (!WITH_O && t + P < ntiles) fetch_tile<D, false>(Kg, key0 + P * kRows, nk, kt == kbuf ? vbuf : kbuf, block, RB);
+    Parts pf[2];
+    if (mine) {
+      f32x16 s, rest;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = s2[i] = 0.f;
+      for (int i = 0; i < 16; ++i) s[i] = rest[i] = 0.f;
+      const auto read = [&](int c, f32x4& a, f32x4& b) {
+        a = lds_read4(kt + (c >> 2) * 256 + koff[2 * (c & 3)]);
+        b = lds_read4(kt + (c >> 2) * 256 + koff[2 * (c & 3) + 1]);
+      };
+      f32x4 a, b;
+      read(0, a, b);
 #pragma unroll
-    for (int c = 0; c < C8; ++c) {
-      const f32x4 kf = lds_read4(strip + koff[c & 7] + (c >> 3) * 256);
-#pragma unroll
-      for (int j = 0; j < 4; j += 2) {
-        s = mfma_f32(kf[j], qf[c][j], s);
-        s2 = mfma_f32(kf[j + 1], qf[c][j + 1], s2);
+      for (int c = 0; c < C16; ++c) {
+        const Parts kp = cut(a, b);
+        if (c + 1 < C16) read(c + 1, a, b);
+        multiply(kp, qf[c], s, rest);
+        if (D == 128) __builtin_amdgcn_sched_barrier(0);  // (more pieces at once do not fit the registers)
       }
-    }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] += s2[i];
-    wait_lds();
-    if (WITH_O) fetch_tile<D, true>(Vg, key0, nk, strip);
-    else fetch_tile<D, false>(Kg, next, nk, strip);
-    const bool masked = key0 + kRows - 1 > off + row0;  // the tile reaches past the block's first row
-    if (masked) {
+      for (int i = 0; i < 16; ++i) s[i] += rest[i];
+      if (key0 + kRows - 1 > off + wrow0) {  // the tile reaches past the block's first row
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (key0 + 8 * (i >> 2) + 4 * h + (i & 3) > newest) s[i] = -INFINITY;
-    }
-    float mx = s[0];
+        for (int i = 0; i < 16; ++i)
+          if (key0 + 8 * (i >> 2) + 4 * h + (i & 3) > newest) s[i] = -INFINITY;
+      }
+      float mx = s[0];
 #pragma unroll
-    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
-    mx = across_rows(mx, OpMax(), false, true);
-    const float m_new = fmaxf(m, mx);
-    if (__any(m_new > m)) {
-      const float corr = exp2f((m - m_new) * scale_log2e);
-      l *= corr;
+      for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+      mx = across_rows(mx, OpMax(), false, true);
+      const float m_new = fmaxf(m, mx);
+      if (__any(m_new > m)) {
+        const float corr = exp2f((m - m_new) * scale_log2e);
+        l *= corr;
+        if (WITH_O) {
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) oacc[db][i] *= corr;
+        }
+        m = m_new;
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f((s[i] - m) * scale_log2e);
+      float sum[4];  // (of few terms each before they join the row's)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum[i] = (s[4 * i] + s[4 * i + 1]) + (s[4 * i + 2] + s[4 * i + 3]);
+      l += (sum[0] + sum[1]) + (sum[2] + sum[3]);
       if (WITH_O) {
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+        for (int j = 0; j < 2; ++j) {
+          float x[8];
 #pragma unroll
-          for (int i = 0; i < 16; ++i) oacc[db][i] *= corr;
-      }
-      m = m_new;
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      s[i] = __builtin_amdgcn_exp2f((s[i] - m) * scale_log2e);
-      l += s[i];
-    }
-    if constexpr (WITH_O) {
-      wait_vm<0>();  // V tile t
-      if (masked && clear_nonfinite<D>(strip)) {
-        odd = true;
-        wait_lds();
-      }
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          const float vf = lds_read1(strip + voff[db & 1] + (db >> 1) * 256 + (8 * (i >> 2) + (i & 3)) * D * 4);
-          oacc[db] = mfma_f32(vf, s[i], oacc[db]);
+          for (int i = 0; i < 8; ++i) x[i] = s[8 * j + i];
+          pf[j] = cut(x);
         }
       }
-      wait_lds();
-      fetch_tile<D, false>(Kg, next, nk, strip);
+    }
+    if constexpr (WITH_O) {
+      arrived();  // V tile t; every wave that shares K tile t has read it
+      if (t + P < ntiles) fetch_tile<D, false>(Kg, key0 + P * kRows, nk, kbuf, block, RB);
+      if (mine) {
+        constexpr int NV = 2 * DB;  // (columns 32 db .., step j), j fastest
+        float x[8];
+        const auto read = [&](int v) {
+          const int db = v >> 1, j = v & 1;
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            x[i] = lds_read1(vbuf + voff[db & 1] + (db >> 1) * 256 + (16 * j + 8 * (i >> 2) + (i & 3)) * D * 4);
+        };
+        f32x16 o;  // of this tile alone: rounded at its own size before it joins the others
+        read(0);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          if (v % 2 == 0) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[i] = 0.f;
+          }
+          const Parts vp = cut(x);
+          if (v + 1 < NV) read(v + 1);
+          multiply(vp, pf[v & 1], o, o);
+          if (v % 2 == 1) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) oacc[v >> 1][i] += o[i];
+          }
+          if (D == 128) __builtin_amdgcn_sched_barrier(0);
+        }
+      }
     }
   }
-  wait_vm<0>();  // the strip is reused below
+  wait_vm_barrier<0>();  // the buffers are reused below
 
-  // ---- the four waves' parts of the 32 rows
+  // ---- the parts' sums
   l = across_rows(l, OpAdd(), false, true);
   if (h == 0) { m_s[wave][l32] = m; l_s[wave][l32] = l; }
-  if (WITH_O && lane == 0) odd_s[wave] = odd;
   __syncthreads();
-  float mall = m_s[0][l32];
+  float mall = m_s[block][l32];
 #pragma unroll
-  for (int w = 1; w < kWaves; ++w) mall = fmaxf(mall, m_s[w][l32]);
+  for (int w = 1; w < P; ++w) mall = fmaxf(mall, m_s[block + RB * w][l32]);
   float lall = 0.f;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) lall += l_s[w][l32] * exp2f((m_s[w][l32] - mall) * scale_log2e);
-  if (wave == 0 && h == 0 && row0 + l32 < n)
-    LSE2[(size_t)g * n + row0 + l32] = fmaf(mall, scale_log2e, log2f(lall));
+  for (int w = 0; w < P; ++w) lall += l_s[block + RB * w][l32] * exp2f((m_s[block + RB * w][l32] - mall) * scale_log2e);
+  if (part == 0 && h == 0 && wrow0 + l32 < n) {
+    LSE2[(size_t)g * n + wrow0 + l32] = fmaf(mall, scale_log2e, log2f(lall));
+    if (!(lall < INFINITY)) again = true;
+  }
   if constexpr (WITH_O) {
     const float f = exp2f((m - mall) * scale_log2e) / lall;
-    // the strip now takes the wave's outputs, [query][d], chunks swizzled as in a tile
+    // a tile's room per wave now takes its outputs, [query][d], chunks swizzled as in a tile
+    lds_char* const strip = (lds_char*)smem + wave * kTileBytes;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -277,34 +384,36 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 2) void attn_f32_kernel(
       }
     __syncthreads();
     constexpr int CPR = D / 4;
-    for (int u = tid; u < kRows * CPR; u += kThreads) {
+    for (int u = tid; u < BM * CPR; u += NT) {
       const int r = u / CPR, c = u % CPR;
       if (row0 + r >= n) break;
       const lds_char* p = (const lds_char*)smem + r * D * 4 + ((c ^ tile_swizzle<false>(r)) << 4);
-      const f32x4 a = (lds_read4(p) + lds_read4(p + kTileBytes)) +
-                      (lds_read4(p + 2 * kTileBytes) + lds_read4(p + 3 * kTileBytes));
+      f32x4 a = lds_read4(p) + lds_read4(p + RB * kTileBytes);
+#pragma unroll
+      for (int w = 2; w < P; w += 2) a += lds_read4(p + RB * w * kTileBytes) + lds_read4(p + RB * (w + 1) * kTileBytes);
       *reinterpret_cast<f32x4*>(O + ((size_t)g * n + row0 + r) * D + c * 4) = a;
-    }
-    if (odd_s[0] || odd_s[1] || odd_s[2] || odd_s[3]) {
-      __syncthreads();
-      add_nonfinite<D>(Q + (size_t)g * n * D, Kg, Vg, LSE2 + (size_t)g * n, O + (size_t)g * n * D, row0, n, off,
-                       (off + row0) / kRows * kRows, scale_log2e);
+      if (!(fabsf(a[0] * 0.f) + fabsf(a[1] * 0.f) + fabsf(a[2] * 0.f) + fabsf(a[3] * 0.f) == 0.f)) again = true;
     }
   }
+  __syncthreads();
+  if (again && tid < kThreads)
+    rows_again<D, WITH_O>(Q + (size_t)g * n * D, Kg, Vg, LSE2 + (size_t)g * n, O + (size_t)g * n * D, row0,
+                          min(n, row0 + BM), off, scale_log2e, reinterpret_cast<float*>(smem));
 }
 
-// One workgroup per 32 keys, whose K rows stay in registers; wave w takes every fourth tile of 32
+// One workgroup per 32 keys, whose K rows stay in registers; wave w takes every NW-th tile of 32
 // query rows of the head's kv_group query heads.  `accumulate`: the result is added to `decay`
 // times what scores[] holds (a chunk: the cached tokens' older scores, decayed by alpha^m);
 // otherwise it replaces it.
-template <int D>
-__global__ __launch_bounds__(kThreads, 2) void scores_f32_kernel(
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void scores_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ LSE2,
     AttnRect rc, int G, int ncb, int first_row, float log2_alpha, const float* __restrict__ alpha_heads,
     float* __restrict__ scores, int s_stride, bool accumulate, float decay, float scale_log2e) {
-  constexpr int C8 = D / 8, kTileBytes = kRows * D * 4;
-  __shared__ __attribute__((aligned(1024))) char smem[kWaves * kTileBytes];
-  __shared__ float part[kWaves][kRows];
+  constexpr int C16 = D / 16, kTileBytes = kRows * D * 4;
+  __shared__ __attribute__((aligned(1024))) char smem[NW * kTileBytes];
+  __shared__ float part[NW][kRows];
+  __shared__ bool again;
   int g, rank;
   if (!ordered_item(G, ncb, g, rank)) return;
   const int c0 = rank * kRows;  // the oldest keys have the most rows
@@ -328,42 +437,43 @@ __global__ __launch_bounds__(kThreads, 2) void scores_f32_kernel(
     fetch_tile<D, false>(Qg + (size_t)hq * n * D, t * kRows, n, qt);
   };
   if (wave < work) fetch(wave);
-  f32x4 kf[C8];  // A operand: lane (key l32, half h) holds the elements 8c + 4h .. + 3
+  Parts kf[C16];  // A operand: lane (key l32, half h) holds the elements 16c + 8h .. + 7
+  const int key = min(c0 + l32, nk - 1);
   {
-    const float* kr = K + ((size_t)g * rc.kv_stride + min(c0 + l32, nk - 1)) * D + 4 * h;
+    const float* kr = K + ((size_t)g * rc.kv_stride + key) * D + 8 * h;
+    f32x4 raw[2 * C16];
 #pragma unroll
-    for (int c = 0; c < C8; ++c) kf[c] = *reinterpret_cast<const f32x4*>(kr + 8 * c);
+    for (int c = 0; c < 2 * C16; ++c) raw[c] = *reinterpret_cast<const f32x4*>(kr + 16 * (c >> 1) + 4 * (c & 1));
+#pragma unroll
+    for (int c = 0; c < 2 * C16; ++c) asm volatile("" : "+v"(raw[c]));  // waited for here, not in every round of the loop
+#pragma unroll
+    for (int c = 0; c < C16; ++c) kf[c] = cut(raw[2 * c], raw[2 * c + 1]);
   }
+  int qoff[8];
 #pragma unroll
-  for (int c = 0; c < C8; ++c) asm volatile("" : "+v"(kf[c]));  // waited for here, not in every round of the loop
-  int qoff[C8 < 8 ? C8 : 8];
-#pragma unroll
-  for (int c = 0; c < 8 && c < C8; ++c) qoff[c] = l32 * D * 4 + (((2 * c + h) ^ tile_swizzle<false>(l32)) << 4);
+  for (int i = 0; i < 8; ++i) qoff[i] = l32 * D * 4 + (((4 * (i >> 1) + 2 * h + (i & 1)) ^ tile_swizzle<false>(l32)) << 4);
+  if (tid == 0) again = false;
   float acc[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 
-  for (int f = wave; f < work; f += kWaves) {
+  for (int f = wave; f < work; f += NW) {
     const int hq = f / nt, r = (t0 + f % nt) * kRows + l32;
     float lse = lg[(size_t)hq * n + min(r, n - 1)];
     asm volatile("" : "+v"(lse));  // with the tile: everything has arrived
     wait_vm<0>();
-    f32x16 s, s2;
+    f32x16 s, rest;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = s2[i] = 0.f;
+    for (int i = 0; i < 16; ++i) s[i] = rest[i] = 0.f;
 #pragma unroll
-    for (int c = 0; c < C8; ++c) {
-      const f32x4 qf = lds_read4(qt + qoff[c & 7] + (c >> 3) * 256);
-#pragma unroll
-      for (int j = 0; j < 4; j += 2) {
-        s = mfma_f32(kf[c][j], qf[j], s);
-        s2 = mfma_f32(kf[c][j + 1], qf[j + 1], s2);
-      }
+    for (int c = 0; c < C16; ++c) {
+      const lds_char* p = qt + (c >> 2) * 256;
+      multiply(kf[c], cut(lds_read4(p + qoff[2 * (c & 3)]), lds_read4(p + qoff[2 * (c & 3) + 1])), s, rest);
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] += s2[i];
+    for (int i = 0; i < 16; ++i) s[i] += rest[i];
     wait_lds();
-    if (f + kWaves < work) fetch(f + kWaves);
+    if (f + NW < work) fetch(f + NW);
     // exponent offset of row r: lse_r - (n-1-r) log2(alpha); rows past the end, and rows whose
     // weight is exactly 0 in fp32 (before first_row), add nothing
     const bool counts = r < n && r >= first_row;
@@ -371,8 +481,7 @@ __global__ __launch_bounds__(kThreads, 2) void scores_f32_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const float p = exp2f(fmaf(s[i], scale_log2e, -lse) + w);
-      const int key = c0 + 8 * (i >> 2) + 4 * h + (i & 3);
-      acc[i] += counts && key <= off + r ? p : 0.f;
+      acc[i] += counts && c0 + 8 * (i >> 2) + 4 * h + (i & 3) <= off + r ? p : 0.f;
     }
   }
 #pragma unroll
@@ -381,10 +490,31 @@ __global__ __launch_bounds__(kThreads, 2) void scores_f32_kernel(
     if (l32 == 0) part[wave][8 * (i >> 2) + 4 * h + (i & 3)] = acc[i];
   }
   __syncthreads();
+  float older = 0.f;
   if (tid < kRows && c0 + tid < nk) {
-    const float sum = (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; w += 4) sum += (part[w][tid] + part[w + 1][tid]) + (part[w + 2][tid] + part[w + 3][tid]);
     float* out = scores + (size_t)g * s_stride + c0 + tid;
+    if (accumulate) older = decay * *out;
     *out = accumulate ? fmaf(decay, *out, sum) : sum;
+    if (!(sum < INFINITY)) again = true;
+  }
+  __syncthreads();
+  if (!again || tid >= kThreads) return;
+  // in plain arithmetic (see rows_again)
+#pragma unroll 1
+  for (int x = 0; x < min(kRows, nk - c0); ++x) {
+    const float* kj = K + ((size_t)g * rc.kv_stride + c0 + x) * D;
+    float sum = 0.f;
+#pragma unroll 1
+    for (int hq = 0; hq < rc.kv_group; ++hq)
+#pragma unroll 1
+      for (int i = max(max(c0 + x - off, first_row), 0) + tid; i < n; i += kThreads)
+        sum += exp2f(fmaf(dot_row<D>(Qg + ((size_t)hq * n + i) * D, kj), scale_log2e, -lg[(size_t)hq * n + i]) +
+                     (float)(n - 1 - i) * log2_alpha);
+    sum = block_sum(sum, &part[0][0]);
+    if (tid == x) scores[(size_t)g * s_stride + c0 + x] = older + sum;
   }
 }
 
@@ -393,19 +523,6 @@ __global__ __launch_bounds__(kThreads, 2) void scores_f32_kernel(
 // prompt has of it.  A short prompt of few heads is done sooner by plain arithmetic: a workgroup per attention row, then one
 // per key (square geometry only).
 constexpr int kShortRows = 512;  // of a prompt, at most
-
-template <int D>
-__device__ __forceinline__ float dot_row(const float* __restrict__ a, const float* __restrict__ b) {
-  float acc = 0.f;
-#pragma unroll
-  for (int c = 0; c < D; c += 4) {
-    const float4 x = *reinterpret_cast<const float4*>(a + c);
-    const float4 y = *reinterpret_cast<const float4*>(b + c);
-    acc = fmaf(x.x, y.x, acc); acc = fmaf(x.y, y.y, acc);
-    acc = fmaf(x.z, y.z, acc); acc = fmaf(x.w, y.w, acc);
-  }
-  return acc;
-}
 
 template <int D>
 __global__ __launch_bounds__(kThreads) void attn_rows_f32_kernel(
@@ -505,16 +622,34 @@ void launch_attn_f32(const float* q, const float* k, const float* v, int G, cons
     else hipLaunchKernelGGL(attn_rows_f32_kernel<128>, rows, dim3(kThreads), 0, st, q, k, v, rc, o, lse2, scale_log2e);
     return;
   }
-  const int nqb = (rc.m + kRows - 1) / kRows - rc.first_row / kRows;  // row blocks to compute
-  const unsigned grid = ordered_grid(GQ, nqb);
-#define A2SF_ATTN_F32(D, WO)                                                                          \
-  hipLaunchKernelGGL((attn_f32_kernel<D, WO>), dim3(grid), dim3(kThreads), 0, st, q, k, v, rc, GQ, nqb, o, \
-                     lse2, scale_log2e)
+  const auto blocks = [&](int rows) { return (rc.m + rows - 1) / rows - rc.first_row / rows; };  // row blocks to compute
+#define A2SF_ATTN_F32(D, WO, RB, NW)                                                                  \
+  hipLaunchKernelGGL((attn_f32_kernel<D, WO, RB, NW>), dim3(ordered_grid(GQ, blocks(kRows * RB))), dim3(NW * 64), 0, st, \
+                     q, k, v, rc, GQ, blocks(kRows * RB), o, lse2, scale_log2e)
+#define A2SF_ATTN_F32_64(WO)                             \
+  do {                                                   \
+    if (all <= 320) A2SF_ATTN_F32(64, WO, 1, 8);         \
+    else if (all <= 1024) A2SF_ATTN_F32(64, WO, 1, 4);   \
+    else A2SF_ATTN_F32(64, WO, 2, 4);                    \
+  } while (0)
+#define A2SF_ATTN_F32_128(WO)                            \
+  do {                                                   \
+    if (all <= 640) A2SF_ATTN_F32(128, WO, 1, 4);        \
+    else A2SF_ATTN_F32(128, WO, 2, 4);                   \
+  } while (0)
+  // Two blocks of rows per workgroup share a tile's loads and put two waves onto every SIMD; while the blocks are few, the chain
+  // of a row's tiles counts, and one block takes all waves (us, one block with eight waves / with four / two blocks: d = 64,
+  // 76 blocks of 32 rows 12.7 / 14.0 / 22.4, 228 14.1 / 17.2 / 27.2, 580 33.5 / 28.0 / 39.8, 1000 35.4 / 25.8 / 28.8, 2000 86.6 /
+  // 66.3 / 61.2, 2820 178 / 147 / 133; d = 128, four waves / two blocks: 38 blocks 41.4 / 73.0, 377 43.6 / 59.7, 752 105.7 / 105.2,
+  // 760 81.4 / 66.7, 1024 102 / 80, 5943 270 / 152.  Eight waves of d = 128 have no registers for the parts).
+  const long long all = (long long)GQ * blocks(kRows);
   if (d == 64) {
-    if (o) A2SF_ATTN_F32(64, true); else A2SF_ATTN_F32(64, false);
+    if (o) A2SF_ATTN_F32_64(true); else A2SF_ATTN_F32_64(false);
   } else {
-    if (o) A2SF_ATTN_F32(128, true); else A2SF_ATTN_F32(128, false);
+    if (o) A2SF_ATTN_F32_128(true); else A2SF_ATTN_F32_128(false);
   }
+#undef A2SF_ATTN_F32_64
+#undef A2SF_ATTN_F32_128
 #undef A2SF_ATTN_F32
 }
 
@@ -536,13 +671,20 @@ void launch_colscores_f32(const float* q, const float* k, const float* lse2, int
     return;
   }
   const int ncb = (keys_per_head + kRows - 1) / kRows;
-  const unsigned grid = ordered_grid(G, ncb);
-  if (d == 64)
-    hipLaunchKernelGGL(scores_f32_kernel<64>, dim3(grid), dim3(kThreads), 0, st, q, k, lse2, rc, G, ncb, first,
-                       l2a, alpha_heads, scores, s_stride, accumulate, decay, scale_log2e);
-  else
-    hipLaunchKernelGGL(scores_f32_kernel<128>, dim3(grid), dim3(kThreads), 0, st, q, k, lse2, rc, G, ncb, first,
-                       l2a, alpha_heads, scores, s_stride, accumulate, decay, scale_log2e);
+#define A2SF_SCORES_F32(D, NW)                                                                        \
+  hipLaunchKernelGGL((scores_f32_kernel<D, NW>), dim3(ordered_grid(G, ncb)), dim3(NW * 64), 0, st, q, k, lse2, rc, G, ncb, first, \
+                     l2a, alpha_heads, scores, s_stride, accumulate, decay, scale_log2e)
+  // Eight waves where the keys are few and every wave has a tile (us, eight waves / four: d = 128, 38 blocks of 32 keys x 33 tiles 20.7
+  // / 27.8, 94 x 376 150 / 230, 256 x 32 22.6 / 27.1, but 264 x 2 17.3 / 11.1, 377 x 3 17.8 / 11.5, 1024 x 3 36 / 22; d = 64, 228 x
+  // 8 7.8 / 8.6, 111 x 24 11.5 / 17.5, 580 x 29 25.9 / 21.0).
+  const int tiles = ((rc.m + kRows - 1) / kRows - first / kRows) * rc.kv_group;
+  const bool few = (long long)G * ncb <= 320 && tiles >= 8;
+  if (d == 64) {
+    if (few) A2SF_SCORES_F32(64, 8); else A2SF_SCORES_F32(64, 4);
+  } else {
+    if (few) A2SF_SCORES_F32(128, 8); else A2SF_SCORES_F32(128, 4);
+  }
+#undef A2SF_SCORES_F32
 }
 
 void launch_prefill_f32(const float* q, const float* k, const float* v, int G, int n, int d,

@@ -134,3 +134,31 @@ def test_selection_among_nan_scores(L):
         for g in range(5):
             want = np.sort(np.lexsort((np.arange(L), -order[g].astype(np.int64)))[: select + recent])
             assert int(n_keep[g]) == select + recent and np.array_equal(keep[g].cpu().numpy(), want), g
+
+
+@pytest.mark.parametrize("d,G,n,cached", [(64, 4, 90, 0), (64, 60, 200, 0), (64, 260, 130, 0), (128, 5, 100, 0), (128, 200, 130, 0),
+                                          (64, 300, 70, 50), (128, 300, 70, 50)])
+def test_fp32_infinite_operands(d, G, n, cached):
+    """Infinities in K and V, finite values at the end of the range: the parts of a number whose products the matrix ops sum
+    are finite for every finite number, and what an infinity does is what plain arithmetic does.  Every launch form."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    total = cached + n
+    q, k, v = rnd(G, 1, n, d), rnd(G, total, d), rnd(G, total, d)
+    at = total - 20
+    q[0, ..., 0], k[0, at, 0] = 1.0, -float("inf")       # a key that no row gives weight
+    v[1, at, 3] = 3.402823e38                            # (the largest bf16 number is smaller)
+    v[2, at, 5] = -float("inf")
+    k[3, at, 1] = float("nan")
+    o = chunk(q, k, v, cached) if cached else prefill(q, k, v)[0]
+    got = o[:4].double().cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        want = rows_by_hand(q[:4], k[:4], v[:4], cached)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(np.where(np.isinf(want), want, 0.0), np.where(np.isinf(got), got, 0.0))
+    finite = np.isfinite(want)
+    scale = np.maximum(1.0, np.abs(np.where(finite, want, 0.0)))
+    assert np.abs((np.where(finite, got, 0.0) - np.where(finite, want, 0.0)) / scale).max() <= parity.O_TOL["f32"]
+    if not cached:
+        s = prefill(q, k, v)[1]
+        assert torch.isfinite(s[:3]).all() and s[0, at] == 0.0 and torch.isnan(s[3, at:]).any()

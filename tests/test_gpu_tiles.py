@@ -540,3 +540,13 @@ def test_stable_step_evicts_in_place(dtype, d, group, budget):
     # (the budget takes its part of the workspace, which decides how many workgroups share a head: fp32 summation order)
     assert torch.allclose(small.scores[live], large.scores[live], rtol=1e-5, atol=0.0)
     assert (o.float() - o2.float()).abs().max().item() <= parity.O_TOL[dtype]
+
+
+@pytest.mark.parametrize("d,G,n", [(64, 20, 512), (64, 21, 489), (64, 64, 512), (64, 65, 481), (64, 300, 40), (64, 40, 1000),
+                                   (128, 40, 512), (128, 41, 481), (128, 321, 63), (128, 130, 200)])
+def test_fp32_forms_of_the_prompt_kernels(d, G, n):
+    """One block of rows per workgroup with eight waves, with four, two blocks; eight or four waves for the scores (by the
+    window of alpha): both sides of every rule."""
+    for alpha in (0.02, 1.0):
+        prompt_and_steps(variant(0, heads=G, d=d, n=n, T=1, select=min(11, n), recent=9, name="fp32 forms"), alpha,
+                         sample=sorted({0, G // 2, G - 1}), steps=1)

@@ -1,4 +1,5 @@
-"""ctypes binding of liba2sf.so - argument marshalling only.
+"""Binding of liba2sf.so - argument marshalling only: through ctypes, and for the plain calls of a serving loop (tensors,
+ints, floats, a Cache) through the host extension _call.so, which does the same without the interpreter.
 
 Every function has the name and the arguments of its C entry point (include/a2sf.h).
 torch tensors are accepted wherever the C side takes a device pointer; torch is used for
@@ -39,11 +40,12 @@ class CacheStruct(ctypes.Structure):
 
 
 _lib = None
+_call = None  # the extension, loaded with the library
 
 
 def lib() -> ctypes.CDLL:
     """The loaded shared library; raises if it has not been built."""
-    global _lib
+    global _lib, _call
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
@@ -96,6 +98,15 @@ def lib() -> ctypes.CDLL:
                                        ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.a2sf_status_string.restype = ctypes.c_char_p
         L.a2sf_status_string.argtypes = [i32]
+        if _call is None:
+            try:
+                from . import _call as extension
+            except ImportError as e:
+                raise RuntimeError(f"{os.path.join(_HERE, '_call.so')} is missing or does not load ({e}): build it with "
+                                   "`python -m paper_2407_20485_amd.build` (there is no fallback path)") from e
+            extension.init(Cache, torch.float32, torch.bfloat16, _raw_stream if _get_device else None, _get_device)
+            _call = extension
+        L.at = {name: ctypes.cast(getattr(L, name), vp).value for name in EXPORTS}
         _lib = L
     return _lib
 
@@ -106,8 +117,8 @@ class A2SFError(RuntimeError):
         super().__init__(f"a2sf status {status}: {a2sf_status_string(status)}")
 
 
-# The generation step of a few heads takes 7 us on the GPU: the marshalling below is on its critical
-# path (32 heads x 205 slots, calls back to back: 14.6 us per call before, 11.5 after).
+# The generation step of a few heads takes 7 us on the GPU: the marshalling is on its critical path.  _call takes the calls
+# whose arguments are plain and answers -1, having done nothing, to all others; those go through the ctypes form below.
 _Tensor = torch.Tensor
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # (absent in builds without a GPU backend)
 _get_device = getattr(torch._C, "_cuda_getDevice", None)
@@ -125,6 +136,10 @@ def _stream(stream):
     if _raw_stream is not None and torch.cuda.is_initialized():
         return _raw_stream(_get_device())
     return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
+
+
+def _entry(name: str) -> int:
+    return (_lib or lib()).at[name]
 
 
 def _check(status: int):
@@ -183,6 +198,11 @@ def a2sf_workspace_bytes(G, n_max, capacity, d, dtype, select, recent) -> int:
 
 def a2sf_prefill(q, k, v, n, alpha, select, recent, cache, o=None, scores_full=None,
                  workspace=None, workspace_bytes=None, stream=None):
+    at = _entry("a2sf_prefill")
+    status = _call.prefill(at, q, k, v, n, None, alpha, select, recent, cache, o, scores_full, workspace,
+                           workspace_bytes, stream)
+    if status >= 0:
+        return _check(status)
     cs = _cache_struct(cache)
     if workspace_bytes is None:
         workspace_bytes = workspace.nbytes if workspace is not None else 0
@@ -203,6 +223,11 @@ def a2sf_prefill_windowed(q, k, v, n, alpha, score_rel_tol, select, recent, cach
 
 def a2sf_prefill_chunk(q, k, v, m, pos0, alpha, select, recent, cache, o=None, workspace=None,
                        workspace_bytes=None, stream=None):
+    at = _entry("a2sf_prefill_chunk")
+    status = _call.prefill_chunk(at, q, k, v, m, pos0, None, alpha, select, recent, cache, o,
+                                 workspace, workspace_bytes, stream)
+    if status >= 0:
+        return _check(status)
     cs = _cache_struct(cache)
     if workspace_bytes is None:
         workspace_bytes = workspace.nbytes if workspace is not None else 0
@@ -213,6 +238,11 @@ def a2sf_prefill_chunk(q, k, v, m, pos0, alpha, select, recent, cache, o=None, w
 
 def a2sf_prefill_chunk_gqa(q, k, v, m, pos0, group, alpha, select, recent, cache, o=None, workspace=None,
                            workspace_bytes=None, stream=None):
+    at = _entry("a2sf_prefill_chunk_gqa")
+    status = _call.prefill_chunk(at, q, k, v, m, pos0, group, alpha, select, recent, cache, o,
+                                 workspace, workspace_bytes, stream)
+    if status >= 0:
+        return _check(status)
     cs = _cache_struct(cache)
     if workspace_bytes is None:
         workspace_bytes = workspace.nbytes if workspace is not None else 0
@@ -223,6 +253,11 @@ def a2sf_prefill_chunk_gqa(q, k, v, m, pos0, group, alpha, select, recent, cache
 
 def a2sf_prefill_gqa(q, k, v, n, group, alpha, select, recent, cache, o=None, scores_full=None,
                      workspace=None, workspace_bytes=None, stream=None):
+    at = _entry("a2sf_prefill_gqa")
+    status = _call.prefill(at, q, k, v, n, group, alpha, select, recent, cache, o, scores_full,
+                           workspace, workspace_bytes, stream)
+    if status >= 0:
+        return _check(status)
     cs = _cache_struct(cache)
     if workspace_bytes is None:
         workspace_bytes = workspace.nbytes if workspace is not None else 0
@@ -233,6 +268,11 @@ def a2sf_prefill_gqa(q, k, v, n, group, alpha, select, recent, cache, o=None, sc
 
 def a2sf_decode_step_gqa(q, k_new, v_new, t_pos, cache, group, alpha, select, recent, o,
                          mode=A2SF_EVICT_FAST, workspace=None, workspace_bytes=None, stream=None):
+    at = _entry("a2sf_decode_step_gqa")
+    status = _call.decode_step(at, q, k_new, v_new, t_pos, cache, group, alpha, select, recent, o,
+                               mode, workspace, workspace_bytes, stream)
+    if status >= 0:
+        return _check(status)
     cs = _cache_struct(cache)
     if workspace_bytes is None:
         workspace_bytes = workspace.nbytes if workspace is not None else 0
@@ -243,6 +283,11 @@ def a2sf_decode_step_gqa(q, k_new, v_new, t_pos, cache, group, alpha, select, re
 
 def a2sf_decode_step(q, k_new, v_new, t_pos, cache, alpha, select, recent, o,
                      mode=A2SF_EVICT_FAST, workspace=None, workspace_bytes=None, stream=None):
+    at = _entry("a2sf_decode_step")
+    status = _call.decode_step(at, q, k_new, v_new, t_pos, cache, None, alpha, select, recent, o, mode,
+                               workspace, workspace_bytes, stream)
+    if status >= 0:
+        return _check(status)
     cs = _cache_struct(cache)
     if workspace_bytes is None:
         workspace_bytes = workspace.nbytes if workspace is not None else 0

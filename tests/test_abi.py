@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2407_20485_amd import binding as B
 
@@ -218,3 +219,32 @@ def test_ideal_similarity_argument_errors():
     assert f(FAKE, FAKE, 16, -1, ctypes.byref(ok_cache), FAKE, None) == B.A2SF_ESHAPE
     assert f(FAKE, FAKE, 16, 3, ctypes.byref(fake_cache(d=96)), FAKE, None) == B.A2SF_ESHAPE
     assert f(FAKE, FAKE, 16, 3, None, FAKE, None) == B.A2SF_EINVAL
+
+
+def test_extension_leaves_unusual_arguments_to_ctypes():
+    """Nothing is called, and nothing raised, for what the extension does not take; what it is given as plain and is wrong
+    on the host comes back as the entry point's status."""
+    B.lib()
+    at = B._entry("a2sf_decode_step")
+    c = B.Cache(2, 12, 64, torch.float32, device="cpu")
+    q = torch.zeros(2, 64)
+    good = dict(q=q, k=q, v=q, t=5, cache=c, group=None, alpha=0.3, select=4, recent=4, o=q, mode=0, ws=None, nbytes=None, stream=None)
+    call = lambda **over: B._call.decode_step(at, *{**good, **over}.values())
+    assert call() == -1  # no tensor on a GPU: the stream is not known
+
+    class Sub(torch.Tensor):
+        pass
+
+    for over in (dict(q=q.as_subclass(Sub)), dict(q=FAKE), dict(t=5.0), dict(t=True), dict(t=1 << 40), dict(alpha=1), dict(alpha="x"),
+                 dict(cache=fake_cache()), dict(group=2.0), dict(nbytes=-1), dict(nbytes=1 << 70), dict(ws=FAKE), dict(stream=7), dict(o=3.5)):
+        assert call(**over) == -1, over
+    broken = B.Cache(2, 12, 64, torch.float32, device="cpu")
+    for name, value in (("dtype", torch.float16), ("G", 2.0), ("k", None), ("pos", 7)):
+        was = getattr(broken, name)
+        setattr(broken, name, value)
+        assert call(cache=broken) == -1
+        setattr(broken, name, was)
+    del broken.len
+    assert call(cache=broken) == -1
+    with pytest.raises(TypeError):
+        B._call.decode_step(at, q)

@@ -550,3 +550,41 @@ def test_fp32_forms_of_the_prompt_kernels(d, G, n):
     for alpha in (0.02, 1.0):
         prompt_and_steps(variant(0, heads=G, d=d, n=n, T=1, select=min(11, n), recent=9, name="fp32 forms"), alpha,
                          sample=sorted({0, G // 2, G - 1}), steps=1)
+
+
+@pytest.mark.parametrize("group", [1, 3])
+def test_calls_through_the_extension_and_through_ctypes(group):
+    """The same calls with a Cache (marshalled by the extension) and with the struct of another cache (ctypes), on a
+    stream of their own: the same results bit for bit, and errors with the same status."""
+    G, n, d, select, recent = 3, 150, 64, 20, 12
+    gen = torch.Generator(device="cuda").manual_seed(group)
+    qs = (G, n, d) if group == 1 else (G, group, n, d)
+    q, k, v = (torch.randn(s, generator=gen, device="cuda").bfloat16() for s in (qs, (G, n, d), (G, n, d)))
+    step = [torch.randn(s, generator=gen, device="cuda").bfloat16() for s in ((G, d) if group == 1 else (G, group, d), (G, d), (G, d))]
+    bytes_ = a2sf.a2sf_workspace_bytes(G * group, n, select + recent + n, d, a2sf.A2SF_BF16, select, recent)
+    results, stream = [], torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    for struct in (False, True):
+        with torch.cuda.stream(stream):
+            cache = a2sf.Cache(G, select + recent + n, d, torch.bfloat16)
+            c = cache.struct() if struct else cache
+            ws = torch.empty(bytes_, dtype=torch.uint8, device="cuda")
+            o, full, o1 = torch.empty_like(q), torch.empty(G, n, device="cuda"), torch.empty_like(step[0])
+            kw = dict(workspace=ws)
+            if group == 1:
+                a2sf.a2sf_prefill(q, k, v, n, 0.5, select, recent, c, o=o, scores_full=full, **kw)
+                a2sf.a2sf_prefill_chunk(q, k, v, n, n, 0.5, select, recent, c, o=o, workspace_bytes=bytes_, **kw)
+                a2sf.a2sf_decode_step(*step, 2 * n, c, 0.5, select, recent, o1, mode=a2sf.A2SF_EVICT_STABLE, **kw)
+            else:
+                a2sf.a2sf_prefill_gqa(q, k, v, n, group, 0.5, select, recent, c, o=o, scores_full=full, **kw)
+                a2sf.a2sf_prefill_chunk_gqa(q, k, v, n, n, group, 0.5, select, recent, c, o=o, workspace_bytes=bytes_, **kw)
+                a2sf.a2sf_decode_step_gqa(*step, 2 * n, c, group, 0.5, select, recent, o1, mode=a2sf.A2SF_EVICT_STABLE, **kw)
+            for bad, status in ((dict(n=0), 2), (dict(alpha=1.5), 1), (dict(q=None), 1), (dict(ws=ws[:16]), 5)):
+                a = {**dict(q=q, n=n, alpha=0.5, ws=ws), **bad}
+                with pytest.raises(a2sf.A2SFError) as e:
+                    a2sf.a2sf_prefill(a["q"], k, v, a["n"], a["alpha"], select, recent, c, workspace=a["ws"])
+                assert e.value.status == status
+        stream.synchronize()
+        assert cache.len.tolist() == [select + recent] * G
+        results.append([o, full, o1] + [t[:, : select + recent] for t in cache.tensors()[:4]])
+    assert all(torch.equal(x, y) for x, y in zip(*results))

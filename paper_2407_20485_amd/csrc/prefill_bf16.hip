@@ -1323,28 +1323,33 @@ __global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_sco
   for (int b = 0; b < KB; ++b)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[b][i] = group_sum<32>(acc[b][i]);
-  const auto each_key = [&](auto f) {  // by the lanes that hold the sums
-    if (l32 == 0) {
+  // Every lane of a half has the half's 16 sums per block; sixteen of them take one each, so that the scores leave in one store.
+  float sum[KB];
 #pragma unroll
-      for (int b = 0; b < KB; ++b)
+  for (int b = 0; b < KB; ++b) {
+    sum[b] = acc[b][0];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) f(b * 32 + 8 * (i >> 2) + 4 * h + (i & 3), acc[b][i]);
-    }
-  };
-  const int w0 = wave * 32 * KB;
+    for (int i = 1; i < 16; ++i) sum[b] = (lane & 15) == i ? acc[b][i] : sum[b];
+  }
+  const int key_l = 8 * ((lane & 15) >> 2) + 4 * h + (lane & 3), w0 = wave * 32 * KB;
   if constexpr (RS > 1) {
-    if (part == 1) each_key([&](int key, float x) { other[w0 + key] = x; });
+    if (part == 1 && l32 < 16) {
+#pragma unroll
+      for (int b = 0; b < KB; ++b) other[w0 + b * 32 + key_l] = sum[b];
+    }
     __syncthreads();
     if (part == 1) return;
   }
-  each_key([&](int key, float x) {
-    if (RS > 1) x += other[w0 + key];
-    if (wc0 + key < nk) {
-      float* out = S + (size_t)g * s_stride + wc0 + key;
-      *out = accumulate && wc0 + key < off ? fmaf(decay, *out, x) : x;
-      if (rc.pos && wc0 + key >= off) rc.pos[(size_t)g * rc.kv_stride + wc0 + key] = rc.pos0 + wc0 + key - off;
-    }
-  });
+  if (l32 >= 16) return;
+#pragma unroll
+  for (int b = 0; b < KB; ++b) {
+    const int key = wc0 + b * 32 + key_l;
+    if (key >= nk) continue;
+    const float x = RS > 1 ? sum[b] + other[w0 + b * 32 + key_l] : sum[b];
+    float* out = S + (size_t)g * s_stride + key;
+    *out = accumulate && key < off ? fmaf(decay, *out, x) : x;
+    if (rc.pos && key >= off) rc.pos[(size_t)g * rc.kv_stride + key] = rc.pos0 + key - off;
+  }
 }
 
 // Workgroups per head of col_scores_tail_kernel: with fewer heads than the chip takes

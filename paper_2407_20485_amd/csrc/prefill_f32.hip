@@ -628,7 +628,7 @@ void launch_attn_f32(const float* q, const float* k, const float* v, int G, cons
                      q, k, v, rc, GQ, blocks(kRows * RB), o, lse2, scale_log2e)
 #define A2SF_ATTN_F32_64(WO)                             \
   do {                                                   \
-    if (all <= 320) A2SF_ATTN_F32(64, WO, 1, 8);         \
+    if (all <= 320 && tiles >= 8) A2SF_ATTN_F32(64, WO, 1, 8); \
     else if (all <= 1024) A2SF_ATTN_F32(64, WO, 1, 4);   \
     else A2SF_ATTN_F32(64, WO, 2, 4);                    \
   } while (0)
@@ -640,9 +640,10 @@ void launch_attn_f32(const float* q, const float* k, const float* v, int G, cons
   // Two blocks of rows per workgroup share a tile's loads and put two waves onto every SIMD; while the blocks are few, the chain
   // of a row's tiles counts, and one block takes all waves (us, one block with eight waves / with four / two blocks: d = 64,
   // 76 blocks of 32 rows 12.7 / 14.0 / 22.4, 228 14.1 / 17.2 / 27.2, 580 33.5 / 28.0 / 39.8, 1000 35.4 / 25.8 / 28.8, 2000 86.6 /
-  // 66.3 / 61.2, 2820 178 / 147 / 133; d = 128, four waves / two blocks: 38 blocks 41.4 / 73.0, 377 43.6 / 59.7, 752 105.7 / 105.2,
+  // 66.3 / 61.2, 2820 178 / 147 / 133, but 80 of two tiles 8.5 / 7.7; d = 128, four waves / two blocks: 38 blocks 41.4 / 73.0, 377 43.6 / 59.7, 752 105.7 / 105.2,
   // 760 81.4 / 66.7, 1024 102 / 80, 5943 270 / 152.  Eight waves of d = 128 have no registers for the parts).
   const long long all = (long long)GQ * blocks(kRows);
+  const int tiles = ((rc.off_heads ? rc.kv_stride : rc.m) + kRows - 1) / kRows;  // of the newest row, at most
   if (d == 64) {
     if (o) A2SF_ATTN_F32_64(true); else A2SF_ATTN_F32_64(false);
   } else {

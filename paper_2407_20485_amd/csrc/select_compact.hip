@@ -46,8 +46,8 @@ constexpr int kSelectOnly = 0, kGather = 1, kInPlace = 2;
 // move in ascending order; a chunk's tokens (to.kin) are the last to.m, in front of them len[g] others.
 template <int T, int IPT, bool SOLO, int MOVE>
 __global__ __launch_bounds__(T) void select_kernel(
-    const float* scores, const int32_t* pos, const int32_t* len, int L, int stride, int select, int recent,
-    int32_t* __restrict__ keep_idx, int32_t* __restrict__ n_keep, MoveTo to) {
+    const float* __restrict__ scores, const int32_t* __restrict__ pos, const int32_t* __restrict__ len, int L, int stride,
+    int select, int recent, int32_t* __restrict__ keep_idx, int32_t* __restrict__ n_keep, MoveTo to) {
   constexpr int NW = SOLO ? 1 : T / 64, NR = IPT > 0 ? IPT : 1;  // waves that search
   constexpr int NT = 3;  // thresholds per round
   __shared__ SelectSmem<NW> sm;
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(T) void select_kernel(
   const int g = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63, wave = SOLO ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
   const int B = select + recent;
-  int Lg = len ? len[g] : L;
+  int Lg = MOVE == kInPlace ? to.len[g] : (len ? len[g] : L);
   int off = to.capacity;  // in place: slots from here on have their rows in the second source
   if constexpr (MOVE == kInPlace) {
     if (to.off_heads && to.off_heads[g] < 0) return;
@@ -66,8 +66,9 @@ __global__ __launch_bounds__(T) void select_kernel(
     }
   }
   Lg = Lg < 0 ? 0 : (Lg > L ? L : Lg);
-  const float* sc = scores + (size_t)g * stride;
-  const int32_t* ps = pos ? pos + (size_t)g * stride : nullptr;
+  // (in place the arrays change: they are not the restricted arguments)
+  const float* sc = (MOVE == kInPlace ? to.s : scores) + (size_t)g * stride;
+  const int32_t* ps = MOVE == kInPlace ? to.p + (size_t)g * stride : (pos ? pos + (size_t)g * stride : nullptr);
   int32_t* out = MOVE ? list : keep_idx + (size_t)g * B;
   const int kept = min(Lg, B);
 
@@ -458,7 +459,7 @@ void launch_select_compact(const a2sf_cache& c, int select, int recent, hipStrea
                            int m2, const int32_t* off_heads) {
   const MoveTo to = {(const u32x4_t*)k2, (const u32x4_t*)v2, (u32x4_t*)c.k, (u32x4_t*)c.v, c.scores, c.pos, c.len,
                      c.capacity, lg_units(row_units(c.d, c.dtype)), m2, off_heads};
-  launch_select_kernel<kInPlace>(c.scores, c.pos, c.len, c.G, c.capacity, c.capacity, select, recent, nullptr, nullptr,
+  launch_select_kernel<kInPlace>(nullptr, nullptr, nullptr, c.G, c.capacity, c.capacity, select, recent, nullptr, nullptr,
                                  to, st);
 }
 

@@ -1154,8 +1154,8 @@ __global__ __launch_bounds__(kThreads, 2) void col_scores_tail_kernel(
 // Geometry as in AttnRect (n = rc.m rows, keys 0 .. off + n - 1, row i sees keys <= off + i).
 // accumulate: the column sums are added to decay * S[] for the keys before off (a chunk: the cached tokens' older
 // scores decayed by alpha^m) instead of replacing it.
-// RS = 2 (without a tolerance): eight waves, the second four take the odd tiles for the same keys, each
-// half with a ring of its own; their sums meet at the end.  For launches whose workgroups are all
+// RS = 2, 4 (without a tolerance): 4 RS waves, of which four take every RS-th tile for the same keys, each
+// part with a ring of its own; their sums meet at the end.  For launches whose workgroups are all
 // resident at once, which last as long as the column block with the most rows.
 template <int D, int KB, int RS>
 __global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_scores_stream_kernel(
@@ -1168,7 +1168,7 @@ __global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_sco
   constexpr int kLds = kStages * kTB + kWaves * kStages * 256;
   __shared__ __attribute__((aligned(1024))) char smem[RS * kLds];
   __shared__ int wave_lim[kWaves];
-  __shared__ float other[RS > 1 ? BC : 1];
+  __shared__ float other[RS > 1 ? RS - 1 : 1][RS > 1 ? BC : 1];
 
   int g, cb;  // column block 0 has the most rows
   if (!launch_item<RS == 1 ? kTwoPerUnit : kOneRound>(G, ncb, g, cb)) return;
@@ -1196,10 +1196,10 @@ __global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_sco
   const int t_last = (n + kTile - 1) / kTile - 1;
   int t_first = max(max(c0 - off, first_row), 0) / kTile;  // oldest tile any wave of the workgroup needs
   lds_char* const lse_s = qs + kStages * kTB + wave * (kStages * 256);
-  // tile f of the sequence is tile t_last - f % per_head of query head f / per_head; this half takes
+  // tile f of the sequence is tile t_last - f % per_head of query head f / per_head; this part takes
   // the tiles part, part + RS, ...
   int per_head = t_last - t_first + 1;
-  // The half's next Q tile into the next ring stage (every wave a quarter of the rows) and the rows'
+  // The part's next Q tile into the next ring stage (every wave a quarter of the rows) and the rows'
   // log-sum-exp values into the wave's own strip of that stage; always issued (past the last tile the
   // last one again, never used), so that the wait counts in the loop are the same for every tile.
   int f_hq = 0, f_i = part, f_stage = 0;  // query head and place in its sequence of the next fetch
@@ -1250,7 +1250,7 @@ __global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_sco
   for (int u = 0; u < steps; ++u, stage = (stage + 1) % kStages, i_seq += RS) {
     while (i_seq >= per_head) i_seq -= per_head;
     const int t = t_last - i_seq;
-    const bool own = RS == 1 || u * RS + part < rc.kv_group * per_head;  // (the second half may be one tile short)
+    const bool own = RS == 1 || u * RS + part < rc.kv_group * per_head;  // (a part may be one tile short)
     // this tile has landed: of this wave's fetches only those of the tiles behind it may still be under way
     wait_vm_barrier<(kStages - 2) * kLoads>();
     fetch();  // into the stage of the previous tile, which every wave has left
@@ -1318,7 +1318,7 @@ __global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_sco
     if (win.on && t <= t_first) break;
   }
   wait_vm<0>();  // tiles fetched ahead of the last one used: let them land
-  // sum over the 32 rows held by the lanes of one half, then over the two halves of the workgroup
+  // sum over the 32 rows held by the lanes of one half, then over the parts of the workgroup
 #pragma unroll
   for (int b = 0; b < KB; ++b)
 #pragma unroll
@@ -1333,19 +1333,21 @@ __global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_sco
   }
   const int key_l = 8 * ((lane & 15) >> 2) + 4 * h + (lane & 3), w0 = wave * 32 * KB;
   if constexpr (RS > 1) {
-    if (part == 1 && l32 < 16) {
+    if (part > 0 && l32 < 16) {
 #pragma unroll
-      for (int b = 0; b < KB; ++b) other[w0 + b * 32 + key_l] = sum[b];
+      for (int b = 0; b < KB; ++b) other[part - 1][w0 + b * 32 + key_l] = sum[b];
     }
     __syncthreads();
-    if (part == 1) return;
+    if (part > 0) return;
   }
   if (l32 >= 16) return;
 #pragma unroll
   for (int b = 0; b < KB; ++b) {
     const int key = wc0 + b * 32 + key_l;
     if (key >= nk) continue;
-    const float x = RS > 1 ? sum[b] + other[w0 + b * 32 + key_l] : sum[b];
+    float x = sum[b];
+#pragma unroll
+    for (int p = 1; p < RS; ++p) x += other[p - 1][w0 + b * 32 + key_l];
     float* out = S + (size_t)g * s_stride + key;
     *out = accumulate && key < off ? fmaf(decay, *out, x) : x;
     if (rc.pos && key >= off) rc.pos[(size_t)g * rc.kv_stride + key] = rc.pos0 + key - off;
@@ -1366,6 +1368,11 @@ inline int tail_key_split(int G, int keys_per_head) {
 // tiles, 8.3 / 9.4 and 100 x 400, 400 blocks, 15.1 / 19.9); beyond that the halves wait for each other (300 x 1000 66 / 113).
 constexpr unsigned kStreamSplitMaxBlocks = 256;
 constexpr int kStreamSplitMinTiles = 4;
+// In four parts: the chain of a tile (products, exponentials, sums: 1.2 us for a wave that shares its SIMD with one other)
+// counts, not the loads: deeper rings make no difference (us, two parts / four: d = 64, one head x 1000, 16 tiles, 12.9 / 12.0, x 4000
+// 40.4 / 31.6, one group of 8 x 1000 78 / 60, 240 blocks of 4 x 16 tiles 43.2 / 35.0, but 9 tiles 9.2 / 9.6; d = 128, one head
+// x 4000 44.4 / 38.7, one group of 8 x 1000 85 / 72, 24 tiles 22.0 / 20.3, 20 18.7 / 18.8, 16 15.3 / 16.0).
+template <int D> constexpr int kStreamFourMinTiles = D == 64 ? 12 : 24;
 // KB = 2, d = 128: see above, and with two wide blocks per unit (8 x 9000, KB = 2 / 1: 223 / 173, 16 x 16000 588 / 617).
 constexpr int kStreamWideMinTiles = 128, kStreamWideMinBlocks = 1024;
 // Up to one block of keys the staging of col_scores_tail_kernel does not pay (1000 heads x 100, streamed / staged: 13.7 / 19.2 us,
@@ -1399,7 +1406,9 @@ void launch_cols(const void* q, const void* k, const float* lse2, int G, const A
   const int tiles = (rc.m + kTile - 1) / kTile - first / kTile;  // per query head, at most
   const long long blocks = (long long)G * ((keys_per_head + kWaves * 32 - 1) / (kWaves * 32));
   const int split_tiles = blocks <= kStreamSplitMaxBlocks ? kStreamSplitMinTiles : 4 * kStreamSplitMinTiles;
-  if (blocks <= 2 * kStreamSplitMaxBlocks && tiles * rc.kv_group >= split_tiles && !(tol > 0.f)) A2SF_STREAM(1, 2);
+  const bool split = !(tol > 0.f);
+  if (split && blocks <= kStreamSplitMaxBlocks && tiles * rc.kv_group >= kStreamFourMinTiles<D>) A2SF_STREAM(1, 4);
+  else if (split && blocks <= 2 * kStreamSplitMaxBlocks && tiles * rc.kv_group >= split_tiles) A2SF_STREAM(1, 2);
   else if (D == 128 && tiles >= kStreamWideMinTiles && blocks >= kStreamWideMinBlocks) A2SF_STREAM((D == 128 ? 2 : 1), 1);
   else A2SF_STREAM(1, 1);
 #undef A2SF_STREAM

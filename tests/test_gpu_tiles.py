@@ -588,3 +588,25 @@ def test_calls_through_the_extension_and_through_ctypes(group):
         assert cache.len.tolist() == [select + recent] * G
         results.append([o, full, o1] + [t[:, : select + recent] for t in cache.tensors()[:4]])
     assert all(torch.equal(x, y) for x, y in zip(*results))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,group,n", [(1, 1, 704), (1, 1, 705), (1, 1, 1472), (1, 1, 1537), (2, 6, 128), (1, 7, 250), (85, 8, 300), (86, 8, 300), (64, 4, 400)])
+def test_scores_by_four_parts(G, group, n, d):
+    """Workgroups whose four parts take every fourth tile of the rows: both sides of the tile counts, numbers of tiles that
+    leave parts without one, groups whose heads follow each other in the sequence."""
+    if group == 1:
+        prompt_and_steps(variant(1, heads=G, d=d, n=n, T=1, select=11, recent=9, name="score parts"), 1.0, steps=1)
+        return
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    q, k, v = (torch.randn(s, generator=gen, device="cuda").bfloat16() for s in ((G, group, n, d), (G, n, d), (G, n, d)))
+    cache = a2sf.Cache(G, 21, d, torch.bfloat16)
+    full, o = torch.zeros(G, n, device="cuda"), torch.empty_like(q)
+    ws = torch.empty(a2sf.a2sf_workspace_bytes(G * group, n, 21, d, a2sf.A2SF_BF16, 11, 9), dtype=torch.uint8, device="cuda")
+    a2sf.a2sf_prefill_gqa(q, k, v, n, group, 1.0, 11, 9, cache, o=o, scores_full=full, workspace=ws)
+    torch.cuda.synchronize()
+    mask = torch.ones(n, n, dtype=torch.bool).tril()
+    for g in sorted({0, G - 1}):
+        z = q[g].double().cpu() @ k[g].double().cpu().T / d ** 0.5
+        want = z.masked_fill(~mask, -float("inf")).softmax(-1).sum((0, 1))
+        assert ((full[g].double().cpu() - want).abs() / want).max() <= parity.SCORE_RTOL

@@ -150,6 +150,12 @@ a2sf_status prefill_impl(const void* q, const void* k, const void* v, int32_t n,
     } else {
       // without outputs only the rows the score kernel will read need their log-sum-exp
       launch_prefill_bf16(qp, kp, vp, Gp, n, d, op, lp, st, op ? 0 : bf16_first_lse_row(n, alpha));
+      const AttnRect rc{n, n, nullptr};
+      if (scores_select_fits(Gp, rc, n, alpha)) {
+        launch_scores_select_bf16(qp, kp, vp, lp, rc, n, alpha, ap, 0.f, scores_full ? sp : nullptr, budget.select,
+                                  budget.recent, cp, st);
+        continue;
+      }
       launch_scores_bf16(qp, kp, lp, Gp, n, d, alpha, ap, tol, sp, st);
     }
     launch_select_gather(kp, vp, sp, n, budget.select, budget.recent, kip, nkp, cp, st);
@@ -283,6 +289,11 @@ a2sf_status chunk_impl(const void* q, const void* k, const void* v, int32_t m, i
                          cache->scores, C, true, decay, st);
   } else {
     launch_attn_bf16(q, cache->k, cache->v, G, rc, d, o, lse2, st);
+    if (!append && scores_select_fits(G, rc, C, alpha)) {
+      launch_scores_select_bf16(q, cache->k, cache->v, lse2, rc, C, alpha, nullptr, decay, nullptr, budget.select,
+                                budget.recent, *cache, st);
+      return launch_status();
+    }
     launch_colscores_bf16(q, cache->k, lse2, G, rc, C, d, alpha, cache->scores, C, true, decay, st);
   }
   if (!append) {
@@ -370,6 +381,11 @@ a2sf_status a2sf_prefill_gqa(const void* q, const void* k, const void* v, int32_
                            false, 0.f, st);
     } else {
       launch_attn_bf16(qp, kp, vp, Gp, rc, d, op, lp, st);
+      if (scores_select_fits(Gp, rc, n, alpha)) {
+        launch_scores_select_bf16(qp, kp, vp, lp, rc, n, alpha, nullptr, 0.f, scores_full ? sp : nullptr, budget.select,
+                                  budget.recent, cp, st);
+        continue;
+      }
       launch_colscores_bf16(qp, kp, lp, Gp, rc, n, d, alpha, sp, n, false, 0.f, st);
     }
     launch_select_gather(kp, vp, sp, n, budget.select, budget.recent, kip, nkp, cp, st);

@@ -21,6 +21,7 @@
 
 #include "a2sf_dev.h"
 #include "a2sf_internal.h"
+#include "select_dev.h"
 
 namespace a2sf {
 namespace {
@@ -1354,6 +1355,109 @@ __global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_sco
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// Scores, selection and moves of a short prompt or chunk in one kernel, one workgroup per K/V head: three launches
+// whose work is a few chains of latencies.  Up to 256 rows that count and KEYS keys: KEYS / 32 waves have a block of 32 keys each in
+// registers, the rows are staged in LDS as in col_scores_tail_kernel, one query head of the group after the other; the
+// scores stay in LDS, where one wave selects from them.  (The exponent offsets are in LDS and the loop over the rows is not
+// unrolled: such a kernel runs once per compute unit, and its instructions have to be fetched first.)
+// MOVE: kGather, a prompt; kInPlace, a chunk, whose new tokens' positions are rc.pos0 ...
+constexpr int kScoreSelectKeys = 512;  // largest form
+template <int D, int MOVE, int KEYS>
+__global__ __launch_bounds__(2 * KEYS) void scores_select_kernel(
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const float* __restrict__ LSE2, AttnRect rc, float decay,
+    int first_row, float log2_alpha, const float* __restrict__ alpha_heads, float scale_log2e, float* __restrict__ scores_full,
+    int select, int recent, MoveTo to) {
+  constexpr int T = 2 * KEYS, KK = D / 16, kTB = kTileBytesOf<D>;
+  __shared__ __attribute__((aligned(1024))) char smem[kTailTiles * kTB];
+  __shared__ float bias[kTailTiles * kTile], z[KEYS];
+  __shared__ int32_t list[KEYS];
+  __shared__ SelectSmem<1> none;
+  lds_char* const qs = (lds_char*)smem;
+  const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  const int n = rc.m;
+  const int off = rect_off(rc, g);
+  if (off < 0) return;  // a head the caller's precondition excludes
+  const int nk = off + n;  // <= KEYS (checked by the host)
+  const bf16_t* K2g = rc.k2 ? (const bf16_t*)rc.k2 + (size_t)g * n * D : nullptr;  // keys off .. from here
+  const int r_lo = (first_row / kTile) * kTile;           // first staged row (sized by the host)
+  head_window(alpha_heads, g, n, first_row, log2_alpha);  // this head's own window inside it
+  const int ntile = (n - r_lo + kTile - 1) / kTile;       // <= kTailTiles (checked by the host)
+  uint4 kf[KK];  // A operand: lane (key l32, half h) holds K[key][16kk + 8h .. +7]
+  {
+    const int r = min(wave * 32 + l32, nk - 1);
+    const bf16_t* row = (K2g && r >= off) ? K2g + (size_t)(r - off) * D : K + ((size_t)g * rc.kv_stride + r) * D;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) kf[kk] = load16(row + kk * 16 + h * 8);
+  }
+  int qoff[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) qoff[kk] = l32 * D * 2 + (((2 * kk + h) ^ k_swizzle<D>(l32)) << 4);
+  const int rb_last = (n - 1 - r_lo) >> 5;  // the row block that holds the newest row
+  const int lim = max(wave * 32 - off, first_row);  // rows before `lim` add nothing to this wave's keys
+  const int rb_first = max(lim - r_lo, 0) >> 5;
+  float acc[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  for (int hq = 0; hq < rc.kv_group; ++hq) {
+    const size_t head = (size_t)g * rc.kv_group + hq;
+    if (hq > 0) __syncthreads();  // every wave is done with the rows of the head before
+    for (int t = wave / kWaves; t < ntile; t += T / kThreads) dma_tile<D, false>(Q + head * n * D, r_lo + t * kTile, n, qs + t * kTB);
+    // exponent offset of every staged row: lse_r - (n-1-r) log2 alpha, infinite where it adds nothing
+    if (tid < kTailTiles * kTile) {
+      const int r = r_lo + tid;
+      const float lse = LSE2[head * n + min(r, n - 1)];
+      bias[tid] = (r < n && r >= first_row) ? lse - (float)(n - 1 - r) * log2_alpha : INFINITY;
+    }
+    wait_vm_barrier<0>();
+    if (wave * 32 < nk) {
+#pragma unroll 1
+      for (int rb = rb_first; rb <= rb_last; ++rb) {
+        f32x16 s;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) s = mfma_bf16(kf[kk], lds_read16(qs + rb * 32 * D * 2 + qoff[kk]), s);
+        const float b = bias[rb * 32 + l32];
+        const int newest = off + r_lo + rb * 32 + l32;  // newest key this lane's row sees
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float p = fast_exp2(fmaf(s[i], scale_log2e, -b));
+          acc[i] += wave * 32 + 8 * (i >> 2) + 4 * h + (i & 3) > newest ? 0.f : p;
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = group_sum<32>(acc[i]);
+  float sum = acc[0];
+#pragma unroll
+  for (int i = 1; i < 16; ++i) sum = (lane & 15) == i ? acc[i] : sum;
+  const int key = wave * 32 + 8 * ((lane & 15) >> 2) + 4 * h + (lane & 3);
+  if (l32 < 16 && key < nk) {
+    if (MOVE == kInPlace && key < off) sum = fmaf(decay, to.s[(size_t)g * to.capacity + key], sum);
+    z[key] = sum;
+    if (scores_full) scores_full[(size_t)g * n + key] = sum;
+  }
+  __syncthreads();
+  const int B = select + recent, kept = min(nk, B);
+  const auto score = [&](int j) { return z[j]; };
+  const auto position = [&](int j) {
+    return MOVE == kGather ? j : (j < off ? to.p[(size_t)g * to.capacity + j] : rc.pos0 + j - off);
+  };
+  if (nk <= B) {
+    if (tid < nk) list[tid] = tid;
+  } else if (wave == 0) {
+    select_slots<1, KEYS / kWave>(score, position, MOVE == kInPlace, nk, select, recent, 0, list, none);
+  }
+  __syncthreads();
+  if (tid == 0) to.len[g] = kept;
+  if constexpr (MOVE == kInPlace) move_rows<T>(to, list, kept, g, off, true, score, position);
+  else gather_rows<T>(to, list, kept, g, n, score);
+}
+
 // Workgroups per head of col_scores_tail_kernel: with fewer heads than the chip takes
 // workgroups (two per compute unit), a head's keys are shared out, in steps of 256 keys.
 inline int tail_key_split(int G, int keys_per_head) {
@@ -1432,6 +1536,48 @@ void launch_colscores_bf16(const void* q, const void* k, const float* lse2, int 
     launch_cols<64>(q, k, lse2, G, rc, keys_per_head, alpha, nullptr, 0.f, scores, s_stride, accumulate, decay, st);
   else
     launch_cols<128>(q, k, lse2, G, rc, keys_per_head, alpha, nullptr, 0.f, scores, s_stride, accumulate, decay, st);
+}
+
+// Up to 256 keys always, but for long chains of row blocks of few heads, which the separate kernels split (us per call, separate / one
+// kernel, d = 128: 32 heads x 50 rows 15.1 / 12.1, x 250 24.6 / 19.5, 1500 x 250 131 / 116, 32 x 4 queries x 120, 16 row
+// blocks, 21.9 / 20.4, but 32 x 6 x 250 at alpha = 0.3, 24, 32.3 / 36.7, chunk of 120 rows of 32 x 4, 16, 32.4 / 33.3; chunk of 50
+// rows of 32 heads 21.1 / 17.1).  Up to 512 keys while every workgroup of 16 waves has a compute unit (32 x 260, alpha = 0.5, 22.9 / 19.7,
+// chunk of 50 rows behind 300 of 32 heads 29.0 / 25.3, of 200 36.2 / 29.6, but 1500 x 260 164 / 174, 600 chunks 77 / 81), and longer
+// prompts only with enough heads to gain from one launch less (500 rows at alpha = 0.3: 200 heads 48 / 46, 32 heads 26.6 / 27.5).
+bool scores_select_fits(int G, const AttnRect& rc, int keys_per_head, float alpha) {
+  float l2a;
+  const int first = first_contributing_row(rc.m, alpha, &l2a);
+  const int rows = rc.m - first / kTile * kTile;
+  if (keys_per_head > kScoreSelectKeys || rows > kTailTiles * kTile) return false;
+  const int chain = (rows + 31) / 32 * rc.kv_group;  // row blocks that a wave goes through
+  if (keys_per_head <= 256) return chain <= (rc.k2 ? 8 : 16) || G >= 200;
+  return G <= 256 && chain <= 8 && (rc.k2 || keys_per_head <= 320 || G >= 128);
+}
+
+void launch_scores_select_bf16(const void* q, const void* k, const void* v, const float* lse2, const AttnRect& rc,
+                               int keys_per_head, float alpha, const float* alpha_heads, float decay, float* scores_full,
+                               int select, int recent, const a2sf_cache& c, hipStream_t st) {
+  const float scale_log2e = 1.4426950408889634f / sqrtf((float)c.d);
+  float l2a;
+  const int first = first_contributing_row(rc.m, alpha, &l2a);
+  const bool chunk = rc.k2 != nullptr;
+  const MoveTo to = {(const u32x4_t*)(chunk ? rc.k2 : k), (const u32x4_t*)(chunk ? rc.v2 : v), (u32x4_t*)c.k, (u32x4_t*)c.v,
+                     c.scores, c.pos, c.len, c.capacity, lg_row_units(c.d / 8), chunk ? rc.m : 0, nullptr};
+#define A2SF_SCORE_SELECT_(D, MOVE, KEYS)                                                             \
+  hipLaunchKernelGGL((scores_select_kernel<D, MOVE, KEYS>), dim3(c.G), dim3(2 * KEYS), 0, st, (const bf16_t*)q, \
+                     (const bf16_t*)k, lse2, rc, decay, first, l2a, alpha_heads, scale_log2e, scores_full, select, recent, to)
+#define A2SF_SCORE_SELECT(D, MOVE)                                               \
+  do {                                                                           \
+    if (keys_per_head <= 256) A2SF_SCORE_SELECT_(D, MOVE, 256);                  \
+    else A2SF_SCORE_SELECT_(D, MOVE, 512);                                       \
+  } while (0)
+  if (c.d == 64) {
+    if (chunk) A2SF_SCORE_SELECT(64, kInPlace); else A2SF_SCORE_SELECT(64, kGather);
+  } else {
+    if (chunk) A2SF_SCORE_SELECT(128, kInPlace); else A2SF_SCORE_SELECT(128, kGather);
+  }
+#undef A2SF_SCORE_SELECT
+#undef A2SF_SCORE_SELECT_
 }
 
 void launch_prefill_bf16(const void* q, const void* k, const void* v, int G, int n, int d,

@@ -21,39 +21,25 @@
 // followed by an ordered emission (prefix sum over the waves) of the surviving slot indices.
 #include "a2sf_dev.h"
 #include "a2sf_internal.h"
+#include "select_dev.h"
 
 namespace a2sf {
 namespace {
 
-// Where the kept rows go, for kernels that select and move them.
-constexpr int kFusedKeep = 512;  // tokens kept per head, at most
-struct MoveTo {
-  const u32x4_t *kin, *vin;  // a prompt's rows [G, L, row]; a chunk's [G, m, row], or null
-  u32x4_t *k, *v;            // [G, capacity, row]
-  float* s;
-  int32_t *p, *len;
-  int capacity, lg_units;    // log2 of the 16-byte units per row
-  int m;                     // in place: tokens of the chunk
-  const int32_t* off_heads;  // in place, may be null: negative entries mark heads to be left alone
-};
-constexpr int kSelectOnly = 0, kGather = 1, kInPlace = 2;
-
 // T threads per head.  SOLO: one of the waves does the search alone (up to 64 * IPT tokens, keys in registers), the others
-// only take part in the copy.  Otherwise all waves do: up to T * IPT tokens with keys in registers, or, with
-// IPT = 0, any number, the keys formed again from memory in every round.
+// only take part in the copy.  Otherwise all waves do.
 // MOVE: the kept indices stay in LDS (B <= kFusedKeep) and the workgroup moves the rows of its head at once.
-// kGather: from a prompt into the cache (pos and len are null).  kInPlace: in the cache, see move_slice for why rows may
-// move in ascending order; a chunk's tokens (to.kin) are the last to.m, in front of them len[g] others.
+// kGather: from a prompt into the cache (pos and len are null).  kInPlace: in the cache; a chunk's tokens (to.kin) are the
+// last to.m, in front of them len[g] others.
 template <int T, int IPT, bool SOLO, int MOVE>
 __global__ __launch_bounds__(T) void select_kernel(
     const float* __restrict__ scores, const int32_t* __restrict__ pos, const int32_t* __restrict__ len, int L, int stride,
     int select, int recent, int32_t* __restrict__ keep_idx, int32_t* __restrict__ n_keep, MoveTo to) {
-  constexpr int NW = SOLO ? 1 : T / 64, NR = IPT > 0 ? IPT : 1;  // waves that search
-  constexpr int NT = 3;  // thresholds per round
+  constexpr int NW = SOLO ? 1 : T / 64;  // waves that search
   __shared__ SelectSmem<NW> sm;
   __shared__ int list[kFusedKeep];
   const int g = blockIdx.x, tid = threadIdx.x;
-  const int lane = tid & 63, wave = SOLO ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = SOLO ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
   const int B = select + recent;
   int Lg = MOVE == kInPlace ? to.len[g] : (len ? len[g] : L);
   int off = to.capacity;  // in place: slots from here on have their rows in the second source
@@ -71,179 +57,26 @@ __global__ __launch_bounds__(T) void select_kernel(
   const int32_t* ps = MOVE == kInPlace ? to.p + (size_t)g * stride : (pos ? pos + (size_t)g * stride : nullptr);
   int32_t* out = MOVE ? list : keep_idx + (size_t)g * B;
   const int kept = min(Lg, B);
+  const auto score = [&](int j) { return sc[j]; };
+  const auto position = [&](int j) { return ps[j]; };
 
   if (Lg <= B) {
     for (int j = tid; j < Lg; j += T) out[j] = j;
   } else if (!SOLO || T == 64 || __builtin_amdgcn_readfirstlane(tid >> 6) == (int)(blockIdx.x / 8) % (T / 64)) {
-    // a wave has 64 * n_it consecutive slots, iteration it its slots j0 + 64 it
-    const int n_it = (Lg + NW * 64 - 1) / (NW * 64);
-    const int j0 = wave * 64 * n_it + lane;
-    const auto each = [&](auto f) {
-      if constexpr (IPT > 0) {
-#pragma unroll
-        for (int it = 0; it < IPT; ++it)
-          if (it < n_it) f(it, j0 + 64 * it);
-      } else {
-        for (int it = 0; it < n_it; ++it) f(it, j0 + 64 * it);
-      }
-    };
-    uint32_t key[NR];
-    if constexpr (IPT > 0)  // requested first
-      each([&](int it, int j) { key[it] = __float_as_uint(sc[j < Lg ? j : 0]); });
-
-    // 1. recent window: positions >= p_recent
-    uint32_t p[NR];  // position + 1, or 0
-    const auto pos_key = [&](int it) -> uint32_t {
-      if constexpr (IPT > 0) return p[it];
-      else { const int j = j0 + 64 * it; return j < Lg ? (uint32_t)ps[j] + 1u : 0u; }
-    };
-    int p_recent = 0;
-    if (recent > 0) {
-      if (!ps) {
-        p_recent = Lg - recent;
-      } else {
-        if constexpr (IPT > 0) each([&](int it, int j) { p[it] = j < Lg ? (uint32_t)ps[j] + 1u : 0u; });
-        // a cache that always kept its newest tokens holds exactly `recent` positions > newest - recent
-        uint32_t newest = 0;
-        int cnt = 0;
-        each([&](int it, int) { newest = max(newest, pos_key(it)); });
-        int most = wave_max_i((int)(newest ^ 0x80000000u));
-        if constexpr (NW > 1) {
-          if (lane == 0) sm.hi[wave] = most;
-          __syncthreads();
-#pragma unroll
-          for (int w = 0; w < NW; ++w) most = max(most, sm.hi[w]);
-        }
-        newest = (uint32_t)__builtin_amdgcn_readfirstlane(most) ^ 0x80000000u;
-        each([&](int it, int) { cnt += __popcll(__ballot(pos_key(it) > newest - (uint32_t)recent)); });
-        if constexpr (NW > 1) {
-          if (lane < 8) sm.cnt[0][wave * 8 + lane] = cnt;
-          __syncthreads();
-          cnt = __builtin_amdgcn_readfirstlane(sum_counts<NW>(sm.cnt[0], lane));
-        }
-        if (cnt == recent) p_recent = (int)(newest - (uint32_t)recent);  // (newest is a position + 1)
-        else p_recent = (int)(kth_largest<NW, NT, IPT>(pos_key, n_it, recent, 0, sm).key - 1u);
-      }
-    }
-    // 2. score threshold.  Keys: 0 past the end, all ones in the recent window (which is always
-    // kept, so that the cut is simply the B-th largest key), the ordered score of the others.
-    const auto form_key = [&](int it, int j, uint32_t bits) -> uint32_t {
-      const bool r = recent > 0 && (ps ? pos_key(it) > (uint32_t)p_recent : j >= p_recent);
-      return j < Lg ? (r ? 0xFFFFFFFFu : score_key(__uint_as_float(bits))) : 0u;
-    };
-    if constexpr (IPT > 0) each([&](int it, int j) { key[it] = form_key(it, j, key[it]); });
-    const auto key_of = [&](int it) -> uint32_t {
-      if constexpr (IPT > 0) return key[it];
-      else { const int j = j0 + 64 * it; return form_key(it, j, __float_as_uint(sc[j < Lg ? j : 0])); }
-    };
-    Cut cut = {0xFFFFFFFFu, -1};
-    if (select > 0) cut = kth_largest<NW, NT, IPT>(key_of, n_it, B, recent, sm);
-    // 3. ties at the cut: the lowest positions stay
-    uint32_t tie_cut = 0u;  // they have 2^31 - position >= tie_cut
-    const auto tie_key = [&](int it) -> uint32_t {
-      const int j = j0 + 64 * it;
-      return j < Lg && key_of(it) == cut.key ? 0x80000000u - (uint32_t)(ps ? ps[j] : j) : 0u;
-    };
-    if (cut.above >= 0) tie_cut = kth_largest<NW, NT, IPT>(tie_key, n_it, B - cut.above, 0, sm).key;
-
-    // 4. ordered emission
-    const auto keeps = [&](int it) -> bool {
-      const uint32_t k = key_of(it);
-      if (cut.above < 0) return k >= cut.key;
-      return k > cut.key || (k == cut.key && tie_key(it) >= tie_cut && tie_cut != 0u);
-    };
-    int base = 0;
-    if constexpr (NW > 1) {
-      int total = 0;
-      each([&](int it, int) { total += __popcll(__ballot(keeps(it))); });
-      __syncthreads();
-      if (lane == 0) sm.lo[wave] = total;
-      __syncthreads();
-#pragma unroll
-      for (int w = 0; w < NW; ++w) base += w < wave ? sm.lo[w] : 0;
-      base = __builtin_amdgcn_readfirstlane(base);
-    }
-    each([&](int it, int j) {
-      const bool k = keeps(it);
-      const unsigned long long mask = __ballot(k);
-      const int at = base + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-      if (k && at < B) out[at] = j;  // bound holds for valid input; guards bad input
-      base += __popcll(mask);
-    });
+    select_slots<NW, IPT>(score, position, ps != nullptr, Lg, select, recent, wave, out, sm);
   }
   if constexpr (MOVE == kSelectOnly) {
     if (tid == 0) n_keep[g] = kept;
     return;
   }
   __syncthreads();
-  if constexpr (MOVE == kInPlace) {
-    if (tid == 0) to.len[g] = kept;
-    if (kept == 0 || (list[kept - 1] == kept - 1 && kept <= off)) return;  // nothing moves (the list ascends)
-    constexpr int U = 4;  // units of K and of V per thread and round
-    const int lg = to.lg_units, rows = U * T >> lg;
-    u32x4_t* const Kg = to.k + (((size_t)g * to.capacity) << lg);
-    u32x4_t* const Vg = to.v + (((size_t)g * to.capacity) << lg);
-    const u32x4_t* const kin = to.kin + (((size_t)g * to.m) << lg);
-    const u32x4_t* const vin = to.vin + (((size_t)g * to.m) << lg);
-    float* const Sg = to.s + (size_t)g * to.capacity;
-    int32_t* const Pg = to.p + (size_t)g * to.capacity;
-    for (int r0 = 0; r0 < kept; r0 += rows) {
-      u32x4_t kx[U], vx[U];
-      bool moves[U];
-#pragma unroll
-      for (int i = 0; i < U; ++i) {
-        const int u = tid + i * T, r = r0 + (u >> lg), c = u & ((1 << lg) - 1);
-        const int src = r < kept ? min(max(list[r], 0), to.capacity - 1) : r;
-        moves[i] = r < kept && (src != r || src >= off);
-        if (moves[i]) {
-          const int at = (src >= off ? min(src - off, to.m - 1) : src) << lg | c;
-          kx[i] = src >= off ? kin[at] : Kg[at];
-          vx[i] = src >= off ? vin[at] : Vg[at];
-        }
-      }
-      float s_val = 0.f;
-      int p_val = 0, dst = -1;
-      if (tid < rows && r0 + tid < kept) {
-        const int src = min(max(list[r0 + tid], 0), to.capacity - 1);
-        if (src != r0 + tid) { dst = r0 + tid; s_val = Sg[src]; p_val = Pg[src]; }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < U; ++i) {
-        const int u = tid + i * T;
-        if (moves[i]) { Kg[(r0 << lg) + u] = kx[i]; Vg[(r0 << lg) + u] = vx[i]; }
-      }
-      if (dst >= 0) { Sg[dst] = s_val; Pg[dst] = p_val; }
-    }
-    return;
-  }
-  // the kept rows: K, V in 16-byte units, four rows' units of each under way per thread
-  const int units = kept << to.lg_units, mask = (1 << to.lg_units) - 1;
-  const size_t in0 = ((size_t)g * L) << to.lg_units, out0 = ((size_t)g * to.capacity) << to.lg_units;
-  for (int u0 = tid; u0 < units; u0 += 4 * T) {
-    u32x4_t kx[4], vx[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int u = u0 + i * T;
-      if (u < units) {
-        const int src = min(max(list[u >> to.lg_units], 0), L - 1);
-        const size_t at = in0 + (((size_t)src) << to.lg_units) + (u & mask);
-        kx[i] = to.kin[at];
-        vx[i] = to.vin[at];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int u = u0 + i * T;
-      if (u < units) { to.k[out0 + u] = kx[i]; to.v[out0 + u] = vx[i]; }
-    }
-  }
-  for (int r = tid; r < kept; r += T) {
-    const int src = min(max(list[r], 0), L - 1);
-    to.s[(size_t)g * to.capacity + r] = sc[src];
-    to.p[(size_t)g * to.capacity + r] = src;
-  }
   if (tid == 0) to.len[g] = kept;
+  if constexpr (MOVE == kInPlace) {
+    if (kept == 0 || (list[kept - 1] == kept - 1 && kept <= off)) return;  // nothing moves (the list ascends)
+    move_rows<T>(to, list, kept, g, off, false, score, position);
+  } else {
+    gather_rows<T>(to, list, kept, g, L, score);
+  }
 }
 
 template <int MOVE>
@@ -412,7 +245,6 @@ __global__ __launch_bounds__(kThreads) void gather_prompt_kernel(
 }
 
 inline int row_units(int d, int dtype) { return d * (dtype == A2SF_BF16 ? 2 : 4) / 16; }
-inline int lg_units(int ru) { return ru == 8 ? 3 : (ru == 16 ? 4 : 5); }
 
 }  // namespace
 
@@ -458,7 +290,7 @@ bool selects_in_place(const a2sf_cache& c, int select, int recent, bool appends)
 void launch_select_compact(const a2sf_cache& c, int select, int recent, hipStream_t st, const void* k2, const void* v2,
                            int m2, const int32_t* off_heads) {
   const MoveTo to = {(const u32x4_t*)k2, (const u32x4_t*)v2, (u32x4_t*)c.k, (u32x4_t*)c.v, c.scores, c.pos, c.len,
-                     c.capacity, lg_units(row_units(c.d, c.dtype)), m2, off_heads};
+                     c.capacity, lg_row_units(row_units(c.d, c.dtype)), m2, off_heads};
   launch_select_kernel<kInPlace>(nullptr, nullptr, nullptr, c.G, c.capacity, c.capacity, select, recent, nullptr, nullptr,
                                  to, st);
 }
@@ -475,7 +307,7 @@ void launch_select_gather(const void* k, const void* v, const float* scores_full
   // rows move 3.4 MB per head, 21 us with 205 workgroups per head.
   if (keep_stride <= kFusedKeep) {
     const MoveTo to = {(const u32x4_t*)k, (const u32x4_t*)v, (u32x4_t*)c.k, (u32x4_t*)c.v, c.scores, c.pos,
-                       c.len, c.capacity, lg_units(ru), 0, nullptr};
+                       c.len, c.capacity, lg_row_units(ru), 0, nullptr};
     launch_select_kernel<kGather>(scores_full, nullptr, nullptr, c.G, n, n, select, recent, nullptr, nullptr, to, st);
     return;
   }

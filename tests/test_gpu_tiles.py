@@ -610,3 +610,54 @@ def test_scores_by_four_parts(G, group, n, d):
         z = q[g].double().cpu() @ k[g].double().cpu().T / d ** 0.5
         want = z.masked_fill(~mask, -float("inf")).softmax(-1).sum((0, 1))
         assert ((full[g].double().cpu() - want).abs() / want).max() <= parity.SCORE_RTOL
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,group,n,alpha", [(3, 1, 1, 0.5), (3, 1, 63, 1.0), (3, 1, 65, 0.0), (3, 1, 256, 1.0), (3, 1, 257, 0.5), (3, 1, 320, 0.3),
+                                             (3, 1, 321, 0.3), (130, 1, 511, 0.4), (130, 1, 512, 0.4), (130, 1, 513, 0.4), (257, 1, 300, 0.3),
+                                             (3, 4, 128, 1.0), (3, 4, 129, 1.0), (200, 8, 200, 0.9), (3, 8, 33, 0.7), (2100, 1, 40, 0.6)])
+def test_scores_selection_and_gather_in_one_kernel(G, group, n, alpha, d):
+    """Both sides of the rules that send a prompt's scores, selection and gather through one kernel.  Scores against float64; the cache,
+    bit for bit, is what a2sf_select makes of them.  With factors per head, without outputs, budgets above n."""
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    q, k, v = (torch.randn(s, generator=gen, device="cuda").bfloat16() for s in ((G, group, n, d), (G, n, d), (G, n, d)))
+    mask = torch.ones(n, n, dtype=torch.bool).tril()
+    heads = sorted({0, G // 2, G - 1})
+    for select, recent, outputs, per_head in ((n // 3 + 1, n // 5, True, False), (n, 3, False, False), (9, 0, True, group == 1)):
+        B = select + recent
+        cache = a2sf.Cache(G, B + 1, d, torch.bfloat16)
+        for t in cache.tensors():
+            t.fill_(7)
+        full, o = torch.full((G, n), 7.0, device="cuda"), torch.empty_like(q) if outputs else None
+        ws = torch.empty(a2sf.a2sf_workspace_bytes(G * group, n, B + 1, d, a2sf.A2SF_BF16, select, recent), dtype=torch.uint8, device="cuda")
+        factors = torch.full((G,), float(np.float32(alpha)))
+        if per_head:
+            factors = (factors * torch.linspace(0.1, 1.0, G)).float()
+            a2sf.a2sf_prefill_alpha_per_head(q, k, v, n, factors.cuda(), alpha, select, recent, cache, o=o, scores_full=full, workspace=ws)
+        else:
+            a2sf.a2sf_prefill_gqa(q, k, v, n, group, alpha, select, recent, cache, o=o, scores_full=full, workspace=ws)
+        keep = torch.zeros((G, B), dtype=torch.int32, device="cuda")
+        n_keep = torch.zeros(G, dtype=torch.int32, device="cuda")
+        a2sf.a2sf_select(full, None, None, G, n, n, select, recent, keep, n_keep)
+        torch.cuda.synchronize()
+        kept = min(n, B)
+        assert cache.len.tolist() == [kept] * G and n_keep.tolist() == [kept] * G
+        at = keep[:, :kept].long()
+        assert torch.equal(cache.pos[:, :kept].long(), at) and torch.equal(cache.scores[:, :kept], full.gather(1, at))
+        rows = at[:, :, None].expand(-1, -1, d)
+        assert torch.equal(cache.k[:, :kept], k.gather(1, rows)) and torch.equal(cache.v[:, :kept], v.gather(1, rows))
+        for g in heads:
+            z = q[g].double().cpu() @ k[g].double().cpu().T / d ** 0.5
+            p = z.masked_fill(~mask, -float("inf")).softmax(-1)
+            w = factors[g].double() ** torch.arange(n - 1, -1, -1).double()
+            want = (w[None, :, None] * p).sum((0, 1))
+            assert ((full[g].double().cpu() - want).abs() <= parity.SCORE_RTOL * want + 1e-30).all()
+            if outputs:
+                assert (o[g].double().cpu() - p @ v[g].double().cpu()).abs().max() <= parity.O_TOL["bf16"]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,group,m", [(40, 1, 152), (40, 1, 153), (256, 1, 60), (257, 1, 160), (40, 2, 128), (40, 2, 130), (210, 4, 140), (20, 1, 256), (20, 1, 257)])
+def test_chunk_scored_and_evicted_in_one_kernel(G, group, m, d):
+    """The same rules for chunks: up to 256 keys and up to 512, few and many heads, long chains of row blocks."""
+    test_bf16_chunk_tiles(G, group, m, d)

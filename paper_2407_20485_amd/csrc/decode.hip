@@ -546,23 +546,31 @@ __device__ __forceinline__ void gqa_outer_products(const uint4& xu, float pa, f3
 // the K sweep, R output accumulators in the V sweep); every query head has its own softmax.
 // The score update adds the SUM of the R probability rows (a token is kept or evicted for the
 // whole group, as Eq.1 of the paper sums over heads that share one pruning decision).
-template <typename T, int D, int R, bool STREAM>
-__global__ __launch_bounds__(kThreads) void decode_gqa_kernel(
+// The R softmaxes run side by side (a group of four waves takes every NW/4-th of them) and the waves' partial outputs of
+// all R heads are summed at once: the workgroup meets six or eight times before the update, whatever R is.  NW = 16 waves while every
+// K/V head has a compute unit to itself: the step is a chain of round trips and of vector work then.  Time per step (head
+// after head, four waves / side by side, four waves / 16 waves):
+//   R = 8, 180 slots, 20 heads, bf16, d = 64   16.7 / 12.0 / 11.8 us     fp32, d = 128  23.9 / 19.8 / 14.5 us
+//   R = 5, 600 slots, 20 heads, bf16, d = 64   20.5 / 18.6 / 13.6 us     fp32, d = 128  39.5 / 37.8 / 20.7 us
+//   R = 8, 1800 slots, 250 heads, bf16, d = 64 61.9 / 57.5 / 36.4 us     fp32, d = 128   165 / 162 / 97.5 us
+//   R = 8, 1800 slots, 900 heads, bf16, d = 64  147 / 137 us             fp32, d = 128   388 / 384 us
+// (one wave a softmax, all of them at once: 260 heads x 2000 slots x 2, fp32, d = 64 53.3 us against 46.0.)
+template <typename T, int D, int R, bool STREAM, int NW>
+__global__ __launch_bounds__(NW * 64) void decode_gqa_kernel(
     const T* __restrict__ q, const T* __restrict__ k_new, const T* __restrict__ v_new, int t_pos,
     T* K, T* V, float* S, int32_t* P, int32_t* len, int capacity, float alpha, int select,
-    int recent, int evict_here, T* __restrict__ o, float scale_log2e) {
+    int recent, int evict_here, T* __restrict__ o, int part_at, float scale_log2e) {
   using Gm = RowGeom<T, D>;
-  constexpr int U = kBlockUnroll;
-  constexpr int ROWS_PER_ITER = kWaves * Gm::RPW * U;
-  extern __shared__ float a[];  // [R][capacity]: logits, then probabilities, of each query head
+  constexpr int U = NW == kWaves ? kBlockUnroll : R * Gm::EPL < 40 ? 4 : 2, NT = NW * 64;  // (16 waves leave a lane 128 registers)
+  constexpr int ROWS_PER_ITER = NW * Gm::RPW * U;
+  extern __shared__ float a[];  // [R][capacity]: logits, then probabilities, of each query head | [NW][R][D]: partial outputs
   __shared__ StepSmem sm;
-  __shared__ float part[kWaves][128];
   const int g = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int sub = lane % Gm::LPR, rgrp = lane / Gm::LPR;
   const int n_old = len[g];
   if (n_old < 0 || n_old >= capacity) {
-    for (int r = 0; r < R; ++r) flag_bad_head<T, D>(o + ((size_t)g * R + r) * D, tid, kThreads);
+    for (int r = 0; r < R; ++r) flag_bad_head<T, D>(o + ((size_t)g * R + r) * D, tid, NT);
     return;
   }
   const int L = n_old + 1;
@@ -576,14 +584,14 @@ __global__ __launch_bounds__(kThreads) void decode_gqa_kernel(
   float* Sg = S + (size_t)g * capacity;
   int32_t* Pg = P + (size_t)g * capacity;
   SlotBatch first;
-  load_slot_batch(first, no_aux, Sg, Pg, tid, n_old, t_pos);
+  if (NW == kWaves || tid < kThreads) load_slot_batch(first, no_aux, Sg, Pg, tid, n_old, t_pos);
 
   // bf16, d = 128, four or eight query heads: both products on the 4x4 matrix instructions (see
   // above; with R >= 4 the vector form is bound by its arithmetic: 640 K/V heads x 2001 slots,
   // R = 8: 228 us per step against 107 us of the same cache with ungrouped heads).  A wave takes
-  // 4 * UM consecutive rows of every round of 4 * UM * kWaves.
+  // 4 * UM consecutive rows of every round of 4 * UM * NW.
   constexpr bool kMatrix = std::is_same<T, bf16_t>::value && D == 128 && R >= 3;   // (R = 2: the vector form is faster here, 108 against 114 us at 640 K/V heads x 2001 slots)
-  constexpr int UM = 8, HB = (R + 3) / 4, MROWS = 4 * UM;   // a last block of fewer than four heads idles its other columns
+  constexpr int UM = NW == kWaves ? 8 : 4, HB = (R + 3) / 4, MROWS = 4 * UM;   // a last block of fewer than four heads idles its other columns
   const int blk = lane >> 2, jl = lane & 3;  // matrix block, row / head inside it
 
   if constexpr (kMatrix) {
@@ -591,7 +599,7 @@ __global__ __launch_bounds__(kThreads) void decode_gqa_kernel(
 #pragma unroll
     for (int h = 0; h < HB; ++h)
       qb[h] = load16(reinterpret_cast<const bf16_t*>(q) + ((size_t)g * R + min(4 * h + jl, R - 1)) * D + 8 * blk);
-    for (int base = wave * MROWS; base < L; base += kWaves * MROWS) {
+    for (int base = wave * MROWS; base < L; base += NW * MROWS) {
       uint4 x[UM];
       gqa_request_rows<UM, STREAM>(reinterpret_cast<const bf16_t*>(Kg), reinterpret_cast<const bf16_t*>(knew),
                                    base, jl, 8 * blk, n_old, x);
@@ -620,13 +628,13 @@ __global__ __launch_bounds__(kThreads) void decode_gqa_kernel(
       uint4 x[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int row = base + (u * kWaves + wave) * Gm::RPW + rgrp;
+        const int row = base + (u * NW + wave) * Gm::RPW + rgrp;
         const T* p = (row == n_old) ? knew : Kg + (size_t)(row < L ? row : 0) * D;
         x[u] = load16_as<STREAM>(p + sub * Gm::EPL);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int row = base + (u * kWaves + wave) * Gm::RPW + rgrp;
+        const int row = base + (u * NW + wave) * Gm::RPW + rgrp;
         float f[Gm::EPL];
         Elem<T>::unpack(x[u], f);
 #pragma unroll
@@ -642,33 +650,85 @@ __global__ __launch_bounds__(kThreads) void decode_gqa_kernel(
   }
   __syncthreads();
 
-  // ---- R softmaxes
-#pragma unroll 1
-  for (int r = 0; r < R; ++r) {
-    float* ar = a + r * capacity;
-    float mx = -INFINITY;
-    for (int j = tid; j < L; j += kThreads) mx = fmaxf(mx, ar[j]);
-    mx = block_max(mx, sm.redf);
-    float sum = 0.f;
-    for (int j = tid; j < L; j += kThreads) {
-      const float p = exp2f(ar[j] - mx);
-      ar[j] = p;
-      sum += p;
+  // ---- R softmaxes side by side: group `quad` of four waves takes heads quad, quad + NG, ...
+  constexpr int NG = NW / kWaves, HG = (R + NG - 1) / NG;
+  __shared__ float red[2][NW][HG];
+  {
+    const int quad = wave / kWaves, t4 = tid % kThreads;
+    const auto mine = [&](int i) { return R % NG == 0 || quad + NG * i < R; };
+    const auto strip = [&](int i) { return a + (quad + NG * i) * capacity; };
+    float mx[HG], sum[HG];
+#pragma unroll
+    for (int i = 0; i < HG; ++i) { mx[i] = -INFINITY; sum[i] = 0.f; }
+    for (int j = t4; j < L; j += kThreads)
+#pragma unroll
+      for (int i = 0; i < HG; ++i)
+        if (mine(i)) mx[i] = fmaxf(mx[i], strip(i)[j]);
+#pragma unroll
+    for (int i = 0; i < HG; ++i) mx[i] = wave_max(mx[i]);
+    if (lane == 0) {
+#pragma unroll
+      for (int i = 0; i < HG; ++i) red[0][wave][i] = mx[i];
     }
-    sum = block_sum(sum, sm.redf);
-    const float inv = 1.0f / sum;
-    for (int j = tid; j < L; j += kThreads) ar[j] *= inv;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < HG; ++i)
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) mx[i] = fmaxf(mx[i], red[0][quad * kWaves + w][i]);
+    for (int j = t4; j < L; j += kThreads)
+#pragma unroll
+      for (int i = 0; i < HG; ++i)
+        if (mine(i)) {
+          const float p = exp2f(strip(i)[j] - mx[i]);
+          strip(i)[j] = p;
+          sum[i] += p;
+        }
+#pragma unroll
+    for (int i = 0; i < HG; ++i) sum[i] = wave_sum(sum[i]);
+    if (lane == 0) {
+#pragma unroll
+      for (int i = 0; i < HG; ++i) red[1][wave][i] = sum[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < HG; ++i) {
+      const float* w = red[1][quad * kWaves] + i;
+      sum[i] = 1.0f / ((w[0] + w[HG]) + (w[2 * HG] + w[3 * HG]));
+    }
+    for (int j = t4; j < L; j += kThreads)
+#pragma unroll
+      for (int i = 0; i < HG; ++i)
+        if (mine(i)) strip(i)[j] *= sum[i];
   }
   __syncthreads();
 
   // ---- V sweep: R output rows
+  float* const part = a + part_at;
+  const bool summed = NW == kWaves && part_at < R * capacity;  // over the probability rows but the first: summed before
+  const auto leave = [&](int r, const float* out) {  // this wave's share of a query head's output
+    if (rgrp == 0) {
+#pragma unroll
+      for (int e = 0; e < Gm::EPL; ++e) part[(wave * R + r) * D + sub * Gm::EPL + e] = out[e];
+    }
+  };
+  const auto sum_rows = [&] {  // the probability rows into the first of them: all that the update reads
+    if (!summed) return;
+    __syncthreads();
+    for (int j = tid; j < L; j += NT) {
+      float p = 0.f;
+#pragma unroll
+      for (int r = 0; r < R; ++r) p += a[r * capacity + j];
+      a[j] = p;
+    }
+    __syncthreads();
+  };
   if constexpr (kMatrix) {
     f32x4_t macc[HB > 0 ? HB : 1][8];  // macc[h][e][i] = o[head 4h+i][8*sub + e], this lane's row group
 #pragma unroll
     for (int h = 0; h < HB; ++h)
 #pragma unroll
       for (int e = 0; e < 8; ++e) macc[h][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    for (int base = wave * MROWS; base < L; base += kWaves * MROWS) {
+    for (int base = wave * MROWS; base < L; base += NW * MROWS) {
       uint4 x[UM];
       gqa_request_rows<UM, STREAM>(reinterpret_cast<const bf16_t*>(Vg), reinterpret_cast<const bf16_t*>(vnew),
                                    base, rgrp, 8 * sub, n_old, x);
@@ -684,6 +744,7 @@ __global__ __launch_bounds__(kThreads) void decode_gqa_kernel(
 #pragma unroll
         for (int h = 0; h < HB; ++h) gqa_outer_products(x[u], pa[u][h], macc[h]);
     }
+    sum_rows();
 #pragma unroll
     for (int h = 0; h < HB; ++h)
 #pragma unroll
@@ -693,8 +754,7 @@ __global__ __launch_bounds__(kThreads) void decode_gqa_kernel(
 #pragma unroll
         for (int e = 0; e < Gm::EPL; ++e) out[e] = macc[h][e < 8 ? e : 0][i];
         v_fold_row_groups<T, D>(out);
-        reduce_output<T, D>(out, part);
-        if (tid < D) Elem<T>::store(o + ((size_t)g * R + 4 * h + i) * D + tid, part[0][tid]);
+        leave(4 * h + i, out);
       }
   } else {
     float acc[R][Gm::EPL];
@@ -706,13 +766,13 @@ __global__ __launch_bounds__(kThreads) void decode_gqa_kernel(
       uint4 x[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int row = base + (u * kWaves + wave) * Gm::RPW + rgrp;
+        const int row = base + (u * NW + wave) * Gm::RPW + rgrp;
         const T* p = (row == n_old) ? vnew : Vg + (size_t)(row < L ? row : 0) * D;
         x[u] = load16_as<STREAM>(p + sub * Gm::EPL);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int row = base + (u * kWaves + wave) * Gm::RPW + rgrp;
+        const int row = base + (u * NW + wave) * Gm::RPW + rgrp;
         float f[Gm::EPL];
         Elem<T>::unpack(x[u], f);
 #pragma unroll
@@ -723,21 +783,35 @@ __global__ __launch_bounds__(kThreads) void decode_gqa_kernel(
         }
       }
     }
+    sum_rows();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       v_fold_row_groups<T, D>(acc[r]);
-      reduce_output<T, D>(acc[r], part);
-      if (tid < D) Elem<T>::store(o + ((size_t)g * R + r) * D + tid, part[0][tid]);
+      leave(r, acc[r]);
     }
   }
 
-  // ---- S <- alpha*S + sum of the R probability rows, eviction as for a single head
+  __syncthreads();
+  for (int i = tid; i < R * D; i += NT) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; w += 4)
+      t += (part[w * R * D + i] + part[(w + 1) * R * D + i]) + (part[(w + 2) * R * D + i] + part[(w + 3) * R * D + i]);
+    Elem<T>::store(o + (size_t)g * R * D + i, t);
+  }
+
+  // ---- S <- alpha*S + sum of the R probability rows, eviction as for a single head (by four waves; a barrier waits
+  // only for waves that have not ended)
+  if (NW > kWaves && tid >= kThreads) return;
   update_and_evict<T, D, true>(
       no_aux,
       [&](int j, float) {
-        float p = 0.f;
+        float p = a[j];
 #pragma unroll
-        for (int r = 0; r < R; ++r) p += a[r * capacity + j];
+        for (int r = 1; r < R; ++r) {
+          const float more = a[r * capacity + j];  // (no branch: the reads of a batch of slots go out together)
+          p += summed ? 0.f : more;
+        }
         return p;
       },
       first, a, n_old, Kg, Vg, Sg, Pg, len + g, knew, vnew, t_pos, alpha, select, recent,
@@ -2246,6 +2320,8 @@ void with_group(int group, F f) {
   }
 }
 
+constexpr size_t kLdsPerCu = 160 * 1024;
+
 template <typename T, int D>
 void launch_gqa_typed(const void* q, const void* k_new, const void* v_new, int t_pos,
                       const a2sf_cache& c, int group, float alpha, int select, int recent,
@@ -2258,7 +2334,12 @@ void launch_gqa_typed(const void* q, const void* k_new, const void* v_new, int t
   // the same cache with ungrouped heads, as far as the scratch memory the caller gave allows.
   if constexpr (kMatrixType) {
     const DecodePlan kv = plan_decode(c.G, c.capacity, D);
-    if (group >= 2 && kv.nsplit > 1 && ws) {
+    // Nearly all compute units have a K/V head: one workgroup of 16 waves each.  Time per step (split / 16 waves), 194 heads x 1000
+    // slots: R = 2 25.1 / 21.4 us, 3 26.9 / 27.3, 4 28.5 / 27.7, 6 35.2 / 29.5, 8 37.8 / 30.2; 240 heads: 26.5 / 24.4,
+    // 28.2 / 28.6, 29.7 / 28.8, 34.1 / 30.7, 36.7 / 31.6; 256 heads x 260 slots: R = 3 16.0 / 12.4, 8 23.6 / 16.0; 130 heads x 1800
+    // x 8: 45.4 / 49.2 (three or four heads fill one block of the matrix instruction: their split form is the cheaper one).
+    const bool nearly_all = c.G >= (group == 3 || group == 4 ? 240 : 192) && c.G <= 256;
+    if (!nearly_all && group >= 2 && kv.nsplit > 1 && ws) {
       const size_t heads = (size_t)c.G * group;
       const size_t fixed = heads * c.capacity * sizeof(float);              // the logits
       const size_t per_split = heads * (2 + D) * sizeof(float);             // (max, sum) and output
@@ -2338,14 +2419,37 @@ void launch_gqa_typed(const void* q, const void* k_new, const void* v_new, int t
   }
   with_group(group, [&](auto rc) {
     constexpr int R = decltype(rc)::value;
-    if (stream)
-      hipLaunchKernelGGL((decode_gqa_kernel<T, D, R, true>), dim3(c.G), dim3(kThreads), lds, st, (const T*)q,
-                         (const T*)k_new, (const T*)v_new, t_pos, (T*)c.k, (T*)c.v, c.scores, c.pos, c.len,
-                         c.capacity, alpha, select, recent, (int)evict_here, (T*)o, scale_log2e);
-    else
-      hipLaunchKernelGGL((decode_gqa_kernel<T, D, R, false>), dim3(c.G), dim3(kThreads), lds, st, (const T*)q,
-                         (const T*)k_new, (const T*)v_new, t_pos, (T*)c.k, (T*)c.v, c.scores, c.pos, c.len,
-                         c.capacity, alpha, select, recent, (int)evict_here, (T*)o, scale_log2e);
+    // logits of A2SF_GQA_MAX_LOGITS at most, and the partial outputs
+    const auto block = [&](auto sc, auto nwc) {
+      constexpr bool STREAM = decltype(sc)::value;
+      constexpr int NW = decltype(nwc)::value, kPart = NW * R * D * (int)sizeof(float);
+      static const hipError_t raised =
+          hipFuncSetAttribute((const void*)decode_gqa_kernel<T, D, R, STREAM, NW>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              A2SF_GQA_MAX_LOGITS * (int)sizeof(float) + kPart);
+      (void)raised;
+      // The partial outputs lie behind the logits or, where a compute unit would hold fewer workgroups then (four at most, by
+      // their registers), over all logits but the first head's: 900 heads x 3000 slots x 3, fp32, d = 128: 472 us behind, 443 over.
+      const size_t over = std::max(lds, c.capacity * sizeof(float) + kPart);
+      const bool apart = NW > kWaves || std::min<size_t>(4, kLdsPerCu / (lds + kPart)) >= std::min<size_t>(4, kLdsPerCu / over);
+      hipLaunchKernelGGL((decode_gqa_kernel<T, D, R, STREAM, NW>), dim3(c.G), dim3(NW * 64), apart ? lds + kPart : over,
+                         st, (const T*)q, (const T*)k_new, (const T*)v_new, t_pos, (T*)c.k, (T*)c.v, c.scores, c.pos,
+                         c.len, c.capacity, alpha, select, recent, (int)evict_here, (T*)o,
+                         apart ? R * c.capacity : c.capacity, scale_log2e);
+    };
+    const std::integral_constant<int, kWaves> four;
+    const std::integral_constant<int, 16> sixteen;
+    // 16 waves from 64 KB of K rows times query heads on: 250 heads x 180 slots x 2, bf16, d = 64 (46 KB): 8.9 us with four, 9.5 with 16;
+    // d = 128 (92 KB): 9.7 / 9.5; fp32 (184 KB) 10.5 / 9.6.  Non-temporal loads there where the cache is
+    // larger than the 256 MB behind the L2s: 250 heads x 3000 x 3, fp32, d = 128 139 us without, 124 with; 250 x 1800 x 8, d = 64 50.6 / 52.5.
+    const size_t row_bytes = (size_t)c.capacity * D * sizeof(T);
+    if (c.G <= 256 && group * row_bytes > 65536) {
+      if (2 * c.G * row_bytes > 256e6) block(std::true_type(), sixteen);
+      else block(std::false_type(), sixteen);
+    } else if (stream) {
+      block(std::true_type(), four);
+    } else {
+      block(std::false_type(), four);
+    }
   });
 }
 

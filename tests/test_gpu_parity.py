@@ -675,6 +675,51 @@ def test_grouped_query_heads_long_caches(dtype, d, group, n, select, recent, spl
     grouped_query_case(dtype, d, group, n, 0.5, 3, 3, select, recent, say, small_decode_ws=not split)
 
 
+@pytest.mark.parametrize("dtype,d,group,G,slots", [("bf16", 64, 2, 5, 300),      # 16 waves, more of them than rows to load at once
+                                                   ("bf16", 64, 7, 5, 65), ("f32", 128, 3, 2, 257), ("f32", 64, 8, 3, 1025),
+                                                   ("bf16", 64, 8, 256, 77), ("bf16", 64, 3, 257, 255),   # 16 / four waves
+                                                   ("f32", 128, 2, 256, 1024),     # 268 MB: non-temporal loads
+                                                   ("bf16", 128, 2, 192, 300), ("bf16", 128, 3, 240, 280), ("bf16", 128, 8, 192, 260),
+                                                   ("f32", 128, 3, 258, 3000),     # partial outputs over the logits
+                                                   ("bf16", 128, 5, 258, 1500), ("bf16", 64, 2, 1, 8191)])
+def test_grouped_query_step_by_whole_workgroups(dtype, d, group, G, slots, say):
+    """Every form of the one-workgroup generation step (four or 16 waves, partial outputs behind the logits or
+    over them, either kind of load): outputs and updated scores of a step that appends, against float64."""
+    cap = slots + 1
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(slots + G + group)
+    c = a2sf.Cache(G, cap, d, dt)
+    c.k.copy_(torch.randn((G, cap, d), device="cuda", generator=gen))
+    c.v.copy_(torch.randn((G, cap, d), device="cuda", generator=gen))
+    c.scores.copy_(torch.rand((G, cap), device="cuda", generator=gen))
+    c.pos.copy_(torch.arange(cap, dtype=torch.int32, device="cuda").repeat(G, 1))
+    c.len.fill_(slots - 1)
+    c.len[0] = max(1, slots // 3)
+    q = torch.randn((G, group, d), device="cuda", generator=gen).to(dt)
+    k, v = (torch.randn((G, d), device="cuda", generator=gen).to(dt) for _ in range(2))
+    start = c.snapshot()
+    o = torch.empty((G, group, d), dtype=dt, device="cuda")
+    ws = torch.empty(a2sf.a2sf_workspace_bytes(G * group, 64, cap, d, a2sf.A2SF_F32 if dtype == "f32" else a2sf.A2SF_BF16,
+                                               slots // 2, slots - slots // 2), dtype=torch.uint8, device="cuda")
+    a2sf.a2sf_decode_step_gqa(q, k, v, cap, c, group, 0.5, slots // 2, slots - slots // 2, o, workspace=ws)
+    torch.cuda.synchronize()
+    o_err = s_err = 0.0
+    for g in {0, 1 % G, G // 2, G - 1}:
+        n = int(start[4][g])
+        K = torch.cat([start[0][g, :n], k[g:g + 1]]).double().cpu()
+        V = torch.cat([start[1][g, :n], v[g:g + 1]]).double().cpu()
+        p = torch.softmax(q[g].double().cpu() @ K.T / d ** 0.5, dim=1)
+        want = torch.cat([0.5 * start[2][g, :n].double().cpu(), torch.zeros(1, dtype=torch.float64)]) + p.sum(0)
+        o_err = max(o_err, (o[g].double().cpu() - p @ V).abs().max().item())
+        s_err = max(s_err, ((c.scores[g, :n + 1].double().cpu() - want).abs() / want).max().item())
+        assert int(c.len[g]) == n + 1 and int(c.pos[g, n]) == cap
+        assert torch.equal(c.k[g, n], k[g]) and torch.equal(c.v[g, n], v[g]) and torch.equal(c.k[g, :n], start[0][g, :n])
+    say(f"  [grouped step {dtype} d={d} {G} x {group} x {slots}] max|o err|={o_err:.2e} max score rel={s_err:.2e}")
+    # outputs: as everywhere; scores: the exponents are logits of magnitude < 10 in fp32 (8 roundings of 2^-24 each at most
+    # reach them after the sum over d), their sum and the update add a few more
+    assert o_err <= parity.O_TOL[dtype] and s_err <= 1e-5
+
+
 @pytest.mark.parametrize("dtype,d,group,n,select,recent", [("bf16", 128, 4, 30, 14, 10),    # 64*2 slots per wave
                                                            ("bf16", 128, 8, 160, 80, 70),   # 64*4 slots, 8 query heads
                                                            ("f32", 64, 2, 310, 150, 150),   # 64*8 slots

@@ -127,8 +127,8 @@ a2sf_status a2sf_prefill(const void* q, const void* k, const void* v, int32_t n,
  * keys off the newest row, which it processes first, and walks back W rows with
  * alpha^W <= score_rel_tol * (1 - alpha) * min_j P[n-1, j].
  *   score_rel_tol  in [0, 1); 0 = every row of nonzero fp32 weight, exactly a2sf_prefill.
- * Everything else as in a2sf_prefill.  The window is applied to bf16 prompts with d = 128;
- * other shapes compute every row (the result is then a2sf_prefill's).  alpha = 1 has no
+ * Everything else as in a2sf_prefill.  The window is applied to bf16 prompts with d = 128 that are
+ * longer than a few hundred rows; other shapes compute every row (the result is then a2sf_prefill's).  alpha = 1 has no
  * window, alpha = 0 only the newest row either way. */
 a2sf_status a2sf_prefill_windowed(const void* q, const void* k, const void* v, int32_t n,
                                   float alpha, float score_rel_tol, a2sf_budget budget,

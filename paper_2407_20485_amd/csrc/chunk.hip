@@ -3,7 +3,8 @@
 // is m such steps with the eviction deferred to the end of the chunk, so that the rows can go
 // through the matrix cores together.)  Attention of the chunk's rows over cache + chunk, the
 // score update and the eviction are the general forms of the prompt-phase kernels and the
-// selection / compaction kernels; only the append is specific.
+// selection / compaction kernels; only the append is specific, and bf16 chunks of moderate budgets do without it: their
+// scores kernel writes the positions, and the selection moves the rows and counts them.
 #include "a2sf_dev.h"
 #include "a2sf_internal.h"
 

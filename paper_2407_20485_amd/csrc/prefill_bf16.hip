@@ -10,8 +10,9 @@
 //             matrix cores, exp2(s - lse_i + (n-1-i) log2 alpha) is formed per element (the
 //             forgetting weight is folded into the exponent) and summed down the tile's
 //             rows.  The n x n probability matrix is never written.
+//  scores_select  column scores, selection and row moves of a short prompt or chunk in one kernel.
 //
-// Both kernels compute the TRANSPOSED logit tile (keys = M, queries = N).  In the 32x32
+// All compute the TRANSPOSED logit tile (keys = M, queries = N).  In the 32x32
 // accumulator layout a lane then owns one query (column l%32) and 16 keys
 // (rows 8*(i/4) + 4*(l/32) + i%4, i = 0..15), so
 //   - row statistics of the softmax are per-lane scalars (one exchange with lane^32),

@@ -12,13 +12,17 @@
 // head's cache (off = tokens cached before the chunk).
 //
 // Products run on v_mfma_f32_32x32x16_bf16, which does sixteen times the multiplications of the fp32 instruction per
-// cycle: every fp32 operand is cut into three bf16 parts of eight bits each, high + middle + low, which together are
-// the number itself, and of the nine products of parts the six above 2^-24 of the whole are summed in fp32
-// (the instruction multiplies exactly).  Sums of corrections are kept apart from the sums of high parts, which makes the
-// result more exact than a chain of fp32 multiply-adds: relative error of products of 128 normal
-// values 8.5e-8, of the fp32 instruction with two chains 1.43e-7, with one 2.04e-7 (1024 values: 1.9e-7, 3.8e-7, 5.7e-7).
-// An infinity has no parts: it makes the sums NaN, and rows whose result is not finite are done again in
-// plain fp32 arithmetic.
+// cycle: every fp32 operand is split into three bf16 parts, high + middle + low, which together are the number itself (the
+// splitting of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For
+// Higher-Precision Computations", 2019), and six of the nine products of parts are summed in fp32 (the instruction
+// multiplies exactly).  High and middle parts are rounded to nearest, so a middle part is at most 2^-8 of its number and a low
+// part 2^-17; what is dropped, middle x low twice and low x low, is at most 2^-24 of the product, with no sign in
+// common: never more than one rounding of fp32, and nothing that adds up (parts that are cut off instead drop up to 2^-21,
+// always towards zero).  The corrections of a logit are summed apart from its high parts; a tile's share of an output is summed
+// on its own.  Relative error against 64 bits, of sums of 128 products, on a model of the arithmetic: normal values 5.7e-8 (fp32
+// multiply-adds 1.5e-7, cut parts 8.2e-8), one nonzero product 2.6e-8 (2.5e-8, 6.4e-8), two 2.7e-8 (3.7e-8, 6.6e-8).
+// An infinity, or what rounds to one (above 2^127.99), has no parts: it makes the sums NaN, and rows whose result is not finite are
+// done again in plain fp32 arithmetic.
 //
 // Operand layouts: lane (x = lane % 32, h = lane / 32) brings A[x][k] and B[k][x] for the eight k of its half;
 // accumulator register i of the lane is row 8 (i/4) + 4 h + i % 4, column x.  Both kernels form the transposed logit
@@ -26,7 +30,7 @@
 // are at once the B operand of step j of O^T = V^T P^T (a half brings the keys 16j + 4h .. +3 and 16j + 8 + 4h .. +3).
 // A sum over d runs in steps of 16 elements, eight to a half, so operands come as 16-byte pieces.
 //
-// Waves fetch 32-row tiles straight into LDS (global_load_lds) and cut what they read from there.  The waves of
+// Waves fetch 32-row tiles straight into LDS (global_load_lds) and split what they read from there.  The waves of
 // a workgroup share 32 or 64 query rows (attention) or 32 keys (scores) and take the tiles in turn, which keeps
 // the chip full from a few hundred rows on and the longest row's chain short; they add up at the end.
 // Scores of 32 heads x 1000 rows (window of 93 rows): 22 us.
@@ -48,31 +52,34 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ f32x16 mfma_bf16(const uint4& a, const uint4& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
-// Eight numbers as three bf16 operands whose sum they are: 24 bits in three times eight, cut and not rounded, so that
-// every difference is exact and no part of a finite number is infinite.
+// Eight numbers as three bf16 operands whose sum they are: 24 bits in three times eight, high and middle rounded to nearest, so that
+// every difference is exact and the last one has no more than eight bits.
 struct Parts {
   uint4 high, middle, low;
 };
-__device__ __forceinline__ Parts cut(const float (&x)[8]) {
+__device__ __forceinline__ Parts split(const float (&x)[8]) {
   uint32_t hi[4], mi[4], lo[4];
+  const auto upper = [](float a, float b) { return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u); };
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    float r[2], rr[2];
+    float h[2], r[2], m[2], rr[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      r[e] = x[2 * i + e] - __uint_as_float(__float_as_uint(x[2 * i + e]) & 0xFFFF0000u);
-      rr[e] = r[e] - __uint_as_float(__float_as_uint(r[e]) & 0xFFFF0000u);
+      // (a pair with a zero below is the rounded number in fp32: a pair of two has to be taken apart again by instructions that wait for each other)
+      h[e] = __uint_as_float(pack_bf16(0.f, x[2 * i + e]));
+      r[e] = x[2 * i + e] - h[e];
+      m[e] = __uint_as_float(pack_bf16(0.f, r[e]));
+      rr[e] = r[e] - m[e];
     }
-    const auto upper = [](float a, float b) { return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u); };
-    hi[i] = upper(x[2 * i], x[2 * i + 1]);
-    mi[i] = upper(r[0], r[1]);
+    hi[i] = upper(h[0], h[1]);
+    mi[i] = upper(m[0], m[1]);
     lo[i] = upper(rr[0], rr[1]);
   }
   return {make_uint4(hi[0], hi[1], hi[2], hi[3]), make_uint4(mi[0], mi[1], mi[2], mi[3]), make_uint4(lo[0], lo[1], lo[2], lo[3])};
 }
-__device__ __forceinline__ Parts cut(const f32x4& a, const f32x4& b) {
+__device__ __forceinline__ Parts split(const f32x4& a, const f32x4& b) {
   const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-  return cut(x);
+  return split(x);
 }
 // sum += the product of the high parts, rest += the five next largest ones
 __device__ __forceinline__ void multiply(const Parts& a, const Parts& b, f32x16& sum, f32x16& rest) {
@@ -104,16 +111,18 @@ template <int D, bool V_LAYOUT>
 __device__ __forceinline__ void fetch_tile(const float* __restrict__ Mg, int row0, int n, lds_char* tile, int first = 0,
                                            int step = 1) {
   constexpr int CPR = D / 4, RPL = 64 / CPR;  // chunks per row, rows per load
-  const int lane = threadIdx.x & 63;
+  int lane = threadIdx.x & 63;
   const float* base = Mg + (size_t)row0 * D;
   const int most = n - 1 - row0;
   if (most >= kRows - 1) {
-    const uint32_t lane0 = (uint32_t)((lane % CPR ^ tile_swizzle<V_LAYOUT>(lane / CPR)) * 16 + lane / CPR * D * 4);
+    uint32_t lane0 = (uint32_t)((lane % CPR ^ tile_swizzle<V_LAYOUT>(lane / CPR)) * 16 + lane / CPR * D * 4);
+    asm volatile("" : "+v"(lane0));  // (the others are formed here: kept over a kernel's loop they are more registers than it has)
 #pragma unroll
     for (int u = 0; u < kRows / RPL; ++u)
       if (u % step == first)
         dma16(base + u * RPL * D, lane0 ^ (uint32_t)(tile_swizzle<V_LAYOUT>(u * RPL) * 16), (uint32_t)(size_t)(tile + u * 1024));
   } else {
+    asm volatile("" : "+v"(lane));
 #pragma unroll
     for (int u = 0; u < kRows / RPL; ++u) {
       const int lrow = u * RPL + lane / CPR, pc = lane % CPR;
@@ -143,7 +152,7 @@ __device__ __forceinline__ float dot_row(const float* __restrict__ a, const floa
 }
 
 // The rows row0 .. end - 1 of a workgroup once more in plain arithmetic, which the matrix ops cannot replace where infinities are
-// about (an infinity cut into parts is NaN, and so is a masked key's probability, 0, times an infinite V element).  Every
+// about (the parts of an infinity are NaN, and so is a masked key's probability, 0, times an infinite V element).  Every
 // row reads only the keys it sees.  lds: kThreads + 8 floats.
 template <int D, bool WITH_O>
 __device__ __forceinline__ void rows_again(const float* Qg, const float* Kg, const float* Vg, float* lse2, float* Og, int row0,
@@ -189,7 +198,7 @@ __device__ __forceinline__ void rows_again(const float* Qg, const float* Kg, con
 // NW waves per workgroup, which has 32 RB query rows: wave w takes the rows 32 (w % RB) .. and every P-th key tile from
 // w / RB on.  The RB waves of a part share its K and its V tile, in buffers of their own: V(t) is under way while the
 // logits of tile t and their exponentials are formed, K(t + P) during the products with V(t).  A tile takes a wave 96 matrix ops
-// (d = 128) of 32 cycles and about a thousand vector instructions, most of them for cutting K and V.  A wave alone on its SIMD
+// (d = 128) of 32 cycles and about a thousand vector instructions, most of them for splitting K and V.  A wave alone on its SIMD
 // issues a vector instruction every six cycles, two of them one every three, so registers are held to what two waves can have.
 // 32 heads x 1000 rows x 128: 80 us (8.2 GFLOP = 102 TFLOP/s of fp32 products, of which a large fp32 matrix product reaches
 // 154; on the fp32 instruction 103 us); 849 x 210: 152 (217).
@@ -238,13 +247,12 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
 #pragma unroll
     for (int c = 0; c < 2 * C16; ++c) raw[c] = *reinterpret_cast<const f32x4*>(qr + 16 * (c >> 1) + 4 * (c & 1));
 #pragma unroll
-    for (int c = 0; c < C16; ++c) qf[c] = cut(raw[2 * c], raw[2 * c + 1]);
+    for (int c = 0; c < C16; ++c) qf[c] = split(raw[2 * c], raw[2 * c + 1]);
 #pragma unroll
     for (int c = 0; c < C16; ++c) asm volatile("" : "+v"(qf[c].high.x));  // formed here, not in every round of the loop
   }
-  int koff[8];  // chunk 4c + 2h + e of row l32: the swizzle reaches the low four chunk bits
-#pragma unroll
-  for (int i = 0; i < 8; ++i) koff[i] = l32 * D * 4 + (((4 * (i >> 1) + 2 * h + (i & 1)) ^ tile_swizzle<false>(l32)) << 4);
+  // chunk 4c + 2h + e of row l32: the swizzle reaches the low four chunk bits, so c and e are an exclusive or with the first one's place
+  const uint32_t koff = l32 * D * 4 + (((2 * h) ^ tile_swizzle<false>(l32)) << 4);
   const int voff[2] = {4 * h * D * 4 + l32 * 4 + h * 128, 4 * h * D * 4 + l32 * 4 + (1 - h) * 128};
 
   f32x16 oacc[WITH_O ? DB : 1];
@@ -269,17 +277,18 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[i] = rest[i] = 0.f;
       const auto read = [&](int c, f32x4& a, f32x4& b) {
-        a = lds_read4(kt + (c >> 2) * 256 + koff[2 * (c & 3)]);
-        b = lds_read4(kt + (c >> 2) * 256 + koff[2 * (c & 3) + 1]);
+        const uint32_t at = (uint32_t)(size_t)kt + koff;
+        a = lds_read4((const lds_char*)(size_t)(at ^ (c & 3) << 6) + (c >> 2) * 256);
+        b = lds_read4((const lds_char*)(size_t)(at ^ ((c & 3) << 6 | 16)) + (c >> 2) * 256);
       };
       f32x4 a, b;
       read(0, a, b);
 #pragma unroll
       for (int c = 0; c < C16; ++c) {
-        const Parts kp = cut(a, b);
+        const Parts kp = split(a, b);
         if (c + 1 < C16) read(c + 1, a, b);
         multiply(kp, qf[c], s, rest);
-        if (D == 128) __builtin_amdgcn_sched_barrier(0);  // (more pieces at once do not fit the registers)
+        __builtin_amdgcn_sched_barrier(0);  // (more pieces at once do not fit the registers)
       }
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[i] += rest[i];
@@ -316,7 +325,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
           float x[8];
 #pragma unroll
           for (int i = 0; i < 8; ++i) x[i] = s[8 * j + i];
-          pf[j] = cut(x);
+          pf[j] = split(x);
         }
       }
     }
@@ -340,14 +349,14 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
 #pragma unroll
             for (int i = 0; i < 16; ++i) o[i] = 0.f;
           }
-          const Parts vp = cut(x);
+          const Parts vp = split(x);
           if (v + 1 < NV) read(v + 1);
           multiply(vp, pf[v & 1], o, o);
           if (v % 2 == 1) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) oacc[v >> 1][i] += o[i];
           }
-          if (D == 128) __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
     }
@@ -447,7 +456,7 @@ __global__ __launch_bounds__(NW * 64, 2) void scores_f32_kernel(
 #pragma unroll
     for (int c = 0; c < 2 * C16; ++c) asm volatile("" : "+v"(raw[c]));  // waited for here, not in every round of the loop
 #pragma unroll
-    for (int c = 0; c < C16; ++c) kf[c] = cut(raw[2 * c], raw[2 * c + 1]);
+    for (int c = 0; c < C16; ++c) kf[c] = split(raw[2 * c], raw[2 * c + 1]);
   }
   int qoff[8];
 #pragma unroll
@@ -468,7 +477,7 @@ __global__ __launch_bounds__(NW * 64, 2) void scores_f32_kernel(
 #pragma unroll
     for (int c = 0; c < C16; ++c) {
       const lds_char* p = qt + (c >> 2) * 256;
-      multiply(kf[c], cut(lds_read4(p + qoff[2 * (c & 3)]), lds_read4(p + qoff[2 * (c & 3) + 1])), s, rest);
+      multiply(kf[c], split(lds_read4(p + qoff[2 * (c & 3)]), lds_read4(p + qoff[2 * (c & 3) + 1])), s, rest);
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] += rest[i];

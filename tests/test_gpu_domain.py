@@ -162,3 +162,65 @@ def test_fp32_infinite_operands(d, G, n, cached):
     if not cached:
         s = prefill(q, k, v)[1]
         assert torch.isfinite(s[:3]).all() and s[0, at] == 0.0 and torch.isnan(s[3, at:]).any()
+
+
+# fp32 prompts by tiles in every launch form (blocks per workgroup, waves), and chunks
+FP32_FORMS = [(64, 21, 200, 0), (64, 60, 200, 0), (64, 260, 130, 0), (64, 300, 70, 50), (128, 11, 200, 0), (128, 200, 130, 0), (128, 300, 70, 50)]
+
+
+@pytest.mark.parametrize("d,G,n,cached", FP32_FORMS)
+def test_fp32_single_products(d, G, n, cached):
+    """Logits that are one product each, of operands whose halves after the eighth bit are all ones (what a cut part drops is
+    largest there) and of random ones: a product is off by no more than two fp32 roundings.  Seen through the probabilities:
+    V is one-hot, key 0 has logit 0, all others -15 to -100."""
+    rng = np.random.default_rng(d + G)
+    total = cached + n
+    unlucky = np.uint32(0x3F80FFFF).view(np.float32)
+    mantissas = lambda shape: np.where(rng.random(shape) < 0.5, unlucky, rng.uniform(1, 2, shape)).astype(np.float32)
+    q, k, v = np.zeros((G, 1, n, d), np.float32), np.zeros((G, total, d), np.float32), np.zeros((G, total, d), np.float32)
+    at = rng.integers(0, d, (G, 1, n, 1))
+    np.put_along_axis(q, at, mantissas(at.shape), 3)
+    k[:, 1:] = -2 * d * mantissas((G, total - 1, d))
+    v[:, np.arange(total), np.arange(total) % d] = 1.0
+    tq, tk, tv = (torch.from_numpy(x).cuda() for x in (q, k, v))
+    o, s = (chunk(tq, tk, tv, cached), None) if cached else prefill(tq, tk, tv, alpha=0.5)
+    heads = sorted({0, G // 2, G - 1})
+    visible = np.arange(total)[None] <= cached + np.arange(n)[:, None]
+    rounding = 2.0 ** -24
+    for g in heads:
+        z = q[g, 0].astype(np.float64) @ k[g].astype(np.float64).T / np.sqrt(d)
+        assert z[:, 1:].max() < -15 and z.min() > -100
+        p = np.exp(np.where(visible, z, -np.inf))
+        p /= p.sum(1, keepdims=True)
+        # two roundings of the product, two of its scaling; exponential, sum and quotient: eight of the result
+        off = p * rounding * (4 * np.abs(z) + 8)
+        want = p @ v[g].astype(np.float64)
+        seen = want > 2.0 ** -108  # (below, parts of a probability are subnormal)
+        assert (np.abs(o[g, 0].double().cpu().numpy() - want) <= off @ v[g])[seen].all()
+        if s is not None:
+            w = 0.5 ** np.arange(n - 1, -1, -1.0)
+            want = w @ p
+            seen = want > 2.0 ** -108
+            assert (np.abs(s[g].double().cpu().numpy() - want) <= w @ off)[seen].all()
+
+
+@pytest.mark.parametrize("d,G,n,cached", [f for f in FP32_FORMS if not f[3]])
+def test_fp32_products_of_one_sign_have_no_bias(d, G, n, cached):
+    """Operands of one sign, a little above a power of two: an error that always has the sign of the product does not average out
+    over the sum or the keys.  The mean error of the logits stays below half a rounding."""
+    rng = np.random.default_rng(d + n)
+    q = rng.uniform(1, 1.0078, (G, 1, n, d)).astype(np.float32)
+    k = -4 * rng.uniform(1, 1.0078, (G, n, d)).astype(np.float32)
+    k[:, 0] = 0
+    v = rng.standard_normal((G, n, d)).astype(np.float32)
+    v[..., 0] = 0
+    v[:, 0] = 0
+    v[:, 0, 0] = 1  # (column 0 of an output: the first key's probability)
+    _, s = prefill(*(torch.from_numpy(x).cuda() for x in (q, k, v)), alpha=0.0)  # the last row's probabilities
+    scale = np.float64(np.float32(np.float32(1.4426950408889634) / np.float32(np.sqrt(np.float32(d)))))
+    errors = []
+    for g in range(0, G, max(1, G // 20)):
+        z = k[g].astype(np.float64) @ q[g, 0, -1].astype(np.float64) * scale  # (as an exponent of 2)
+        got = np.log2(s[g].double().cpu().numpy())[1:]
+        errors.append((got - (z - np.log2(np.exp2(z).sum()))[1:]) / z[1:])
+    assert abs(np.mean(errors)) <= 2.0 ** -25, np.mean(errors) * 2 ** 24

@@ -21,8 +21,9 @@
 // always towards zero).  The corrections of a logit are summed apart from its high parts; a tile's share of an output is summed
 // on its own.  Relative error against 64 bits, of sums of 128 products, on a model of the arithmetic: normal values 5.7e-8 (fp32
 // multiply-adds 1.5e-7, cut parts 8.2e-8), one nonzero product 2.6e-8 (2.5e-8, 6.4e-8), two 2.7e-8 (3.7e-8, 6.6e-8).
-// An infinity, or what rounds to one (above 2^127.99), has no parts: it makes the sums NaN, and rows whose result is not finite are
-// done again in plain fp32 arithmetic.
+//
+// An infinity, a NaN and what rounds to one (above 2^127.99) have no parts.  A workgroup whose results are not finite does its block
+// once more, with the logits that are not finite and the products of such values in plain fp32 arithmetic (`careful` below).
 //
 // Operand layouts: lane (x = lane % 32, h = lane / 32) brings A[x][k] and B[k][x] for the eight k of its half;
 // accumulator register i of the lane is row 8 (i/4) + 4 h + i % 4, column x.  Both kernels form the transposed logit
@@ -30,11 +31,13 @@
 // are at once the B operand of step j of O^T = V^T P^T (a half brings the keys 16j + 4h .. +3 and 16j + 8 + 4h .. +3).
 // A sum over d runs in steps of 16 elements, eight to a half, so operands come as 16-byte pieces.
 //
-// Waves fetch 32-row tiles straight into LDS (global_load_lds) and split what they read from there.  The waves of
+// Waves fetch 32-row tiles straight into LDS (global_load_lds) and cut what they read from there.  The waves of
 // a workgroup share 32 or 64 query rows (attention) or 32 keys (scores) and take the tiles in turn, which keeps
 // the chip full from a few hundred rows on and the longest row's chain short; they add up at the end.
 // Scores of 32 heads x 1000 rows (window of 93 rows): 22 us.
 #include <math.h>
+
+#include <type_traits>
 
 #include "a2sf_dev.h"
 #include "a2sf_internal.h"
@@ -80,6 +83,14 @@ __device__ __forceinline__ Parts split(const float (&x)[8]) {
 __device__ __forceinline__ Parts split(const f32x4& a, const f32x4& b) {
   const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
   return split(x);
+}
+// The number that element e of eight was split from.
+__device__ __forceinline__ float joined(const Parts& p, int e) {
+  const auto part = [&](const uint4& w) {
+    const uint32_t pair = (e >> 1) == 0 ? w.x : (e >> 1) == 1 ? w.y : (e >> 1) == 2 ? w.z : w.w;
+    return __uint_as_float(e & 1 ? pair & 0xFFFF0000u : pair << 16);
+  };
+  return (part(p.high) + part(p.middle)) + part(p.low);
 }
 // sum += the product of the high parts, rest += the five next largest ones
 __device__ __forceinline__ void multiply(const Parts& a, const Parts& b, f32x16& sum, f32x16& rest) {
@@ -151,54 +162,35 @@ __device__ __forceinline__ float dot_row(const float* __restrict__ a, const floa
   return acc;
 }
 
-// The rows row0 .. end - 1 of a workgroup once more in plain arithmetic, which the matrix ops cannot replace where infinities are
-// about (the parts of an infinity are NaN, and so is a masked key's probability, 0, times an infinite V element).  Every
-// row reads only the keys it sees.  lds: kThreads + 8 floats.
-template <int D, bool WITH_O>
-__device__ __forceinline__ void rows_again(const float* Qg, const float* Kg, const float* Vg, float* lse2, float* Og, int row0,
-                                           int end, int off, float scale_log2e, float* lds) {
-  const int tid = threadIdx.x, c = tid % D;
-  float* const red = lds + kThreads;
-#pragma unroll 1
-  for (int r = row0; r < end; ++r) {
-    const int nk = off + r + 1;
-    const float* q = Qg + (size_t)r * D;
-    float m = kLowest, l = 0.f;
-#pragma unroll 1
-    for (int j = tid; j < nk; j += kThreads) {
-      const float s = dot_row<D>(q, Kg + (size_t)j * D), up = fmaxf(m, s);
-      l = l * exp2f((m - up) * scale_log2e) + exp2f((s - up) * scale_log2e);
-      m = up;
-    }
-    const float all = block_max(m, red);
-    l = block_sum(l * exp2f((m - all) * scale_log2e), red);
-    if (tid == 0) lse2[r] = fmaf(all, scale_log2e, log2f(l));
-    if (!WITH_O) continue;
-    float acc = 0.f;
-#pragma unroll 1
-    for (int j0 = 0; j0 < nk; j0 += kThreads) {
-      __syncthreads();
-      if (j0 + tid < nk) lds[tid] = exp2f((dot_row<D>(q, Kg + (size_t)(j0 + tid) * D) - all) * scale_log2e);
-      __syncthreads();
-      for (int j = tid / D; j < min(kThreads, nk - j0); j += kThreads / D) acc = fmaf(lds[j], Vg[(size_t)(j0 + j) * D + c], acc);
-    }
-    __syncthreads();
-    lds[tid] = acc;
-    __syncthreads();
-    if (tid < D) {
-      float t = 0.f;
+__device__ __forceinline__ bool finite(float x) { return fabsf(x) < INFINITY; }
+__device__ __forceinline__ bool has_parts(float x) { return fabsf(x) <= 0x1p127f; }
+
+// The 16 logits of a lane in plain arithmetic.  own(c): the piece c of four elements of the lane's own row; other(row, c): of the row
+// (of the tile's 32) that register i belongs to.
+template <int D, typename OwnFn, typename OtherFn>
+__device__ __forceinline__ f32x16 plain_logits(int h, OwnFn own, OtherFn other) {
+  f32x16 s;
 #pragma unroll
-      for (int p = 0; p < kThreads / D; ++p) t += lds[p * D + tid];
-      Og[(size_t)r * D + tid] = t / l;
+  for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll 1
+  for (int c = 0; c < D / 4; ++c) {
+    const f32x4 x = own(c);
+    asm volatile("" : "+v"(h));  // (no addresses kept from round to round: the registers are those of the products)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const f32x4 y = other(8 * (i >> 2) + 4 * h + (i & 3), c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[i] = fmaf(x[e], y[e], s[i]);
+      if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // (no more registers than the rest of the kernel has)
     }
-    __syncthreads();
   }
+  return s;
 }
 
 // NW waves per workgroup, which has 32 RB query rows: wave w takes the rows 32 (w % RB) .. and every P-th key tile from
 // w / RB on.  The RB waves of a part share its K and its V tile, in buffers of their own: V(t) is under way while the
 // logits of tile t and their exponentials are formed, K(t + P) during the products with V(t).  A tile takes a wave 96 matrix ops
-// (d = 128) of 32 cycles and about a thousand vector instructions, most of them for splitting K and V.  A wave alone on its SIMD
+// (d = 128) of 32 cycles and about a thousand vector instructions, most of them for cutting K and V.  A wave alone on its SIMD
 // issues a vector instruction every six cycles, two of them one every three, so registers are held to what two waves can have.
 // 32 heads x 1000 rows x 128: 80 us (8.2 GFLOP = 102 TFLOP/s of fp32 products, of which a large fp32 matrix product reaches
 // 154; on the fp32 instruction 103 us); 849 x 210: 152 (217).
@@ -218,196 +210,261 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
   int g, rank;
   if (!ordered_item(GQ, nqb, g, rank)) return;
   const int qb = rc.first_row / BM + nqb - 1 - rank;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), block = wave % RB, part = wave / RB;
-  const int l32 = lane & 31, h = lane >> 5;
-  const int n = rc.m, row0 = qb * BM, wrow0 = row0 + kRows * block;
+  const int n = rc.m, row0 = qb * BM;
   const int gk = g / rc.kv_group;  // the K/V head this query head reads
   const int off = rc.off_heads ? rc.off_heads[gk] : 0;
   if (off < 0) {  // a head the caller's precondition excludes: its rows are flagged
     if (WITH_O)
-      for (int e = tid; e < min(BM, n - row0) * D; e += NT)
+      for (int e = threadIdx.x; e < min(BM, n - row0) * D; e += NT)
         O[((size_t)g * n + row0) * D + e] = __int_as_float(0x7FC00000);
     return;
   }
   const int nk = off + n;
   const float* Kg = K + (size_t)gk * rc.kv_stride * D;
   const float* Vg = V + (size_t)gk * rc.kv_stride * D;
-  lds_char* const kbuf = (lds_char*)smem + part * 2 * kTileBytes;
-  lds_char* const vbuf = kbuf + kTileBytes;  // (without outputs: a second K buffer)
-
   const int ntiles = (off + min(n, row0 + BM) - 1) / kRows + 1;
-  const int nt_wave = wrow0 < n ? (off + min(n, wrow0 + kRows) - 1) / kRows + 1 : 0;  // tiles this wave's rows see
-  if (part < ntiles) fetch_tile<D, false>(Kg, part * kRows, nk, kbuf, block, RB);
-  // Q (B operand): lane (query l32, half h) holds the elements 16c + 8h .. + 7
-  Parts qf[C16];
-  {
-    const float* qr = Q + ((size_t)g * n + min(wrow0 + l32, n - 1)) * D + 8 * h;
-    f32x4 raw[2 * C16];
-#pragma unroll
-    for (int c = 0; c < 2 * C16; ++c) raw[c] = *reinterpret_cast<const f32x4*>(qr + 16 * (c >> 1) + 4 * (c & 1));
-#pragma unroll
-    for (int c = 0; c < C16; ++c) qf[c] = split(raw[2 * c], raw[2 * c + 1]);
-#pragma unroll
-    for (int c = 0; c < C16; ++c) asm volatile("" : "+v"(qf[c].high.x));  // formed here, not in every round of the loop
-  }
-  // chunk 4c + 2h + e of row l32: the swizzle reaches the low four chunk bits, so c and e are an exclusive or with the first one's place
-  const uint32_t koff = l32 * D * 4 + (((2 * h) ^ tile_swizzle<false>(l32)) << 4);
-  const int voff[2] = {4 * h * D * 4 + l32 * 4 + h * 128, 4 * h * D * 4 + l32 * 4 + (1 - h) * 128};
 
-  f32x16 oacc[WITH_O ? DB : 1];
+  // The whole block.  `careful`: the logits and products of operands without parts in plain arithmetic, tile by tile (a block
+  // takes about twice the time, a tile that has them four times; a number without parts in V costs its key 500 instructions).
+  const auto pass = [&](auto careful_) __attribute__((always_inline)) {
+    constexpr bool careful = decltype(careful_)::value;
+    int tid = threadIdx.x;
+    if (careful) asm volatile("" : "+v"(tid));  // (nothing lives on from one pass to the other)
+    const int lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), block = wave % RB, part = wave / RB;
+    const int wrow0 = row0 + kRows * block;
+    lds_char* const kbuf = (lds_char*)smem + part * 2 * kTileBytes;
+    lds_char* const vbuf = kbuf + kTileBytes;  // (without outputs: a second K buffer)
+    const int nt_wave = wrow0 < n ? (off + min(n, wrow0 + kRows) - 1) / kRows + 1 : 0;  // tiles this wave's rows see
+    // chunk 4c + 2h + e of row l32: the swizzle reaches the low four chunk bits, so c and e are an exclusive or with the first one's place
+    const uint32_t koff = l32 * D * 4 + (((2 * h) ^ tile_swizzle<false>(l32)) << 4);
+    const int voff[2] = {4 * h * D * 4 + l32 * 4 + h * 128, 4 * h * D * 4 + l32 * 4 + (1 - h) * 128};
+    const int newest = off + wrow0 + l32;  // newest key this lane's row sees
+    const float* const q_row = Q + ((size_t)g * n + min(wrow0 + l32, n - 1)) * D;
+    if (part < ntiles) fetch_tile<D, false>(Kg, part * kRows, nk, kbuf, block, RB);
+    // Q (B operand): lane (query l32, half h) holds the elements 16c + 8h .. + 7; a careful pass splits them for every tile again, which
+    // leaves it registers for the plain arithmetic (memory for spilled ones is paid for by every workgroup, at its start)
+    Parts qf[careful ? 1 : C16];
+    const auto query = [&](int c) -> Parts {
+      if constexpr (!careful) return qf[c];
+      const float* qr = q_row + 16 * c + 8 * h;
+      asm volatile("" : "+v"(qr));
+      return split(*reinterpret_cast<const f32x4*>(qr), *reinterpret_cast<const f32x4*>(qr + 4));
+    };
+    if constexpr (!careful) {
+      const float* qr = q_row + 8 * h;
+      f32x4 raw[2 * C16];
 #pragma unroll
-  for (int db = 0; db < (WITH_O ? DB : 1); ++db)
+      for (int c = 0; c < 2 * C16; ++c) raw[c] = *reinterpret_cast<const f32x4*>(qr + 16 * (c >> 1) + 4 * (c & 1));
 #pragma unroll
-    for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
-  float m = kLowest, l = 0.f;
-  const int newest = off + wrow0 + l32;  // newest key this lane's row sees
-  if (tid == 0) again = false;
+      for (int c = 0; c < C16; ++c) qf[c] = split(raw[2 * c], raw[2 * c + 1]);
+#pragma unroll
+      for (int c = 0; c < C16; ++c) asm volatile("" : "+v"(qf[c].high.x));  // formed here, not in every round of the loop
+      if (tid == 0) again = false;
+    }
 
-  for (int t = part, step = 0; t < ntiles + part; t += P, ++step) {  // (the parts take the same number of steps)
-    const int key0 = t * kRows;
-    const bool mine = t < nt_wave;
-    lds_char* const kt = WITH_O || step % 2 == 0 ? kbuf : vbuf;
-    arrived();  // K tile t; the other buffer is free
-    if (WITH_O && t < ntiles) fetch_tile<D, true>(Vg, key0, nk, vbuf, block, RB);
-    if (!WITH_O && t + P < ntiles) fetch_tile<D, false>(Kg, key0 + P * kRows, nk, kt == kbuf ? vbuf : kbuf, block, RB);
-    Parts pf[2];
-    if (mine) {
-      f32x16 s, rest;
+    f32x16 oacc[WITH_O ? DB : 1];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s[i] = rest[i] = 0.f;
-      const auto read = [&](int c, f32x4& a, f32x4& b) {
-        const uint32_t at = (uint32_t)(size_t)kt + koff;
-        a = lds_read4((const lds_char*)(size_t)(at ^ (c & 3) << 6) + (c >> 2) * 256);
-        b = lds_read4((const lds_char*)(size_t)(at ^ ((c & 3) << 6 | 16)) + (c >> 2) * 256);
-      };
-      f32x4 a, b;
-      read(0, a, b);
+    for (int db = 0; db < (WITH_O ? DB : 1); ++db)
 #pragma unroll
-      for (int c = 0; c < C16; ++c) {
-        const Parts kp = split(a, b);
-        if (c + 1 < C16) read(c + 1, a, b);
-        multiply(kp, qf[c], s, rest);
-        __builtin_amdgcn_sched_barrier(0);  // (more pieces at once do not fit the registers)
-      }
+      for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
+    float m = kLowest, l = 0.f;
+
+    for (int t = part, step = 0; t < ntiles + part; t += P, ++step) {  // (the parts take the same number of steps)
+      const int key0 = t * kRows;
+      const bool mine = t < nt_wave;
+      lds_char* const kt = WITH_O || step % 2 == 0 ? kbuf : vbuf;
+      arrived();  // K tile t; the other buffer is free
+      if (WITH_O && t < ntiles) fetch_tile<D, true>(Vg, key0, nk, vbuf, block, RB);
+      if (!WITH_O && t + P < ntiles) fetch_tile<D, false>(Kg, key0 + P * kRows, nk, kt == kbuf ? vbuf : kbuf, block, RB);
+      Parts pf[2];
+      if (mine) {
+        f32x16 s, rest;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s[i] += rest[i];
-      if (key0 + kRows - 1 > off + wrow0) {  // the tile reaches past the block's first row
+        for (int i = 0; i < 16; ++i) s[i] = rest[i] = 0.f;
+        const auto read = [&](int c, f32x4& a, f32x4& b) {
+          const uint32_t at = (uint32_t)(size_t)kt + koff;
+          a = lds_read4((const lds_char*)(size_t)(at ^ (c & 3) << 6) + (c >> 2) * 256);
+          b = lds_read4((const lds_char*)(size_t)(at ^ ((c & 3) << 6 | 16)) + (c >> 2) * 256);
+        };
+        f32x4 a, b;
+        read(0, a, b);
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (key0 + 8 * (i >> 2) + 4 * h + (i & 3) > newest) s[i] = -INFINITY;
-      }
-      float mx = s[0];
+        for (int c = 0; c < C16; ++c) {
+          const Parts kp = split(a, b);
+          if (c + 1 < C16) read(c + 1, a, b);
+          multiply(kp, query(c), s, rest);
+          __builtin_amdgcn_sched_barrier(0);  // (more pieces at once do not fit the registers)
+        }
 #pragma unroll
-      for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
-      mx = across_rows(mx, OpMax(), false, true);
-      const float m_new = fmaxf(m, mx);
-      if (__any(m_new > m)) {
-        const float corr = exp2f((m - m_new) * scale_log2e);
-        l *= corr;
+        for (int i = 0; i < 16; ++i) s[i] += rest[i];
+        if constexpr (careful) {
+          bool some = false;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) some |= !finite(s[i]);
+          if (__any(some)) {
+            const f32x16 exact = plain_logits<D>(
+                h, [&](int c) { return *reinterpret_cast<const f32x4*>(q_row + 4 * c); },
+                [&](int row, int c) { return lds_read4(kt + row * D * 4 + ((c ^ tile_swizzle<false>(row)) << 4)); });
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = finite(s[i]) ? s[i] : exact[i];
+          }
+        }
+        if (key0 + kRows - 1 > off + wrow0) {  // the tile reaches past the block's first row
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (key0 + 8 * (i >> 2) + 4 * h + (i & 3) > newest) s[i] = -INFINITY;
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+        mx = across_rows(mx, OpMax(), false, true);
+        const float m_new = fmaxf(m, mx);
+        if (__any(m_new > m)) {
+          const float corr = exp2f((m - m_new) * scale_log2e);
+          l *= corr;
+          if (WITH_O) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+              for (int i = 0; i < 16; ++i) oacc[db][i] *= corr;
+          }
+          m = m_new;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f((s[i] - m) * scale_log2e);
+        float sum[4];  // (of few terms each before they join the row's)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] = (s[4 * i] + s[4 * i + 1]) + (s[4 * i + 2] + s[4 * i + 3]);
+        l += (sum[0] + sum[1]) + (sum[2] + sum[3]);
         if (WITH_O) {
 #pragma unroll
-          for (int db = 0; db < DB; ++db)
+          for (int j = 0; j < 2; ++j) {
+            float x[8];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[db][i] *= corr;
+            for (int i = 0; i < 8; ++i) x[i] = s[8 * j + i];
+            pf[j] = split(x);
+          }
         }
-        m = m_new;
       }
-#pragma unroll
-      for (int i = 0; i < 16; ++i) s[i] = __builtin_amdgcn_exp2f((s[i] - m) * scale_log2e);
-      float sum[4];  // (of few terms each before they join the row's)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) sum[i] = (s[4 * i] + s[4 * i + 1]) + (s[4 * i + 2] + s[4 * i + 3]);
-      l += (sum[0] + sum[1]) + (sum[2] + sum[3]);
-      if (WITH_O) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
+      if constexpr (WITH_O) {
+        arrived();  // V tile t; every wave that shares K tile t has read it
+        if (t + P < ntiles) fetch_tile<D, false>(Kg, key0 + P * kRows, nk, kbuf, block, RB);
+        if (mine) {
+          constexpr int NV = 2 * DB;  // (columns 32 db .., step j), j fastest
           float x[8];
+          const auto read = [&](int v) {
+            const int db = v >> 1, j = v & 1;
 #pragma unroll
-          for (int i = 0; i < 8; ++i) x[i] = s[8 * j + i];
-          pf[j] = split(x);
+            for (int i = 0; i < 8; ++i)
+              x[i] = lds_read1(vbuf + voff[db & 1] + (db >> 1) * 256 + (16 * j + 8 * (i >> 2) + (i & 3)) * D * 4);
+          };
+          f32x16 o;  // of this tile alone: rounded at its own size before it joins the others
+          read(0);
+#pragma unroll
+          for (int v = 0; v < NV; ++v) {
+            if (v % 2 == 0) {
+#pragma unroll
+              for (int i = 0; i < 16; ++i) o[i] = 0.f;
+            }
+            if constexpr (careful) {
+#pragma unroll
+              for (int i = 0; i < 8; ++i) x[i] = has_parts(x[i]) ? x[i] : 0.f;
+            }
+            const Parts vp = split(x);
+            if (v + 1 < NV) read(v + 1);
+            multiply(vp, pf[v & 1], o, o);
+            if (v % 2 == 1) {
+#pragma unroll
+              for (int i = 0; i < 16; ++i) oacc[v >> 1][i] += o[i];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if constexpr (careful) {
+            // what was left out: p v for every v without parts, by the rows that see its key
+#pragma unroll 1
+            for (int key = 0; key < kRows; ++key) {
+              const lds_char* const v_row = vbuf + key * D * 4;
+              bool some = !has_parts(lds_read1(v_row + lane * 4));
+              if (D == 128) some |= !has_parts(lds_read1(v_row + 256 + lane * 4));
+              if (!__any(some)) continue;
+              const int at = 4 * (key >> 3) + (key & 3);  // its register, in the lanes of half (key >> 2) & 1
+              float p = 0.f;
+#pragma unroll
+              for (int j = 0; j < 2; ++j)  // (put together again for every key: no registers for sixteen numbers)
+                asm volatile("" : "+v"(pf[j].high.x), "+v"(pf[j].high.y), "+v"(pf[j].high.z), "+v"(pf[j].high.w), "+v"(pf[j].middle.x),
+                             "+v"(pf[j].middle.y), "+v"(pf[j].middle.z), "+v"(pf[j].middle.w), "+v"(pf[j].low.x),
+                             "+v"(pf[j].low.y), "+v"(pf[j].low.z), "+v"(pf[j].low.w));
+#pragma unroll
+              for (int i = 0; i < 16; ++i) p = at == i ? joined(pf[i >> 3], i & 7) : p;
+              const float theirs = __shfl_xor(p, 32);
+              p = ((key >> 2) & 1) == h ? p : theirs;
+#pragma unroll
+              for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                  const f32x4 v4 = lds_read4(v_row + (((8 * db + 2 * i4 + h) ^ tile_swizzle<true>(key)) << 4));
+#pragma unroll
+                  for (int e = 0; e < 4; ++e)
+                    if (key0 + key <= newest && !has_parts(v4[e])) oacc[db][4 * i4 + e] = fmaf(p, v4[e], oacc[db][4 * i4 + e]);
+                  __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+          }
         }
       }
+    }
+    wait_vm_barrier<0>();  // the buffers are reused below
+
+    // ---- the parts' sums
+    l = across_rows(l, OpAdd(), false, true);
+    if (h == 0) { m_s[wave][l32] = m; l_s[wave][l32] = l; }
+    __syncthreads();
+    float mall = m_s[block][l32];
+#pragma unroll
+    for (int w = 1; w < P; ++w) mall = fmaxf(mall, m_s[block + RB * w][l32]);
+    float lall = 0.f;
+#pragma unroll
+    for (int w = 0; w < P; ++w) lall += l_s[block + RB * w][l32] * exp2f((m_s[block + RB * w][l32] - mall) * scale_log2e);
+    if (part == 0 && h == 0 && wrow0 + l32 < n) {
+      float* const lse = LSE2 + (size_t)g * n + wrow0 + l32;
+      // (a sum that was finite stands, whatever the outputs are: the scores' logits are those it was formed from)
+      if (!careful || !finite(*lse)) *lse = fmaf(mall, scale_log2e, log2f(lall));
+      if (!careful && !(lall > 0.f && lall < INFINITY)) again = true;
     }
     if constexpr (WITH_O) {
-      arrived();  // V tile t; every wave that shares K tile t has read it
-      if (t + P < ntiles) fetch_tile<D, false>(Kg, key0 + P * kRows, nk, kbuf, block, RB);
-      if (mine) {
-        constexpr int NV = 2 * DB;  // (columns 32 db .., step j), j fastest
-        float x[8];
-        const auto read = [&](int v) {
-          const int db = v >> 1, j = v & 1;
+      const float f = exp2f((m - mall) * scale_log2e) / lall;
+      // a tile's room per wave now takes its outputs, [query][d], chunks swizzled as in a tile
+      lds_char* const strip = (lds_char*)smem + wave * kTileBytes;
 #pragma unroll
-          for (int i = 0; i < 8; ++i)
-            x[i] = lds_read1(vbuf + voff[db & 1] + (db >> 1) * 256 + (16 * j + 8 * (i >> 2) + (i & 3)) * D * 4);
-        };
-        f32x16 o;  // of this tile alone: rounded at its own size before it joins the others
-        read(0);
+      for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          if (v % 2 == 0) {
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const f32x4 w = {oacc[db][4 * i4] * f, oacc[db][4 * i4 + 1] * f, oacc[db][4 * i4 + 2] * f,
+                           oacc[db][4 * i4 + 3] * f};
+          const int chunk = 8 * db + 2 * i4 + h;
+          *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(
+              strip + l32 * D * 4 + ((chunk ^ tile_swizzle<false>(l32)) << 4)) = w;
+        }
+      __syncthreads();
+      constexpr int CPR = D / 4;
+      for (int u = tid; u < BM * CPR; u += NT) {
+        const int r = u / CPR, c = u % CPR;
+        if (row0 + r >= n) break;
+        const lds_char* p = (const lds_char*)smem + r * D * 4 + ((c ^ tile_swizzle<false>(r)) << 4);
+        f32x4 a = lds_read4(p) + lds_read4(p + RB * kTileBytes);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) o[i] = 0.f;
-          }
-          const Parts vp = split(x);
-          if (v + 1 < NV) read(v + 1);
-          multiply(vp, pf[v & 1], o, o);
-          if (v % 2 == 1) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[v >> 1][i] += o[i];
-          }
-          __builtin_amdgcn_sched_barrier(0);
+        for (int w = 2; w < P; w += 2) a += lds_read4(p + RB * w * kTileBytes) + lds_read4(p + RB * (w + 1) * kTileBytes);
+        *reinterpret_cast<f32x4*>(O + ((size_t)g * n + row0 + r) * D + c * 4) = a;
+        if constexpr (!careful) {
+          if (!(fabsf(a[0] * 0.f) + fabsf(a[1] * 0.f) + fabsf(a[2] * 0.f) + fabsf(a[3] * 0.f) == 0.f)) again = true;
         }
       }
     }
-  }
-  wait_vm_barrier<0>();  // the buffers are reused below
-
-  // ---- the parts' sums
-  l = across_rows(l, OpAdd(), false, true);
-  if (h == 0) { m_s[wave][l32] = m; l_s[wave][l32] = l; }
+  };
+  pass(std::false_type{});
   __syncthreads();
-  float mall = m_s[block][l32];
-#pragma unroll
-  for (int w = 1; w < P; ++w) mall = fmaxf(mall, m_s[block + RB * w][l32]);
-  float lall = 0.f;
-#pragma unroll
-  for (int w = 0; w < P; ++w) lall += l_s[block + RB * w][l32] * exp2f((m_s[block + RB * w][l32] - mall) * scale_log2e);
-  if (part == 0 && h == 0 && wrow0 + l32 < n) {
-    LSE2[(size_t)g * n + wrow0 + l32] = fmaf(mall, scale_log2e, log2f(lall));
-    if (!(lall < INFINITY)) again = true;
-  }
-  if constexpr (WITH_O) {
-    const float f = exp2f((m - mall) * scale_log2e) / lall;
-    // a tile's room per wave now takes its outputs, [query][d], chunks swizzled as in a tile
-    lds_char* const strip = (lds_char*)smem + wave * kTileBytes;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        const f32x4 w = {oacc[db][4 * i4] * f, oacc[db][4 * i4 + 1] * f, oacc[db][4 * i4 + 2] * f,
-                         oacc[db][4 * i4 + 3] * f};
-        const int chunk = 8 * db + 2 * i4 + h;
-        *reinterpret_cast<__attribute__((address_space(3))) f32x4*>(
-            strip + l32 * D * 4 + ((chunk ^ tile_swizzle<false>(l32)) << 4)) = w;
-      }
-    __syncthreads();
-    constexpr int CPR = D / 4;
-    for (int u = tid; u < BM * CPR; u += NT) {
-      const int r = u / CPR, c = u % CPR;
-      if (row0 + r >= n) break;
-      const lds_char* p = (const lds_char*)smem + r * D * 4 + ((c ^ tile_swizzle<false>(r)) << 4);
-      f32x4 a = lds_read4(p) + lds_read4(p + RB * kTileBytes);
-#pragma unroll
-      for (int w = 2; w < P; w += 2) a += lds_read4(p + RB * w * kTileBytes) + lds_read4(p + RB * (w + 1) * kTileBytes);
-      *reinterpret_cast<f32x4*>(O + ((size_t)g * n + row0 + r) * D + c * 4) = a;
-      if (!(fabsf(a[0] * 0.f) + fabsf(a[1] * 0.f) + fabsf(a[2] * 0.f) + fabsf(a[3] * 0.f) == 0.f)) again = true;
-    }
-  }
-  __syncthreads();
-  if (again && tid < kThreads)
-    rows_again<D, WITH_O>(Q + (size_t)g * n * D, Kg, Vg, LSE2 + (size_t)g * n, O + (size_t)g * n * D, row0,
-                          min(n, row0 + BM), off, scale_log2e, reinterpret_cast<float*>(smem));
+  if (again) pass(std::true_type{});
 }
 
 // One workgroup per 32 keys, whose K rows stay in registers; wave w takes every NW-th tile of 32
@@ -415,7 +472,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
 // times what scores[] holds (a chunk: the cached tokens' older scores, decayed by alpha^m);
 // otherwise it replaces it.
 template <int D, int NW>
-__global__ __launch_bounds__(NW * 64, 2) void scores_f32_kernel(
+__global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 2) void scores_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ LSE2,
     AttnRect rc, int G, int ncb, int first_row, float log2_alpha, const float* __restrict__ alpha_heads,
     float* __restrict__ scores, int s_stride, bool accumulate, float decay, float scale_log2e) {
@@ -426,9 +483,6 @@ __global__ __launch_bounds__(NW * 64, 2) void scores_f32_kernel(
   int g, rank;
   if (!ordered_item(G, ncb, g, rank)) return;
   const int c0 = rank * kRows;  // the oldest keys have the most rows
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, h = lane >> 5;
   const int n = rc.m;
   const int off = rc.off_heads ? rc.off_heads[g] : 0;
   const int nk = off + n;
@@ -436,95 +490,114 @@ __global__ __launch_bounds__(NW * 64, 2) void scores_f32_kernel(
   head_window(alpha_heads, g, n, first_row, log2_alpha);
   const float* Qg = Q + (size_t)g * rc.kv_group * n * D;  // the group's rows lie one head after the other
   const float* lg = LSE2 + (size_t)g * rc.kv_group * n;
-  lds_char* const qt = (lds_char*)smem + wave * kTileBytes;
-
+  const float* const Kg = K + (size_t)g * rc.kv_stride * D;
   const int t0 = max(max(c0 - off, first_row), 0) / kRows;  // first row tile that counts
   const int nt = (n + kRows - 1) / kRows - t0;              // tiles per query head
   const int work = nt * rc.kv_group;
-  auto fetch = [&](int f) {
-    const int hq = f / nt, t = t0 + f % nt;
-    fetch_tile<D, false>(Qg + (size_t)hq * n * D, t * kRows, n, qt);
-  };
-  if (wave < work) fetch(wave);
-  Parts kf[C16];  // A operand: lane (key l32, half h) holds the elements 16c + 8h .. + 7
-  const int key = min(c0 + l32, nk - 1);
-  {
-    const float* kr = K + ((size_t)g * rc.kv_stride + key) * D + 8 * h;
-    f32x4 raw[2 * C16];
-#pragma unroll
-    for (int c = 0; c < 2 * C16; ++c) raw[c] = *reinterpret_cast<const f32x4*>(kr + 16 * (c >> 1) + 4 * (c & 1));
-#pragma unroll
-    for (int c = 0; c < 2 * C16; ++c) asm volatile("" : "+v"(raw[c]));  // waited for here, not in every round of the loop
-#pragma unroll
-    for (int c = 0; c < C16; ++c) kf[c] = split(raw[2 * c], raw[2 * c + 1]);
-  }
-  int qoff[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) qoff[i] = l32 * D * 4 + (((4 * (i >> 1) + 2 * h + (i & 1)) ^ tile_swizzle<false>(l32)) << 4);
-  if (tid == 0) again = false;
-  float acc[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
 
-  for (int f = wave; f < work; f += NW) {
-    const int hq = f / nt, r = (t0 + f % nt) * kRows + l32;
-    float lse = lg[(size_t)hq * n + min(r, n - 1)];
-    asm volatile("" : "+v"(lse));  // with the tile: everything has arrived
-    wait_vm<0>();
-    f32x16 s, rest;
+  // The sum of key c0 + tid, for tid < 32.  `careful`: logits of operands without parts in plain arithmetic.
+  const auto total = [&](auto careful_) __attribute__((always_inline)) -> float {
+    constexpr bool careful = decltype(careful_)::value;
+    int tid = threadIdx.x;
+    if (careful) asm volatile("" : "+v"(tid));  // (nothing lives on from one pass to the other)
+    const int lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    lds_char* const qt = (lds_char*)smem + wave * kTileBytes;
+    auto fetch = [&](int f) {
+      const int hq = f / nt, t = t0 + f % nt;
+      fetch_tile<D, false>(Qg + (size_t)hq * n * D, t * kRows, n, qt);
+    };
+    if (wave < work) fetch(wave);
+    Parts kf[careful ? 1 : C16];  // A operand: lane (key l32, half h) holds the elements 16c + 8h .. + 7
+    const float* const k_row = Kg + (size_t)min(c0 + l32, nk - 1) * D + 8 * h;
+    const auto key_parts = [&](int c) -> Parts {
+      if constexpr (!careful) return kf[c];
+      const float* kr = k_row + 16 * c;
+      asm volatile("" : "+v"(kr));
+      return split(*reinterpret_cast<const f32x4*>(kr), *reinterpret_cast<const f32x4*>(kr + 4));
+    };
+    if constexpr (!careful) {
+      f32x4 raw[2 * C16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = rest[i] = 0.f;
+      for (int c = 0; c < 2 * C16; ++c) raw[c] = *reinterpret_cast<const f32x4*>(k_row + 16 * (c >> 1) + 4 * (c & 1));
 #pragma unroll
-    for (int c = 0; c < C16; ++c) {
-      const lds_char* p = qt + (c >> 2) * 256;
-      multiply(kf[c], split(lds_read4(p + qoff[2 * (c & 3)]), lds_read4(p + qoff[2 * (c & 3) + 1])), s, rest);
+      for (int c = 0; c < 2 * C16; ++c) asm volatile("" : "+v"(raw[c]));  // waited for here, not in every round of the loop
+#pragma unroll
+      for (int c = 0; c < C16; ++c) kf[c] = split(raw[2 * c], raw[2 * c + 1]);
+      if (tid == 0) again = false;
     }
+    int qoff[8];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] += rest[i];
-    wait_lds();
-    if (f + NW < work) fetch(f + NW);
-    // exponent offset of row r: lse_r - (n-1-r) log2(alpha); rows past the end, and rows whose
-    // weight is exactly 0 in fp32 (before first_row), add nothing
-    const bool counts = r < n && r >= first_row;
-    const float w = (float)(n - 1 - r) * log2_alpha;
+    for (int i = 0; i < 8; ++i) qoff[i] = l32 * D * 4 + (((4 * (i >> 1) + 2 * h + (i & 1)) ^ tile_swizzle<false>(l32)) << 4);
+    float acc[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+
+    for (int f = wave; f < work; f += NW) {
+      const int hq = f / nt, r = (t0 + f % nt) * kRows + l32;
+      float lse = lg[(size_t)hq * n + min(r, n - 1)];
+      asm volatile("" : "+v"(lse));  // with the tile: everything has arrived
+      wait_vm<0>();
+      f32x16 s, rest;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = rest[i] = 0.f;
+#pragma unroll
+      for (int c = 0; c < C16; ++c) {
+        const lds_char* p = qt + (c >> 2) * 256;
+        multiply(key_parts(c), split(lds_read4(p + qoff[2 * (c & 3)]), lds_read4(p + qoff[2 * (c & 3) + 1])), s, rest);
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] += rest[i];
+      if constexpr (careful) {
+        bool some = false;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) some |= !finite(s[i]);
+        if (__any(some && lse == lse)) {  // (a row whose sum is NaN stays so)
+          const f32x16 exact = plain_logits<D>(
+              h, [&](int c) { return lds_read4(qt + l32 * D * 4 + ((c ^ tile_swizzle<false>(l32)) << 4)); },
+              [&](int row, int c) { return *reinterpret_cast<const f32x4*>(Kg + (size_t)min(c0 + row, nk - 1) * D + 4 * c); });
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[i] = finite(s[i]) ? s[i] : exact[i];
+        }
+      }
+      wait_lds();
+      if (f + NW < work) fetch(f + NW);
+      // exponent offset of row r: lse_r - (n-1-r) log2(alpha); rows past the end, and rows whose
+      // weight is exactly 0 in fp32 (before first_row), add nothing
+      const bool counts = r < n && r >= first_row;
+      const float w = (float)(n - 1 - r) * log2_alpha;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float p = exp2f(fmaf(s[i], scale_log2e, -lse) + w);
+        acc[i] += counts && c0 + 8 * (i >> 2) + 4 * h + (i & 3) <= off + r ? p : 0.f;
+      }
+    }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const float p = exp2f(fmaf(s[i], scale_log2e, -lse) + w);
-      acc[i] += counts && c0 + 8 * (i >> 2) + 4 * h + (i & 3) <= off + r ? p : 0.f;
+      acc[i] = group_sum<32>(acc[i]);  // over the 32 rows held by the lanes of one half
+      if (l32 == 0) part[wave][8 * (i >> 2) + 4 * h + (i & 3)] = acc[i];
     }
-  }
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    acc[i] = group_sum<32>(acc[i]);  // over the 32 rows held by the lanes of one half
-    if (l32 == 0) part[wave][8 * (i >> 2) + 4 * h + (i & 3)] = acc[i];
-  }
-  __syncthreads();
-  float older = 0.f;
-  if (tid < kRows && c0 + tid < nk) {
+    __syncthreads();
     float sum = 0.f;
+    if (tid < kRows) {
 #pragma unroll
-    for (int w = 0; w < NW; w += 4) sum += (part[w][tid] + part[w + 1][tid]) + (part[w + 2][tid] + part[w + 3][tid]);
-    float* out = scores + (size_t)g * s_stride + c0 + tid;
-    if (accumulate) older = decay * *out;
-    *out = accumulate ? fmaf(decay, *out, sum) : sum;
+      for (int w = 0; w < NW; w += 4) sum += (part[w][tid] + part[w + 1][tid]) + (part[w + 2][tid] + part[w + 3][tid]);
+    }
+    return sum;
+  };
+  const int tid = threadIdx.x;
+  const bool live = tid < kRows && c0 + tid < nk;
+  float* const out = scores + (size_t)g * s_stride + c0 + tid;
+  float sum = total(std::false_type{});
+  const float older = live && accumulate ? *out : 0.f;
+  if (live) {
+    *out = accumulate ? fmaf(decay, older, sum) : sum;
     if (!(sum < INFINITY)) again = true;
   }
   __syncthreads();
-  if (!again || tid >= kThreads) return;
-  // in plain arithmetic (see rows_again)
-#pragma unroll 1
-  for (int x = 0; x < min(kRows, nk - c0); ++x) {
-    const float* kj = K + ((size_t)g * rc.kv_stride + c0 + x) * D;
-    float sum = 0.f;
-#pragma unroll 1
-    for (int hq = 0; hq < rc.kv_group; ++hq)
-#pragma unroll 1
-      for (int i = max(max(c0 + x - off, first_row), 0) + tid; i < n; i += kThreads)
-        sum += exp2f(fmaf(dot_row<D>(Qg + ((size_t)hq * n + i) * D, kj), scale_log2e, -lg[(size_t)hq * n + i]) +
-                     (float)(n - 1 - i) * log2_alpha);
-    sum = block_sum(sum, &part[0][0]);
-    if (tid == x) scores[(size_t)g * s_stride + c0 + x] = older + sum;
-  }
+  if (!again) return;
+  sum = total(std::true_type{});
+  if (live) *out = accumulate ? fmaf(decay, older, sum) : sum;
 }
 
 // ---- short prompts -------------------------------------------------------------------------

@@ -224,3 +224,30 @@ def test_fp32_products_of_one_sign_have_no_bias(d, G, n, cached):
         got = np.log2(s[g].double().cpu().numpy())[1:]
         errors.append((got - (z - np.log2(np.exp2(z).sum()))[1:]) / z[1:])
     assert abs(np.mean(errors)) <= 2.0 ** -25, np.mean(errors) * 2 ** 24
+
+
+@pytest.mark.parametrize("d,G,n,cached", [f for f in FP32_FORMS if not f[3]])
+def test_fp32_large_logits_beside_infinities(d, G, n, cached):
+    """Logits of 1e7 and more, whose last bits decide: an infinity in V changes neither the scores nor any other output, and one in a key
+    that gets no weight either way changes nothing at all."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    q, k, v = rnd(G, 1, n, d) * 3e3, rnd(G, n, d) * 3e3, rnd(G, n, d)
+    q[..., 0] = 1.0
+    at = n - 20
+    k[:, at] = 0
+    k[:, at, 0] = -1e30
+    o, s = prefill(q, k, v)
+    assert torch.isfinite(s).all() and torch.isfinite(o).all()
+    v[:, 3, 5], v[:, n // 2, 7] = float("inf"), float("nan")
+    o2, s2 = prefill(q, k, v)
+    assert torch.equal(s, s2)
+    same = torch.ones_like(o, dtype=torch.bool)
+    same[:, :, 3:, 5], same[:, :, n // 2:, 7] = False, False
+    assert torch.equal(o[same], o2[same])
+    assert not torch.isfinite(o2[:, :, 3:, 5]).any() and torch.isnan(o2[:, :, n // 2:, 7]).all()
+    v[:, 3, 5], v[:, n // 2, 7] = 0.25, 0.25
+    o, s = prefill(q, k, v)
+    k[:, at, 0] = -float("inf")
+    o2, s2 = prefill(q, k, v)
+    assert torch.equal(s, s2) and torch.equal(o, o2)

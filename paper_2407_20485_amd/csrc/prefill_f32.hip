@@ -22,8 +22,13 @@
 // on its own.  Relative error against 64 bits, of sums of 128 products, on a model of the arithmetic: normal values 5.7e-8 (fp32
 // multiply-adds 1.5e-7, cut parts 8.2e-8), one nonzero product 2.6e-8 (2.5e-8, 6.4e-8), two 2.7e-8 (3.7e-8, 6.6e-8).
 //
-// An infinity, a NaN and what rounds to one (above 2^127.99) have no parts.  A workgroup whose results are not finite does its block
-// once more, with the logits that are not finite and the products of such values in plain fp32 arithmetic (`careful` below).
+// Not every number has its parts in the range of bf16: an infinity, a NaN and what rounds to one (above 2^127.99) have none, and the
+// parts of a number below 2^-110 end at 2^-133, where a subnormal bf16 does.  What that costs is 2^-134 times the other operand, so it
+// matters where the other one is large, or the result small: a workgroup that has rows with numbers below 2^-110 or above
+// 2^100 (of Q in the attention, of K in the scores), or outputs below 2^-106 or not finite, does its block once more with
+// such logits and products in plain fp32 arithmetic, or in parts of larger multiples (`careful` below).  What is left is 2^-20
+// of a logit's unit and 2^-28 of an output; probabilities below 2^-110 of their row's largest are off by up to 2^-134, where the
+// exponential itself ends at 2^-126.
 //
 // Operand layouts: lane (x = lane % 32, h = lane / 32) brings A[x][k] and B[k][x] for the eight k of its half;
 // accumulator register i of the lane is row 8 (i/4) + 4 h + i % 4, column x.  Both kernels form the transposed logit
@@ -162,8 +167,45 @@ __device__ __forceinline__ float dot_row(const float* __restrict__ a, const floa
   return acc;
 }
 
+// Which operands the parts cannot stand for (see the top of the file).
+constexpr float kSmallestSplit = 0x1p-110f, kLargestSplit = 0x1p127f, kLargestRow = 0x1p100f, kSmallestSum = 0x1p-106f, kLargest = 3.402823466e38f;
+__device__ __forceinline__ bool has_parts(float x) { return x == 0.f || (fabsf(x) >= kSmallestSplit && fabsf(x) <= kLargestSplit); }
 __device__ __forceinline__ bool finite(float x) { return fabsf(x) < INFINITY; }
-__device__ __forceinline__ bool has_parts(float x) { return fabsf(x) <= 0x1p127f; }
+// The extremes of numbers, and where a zero may be the least of them, whether another one is too small.
+struct Extremes {
+  float most = 0.f, least = INFINITY;
+  __device__ __forceinline__ void see(const f32x4& x) {
+    most = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(x[0]), fabsf(x[1])), most);
+    most = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(x[2]), fabsf(x[3])), most);
+    least = fminf(fminf(fabsf(x[0]), fabsf(x[1])), least);
+    least = fminf(fminf(fabsf(x[2]), fabsf(x[3])), least);
+  }
+};
+__device__ __forceinline__ bool any_below(const f32x4& x, float least) {
+  bool below = false;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) below |= x[e] != 0.f && fabsf(x[e]) < least;
+  return below;
+}
+// Of a row of Q or K: its logits are not those of the parts where the other operand's row has large numbers, or at all.
+constexpr int kSmallNumbers = 1, kLargeNumbers = 2;
+// ... of the pieces first, first + step, ... of `raw`
+template <int N>
+__device__ __forceinline__ int odd_numbers(const f32x4 (&raw)[N], int first, int step) {
+  Extremes seen;
+  int odd = 0;
+#pragma unroll
+  for (int p = 0; p < step; ++p)
+    if (p == first) {
+#pragma unroll
+      for (int c = p; c < N; c += step) seen.see(raw[c]);
+      if (seen.least < kSmallestSplit) {
+#pragma unroll
+        for (int c = p; c < N; c += step) odd |= any_below(raw[c], kSmallestSplit) ? kSmallNumbers : 0;
+      }
+    }
+  return seen.most > kLargestRow ? odd | kLargeNumbers : odd;
+}
 
 // The 16 logits of a lane in plain arithmetic.  own(c): the piece c of four elements of the lane's own row; other(row, c): of the row
 // (of the tile's 32) that register i belongs to.
@@ -202,6 +244,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
   __shared__ __attribute__((aligned(1024))) char smem[2 * P * kTileBytes];
   __shared__ float m_s[NW][kRows], l_s[NW][kRows];
   __shared__ bool again;
+  __shared__ int odd_rows[BM];
   const auto arrived = [] {  // this wave's loads, and those of the waves it shares tiles with
     if (RB == 1) { wait_vm<0>(); wait_lds(); }
     else wait_vm_barrier<0>();
@@ -245,13 +288,16 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
     // Q (B operand): lane (query l32, half h) holds the elements 16c + 8h .. + 7; a careful pass splits them for every tile again, which
     // leaves it registers for the plain arithmetic (memory for spilled ones is paid for by every workgroup, at its start)
     Parts qf[careful ? 1 : C16];
+    int odd = 0;  // kSmallNumbers ... of this part's share of the row
     const auto query = [&](int c) -> Parts {
       if constexpr (!careful) return qf[c];
       const float* qr = q_row + 16 * c + 8 * h;
       asm volatile("" : "+v"(qr));
       return split(*reinterpret_cast<const f32x4*>(qr), *reinterpret_cast<const f32x4*>(qr + 4));
     };
-    if constexpr (!careful) {
+    if constexpr (careful) {
+      odd = odd_rows[kRows * block + l32];
+    } else {
       const float* qr = q_row + 8 * h;
       f32x4 raw[2 * C16];
 #pragma unroll
@@ -260,6 +306,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
       for (int c = 0; c < C16; ++c) qf[c] = split(raw[2 * c], raw[2 * c + 1]);
 #pragma unroll
       for (int c = 0; c < C16; ++c) asm volatile("" : "+v"(qf[c].high.x));  // formed here, not in every round of the loop
+      odd = odd_numbers(raw, part, P);
+      if (tid < BM) odd_rows[tid] = 0;
       if (tid == 0) again = false;
     }
 
@@ -288,10 +336,12 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
           b = lds_read4((const lds_char*)(size_t)(at ^ ((c & 3) << 6 | 16)) + (c >> 2) * 256);
         };
         f32x4 a, b;
+        Extremes keys;
         read(0, a, b);
 #pragma unroll
         for (int c = 0; c < C16; ++c) {
           const Parts kp = split(a, b);
+          if constexpr (careful) { keys.see(a); keys.see(b); }
           if (c + 1 < C16) read(c + 1, a, b);
           multiply(kp, query(c), s, rest);
           __builtin_amdgcn_sched_barrier(0);  // (more pieces at once do not fit the registers)
@@ -299,7 +349,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[i] += rest[i];
         if constexpr (careful) {
-          bool some = false;
+          const bool plain_row = (odd & kLargeNumbers) || ((odd & kSmallNumbers) && __any(keys.most > kLargestRow));
+          bool some = plain_row;
 #pragma unroll
           for (int i = 0; i < 16; ++i) some |= !finite(s[i]);
           if (__any(some)) {
@@ -307,7 +358,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
                 h, [&](int c) { return *reinterpret_cast<const f32x4*>(q_row + 4 * c); },
                 [&](int row, int c) { return lds_read4(kt + row * D * 4 + ((c ^ tile_swizzle<false>(row)) << 4)); });
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[i] = finite(s[i]) ? s[i] : exact[i];
+            for (int i = 0; i < 16; ++i) s[i] = plain_row || !finite(s[i]) ? exact[i] : s[i];
           }
         }
         if (key0 + kRows - 1 > off + wrow0) {  // the tile reaches past the block's first row
@@ -359,6 +410,17 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
             for (int i = 0; i < 8; ++i)
               x[i] = lds_read1(vbuf + voff[db & 1] + (db >> 1) * 256 + (16 * j + 8 * (i >> 2) + (i & 3)) * D * 4);
           };
+          float up = 1.f, down = 1.f;  // careful: small numbers are split as multiples where that makes none too large
+          if constexpr (careful) {
+            float most = 0.f;
+#pragma unroll 1
+            for (int u = 0; u < D / 8; ++u) {
+              const f32x4 y = lds_read4(vbuf + u * 1024 + lane * 16);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) most = fmaxf(most, finite(y[e]) ? fabsf(y[e]) : 0.f);
+            }
+            if (wave_max(most) <= 0x1p60f) { up = 0x1p64f; down = 0x1p-64f; }
+          }
           f32x16 o;  // of this tile alone: rounded at its own size before it joins the others
           read(0);
 #pragma unroll
@@ -369,14 +431,14 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
             }
             if constexpr (careful) {
 #pragma unroll
-              for (int i = 0; i < 8; ++i) x[i] = has_parts(x[i]) ? x[i] : 0.f;
+              for (int i = 0; i < 8; ++i) x[i] = has_parts(x[i] * up) ? x[i] * up : 0.f;
             }
             const Parts vp = split(x);
             if (v + 1 < NV) read(v + 1);
             multiply(vp, pf[v & 1], o, o);
             if (v % 2 == 1) {
 #pragma unroll
-              for (int i = 0; i < 16; ++i) oacc[v >> 1][i] += o[i];
+              for (int i = 0; i < 16; ++i) oacc[v >> 1][i] += careful ? o[i] * down : o[i];
             }
             __builtin_amdgcn_sched_barrier(0);
           }
@@ -385,8 +447,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
 #pragma unroll 1
             for (int key = 0; key < kRows; ++key) {
               const lds_char* const v_row = vbuf + key * D * 4;
-              bool some = !has_parts(lds_read1(v_row + lane * 4));
-              if (D == 128) some |= !has_parts(lds_read1(v_row + 256 + lane * 4));
+              bool some = !has_parts(lds_read1(v_row + lane * 4) * up);
+              if (D == 128) some |= !has_parts(lds_read1(v_row + 256 + lane * 4) * up);
               if (!__any(some)) continue;
               const int at = 4 * (key >> 3) + (key & 3);  // its register, in the lanes of half (key >> 2) & 1
               float p = 0.f;
@@ -406,7 +468,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
                   const f32x4 v4 = lds_read4(v_row + (((8 * db + 2 * i4 + h) ^ tile_swizzle<true>(key)) << 4));
 #pragma unroll
                   for (int e = 0; e < 4; ++e)
-                    if (key0 + key <= newest && !has_parts(v4[e])) oacc[db][4 * i4 + e] = fmaf(p, v4[e], oacc[db][4 * i4 + e]);
+                    if (key0 + key <= newest && !has_parts(v4[e] * up)) oacc[db][4 * i4 + e] = fmaf(p, v4[e], oacc[db][4 * i4 + e]);
                   __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -415,6 +477,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
       }
     }
     wait_vm_barrier<0>();  // the buffers are reused below
+    if (!careful && odd) { atomicOr(&odd_rows[kRows * block + l32], odd); again = true; }
 
     // ---- the parts' sums
     l = across_rows(l, OpAdd(), false, true);
@@ -429,7 +492,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
     if (part == 0 && h == 0 && wrow0 + l32 < n) {
       float* const lse = LSE2 + (size_t)g * n + wrow0 + l32;
       // (a sum that was finite stands, whatever the outputs are: the scores' logits are those it was formed from)
-      if (!careful || !finite(*lse)) *lse = fmaf(mall, scale_log2e, log2f(lall));
+      if (!careful || odd || !finite(*lse)) *lse = fmaf(mall, scale_log2e, log2f(lall));
       if (!careful && !(lall > 0.f && lall < INFINITY)) again = true;
     }
     if constexpr (WITH_O) {
@@ -457,7 +520,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
         for (int w = 2; w < P; w += 2) a += lds_read4(p + RB * w * kTileBytes) + lds_read4(p + RB * (w + 1) * kTileBytes);
         *reinterpret_cast<f32x4*>(O + ((size_t)g * n + row0 + r) * D + c * 4) = a;
         if constexpr (!careful) {
-          if (!(fabsf(a[0] * 0.f) + fabsf(a[1] * 0.f) + fabsf(a[2] * 0.f) + fabsf(a[3] * 0.f) == 0.f)) again = true;
+          Extremes seen;
+          seen.see(a);
+          if (!(seen.most <= kLargest) || (seen.least < kSmallestSum && any_below(a, kSmallestSum))) again = true;
         }
       }
     }
@@ -480,6 +545,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 2) void scores_f32_kernel(
   __shared__ __attribute__((aligned(1024))) char smem[NW * kTileBytes];
   __shared__ float part[NW][kRows];
   __shared__ bool again;
+  __shared__ int odd_keys[kRows];
   int g, rank;
   if (!ordered_item(G, ncb, g, rank)) return;
   const int c0 = rank * kRows;  // the oldest keys have the most rows
@@ -509,6 +575,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 2) void scores_f32_kernel(
     };
     if (wave < work) fetch(wave);
     Parts kf[careful ? 1 : C16];  // A operand: lane (key l32, half h) holds the elements 16c + 8h .. + 7
+    int odd = 0;  // kSmallNumbers ... of this wave's share of the lane's key
+    uint32_t small_keys = 0, large_keys = 0;
     const float* const k_row = Kg + (size_t)min(c0 + l32, nk - 1) * D + 8 * h;
     const auto key_parts = [&](int c) -> Parts {
       if constexpr (!careful) return kf[c];
@@ -516,7 +584,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 2) void scores_f32_kernel(
       asm volatile("" : "+v"(kr));
       return split(*reinterpret_cast<const f32x4*>(kr), *reinterpret_cast<const f32x4*>(kr + 4));
     };
-    if constexpr (!careful) {
+    if constexpr (careful) {
+      small_keys = (uint32_t)__ballot(odd_keys[l32] & kSmallNumbers);
+      large_keys = (uint32_t)__ballot(odd_keys[l32] & kLargeNumbers);
+    } else {
       f32x4 raw[2 * C16];
 #pragma unroll
       for (int c = 0; c < 2 * C16; ++c) raw[c] = *reinterpret_cast<const f32x4*>(k_row + 16 * (c >> 1) + 4 * (c & 1));
@@ -524,7 +595,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 2) void scores_f32_kernel(
       for (int c = 0; c < 2 * C16; ++c) asm volatile("" : "+v"(raw[c]));  // waited for here, not in every round of the loop
 #pragma unroll
       for (int c = 0; c < C16; ++c) kf[c] = split(raw[2 * c], raw[2 * c + 1]);
+      odd = odd_numbers(raw, wave, NW);
       if (tid == 0) again = false;
+      if (tid < kRows) odd_keys[tid] = 0;
     }
     int qoff[8];
 #pragma unroll
@@ -541,23 +614,29 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 2) void scores_f32_kernel(
       f32x16 s, rest;
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[i] = rest[i] = 0.f;
+      Extremes queries;
 #pragma unroll
       for (int c = 0; c < C16; ++c) {
         const lds_char* p = qt + (c >> 2) * 256;
-        multiply(key_parts(c), split(lds_read4(p + qoff[2 * (c & 3)]), lds_read4(p + qoff[2 * (c & 3) + 1])), s, rest);
+        const f32x4 a = lds_read4(p + qoff[2 * (c & 3)]), b = lds_read4(p + qoff[2 * (c & 3) + 1]);
+        if constexpr (careful) { queries.see(a); queries.see(b); }
+        multiply(key_parts(c), split(a, b), s, rest);
       }
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[i] += rest[i];
       if constexpr (careful) {
+        const auto key_of = [&](int i) { return 8 * (i >> 2) + 4 * h + (i & 3); };
+        const uint32_t plain_keys = large_keys | (__any(queries.most > kLargestRow) ? small_keys : 0);
+        const auto plain = [&](int i) { return (plain_keys >> key_of(i) & 1) || !finite(s[i]); };
         bool some = false;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) some |= !finite(s[i]);
+        for (int i = 0; i < 16; ++i) some |= plain(i);
         if (__any(some && lse == lse)) {  // (a row whose sum is NaN stays so)
           const f32x16 exact = plain_logits<D>(
               h, [&](int c) { return lds_read4(qt + l32 * D * 4 + ((c ^ tile_swizzle<false>(l32)) << 4)); },
               [&](int row, int c) { return *reinterpret_cast<const f32x4*>(Kg + (size_t)min(c0 + row, nk - 1) * D + 4 * c); });
 #pragma unroll
-          for (int i = 0; i < 16; ++i) s[i] = finite(s[i]) ? s[i] : exact[i];
+          for (int i = 0; i < 16; ++i) s[i] = plain(i) ? exact[i] : s[i];
         }
       }
       wait_lds();
@@ -578,6 +657,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 2) void scores_f32_kernel(
       if (l32 == 0) part[wave][8 * (i >> 2) + 4 * h + (i & 3)] = acc[i];
     }
     __syncthreads();
+    if (!careful && odd) { atomicOr(&odd_keys[l32], odd); again = true; }
     float sum = 0.f;
     if (tid < kRows) {
 #pragma unroll

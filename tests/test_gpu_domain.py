@@ -226,6 +226,53 @@ def test_fp32_products_of_one_sign_have_no_bias(d, G, n, cached):
     assert abs(np.mean(errors)) <= 2.0 ** -25, np.mean(errors) * 2 ** 24
 
 
+@pytest.mark.parametrize("d,G,n,cached", FP32_FORMS)
+@pytest.mark.parametrize("form", ["small q", "small k", "small v", "smallest v", "sparse v", "v of one sign"])
+def test_fp32_operands_at_the_lower_end(d, G, n, cached, form):
+    """Numbers whose low bf16 parts would be subnormal or nothing: results are those of fp32 arithmetic."""
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    total = cached + n
+    q, k, v = rnd(G, 1, n, d), rnd(G, total, d), rnd(G, total, d)
+    up = 1.0
+    if form == "small q":
+        q, k = q * 2.0 ** -120, k * 2.0 ** 121
+    elif form == "small k":
+        q, k = q * 2.0 ** 120, k * 2.0 ** -119
+    elif form == "small v":
+        up = 2.0 ** 112
+    elif form == "smallest v":
+        up = 2.0 ** 121
+    elif form == "v of one sign":  # outputs of 2^-104 up: as split, low parts of which are subnormal
+        up = 2.0 ** 104
+        v = v.abs() + 1
+    else:  # columns with one small number each among zeros, and columns of ordinary numbers
+        up = 2.0 ** 110
+        v[:, ::2, ::3] = 0
+        v[:, 1::2, ::3] /= up
+    if form in ("small v", "smallest v", "v of one sign"):
+        v /= up
+    o, s = (chunk(q, k, v, cached), None) if cached else prefill(q, k, v)
+    heads = sorted({0, G // 2, G - 1})
+    q, k, v = q[heads], k[heads], v[heads]
+    want, got = rows_by_hand(q, k, v, cached), o[heads].double().cpu().numpy()
+    error = np.abs(got - want)
+    if form == "sparse v":
+        assert error[..., ::3].max() * up <= parity.O_TOL["f32"]
+        error[..., ::3] = 0
+        up = 1.0
+    assert error.max() * up <= parity.O_TOL["f32"]
+    if form.endswith(("v", "sign")) and not cached:  # the first row has one key: its value itself, but for the order of three parts
+        assert (error[:, 0, 0] <= 2.0 ** -23 * np.abs(want[:, 0, 0])).all()
+    if s is not None:
+        mask = np.tril(np.ones((n, n), bool))
+        for i, g in enumerate(heads):
+            z = parity.to_f64(q[i, 0]) @ parity.to_f64(k[i]).T / np.sqrt(d)
+            p = np.exp(np.where(mask, z, -np.inf))
+            want = (p / p.sum(1, keepdims=True)).sum(0)
+            assert (np.abs(s[g].double().cpu().numpy() - want) / want).max() <= parity.SCORE_RTOL
+
+
 @pytest.mark.parametrize("d,G,n,cached", [f for f in FP32_FORMS if not f[3]])
 def test_fp32_large_logits_beside_infinities(d, G, n, cached):
     """Logits of 1e7 and more, whose last bits decide: an infinity in V changes neither the scores nor any other output, and one in a key

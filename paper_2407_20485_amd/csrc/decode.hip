@@ -233,7 +233,7 @@ __device__ __forceinline__ unsigned long long evict_key(float score, int pos) {
 // positions, then evicts one token at a time, moving the last live row into the hole.  Every eviction is a
 // chain of barriers, which four waves pass sooner than 16: Few does them, the other waves end before (a barrier
 // waits only for waves that have not ended).  1024 threads that merge splits, 500 slots, 250 evicted: 349 us with
-// all waves, 311 here; 3000 slots with gaps: 2130 us where 256 threads do all, 524 here.
+// all waves, 311 here.
 template <typename Grp, typename T, int D, typename Few = Grp>
 __device__ void evict_general(float* a, int n_old, int excess, T* Kg, T* Vg, float* Sg,
                               int32_t* Pg, int32_t* len_g, const T* knew, const T* vnew,
@@ -245,15 +245,34 @@ __device__ void evict_general(float* a, int n_old, int excess, T* Kg, T* Vg, flo
   copy_kv_row<Grp, T, D>(Kg + (size_t)n_old * D, knew, Vg + (size_t)n_old * D, vnew);
   __threadfence_block();
   Grp::sync();
-  // protected tokens get score +inf in LDS (their real score is already in Sg)
-  for (int j = tid; j < L; j += Grp::kSize) {
-    const int pj = Pg[j];
-    int newer = 0;
-    for (int i = 0; i < L; ++i) newer += Pg[i] > pj;
-    if (newer < recent) a[j] = INFINITY;
-  }
-  Grp::sync();
   if (Few::kSize < Grp::kSize && tid >= Few::kSize) return;
+  // Protected tokens get score +inf in LDS (their real score is already in Sg): those from the recent-th largest position on, which
+  // is found bit by bit, from the highest bit of the newest position.  (Counting every token's newer ones is L^2 reads: us per step with
+  // a gap, counted / so, bf16, d = 128: 224 x 2 x 1400 slots 544 / 41, 32 x 1 x 4096 956 / 41, 2000 x 1 x 1400 1214 / 249.)
+  if (recent > 0) {
+    const auto place = [&](int j) { return (uint32_t)Pg[j] ^ 0x80000000u; };  // in the order of the positions
+    unsigned long long below = ~0ull;
+#pragma unroll 1
+    for (int j = tid; j < L; j += Few::kSize) below = min(below, (unsigned long long)~place(j));
+    const uint32_t most = ~__builtin_amdgcn_readfirstlane((uint32_t)Few::min_u64(below, sm));
+    const auto reaches = [&](uint32_t at) {
+      int count = 0;
+#pragma unroll 1
+      for (int j = tid; j < L; j += Few::kSize) count += place(j) >= at;
+      return __builtin_amdgcn_readfirstlane(Few::sum_i(count, sm)) >= recent;
+    };
+    uint32_t oldest = 0, step = 1u << 30;
+    if (reaches(0x80000000u)) {
+      oldest = 0x80000000u;
+      while (step > 1 && !(most & step)) step >>= 1;
+    }
+    for (; step; step >>= 1)
+      if (reaches(oldest | step)) oldest |= step;
+#pragma unroll 1
+    for (int j = tid; j < L; j += Few::kSize)
+      if (place(j) >= oldest) a[j] = INFINITY;
+    Few::sync();
+  }
   int live = L;
   for (int it = 0; it < excess; ++it) {
     unsigned long long b = ~0ull;
@@ -1551,8 +1570,12 @@ constexpr int kSmallMaxHeads = 255, kSmallMaxHeadsStable = 4095;
 template <typename T, int D>
 constexpr int kSmallRows = kSmallWaves * RowGeom<T, D>::RPW;  // rows of one pass
 
+// The form that two workgroups to a compute unit have registers for (the others would spill).
+template <typename T, int D, int NP>
+constexpr bool kSmallTwoPerUnit = std::is_same<T, float>::value && D == 128 && NP == 4;
+
 template <typename T, int D, int NP>  // NP passes of kSmallRows rows each
-__global__ __launch_bounds__(kSmallWaves * 64) void decode_small_kernel(
+__global__ __launch_bounds__(kSmallWaves * 64, (kSmallTwoPerUnit<T, D, NP> ? 8 : 4)) void decode_small_kernel(
     const T* __restrict__ q, const T* __restrict__ k_new, const T* __restrict__ v_new, int t_pos,
     T* K, T* V, float* S, int32_t* P, int32_t* len, int capacity, float alpha,
     const float* __restrict__ alpha_heads, int select, int recent, int evict, T* __restrict__ o,
@@ -2336,7 +2359,8 @@ void launch_gqa_typed(const void* q, const void* k_new, const void* v_new, int t
     const DecodePlan kv = plan_decode(c.G, c.capacity, D);
     // Nearly all compute units have a K/V head: one workgroup of 16 waves each.  Time per step (split / 16 waves), 194 heads x 1000
     // slots: R = 2 25.1 / 21.4 us, 3 26.9 / 27.3, 4 28.5 / 27.7, 6 35.2 / 29.5, 8 37.8 / 30.2; 240 heads: 26.5 / 24.4,
-    // 28.2 / 28.6, 29.7 / 28.8, 34.1 / 30.7, 36.7 / 31.6; 256 heads x 260 slots: R = 3 16.0 / 12.4, 8 23.6 / 16.0; 130 heads x 1800
+    // 28.2 / 28.6, 29.7 / 28.8, 34.1 / 30.7, 36.7 / 31.6; 256 heads x 260 slots: R = 3 16.0 / 12.4, 8 23.6 / 16.0; longer caches, up to all
+    // logits that a call takes, gain more: 192 heads x 8192 x 2 152 / 130, 256 183 / 168, 256 x 5400 x 3 131 / 116, x 4096 x 4 101 / 86; 130 heads x 1800
     // x 8: 45.4 / 49.2 (three or four heads fill one block of the matrix instruction: their split form is the cheaper one).
     const bool nearly_all = c.G >= (group == 3 || group == 4 ? 240 : 192) && c.G <= 256;
     if (!nearly_all && group >= 2 && kv.nsplit > 1 && ws) {

@@ -264,6 +264,46 @@ def test_split_step_sizes(dtype, d, group, B):
             parity.compare_scores(cache.scores[g, :kept].cpu().numpy()[order], c.S, f"head {g} step {t}")
 
 
+@pytest.mark.parametrize("dtype,d,group,G,B", [("bf16", 64, 7, 5, 65), ("f32", 128, 3, 5, 257), ("f32", 64, 8, 5, 1025), ("bf16", 64, 2, 5, 8000),
+                                               ("bf16", 128, 2, 192, 300), ("bf16", 128, 8, 192, 1200), ("bf16", 64, 3, 257, 255),
+                                               ("f32", 128, 8, 257, 2039)])  # (the last: partial outputs over the logits)
+def test_grouped_steps_of_whole_workgroups_evict(dtype, d, group, G, B):
+    """Every form of the one-workgroup grouped step (16 / four waves, partial outputs behind the logits or over them) through
+    the eviction: full heads, heads that evict several tokens, heads whose newest positions have gaps, filling ones."""
+    gen = torch.Generator(device="cuda").manual_seed(B + d)
+    dt = parity.torch_dtype(dtype)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(dt)
+    cap, t0 = B + 9, 2 * B + 10
+    cache = a2sf.Cache(G, cap, d, dt)
+    cache.k.copy_(rnd(*cache.k.shape)), cache.v.copy_(rnd(*cache.v.shape))
+    cache.scores.copy_(torch.rand(G, cap, generator=gen, device="cuda"))
+    cache.pos[:, :B] = torch.arange(t0 - B, t0, device="cuda").int()
+    cache.len.fill_(B)
+    lens = {0: B, 1: B + 5, 2: B, 3: B - 2, G - 1: B}
+    for g, L in lens.items():
+        pos = np.arange(t0 - L, t0) if g not in (2, G - 1) else np.random.default_rng(B + g).permutation(t0 - 1)[:L]
+        cache.pos[g, :L] = torch.as_tensor(pos.astype(np.int32), device="cuda")
+        cache.len[g] = L
+    oc = {g: orc.HeadCache(*(parity.to_f64(x[g, :L]) for x in (cache.k, cache.v, cache.scores)),
+                           cache.pos[g, :L].cpu().numpy().astype(np.int64)) for g, L in lens.items()}
+    for t, (select, recent) in enumerate([(B - B // 3, B // 3), (B - B // 3, B // 3), (B // 4, B // 2)], t0):
+        q, kn, vn = rnd(G, group, d), rnd(G, d), rnd(G, d)
+        o = torch.full((G, group, d), float("nan"), dtype=dt, device="cuda")
+        a2sf.a2sf_decode_step_gqa(q, kn, vn, t, cache, group, 0.7, select, recent, o)
+        torch.cuda.synchronize()
+        for g in lens:
+            kept = int(cache.len[g])
+            pos = cache.pos[g, :kept].cpu().numpy().astype(np.int64)
+            o_ref, _ = orc.gqa_attend_and_update(oc[g], parity.to_f64(q[g]), parity.to_f64(kn[g]), parity.to_f64(vn[g]), t, float(np.float32(0.7)))
+            orc.evict(oc[g], select, recent, forced_retained=pos.tolist(), margin=parity.MARGIN)
+            assert np.abs(parity.to_f64(o[g]) - o_ref).max() <= parity.O_TOL[dtype]
+            order = np.argsort(pos, kind="stable")
+            c = oc[g].sorted_by_pos()
+            assert np.array_equal(pos[order], c.pos)
+            assert np.array_equal(parity.to_f64(cache.k[g, :kept])[order], c.K) and np.array_equal(parity.to_f64(cache.v[g, :kept])[order], c.V)
+            parity.compare_scores(cache.scores[g, :kept].cpu().numpy()[order], c.S, f"head {g} step {t}")
+
+
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64), ("bf16", 128)])
 @pytest.mark.parametrize("G,n", [(1, 700), (5, 400), (8, 97), (9, 33), (45, 300), (70, 260), (131, 129), (515, 140)])
 def test_launch_order_covers_every_block(dtype, d, G, n):

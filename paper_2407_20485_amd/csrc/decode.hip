@@ -2451,10 +2451,17 @@ void launch_gqa_typed(const void* q, const void* k_new, const void* v_new, int t
           hipFuncSetAttribute((const void*)decode_gqa_kernel<T, D, R, STREAM, NW>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               A2SF_GQA_MAX_LOGITS * (int)sizeof(float) + kPart);
       (void)raised;
-      // The partial outputs lie behind the logits or, where a compute unit would hold fewer workgroups then (four at most, by
-      // their registers), over all logits but the first head's: 900 heads x 3000 slots x 3, fp32, d = 128: 472 us behind, 443 over.
+      // The partial outputs lie behind the logits or, where the heads then go through the chip in fewer rounds (up to four workgroups
+      // to a compute unit, by their registers), over all logits but the first head's (us, behind / over, d = 128: 640 heads x 4000 x 3 bf16
+      // 272 / 220, fp32 520 / 428, 1000 x 3000 x 4 fp32 528 / 483, 1600 x 4000 x 3 bf16 580 / 562, but in as many rounds 1000 x 4000 x 3 bf16
+      // 327 / 360, fp32 616 / 680).
       const size_t over = std::max(lds, c.capacity * sizeof(float) + kPart);
-      const bool apart = NW > kWaves || std::min<size_t>(4, kLdsPerCu / (lds + kPart)) >= std::min<size_t>(4, kLdsPerCu / over);
+      const auto rounds = [&](size_t dynamic) {
+        const size_t bytes = (dynamic + 512 + 1279) / 1280 * 1280;  // with the kernel's own variables, in the units LDS is given out in
+        const size_t at_once = 256 * std::min<size_t>(4, kLdsPerCu / bytes);
+        return (c.G + at_once - 1) / at_once;
+      };
+      const bool apart = NW > kWaves || rounds(lds + kPart) <= rounds(over);
       hipLaunchKernelGGL((decode_gqa_kernel<T, D, R, STREAM, NW>), dim3(c.G), dim3(NW * 64), apart ? lds + kPart : over,
                          st, (const T*)q, (const T*)k_new, (const T*)v_new, t_pos, (T*)c.k, (T*)c.v, c.scores, c.pos,
                          c.len, c.capacity, alpha, select, recent, (int)evict_here, (T*)o,

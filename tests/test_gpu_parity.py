@@ -680,7 +680,7 @@ def test_grouped_query_heads_long_caches(dtype, d, group, n, select, recent, spl
                                                    ("bf16", 64, 8, 256, 77), ("bf16", 64, 3, 257, 255),   # 16 / four waves
                                                    ("f32", 128, 2, 256, 1024),     # 268 MB: non-temporal loads
                                                    ("bf16", 128, 2, 192, 300), ("bf16", 128, 3, 240, 280), ("bf16", 128, 8, 192, 260),
-                                                   ("f32", 128, 3, 258, 3000),     # partial outputs over the logits
+                                                   ("f32", 128, 3, 258, 3000), ("f32", 128, 8, 257, 2040),     # partial outputs behind the logits / over them
                                                    ("bf16", 128, 5, 258, 1500), ("bf16", 64, 2, 1, 8191)])
 def test_grouped_query_step_by_whole_workgroups(dtype, d, group, G, slots, say):
     """Every form of the one-workgroup generation step (four or 16 waves, partial outputs behind the logits or

@@ -1,5 +1,6 @@
 """Binding of liba2sf.so - argument marshalling only: through ctypes, and for the plain calls of a serving loop (tensors,
-ints, floats, a Cache) through the host extension _call.so, which does the same without the interpreter.
+ints, floats, a Cache) through the host extension _call.so, which does the same without the interpreter (all through ctypes, with
+a warning, where it is missing or was built for another torch).
 
 Every function has the name and the arguments of its C entry point (include/a2sf.h).
 torch tensors are accepted wherever the C side takes a device pointer; torch is used for
@@ -10,6 +11,8 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import warnings
 
 import torch
 
@@ -99,16 +102,36 @@ def lib() -> ctypes.CDLL:
         L.a2sf_status_string.restype = ctypes.c_char_p
         L.a2sf_status_string.argtypes = [i32]
         if _call is None:
-            try:
-                from . import _call as extension
-            except ImportError as e:
-                raise RuntimeError(f"{os.path.join(_HERE, '_call.so')} is missing or does not load ({e}): build it with "
-                                   "`python -m paper_2407_20485_amd.build` (there is no fallback path)") from e
-            extension.init(Cache, torch.float32, torch.bfloat16, _raw_stream if _get_device else None, _get_device)
-            _call = extension
+            _call = _load_extension()
         L.at = {name: ctypes.cast(getattr(L, name), vp).value for name in EXPORTS}
         _lib = L
     return _lib
+
+
+class _NoExtension:
+    """Every call goes through ctypes."""
+
+    @staticmethod
+    def _leave(*args):
+        return -1
+
+    decode_step = prefill = prefill_chunk = _leave
+
+
+def _load_extension():
+    """_call, if it is there and was built against this torch and this Python; the library itself needs neither."""
+    try:
+        from . import _call as extension
+        running = f"torch {torch.__version__.split('+')[0]}, Python {sys.version_info[0]}.{sys.version_info[1]}"
+        built_for = getattr(extension, "built_for", "something older")
+        if built_for != running:
+            raise ImportError(f"built for {built_for}, not {running}")
+    except ImportError as e:
+        warnings.warn(f"{os.path.join(_HERE, '_call.so')} is missing or does not load ({e}): steps, prompts and chunks take 2 us more host "
+                      "time each; build it with `python -m paper_2407_20485_amd.build`", RuntimeWarning, stacklevel=3)
+        return _NoExtension
+    extension.init(Cache, torch.float32, torch.bfloat16, _raw_stream if _get_device else None, _get_device)
+    return extension
 
 
 class A2SFError(RuntimeError):

@@ -11,6 +11,7 @@
 #include <exception>
 
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include "../../include/a2sf.h"
 
@@ -203,10 +204,19 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_call", nullptr, -1, methods, null
 
 }  // namespace
 
+#define A2SF_STR_(x) #x
+#define A2SF_STR(x) A2SF_STR_(x)
 PyMODINIT_FUNC PyInit__call() {
   PyObject** const names[] = {&n_k, &n_v, &n_scores, &n_pos, &n_len, &n_G, &n_capacity, &n_d, &n_dtype};
   const char* const text[] = {"k", "v", "scores", "pos", "len", "G", "capacity", "d", "dtype"};
   for (int i = 0; i < 9; ++i)
     if (!*names[i] && !(*names[i] = PyUnicode_InternFromString(text[i]))) return nullptr;
-  return PyModule_Create(&module);
+  PyObject* m = PyModule_Create(&module);
+  // (binding.py does without the extension where these are not the ones that run)
+  const char* const built_for = "torch " TORCH_VERSION ", Python " A2SF_STR(PY_MAJOR_VERSION) "." A2SF_STR(PY_MINOR_VERSION);
+  if (m && PyModule_AddStringConstant(m, "built_for", built_for) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
 }

@@ -3,6 +3,8 @@ include/a2sf.h declares, and rejects bad arguments on the host before any launch
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -248,3 +250,33 @@ def test_extension_leaves_unusual_arguments_to_ctypes():
     assert call(cache=broken) == -1
     with pytest.raises(TypeError):
         B._call.decode_step(at, q)
+
+
+@pytest.mark.parametrize("why", ["missing", "built for another torch"])
+def test_library_works_without_the_extension(why):
+    """The library does not depend on torch's ABI; without the extension every call goes through ctypes, with the same errors."""
+    replaced = "None" if why == "missing" else "types.SimpleNamespace(built_for='torch 1.0.0, Python 2.7')"
+    code = f"""
+import sys, types, warnings
+import torch
+import paper_2407_20485_amd
+sys.modules['paper_2407_20485_amd._call'] = {replaced}
+if {replaced}: paper_2407_20485_amd._call = {replaced}
+from paper_2407_20485_amd import binding as B
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter('always')
+    assert B.a2sf_workspace_bytes(2, 8, 12, 64, B.A2SF_F32, 4, 4) > 0
+assert len(seen) == 1 and seen[0].category is RuntimeWarning
+q = torch.zeros(2, 64)
+c = B.Cache(2, 12, 64, torch.float32, device='cpu')
+calls = [lambda a: B.a2sf_decode_step(q, q, q, 5, c, a, 4, 4, q), lambda a: B.a2sf_prefill(q, q, q, 1, a, 4, 4, c, o=q),
+         lambda a: B.a2sf_decode_step_gqa(q, q, q, 5, c, 2, a, 4, 4, q), lambda a: B.a2sf_prefill_chunk(q, q, q, 1, 0, a, 4, 4, c, o=q),
+         lambda a: B.a2sf_prefill_gqa(q, q, q, 1, 2, a, 4, 4, c, o=q), lambda a: B.a2sf_prefill_chunk_gqa(q, q, q, 1, 0, 2, a, 4, 4, c, o=q)]
+for call in calls:
+    try:
+        call(2.0)
+        raise SystemExit('no error')
+    except B.A2SFError as e:
+        assert e.status == B.A2SF_EINVAL
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))

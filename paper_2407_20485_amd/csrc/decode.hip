@@ -673,7 +673,7 @@ __global__ __launch_bounds__(NW * 64) void decode_gqa_kernel(
   constexpr int NG = NW / kWaves, HG = (R + NG - 1) / NG;
   __shared__ float red[2][NW][HG];
   {
-    const int quad = wave / kWaves, t4 = tid % kThreads;
+    const int quad = NG == 1 ? 0 : wave / kWaves, t4 = tid % kThreads;
     const auto mine = [&](int i) { return R % NG == 0 || quad + NG * i < R; };
     const auto strip = [&](int i) { return a + (quad + NG * i) * capacity; };
     float mx[HG], sum[HG];
@@ -694,14 +694,18 @@ __global__ __launch_bounds__(NW * 64) void decode_gqa_kernel(
     for (int i = 0; i < HG; ++i)
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) mx[i] = fmaxf(mx[i], red[0][quad * kWaves + w][i]);
-    for (int j = t4; j < L; j += kThreads)
+    for (int j = t4; j < L; j += kThreads) {
+      float z[HG];  // (all read before the first is written: the compiler does not know the strips apart)
+#pragma unroll
+      for (int i = 0; i < HG; ++i) z[i] = mine(i) ? strip(i)[j] : -INFINITY;
 #pragma unroll
       for (int i = 0; i < HG; ++i)
         if (mine(i)) {
-          const float p = exp2f(strip(i)[j] - mx[i]);
+          const float p = exp2f(z[i] - mx[i]);
           strip(i)[j] = p;
           sum[i] += p;
         }
+    }
 #pragma unroll
     for (int i = 0; i < HG; ++i) sum[i] = wave_sum(sum[i]);
     if (lane == 0) {
@@ -714,10 +718,14 @@ __global__ __launch_bounds__(NW * 64) void decode_gqa_kernel(
       const float* w = red[1][quad * kWaves] + i;
       sum[i] = 1.0f / ((w[0] + w[HG]) + (w[2 * HG] + w[3 * HG]));
     }
-    for (int j = t4; j < L; j += kThreads)
+    for (int j = t4; j < L; j += kThreads) {
+      float p[HG];
+#pragma unroll
+      for (int i = 0; i < HG; ++i) p[i] = mine(i) ? strip(i)[j] : 0.f;
 #pragma unroll
       for (int i = 0; i < HG; ++i)
-        if (mine(i)) strip(i)[j] *= sum[i];
+        if (mine(i)) strip(i)[j] = p[i] * sum[i];
+    }
   }
   __syncthreads();
 

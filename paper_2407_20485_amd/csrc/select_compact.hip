@@ -91,13 +91,19 @@ void launch_select_kernel(const float* scores, const int32_t* pos, const int32_t
   // 8000 x 1000 34 / 48, but 1500 x 1024 16.7 / 14.3 and 300 x 1024 14.5 / 8.4).  Up to 2048 slots four waves, or eight where
   // every head's workgroup has a compute unit (2048 slots, four / eight: 32 heads 12.0 / 10.2, 1500 heads 20.2 / 25.1; 16 of
   // them: 12.3 and 58.7).  Copying workgroups have more waves while there are few heads.
-  const bool copies = MOVE != kSelectOnly, few = G <= 512;
-  if (L <= 256 && !copies) A2SF_SELECT(64, 4, true);
-  else if (L <= 256 && few) A2SF_SELECT(512, 4, true);
-  else if (L <= 256) A2SF_SELECT(256, 4, true);
-  else if (L <= 512 && !copies && !few) A2SF_SELECT(64, 8, true);
-  else if (L <= 1024 && !copies && G > 2048) A2SF_SELECT(64, 16, true);
-  else if (L <= 1024 && !(copies && few)) A2SF_SELECT(256, 4, false);
+  constexpr bool copies = MOVE != kSelectOnly;
+  const bool few = G <= 512;
+  if constexpr (copies) {
+    if (L <= 256) {
+      if (few) A2SF_SELECT(512, 4, true); else A2SF_SELECT(256, 4, true);
+      return;
+    }
+  } else {
+    if (L <= 256) { A2SF_SELECT(64, 4, true); return; }
+    if (L <= 512 && !few) { A2SF_SELECT(64, 8, true); return; }
+    if (L <= 1024 && G > 2048) { A2SF_SELECT(64, 16, true); return; }
+  }
+  if (L <= 1024 && !(copies && few)) A2SF_SELECT(256, 4, false);
   else if (L <= 2048 && !few) A2SF_SELECT(256, 8, false);
   else if (L <= 2048) A2SF_SELECT(512, 4, false);
   else if (L <= 4096) A2SF_SELECT(1024, 4, false);

@@ -540,6 +540,53 @@ def test_chunk_evicts_in_place(dtype, d, budget, m, G):
             assert torch.equal(x[g, :kept], y[g, :kept]), g
 
 
+@pytest.mark.parametrize("d,group,G,m,L0,budget", [(128, 1, 6, 60, 400, 300),    # the moves take two rounds
+                                                   (128, 2, 6, 50, 440, 257), (64, 1, 200, 33, 460, 440), (64, 3, 6, 60, 300, 77),
+                                                   (128, 1, 6, 100, 120, 110), (64, 2, 6, 1, 255, 200), (128, 8, 6, 20, 200, 1)])
+def test_short_chunks_in_one_kernel(d, group, G, m, L0, budget):
+    """Chunks of caches that one kernel scores, selects from and moves: full heads, one without room for the chunk, one of an
+    invalid length (both stay as they are), newest positions with gaps, a head that is far from full and an empty one."""
+    cap, pos0, alpha = L0 + m, 1000, np.float32(0.8)
+    assert cap <= 512
+    select = budget * 2 // 3
+    recent = budget - select
+    gen = torch.Generator(device="cuda").manual_seed(m + d + budget)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").bfloat16()
+    cache = a2sf.Cache(G, cap, d, torch.bfloat16)
+    cache.k.copy_(rnd(G, cap, d)), cache.v.copy_(rnd(G, cap, d))
+    cache.scores.copy_(torch.rand(G, cap, generator=gen, device="cuda"))
+    lens = [L0] * G
+    lens[1:6] = L0 + 1, -1, L0, L0 // 3, 0
+    rng = np.random.default_rng(m + d)
+    for g, L in enumerate(lens):
+        n = max(L, 0)
+        pos = np.sort(rng.permutation(pos0)[:n]) if g == 3 else np.arange(pos0 - n, pos0)
+        cache.pos[g, :n] = torch.as_tensor(pos.astype(np.int32), device="cuda")
+    cache.len.copy_(torch.tensor(lens, dtype=torch.int32))
+    sample = sorted({0, 3, 4, 5, G - 1})
+    oc = {g: orc.HeadCache(*(parity.to_f64(x[g, : lens[g]]) for x in (cache.k, cache.v, cache.scores)),
+                           cache.pos[g, : lens[g]].cpu().numpy().astype(np.int64)) for g in sample}
+    before = cache.snapshot()
+    q, k, v = rnd(G, group, m, d), rnd(G, m, d), rnd(G, m, d)
+    ws = torch.empty(a2sf.a2sf_workspace_bytes(G * group, m, cap, d, a2sf.A2SF_BF16, select, recent), dtype=torch.uint8, device="cuda")
+    o = torch.zeros((G, group, m, d), dtype=torch.bfloat16, device="cuda")
+    a2sf.a2sf_prefill_chunk_gqa(q, k, v, m, pos0, group, float(alpha), select, recent, cache, o=o, workspace=ws)
+    torch.cuda.synchronize()
+    for g in (1, 2):
+        assert torch.isnan(o[g]).all() and all(torch.equal(x[g], y[g]) for x, y in zip(cache.tensors(), before))
+    for g in sample:
+        kept = int(cache.len[g])
+        assert kept == min(lens[g] + m, budget)
+        pos = cache.pos[g, :kept].cpu().numpy().astype(np.int64)
+        O, _, _ = orc.gqa_prefill_chunk(oc[g], parity.to_f64(q[g]), parity.to_f64(k[g]), parity.to_f64(v[g]), pos0, float(alpha),
+                                        select, recent, forced_retained=pos.tolist(), margin=parity.MARGIN)
+        assert np.abs(parity.to_f64(o[g]) - O).max() <= parity.O_TOL["bf16"]
+        c = oc[g].sorted_by_pos()
+        assert np.array_equal(pos, c.pos)
+        assert np.array_equal(parity.to_f64(cache.k[g, :kept]), c.K) and np.array_equal(parity.to_f64(cache.v[g, :kept]), c.V)
+        parity.compare_scores(cache.scores[g, :kept].cpu().numpy(), c.S, f"head {g}")
+
+
 @pytest.mark.parametrize("dtype,d,group", [("bf16", 64, 1), ("bf16", 128, 2), ("f32", 64, 3), ("f32", 128, 1)])
 @pytest.mark.parametrize("budget", [40, 256, 257, 511, 512, 513])
 def test_stable_step_evicts_in_place(dtype, d, group, budget):

@@ -116,13 +116,13 @@ void launch_attn_bf16(const void* q, const void* k, const void* v, int G, const 
 void launch_colscores_bf16(const void* q, const void* k, const float* lse2, int G,
                            const AttnRect& rc, int keys_per_head, int d, float alpha, float* scores,
                            int s_stride, bool accumulate, float decay, hipStream_t st);
-// first_row > 0 (only with o == null): rows before it need no log-sum-exp
 // Column scores, selection and moves in one kernel, where scores_select_fits (a prompt's score tolerance is not used): a prompt
 // (square rc, into the empty cache; scores_full may be null) or, with rc.k2, a chunk (in place; `decay` as above).
 bool scores_select_fits(int G, const AttnRect& rc, int keys_per_head, float alpha);
 void launch_scores_select_bf16(const void* q, const void* k, const void* v, const float* lse2, const AttnRect& rc,
                                int keys_per_head, float alpha, const float* alpha_heads, float decay, float* scores_full,
                                int select, int recent, const a2sf_cache& c, hipStream_t st);
+// first_row > 0 (only with o == null): rows before it need no log-sum-exp
 void launch_prefill_bf16(const void* q, const void* k, const void* v, int G, int n, int d,
                          void* o, float* lse2, hipStream_t st, int first_row = 0);
 // First prompt row whose log-sum-exp launch_scores_bf16 reads for these sizes (Section 3.3: the

@@ -1362,11 +1362,12 @@ __global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_sco
 // registers, the rows are staged in LDS as in col_scores_tail_kernel, one query head of the group after the other; the
 // scores stay in LDS, where one wave selects from them.  (The exponent offsets are in LDS and the loop over the rows is not
 // unrolled: such a kernel runs once per compute unit, and its instructions have to be fetched first.)
-// MOVE: kGather, a prompt; kInPlace, a chunk, whose new tokens' positions are rc.pos0 ...
+// MOVE: kGather, a prompt; kInPlace, a chunk, whose new tokens' positions are rc.pos0 ... (K is then the cache, whose rows change: it
+// is not a restricted argument).
 constexpr int kScoreSelectKeys = 512;  // largest form
 template <int D, int MOVE, int KEYS>
 __global__ __launch_bounds__(2 * KEYS) void scores_select_kernel(
-    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const float* __restrict__ LSE2, AttnRect rc, float decay,
+    const bf16_t* __restrict__ Q, const bf16_t* K, const float* __restrict__ LSE2, AttnRect rc, float decay,
     int first_row, float log2_alpha, const float* __restrict__ alpha_heads, float scale_log2e, float* __restrict__ scores_full,
     int select, int recent, MoveTo to) {
   constexpr int T = 2 * KEYS, KK = D / 16, kTB = kTileBytesOf<D>;

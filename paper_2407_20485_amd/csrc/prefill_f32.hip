@@ -681,10 +681,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 2) void scores_f32_kernel(
 }
 
 // ---- short prompts -------------------------------------------------------------------------
-// A matrix op of 64 cycles per two elements makes a tile of 32 rows a chain of 8000 cycles and more, whatever the
-// prompt has of it.  A short prompt of few heads is done sooner by plain arithmetic: a workgroup per attention row, then one
+// A tile of 32 rows is a chain of 96 matrix ops (d = 128) of 32 cycles and the vector work between them, 3000 cycles and more, whatever
+// the prompt has of it.  A short prompt of few heads is done sooner by plain arithmetic: a workgroup per attention row, then one
 // per key (square geometry only).
-constexpr int kShortRows = 512;  // of a prompt, at most
+constexpr int kShortRows = 352;  // of a prompt, at most
 
 template <int D>
 __global__ __launch_bounds__(kThreads) void attn_rows_f32_kernel(
@@ -766,12 +766,13 @@ int first_contributing_row(int n, float alpha, float* log2_alpha) {
 }
 
 // The kernels by rows cost G n workgroups of up to n keys, those by tiles a chain of n / 128: they meet where G n^1.5 is
-// about constant (us, attention and scores, rows / tiles: d = 128, 1 head x 200 21 / 23, x 300 30 / 30, 8 x 64 13 / 19, 8
-// x 130 28 / 23, 40 x 20 13 / 18, 40 x 48 26 / 20, 300 x 5 14 / 19, 300 x 12 32 / 20; d = 64, 1 x 420 23 / 26, 8 x 96 11 /
-// 14, 40 x 32 9 / 14, 40 x 64 18 / 14, 300 x 5 8 / 14, 300 x 20 23 / 15).
+// about constant, but for one head, whose rows grow longer than that takes (us per call, rows / tiles: d = 128, 1 head x 239 rows 25.7
+// / 28.9, x 299 31.5 / 33.1, x 359 38.3 / 34.6, 2 x 188 26.2 / 28.9, x 226 30.9 / 29.9, 4 x 178 29.3 / 29.8, 8 x 89 20.6 / 23.4, x 112 24.8 /
+// 22.9, 32 x 29 15.3 / 22.3, 120 x 18 20.3 / 20.2; d = 64, 1 x 268 19.5 / 22.5, x 358 22.1 / 22.4, x 448 26.2 / 24.9, 2 x 225 19.1 / 21.4, x 282
+// 22.4 / 22.6, 4 x 213 22.6 / 22.2, 8 x 112 15.3 / 17.4, x 168 22.8 / 21.4, 32 x 44 12.3 / 16.7, x 66 17.6 / 17.6).
 static bool short_prompt(int G, const AttnRect& rc, int d) {
   const double rows = (double)G * rc.kv_group * rc.m;
-  return !rc.off_heads && rc.m <= kShortRows && rows * rows * rc.m <= (d == 64 ? 90e6 : 27e6);
+  return !rc.off_heads && rc.m <= (d == 64 ? kShortRows : 320) && rows * rows * rc.m <= (d == 64 ? 90e6 : 45e6);
 }
 
 void launch_attn_f32(const float* q, const float* k, const float* v, int G, const AttnRect& rc,

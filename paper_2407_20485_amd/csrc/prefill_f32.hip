@@ -684,7 +684,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 2) void scores_f32_kernel(
 // A tile of 32 rows is a chain of 96 matrix ops (d = 128) of 32 cycles and the vector work between them, 3000 cycles and more, whatever
 // the prompt has of it.  A short prompt of few heads is done sooner by plain arithmetic: a workgroup per attention row, then one
 // per key (square geometry only).
-constexpr int kShortRows = 352;  // of a prompt, at most
+constexpr int kShortRows = 384;  // of a prompt, at most
 
 template <int D>
 __global__ __launch_bounds__(kThreads) void attn_rows_f32_kernel(

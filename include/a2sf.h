@@ -109,8 +109,10 @@ size_t a2sf_workspace_bytes(int32_t G, int32_t n_max, int32_t capacity, int32_t 
  *                exactly 0 in fp32 are not visited at all where the scores do not need them.
  *   scores_full  out [G, n] fp32: the Eq.5 score of every prompt token; may be NULL.
  * The n x n probability matrix is never written to memory.
- * Range of values: fp32 logits may take any finite value, and an infinity or NaN in a row of V
- * reaches only the rows that see it.  bf16 works on tiles of 64 keys: an infinity or NaN in a row
+ * Range of values: fp32 results have the precision of fp32 arithmetic for all normal numbers;
+ * logits may take any finite value, and an infinity or NaN in a row of V reaches only the
+ * rows that see it (such rows, and some of numbers beyond 2^100 or below 2^-110, take two to five
+ * times as long).  bf16 works on tiles of 64 keys: an infinity or NaN in a row
  * of V may also reach earlier rows of its tile, as NaN, and a row whose logits (q . k / sqrt(d)) all
  * lie below about -7e29 comes out as NaN.  The same holds for a2sf_prefill_chunk. */
 a2sf_status a2sf_prefill(const void* q, const void* k, const void* v, int32_t n, float alpha,

@@ -1358,21 +1358,23 @@ __global__ __launch_bounds__(kThreads * RS, (KB == 1 ? 4 : 2) / RS) void col_sco
 
 // ---------------------------------------------------------------------------------------
 // Scores, selection and moves of a short prompt or chunk in one kernel, one workgroup per K/V head: three launches
-// whose work is a few chains of latencies.  Up to 256 rows that count and KEYS keys: KEYS / 32 waves have a block of 32 keys each in
+// whose work is a few chains of latencies.  Up to 256 rows that count and KEYS keys: KEYS / 32 waves (of four at least) have a block of 32 keys each in
 // registers, the rows are staged in LDS as in col_scores_tail_kernel, one query head of the group after the other; the
 // scores stay in LDS, where one wave selects from them.  (The exponent offsets are in LDS and the loop over the rows is not
 // unrolled: such a kernel runs once per compute unit, and its instructions have to be fetched first.)
 // MOVE: kGather, a prompt; kInPlace, a chunk, whose new tokens' positions are rc.pos0 ... (K is then the cache, whose rows change: it
 // is not a restricted argument).
 constexpr int kScoreSelectKeys = 512;  // largest form
+template <int KEYS> constexpr int kScoreSelectThreads = KEYS < kThreads / 2 ? kThreads : 2 * KEYS;
 template <int D, int MOVE, int KEYS>
-__global__ __launch_bounds__(2 * KEYS) void scores_select_kernel(
+__global__ __launch_bounds__(kScoreSelectThreads<KEYS>) void scores_select_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* K, const float* __restrict__ LSE2, AttnRect rc, float decay,
     int first_row, float log2_alpha, const float* __restrict__ alpha_heads, float scale_log2e, float* __restrict__ scores_full,
     int select, int recent, MoveTo to) {
-  constexpr int T = 2 * KEYS, KK = D / 16, kTB = kTileBytesOf<D>;
-  __shared__ __attribute__((aligned(1024))) char smem[kTailTiles * kTB];
-  __shared__ float bias[kTailTiles * kTile], z[KEYS];
+  constexpr int T = kScoreSelectThreads<KEYS>, KK = D / 16, kTB = kTileBytesOf<D>;
+  constexpr int TILES = KEYS < kTailTiles * kTile ? KEYS / kTile : kTailTiles;  // (no more rows than keys)
+  __shared__ __attribute__((aligned(1024))) char smem[TILES * kTB];
+  __shared__ float bias[TILES * kTile], z[KEYS];
   __shared__ int32_t list[KEYS];
   __shared__ SelectSmem<1> none;
   lds_char* const qs = (lds_char*)smem;
@@ -1386,7 +1388,7 @@ __global__ __launch_bounds__(2 * KEYS) void scores_select_kernel(
   const bf16_t* K2g = rc.k2 ? (const bf16_t*)rc.k2 + (size_t)g * n * D : nullptr;  // keys off .. from here
   const int r_lo = (first_row / kTile) * kTile;           // first staged row (sized by the host)
   head_window(alpha_heads, g, n, first_row, log2_alpha);  // this head's own window inside it
-  const int ntile = (n - r_lo + kTile - 1) / kTile;       // <= kTailTiles (checked by the host)
+  const int ntile = (n - r_lo + kTile - 1) / kTile;       // <= TILES (checked by the host)
   uint4 kf[KK];  // A operand: lane (key l32, half h) holds K[key][16kk + 8h .. +7]
   {
     const int r = min(wave * 32 + l32, nk - 1);
@@ -1408,7 +1410,7 @@ __global__ __launch_bounds__(2 * KEYS) void scores_select_kernel(
     if (hq > 0) __syncthreads();  // every wave is done with the rows of the head before
     for (int t = wave / kWaves; t < ntile; t += T / kThreads) dma_tile<D, false>(Q + head * n * D, r_lo + t * kTile, n, qs + t * kTB);
     // exponent offset of every staged row: lse_r - (n-1-r) log2 alpha, infinite where it adds nothing
-    if (tid < kTailTiles * kTile) {
+    if (tid < TILES * kTile) {
       const int r = r_lo + tid;
       const float lse = LSE2[head * n + min(r, n - 1)];
       bias[tid] = (r < n && r >= first_row) ? lse - (float)(n - 1 - r) * log2_alpha : INFINITY;
@@ -1566,11 +1568,17 @@ void launch_scores_select_bf16(const void* q, const void* k, const void* v, cons
   const MoveTo to = {(const u32x4_t*)(chunk ? rc.k2 : k), (const u32x4_t*)(chunk ? rc.v2 : v), (u32x4_t*)c.k, (u32x4_t*)c.v,
                      c.scores, c.pos, c.len, c.capacity, lg_row_units(c.d / 8), chunk ? rc.m : 0, nullptr};
 #define A2SF_SCORE_SELECT_(D, MOVE, KEYS)                                                             \
-  hipLaunchKernelGGL((scores_select_kernel<D, MOVE, KEYS>), dim3(c.G), dim3(2 * KEYS), 0, st, (const bf16_t*)q, \
+  hipLaunchKernelGGL((scores_select_kernel<D, MOVE, KEYS>), dim3(c.G), dim3(kScoreSelectThreads<KEYS>), 0, st, (const bf16_t*)q, \
                      (const bf16_t*)k, lse2, rc, decay, first, l2a, alpha_heads, scale_log2e, scores_full, select, recent, to)
+  // Smaller forms leave a compute unit room for more heads: with a room of 256 rows and eight waves whatever the prompt has, many short
+  // heads took longer than in two kernels (us per call, two kernels / KEYS = 256 / by size, d = 128: 3000 heads x 34 rows 55.4 / 61.2 / 48.7, 622 x 5
+  // queries x 34 48.1 / 52.3 / 44.6, 1345 x 100 50.0 / 50.8 / 45.6, chunks of 30 rows of 1500 heads behind 34 56.8 / 46.2 / 39.7).  For few heads the
+  // waves count that move the rows (KEYS = 128 at 32 heads, 20 rows behind 100: 17.2 / 17.9).
 #define A2SF_SCORE_SELECT(D, MOVE)                                               \
   do {                                                                           \
-    if (keys_per_head <= 256) A2SF_SCORE_SELECT_(D, MOVE, 256);                  \
+    if (keys_per_head <= 64) A2SF_SCORE_SELECT_(D, MOVE, 64);                    \
+    else if (keys_per_head <= 128 && c.G > 512) A2SF_SCORE_SELECT_(D, MOVE, 128); \
+    else if (keys_per_head <= 256) A2SF_SCORE_SELECT_(D, MOVE, 256);             \
     else A2SF_SCORE_SELECT_(D, MOVE, 512);                                       \
   } while (0)
   if (c.d == 64) {

@@ -146,7 +146,7 @@ def test_gather_list_lengths(dtype, d, budget, n):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("G,n", [(300, 1), (300, 63), (300, 65), (150, 130), (150, 200), (40, 700), (3, 64), (3, 449)])
+@pytest.mark.parametrize("G,n", [(300, 1), (300, 63), (300, 65), (150, 130), (150, 200), (40, 700), (3, 64), (3, 449), (520, 64), (520, 65), (520, 128), (520, 129)])
 def test_bf16_prompt_tiles(G, n, d):
     """Up to 256 row blocks of 128 the keys of a row are split between the two halves of a workgroup (few
     heads: one to eight tiles, odd and even numbers of them), above that they are not; the streaming
@@ -542,7 +542,8 @@ def test_chunk_evicts_in_place(dtype, d, budget, m, G):
 
 @pytest.mark.parametrize("d,group,G,m,L0,budget", [(128, 1, 6, 60, 400, 300),    # the moves take two rounds
                                                    (128, 2, 6, 50, 440, 257), (64, 1, 200, 33, 460, 440), (64, 3, 6, 60, 300, 77),
-                                                   (128, 1, 6, 100, 120, 110), (64, 2, 6, 1, 255, 200), (128, 8, 6, 20, 200, 1)])
+                                                   (128, 1, 6, 100, 120, 110), (64, 2, 6, 1, 255, 200), (128, 8, 6, 20, 200, 1),
+                                                   (128, 1, 6, 20, 44, 30), (64, 3, 6, 63, 1, 1), (64, 2, 520, 28, 100, 60), (128, 1, 520, 128 - 65, 65, 65)])
 def test_short_chunks_in_one_kernel(d, group, G, m, L0, budget):
     """Chunks of caches that one kernel scores, selects from and moves: full heads, one without room for the chunk, one of an
     invalid length (both stay as they are), newest positions with gaps, a head that is far from full and an empty one."""

@@ -515,7 +515,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 && RB == 2 ? 3 : (RB == 1 && NW ==
         const int r = u / CPR, c = u % CPR;
         if (row0 + r >= n) break;
         const lds_char* p = (const lds_char*)smem + r * D * 4 + ((c ^ tile_swizzle<false>(r)) << 4);
-        f32x4 a = lds_read4(p) + lds_read4(p + RB * kTileBytes);
+        f32x4 a = lds_read4(p);
+        if constexpr (P > 1) a += lds_read4(p + RB * kTileBytes);
 #pragma unroll
         for (int w = 2; w < P; w += 2) a += lds_read4(p + RB * w * kTileBytes) + lds_read4(p + RB * (w + 1) * kTileBytes);
         *reinterpret_cast<f32x4*>(O + ((size_t)g * n + row0 + r) * D + c * 4) = a;
@@ -661,7 +662,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 2) void scores_f32_kernel(
     float sum = 0.f;
     if (tid < kRows) {
 #pragma unroll
-      for (int w = 0; w < NW; w += 4) sum += (part[w][tid] + part[w + 1][tid]) + (part[w + 2][tid] + part[w + 3][tid]);
+      for (int w = 0; w + 3 < NW; w += 4) sum += (part[w][tid] + part[w + 1][tid]) + (part[w + 2][tid] + part[w + 3][tid]);
+      if constexpr (NW == 1) sum = part[0][tid];
     }
     return sum;
   };
@@ -791,13 +793,15 @@ void launch_attn_f32(const float* q, const float* k, const float* v, int G, cons
                      q, k, v, rc, GQ, blocks(kRows * RB), o, lse2, scale_log2e)
 #define A2SF_ATTN_F32_64(WO)                             \
   do {                                                   \
-    if (all <= 320 && tiles >= 8) A2SF_ATTN_F32(64, WO, 1, 8); \
+    if (alone) A2SF_ATTN_F32(64, WO, 1, 1);              \
+    else if (all <= 320 && tiles >= 8) A2SF_ATTN_F32(64, WO, 1, 8); \
     else if (all <= 1024) A2SF_ATTN_F32(64, WO, 1, 4);   \
     else A2SF_ATTN_F32(64, WO, 2, 4);                    \
   } while (0)
 #define A2SF_ATTN_F32_128(WO)                            \
   do {                                                   \
-    if (all <= 640) A2SF_ATTN_F32(128, WO, 1, 4);        \
+    if (alone) A2SF_ATTN_F32(128, WO, 1, 1);             \
+    else if (all <= 640) A2SF_ATTN_F32(128, WO, 1, 4);   \
     else A2SF_ATTN_F32(128, WO, 2, 4);                   \
   } while (0)
   // Two blocks of rows per workgroup share a tile's loads and put two waves onto every SIMD; while the blocks are few, the chain
@@ -807,6 +811,9 @@ void launch_attn_f32(const float* q, const float* k, const float* v, int G, cons
   // 760 81.4 / 66.7, 1024 102 / 80, 5943 270 / 152.  Eight waves of d = 128 have no registers for the parts).
   const long long all = (long long)GQ * blocks(kRows);
   const int tiles = ((rc.off_heads ? rc.kv_stride : rc.m) + kRows - 1) / kRows;  // of the newest row, at most
+  // One tile in all: one wave per workgroup (us per call, four waves / one: d = 64, 400 heads x 15 rows 17.3 / 15.7, 800 x 15 28.0 / 17.1, 2000 x 32 49.4 /
+  // 32.8; d = 128, 400 x 15 29.9 / 21.3, 800 x 32 50.0 / 33.9, 2000 x 6 68.1 / 33.3; scores included).
+  const bool alone = tiles == 1;
   if (d == 64) {
     if (o) A2SF_ATTN_F32_64(true); else A2SF_ATTN_F32_64(false);
   } else {
@@ -841,12 +848,13 @@ void launch_colscores_f32(const float* q, const float* k, const float* lse2, int
   // Eight waves where the keys are few and every wave has a tile (us, eight waves / four: d = 128, 38 blocks of 32 keys x 33 tiles 20.7
   // / 27.8, 94 x 376 150 / 230, 256 x 32 22.6 / 27.1, but 264 x 2 17.3 / 11.1, 377 x 3 17.8 / 11.5, 1024 x 3 36 / 22; d = 64, 228 x
   // 8 7.8 / 8.6, 111 x 24 11.5 / 17.5, 580 x 29 25.9 / 21.0).
+  // One tile of rows: one wave (chunks of 2 rows behind 150, d = 128: 300 heads 74 / 56, 1307 heads 211 / 138; 32 heads 33.7 / 32.7).
   const int tiles = ((rc.m + kRows - 1) / kRows - first / kRows) * rc.kv_group;
   const bool few = (long long)G * ncb <= 320 && tiles >= 8;
   if (d == 64) {
-    if (few) A2SF_SCORES_F32(64, 8); else A2SF_SCORES_F32(64, 4);
+    if (tiles == 1) A2SF_SCORES_F32(64, 1); else if (few) A2SF_SCORES_F32(64, 8); else A2SF_SCORES_F32(64, 4);
   } else {
-    if (few) A2SF_SCORES_F32(128, 8); else A2SF_SCORES_F32(128, 4);
+    if (tiles == 1) A2SF_SCORES_F32(128, 1); else if (few) A2SF_SCORES_F32(128, 8); else A2SF_SCORES_F32(128, 4);
   }
 #undef A2SF_SCORES_F32
 }

@@ -663,7 +663,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 3 : 2) void scores_f32_kernel(
     if (tid < kRows) {
 #pragma unroll
       for (int w = 0; w + 3 < NW; w += 4) sum += (part[w][tid] + part[w + 1][tid]) + (part[w + 2][tid] + part[w + 3][tid]);
-      if constexpr (NW == 1) sum = part[0][tid];
+      if constexpr (NW < 4) sum = NW == 1 ? part[0][tid] : part[0][tid] + part[NW - 1][tid];
     }
     return sum;
   };
@@ -793,14 +793,16 @@ void launch_attn_f32(const float* q, const float* k, const float* v, int G, cons
                      q, k, v, rc, GQ, blocks(kRows * RB), o, lse2, scale_log2e)
 #define A2SF_ATTN_F32_64(WO)                             \
   do {                                                   \
-    if (alone) A2SF_ATTN_F32(64, WO, 1, 1);              \
+    if (tiles == 1) A2SF_ATTN_F32(64, WO, 1, 1);         \
     else if (all <= 320 && tiles >= 8) A2SF_ATTN_F32(64, WO, 1, 8); \
+    else if (all <= 1024 && tiles == 2) A2SF_ATTN_F32(64, WO, 1, 2); \
     else if (all <= 1024) A2SF_ATTN_F32(64, WO, 1, 4);   \
     else A2SF_ATTN_F32(64, WO, 2, 4);                    \
   } while (0)
 #define A2SF_ATTN_F32_128(WO)                            \
   do {                                                   \
-    if (alone) A2SF_ATTN_F32(128, WO, 1, 1);             \
+    if (tiles == 1) A2SF_ATTN_F32(128, WO, 1, 1);        \
+    else if (all <= 640 && tiles == 2) A2SF_ATTN_F32(128, WO, 1, 2); \
     else if (all <= 640) A2SF_ATTN_F32(128, WO, 1, 4);   \
     else A2SF_ATTN_F32(128, WO, 2, 4);                   \
   } while (0)
@@ -811,9 +813,10 @@ void launch_attn_f32(const float* q, const float* k, const float* v, int G, cons
   // 760 81.4 / 66.7, 1024 102 / 80, 5943 270 / 152.  Eight waves of d = 128 have no registers for the parts).
   const long long all = (long long)GQ * blocks(kRows);
   const int tiles = ((rc.off_heads ? rc.kv_stride : rc.m) + kRows - 1) / kRows;  // of the newest row, at most
-  // One tile in all: one wave per workgroup (us per call, four waves / one: d = 64, 400 heads x 15 rows 17.3 / 15.7, 800 x 15 28.0 / 17.1, 2000 x 32 49.4 /
-  // 32.8; d = 128, 400 x 15 29.9 / 21.3, 800 x 32 50.0 / 33.9, 2000 x 6 68.1 / 33.3; scores included).
-  const bool alone = tiles == 1;
+  // One tile in all: one wave per workgroup, which leaves room for many (us per call, four waves / one: d = 64, 400 heads x 15 rows 17.3 / 15.7, 800 x
+  // 15 28.0 / 17.1, 2000 x 32 49.4 / 32.8; d = 128, 400 x 15 29.9 / 21.3, 800 x 32 50.0 / 33.9, 2000 x 6 68.1 / 33.3; scores included).  Two: two waves
+  // (four / two: d = 64, 400 x 64 27.4 / 21.5; d = 128, 200 x 64 31.7 / 23.7, 60 x 64 21.8 / 20.7), but two blocks of rows where those are
+  // taken (two blocks / two waves: d = 64, 2000 x 64 48.6 / 52.0; d = 128, 400 x 64 31.5 / 37.0).
   if (d == 64) {
     if (o) A2SF_ATTN_F32_64(true); else A2SF_ATTN_F32_64(false);
   } else {
@@ -848,13 +851,14 @@ void launch_colscores_f32(const float* q, const float* k, const float* lse2, int
   // Eight waves where the keys are few and every wave has a tile (us, eight waves / four: d = 128, 38 blocks of 32 keys x 33 tiles 20.7
   // / 27.8, 94 x 376 150 / 230, 256 x 32 22.6 / 27.1, but 264 x 2 17.3 / 11.1, 377 x 3 17.8 / 11.5, 1024 x 3 36 / 22; d = 64, 228 x
   // 8 7.8 / 8.6, 111 x 24 11.5 / 17.5, 580 x 29 25.9 / 21.0).
-  // One tile of rows: one wave (chunks of 2 rows behind 150, d = 128: 300 heads 74 / 56, 1307 heads 211 / 138; 32 heads 33.7 / 32.7).
+  // One tile of rows: one wave (us per call, four / one, chunks of 2 rows behind 150, d = 128: 300 heads 74 / 56, 1307 heads 211 / 138; 32 heads 33.7 /
+  // 32.7).  Two: two waves (four / two, chunks of 60 rows behind 200: 300 heads 124 / 107, 1307 heads 412 / 318; 32 heads 46.5 / 45.5).
   const int tiles = ((rc.m + kRows - 1) / kRows - first / kRows) * rc.kv_group;
   const bool few = (long long)G * ncb <= 320 && tiles >= 8;
   if (d == 64) {
-    if (tiles == 1) A2SF_SCORES_F32(64, 1); else if (few) A2SF_SCORES_F32(64, 8); else A2SF_SCORES_F32(64, 4);
+    if (tiles == 1) A2SF_SCORES_F32(64, 1); else if (tiles == 2) A2SF_SCORES_F32(64, 2); else if (few) A2SF_SCORES_F32(64, 8); else A2SF_SCORES_F32(64, 4);
   } else {
-    if (tiles == 1) A2SF_SCORES_F32(128, 1); else if (few) A2SF_SCORES_F32(128, 8); else A2SF_SCORES_F32(128, 4);
+    if (tiles == 1) A2SF_SCORES_F32(128, 1); else if (tiles == 2) A2SF_SCORES_F32(128, 2); else if (few) A2SF_SCORES_F32(128, 8); else A2SF_SCORES_F32(128, 4);
   }
 #undef A2SF_SCORES_F32
 }

@@ -166,7 +166,8 @@ def test_fp32_infinite_operands(d, G, n, cached):
 
 # fp32 prompts by tiles in every launch form (blocks per workgroup, waves), and chunks
 FP32_FORMS = [(64, 21, 200, 0), (64, 60, 200, 0), (64, 260, 130, 0), (64, 300, 70, 50), (128, 11, 200, 0), (128, 200, 130, 0), (128, 300, 70, 50),
-              (64, 700, 32, 0), (128, 430, 31, 0), (128, 300, 20, 50)]  # one tile: one wave (the last: for the scores)
+              (64, 700, 32, 0), (128, 430, 31, 0), (128, 300, 20, 50),  # one tile: one wave (the last: for the scores)
+              (64, 200, 40, 0), (128, 70, 64, 0), (64, 70, 20, 13)]  # two tiles: two waves
 
 
 @pytest.mark.parametrize("d,G,n,cached", FP32_FORMS)

@@ -768,13 +768,15 @@ int first_contributing_row(int n, float alpha, float* log2_alpha) {
 }
 
 // The kernels by rows cost G n workgroups of up to n keys, those by tiles a chain of n / 128: they meet where G n^1.5 is
-// about constant, but for one head, whose rows grow longer than that takes (us per call, rows / tiles: d = 128, 1 head x 239 rows 25.7
-// / 28.9, x 299 31.5 / 33.1, x 359 38.3 / 34.6, 2 x 188 26.2 / 28.9, x 226 30.9 / 29.9, 4 x 178 29.3 / 29.8, 8 x 89 20.6 / 23.4, x 112 24.8 /
-// 22.9, 32 x 29 15.3 / 22.3, 120 x 18 20.3 / 20.2; d = 64, 1 x 268 19.5 / 22.5, x 358 22.1 / 22.4, x 448 26.2 / 24.9, 2 x 225 19.1 / 21.4, x 282
-// 22.4 / 22.6, 4 x 213 22.6 / 22.2, 8 x 112 15.3 / 17.4, x 168 22.8 / 21.4, 32 x 44 12.3 / 16.7, x 66 17.6 / 17.6).
+// about constant, but for one head, whose rows grow longer than that takes, and for many heads of a few rows of d = 128 (us per call, rows / tiles:
+// d = 128, 1 head x 239 rows 25.7 / 28.9, x 299 31.5 / 33.1, x 359 38.3 / 34.6, 2 x 188 26.2 / 28.9, x 226 30.9 / 29.9, 4 x 140 24.8 / 28.6, x 178
+// 29.3 / 29.8, 8 x 89 20.6 / 23.2, x 112 24.8 / 22.9, 32 x 35 17.9 / 20.6, 60 x 23 17.8 / 20.9, 120 x 14 17.6 / 18.8, 300 x 6 17.4 / 19.0, x 7 19.3 /
+// 19.3, 1000 x 2 17.6 / 19.9, x 3 22.4 / 20.4; d = 64, 1 x 268 19.5 / 22.5, x 358 22.1 / 22.4, x 448 26.2 / 24.9, 2 x 225 19.1 / 21.4, x 282 22.4 / 22.6,
+// 4 x 213 22.5 / 22.4, 16 x 74 14.6 / 17.9, 32 x 44 12.8 / 15.8, 120 x 18 12.0 / 14.8, 300 x 10 12.6 / 15.0, 1000 x 4 13.9 / 15.5).
 static bool short_prompt(int G, const AttnRect& rc, int d) {
-  const double rows = (double)G * rc.kv_group * rc.m;
-  return !rc.off_heads && rc.m <= (d == 64 ? kShortRows : 320) && rows * rows * rc.m <= (d == 64 ? 90e6 : 45e6);
+  const double rows = (double)G * rc.kv_group * rc.m, work = rows * rows * rc.m;
+  if (rc.off_heads) return false;
+  return d == 64 ? rc.m <= kShortRows && work <= 90e6 : rc.m <= 320 && rows <= 2100 && work <= 45e6;
 }
 
 void launch_attn_f32(const float* q, const float* k, const float* v, int G, const AttnRect& rc,

@@ -804,8 +804,8 @@ void launch_attn_f32(const float* q, const float* k, const float* v, int G, cons
 #define A2SF_ATTN_F32_128(WO)                            \
   do {                                                   \
     if (tiles == 1) A2SF_ATTN_F32(128, WO, 1, 1);        \
-    else if (all <= 640 && tiles == 2) A2SF_ATTN_F32(128, WO, 1, 2); \
-    else if (all <= 640) A2SF_ATTN_F32(128, WO, 1, 4);   \
+    else if (all <= one_block && tiles == 2) A2SF_ATTN_F32(128, WO, 1, 2); \
+    else if (all <= one_block) A2SF_ATTN_F32(128, WO, 1, 4); \
     else A2SF_ATTN_F32(128, WO, 2, 4);                   \
   } while (0)
   // Two blocks of rows per workgroup share a tile's loads and put two waves onto every SIMD; while the blocks are few, the chain
@@ -819,6 +819,9 @@ void launch_attn_f32(const float* q, const float* k, const float* v, int G, cons
   // 15 28.0 / 17.1, 2000 x 32 49.4 / 32.8; d = 128, 400 x 15 29.9 / 21.3, 800 x 32 50.0 / 33.9, 2000 x 6 68.1 / 33.3; scores included).  Two: two waves
   // (four / two: d = 64, 400 x 64 27.4 / 21.5; d = 128, 200 x 64 31.7 / 23.7, 60 x 64 21.8 / 20.7), but two blocks of rows where those are
   // taken (two blocks / two waves: d = 64, 2000 x 64 48.6 / 52.0; d = 128, 400 x 64 31.5 / 37.0).
+  // d = 128, 513 to 640 blocks: one block per workgroup takes a third round, which only long chains are worth (us per call, one block / two: 64 x 320
+  // 65.6 / 56.2, 180 x 96 50.8 / 40.6, 32 x 610 74.2 / 70.5, but 20 x 870 78.7 / 83.1, 9 x 1900 111 / 141).
+  const long long one_block = tiles > 24 ? 640 : 512;
   if (d == 64) {
     if (o) A2SF_ATTN_F32_64(true); else A2SF_ATTN_F32_64(false);
   } else {
